@@ -1,0 +1,828 @@
+// Kernels of the coefficient form (d2q37_coeff.h) and their launchers: the
+// fused step, the transposed step, the way in from and out to the 37
+// populations, and the readers of the state.
+//
+// The sweep (fused step and transposed step).  One wave64 takes 56 rows of TX
+// consecutive columns: its lanes hold the rows y0 - 4 .. y0 + 59, four of
+// them halo on each side, so that a population hopping up to three rows finds
+// its target inside the wave, and stores start 128-byte aligned (56 rows of
+// 16-byte pairs).  The wave walks over the TX + 6 source columns.  For each
+// it loads the site's 15 coefficients, rebuilds the populations of every
+// e_x group that reaches one of its TX columns, passes them to their target
+// row through a wave-private LDS buffer (no barrier: a wave's LDS accesses
+// are in order) and adds them to the target's 15 sums; a column is complete
+// six source columns after its first and is collided and stored at once.
+//
+// What bounds it and why this split.  The step moves 240 bytes per site
+// (15 FP64 in, 15 out) instead of the 592 of the 37-population kernel.
+// Rebuilding populations is done once per (source site, e_x group) whatever
+// TX is; TX trades registers (30 VGPRs per column: 4, 3, 2 waves per SIMD at
+// TX = 2, 3, 4) against re-reading source columns ((TX + 6) / TX times, from
+// the XCD's L2: measured 1.07 x, 1.22 x, 1.22 x of the state fetched past L2
+// at TX = 2, 3, 4).  16-byte accesses matter: with 8-byte ones the L1
+// handles half the bytes per cycle (230 against 200 us at 1920 x 2048).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "d2q37_coeff.h"
+#include "d2q37_launch.h"
+#include "d2q37_tiles.h"
+
+namespace d2q37 {
+
+namespace {
+
+typedef double v2d __attribute__((ext_vector_type(2)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+
+constexpr int kHalo = 4;             // halo rows on each side of a wave
+constexpr int kRows = 64 - 2 * kHalo;  // target rows of a wave
+constexpr int kWaves = 4;            // waves per workgroup (independent)
+constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit buffer, gfx9 family
+constexpr int kNonTemporal = 2;           // cache policy bits of a streaming store
+// Lane offset of rows that do not exist: it, its half, and either of them plus
+// any plane's offset lie beyond every column (NC * pitch * 8 < 2^31 bytes), so
+// loads give 0 and stores do nothing.
+constexpr unsigned kOutside = 0x80000000u;
+
+// orders the wave's own LDS accesses (no instruction)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t column_rsrc(const double* buf, const CGeom& g,
+                                                              int x) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(buf + x * g.cs), (short)0,
+                                           NC * g.pitch * 8u, kBufferWord3);
+}
+
+// coefficients of row `row_bytes / 16` of a column (zero where row_bytes is kOutside)
+__device__ __forceinline__ void load_column(__amdgpu_buffer_rsrc_t r, const CGeom& g,
+                                            unsigned row_bytes, double (&b)[NC]) {
+#pragma unroll
+  for (int m = 0; m < NC / 2; ++m) {
+    const v2d d = __builtin_bit_cast(
+        v2d, __builtin_amdgcn_raw_buffer_load_b128(r, row_bytes, m * g.pitch * 16u, 0));
+    b[2 * m] = d.x;
+    b[2 * m + 1] = d.y;
+  }
+  b[NC - 1] = __builtin_bit_cast(
+      double, __builtin_amdgcn_raw_buffer_load_b64(r, row_bytes >> 1, (NC - 1) * g.pitch * 8u, 0));
+}
+
+// Stores are streamed past the caches: the next step reads them only after
+// the whole lattice (kOutside: not stored).  The plane is added to the lane's
+// offset, not given as the scalar offset of the instruction: with a scalar
+// offset the compiler lets the next vector instruction overwrite the data of
+// a 16-byte store, which here changed the low word of a few stored values in
+// a million.
+__device__ __forceinline__ void store_column(__amdgpu_buffer_rsrc_t r, const CGeom& g,
+                                             unsigned row_bytes, const double (&b)[NC]) {
+#pragma unroll
+  for (int m = 0; m < NC / 2; ++m)
+    __builtin_amdgcn_raw_buffer_store_b128(
+        __builtin_bit_cast(v4u, (v2d{b[2 * m], b[2 * m + 1]})), r, row_bytes + m * g.pitch * 16u,
+        0, kNonTemporal);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, b[NC - 1]), r,
+                                        (row_bytes >> 1) + (NC - 1) * g.pitch * 8u, 0,
+                                        kNonTemporal);
+}
+
+// LDS of one wave: per target column six rows of 64 populations ((ex, +-k),
+// k = 1..3), with room for the lanes' shifts at both ends.
+constexpr int kSlot = 6 * 64;
+template <int TX>
+constexpr int kWaveLds = TX * kSlot + 2 * kHalo;
+
+template <class K>
+constexpr int kShift = 1;  // (ex, +k) arrives from the row k below its target
+template <>
+constexpr int kShift<Adjoint> = -1;  // the transposed hop
+
+template <class K, int ex>
+__device__ __forceinline__ void put_group(const double (&b)[NC], double* lds, int lane,
+                                          double& zero) {
+  Group f;
+  expand_group<K, ex>(b, f);
+  zero = f.zero;
+#pragma unroll
+  for (int k = 1; k <= reach(ex); ++k) {
+    lds[(2 * k - 2) * 64 + lane] = f.plus[k - 1];
+    lds[(2 * k - 1) * 64 + lane] = f.minus[k - 1];
+  }
+}
+template <class K, int ex>
+__device__ __forceinline__ void get_group(const double* lds, int lane, double zero, Group& f) {
+  f.zero = zero;
+#pragma unroll
+  for (int k = 1; k <= reach(ex); ++k) {
+    f.plus[k - 1] = lds[(2 * k - 2) * 64 + lane - kShift<K> * k];
+    f.minus[k - 1] = lds[(2 * k - 1) * 64 + lane + kShift<K> * k];
+  }
+}
+
+// Row of this lane: its index, whether it exists, its byte offset in a pair
+// plane for loads, and for stores (only the wave's own rows).
+struct Row {
+  int y;
+  bool in;
+  unsigned load, store;
+};
+__device__ __forceinline__ Row wave_row(const CGeom& g, int w, int lane) {
+  Row r;
+  r.y = w * kRows - kHalo + lane;
+  r.in = r.y >= 0 && r.y < g.ly;
+  int y = r.y;
+  if (g.periodic) {  // rows beyond the three that are read may fold anywhere
+    if (y < 0) y += g.ly;
+    if (y >= g.ly) y -= g.ly;
+    if (y < 0 || y >= g.ly) y = 0;
+  }
+  r.load = r.in || g.periodic ? unsigned(y) * 16u : kOutside;
+  r.store = r.in && lane >= kHalo && lane < kHalo + kRows ? unsigned(r.y) * 16u : kOutside;
+  return r;
+}
+
+// Wave of this workgroup: rows w, first column x0; false beyond the lattice.
+template <int TX>
+__device__ __forceinline__ bool wave_tile(const CGeom& g, unsigned nb, int& w, int& x0) {
+  const unsigned wave = unsigned(__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)));
+  const unsigned t = tile_index(nb) * kWaves + wave;
+  w = int(t % unsigned(g.nw));
+  x0 = int(t / unsigned(g.nw)) * TX;
+  return x0 < g.lx;
+}
+
+// The sweep of one wave.  Target t of the TX columns (in the order of the
+// walk) takes the e_x group t + 3 - j of source column j, so every target
+// receives its groups in the order 3, 2, .., -3.  Site: what is done with a
+// finished target (walls, local operator, store).
+template <class K, int TX, int kAhead, class Site>
+struct Sweep {
+  const double* src;
+  const CGeom& g;
+  const Site& site;
+  int x0, lane;
+  Row row;
+  double* lds;
+  double b[kAhead][NC];  // source columns in flight
+  double a[TX][NC];      // sums of the targets
+  double zero[TX];
+
+  __device__ __forceinline__ int source(int j) const {
+    int x = K::wdown(0) == 1.0 ? x0 - 3 + j : x0 + TX + 2 - j;
+    x = x < 0 ? x + g.lx : (x >= g.lx ? x - g.lx : x);
+    return x;  // (lx >= 6: one wrap reaches every column of a ragged last tile too)
+  }
+  __device__ __forceinline__ int target(int t) const {
+    return K::wdown(0) == 1.0 ? x0 + t : x0 + TX - 1 - t;
+  }
+  __device__ __forceinline__ void load(int j, double (&v)[NC]) {
+    load_column(column_rsrc(src, g, source(j)), g, row.load, v);
+  }
+  template <int j, int t>
+  __device__ __forceinline__ void put() {
+    if constexpr (t < TX) {
+      constexpr int ex = t + 3 - j;
+      if constexpr (ex >= -3 && ex <= 3)
+        put_group<K, ex>(b[j % kAhead], lds + t * kSlot, lane, zero[t]);
+      put<j, t + 1>();
+    }
+  }
+  template <int j, int t>
+  __device__ __forceinline__ void get() {
+    if constexpr (t < TX) {
+      constexpr int ex = t + 3 - j;
+      if constexpr (ex >= -3 && ex <= 3) {
+        Group f;
+        get_group<K, ex>(lds + t * kSlot, lane, zero[t], f);
+        project_group<K, ex>(f, a[t]);
+        // keeps the sums here: left to itself the compiler defers them to
+        // the end and holds every group of the target in registers (127
+        // instead of 87 VGPRs at TX = 1, spills from TX = 3)
+#pragma unroll
+        for (int k = 0; k < NC; ++k) asm volatile("" : "+v"(a[t][k]));
+      }
+      get<j, t + 1>();
+    }
+  }
+  template <int j>
+  __device__ __forceinline__ void walk() {
+    if constexpr (j < TX + 6) {
+      typename Site::Input in;
+      if constexpr (j >= 6) site.load(in, target(j - 6), row);
+      put<j, 0>();
+      // the next column's loads go out before this one's exchange and sums
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (j + kAhead < TX + 6) load(j + kAhead, b[j % kAhead]);
+      __builtin_amdgcn_sched_barrier(0);
+      wave_lds_fence();
+      get<j, 0>();
+      wave_lds_fence();
+      if constexpr (j >= 6) site.finish(in, a[j - 6], target(j - 6), row);
+      walk<j + 1>();
+    }
+  }
+  template <int j = 0>
+  __device__ __forceinline__ void prefetch() {
+    if constexpr (j < kAhead) {
+      load(j, b[j]);
+      prefetch<j + 1>();
+    }
+  }
+};
+
+// Forward: walls on the six wall rows, optional tape of the pre-collision
+// moments (rho, j_x, j_y, sum |c|^2 f), collide, store.
+template <bool kTape>
+struct StepSite {
+  double* dst;
+  const CGeom& g;
+  const Phys& P;
+  const WallTable& wt;
+  double* tape;
+  struct Input {};
+  __device__ __forceinline__ void load(Input&, int, const Row&) const {}
+  __device__ __forceinline__ void finish(const Input&, double (&a)[NC], int x,
+                                         const Row& r) const {
+    if (x >= g.lx) return;  // ragged last tile
+    int i;
+    if (r.in && wall_row(g, r.y, i)) wall_coeffs(a, wt, i);
+    if (kTape) {
+      if (r.store != kOutside) {
+        const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + r.y;
+        tape[s] = a[slot(0, 0)];
+        tape[S2 + s] = a[slot(1, 0)];
+        tape[2 * S2 + s] = a[slot(0, 1)];
+        tape[3 * S2 + s] = mad(2.0, a[slot(0, 0)], a[slot(2, 0)] + a[slot(0, 2)]);
+      }
+    }
+    collide_coeffs(a, P);
+    store_column(column_rsrc(dst, g, x), g, r.store, a);
+  }
+};
+
+// Adjoint: the step's moments from the tape, C^T and B^T, store.
+struct AdjointSite {
+  double* dst;
+  const CGeom& g;
+  const Phys& P;
+  const WallTable& wt;
+  const double* tape;
+  struct Input {
+    double m[4];
+  };
+  __device__ __forceinline__ void load(Input& in, int x, const Row& r) const {
+    const bool ok = x < g.lx && r.in;
+    const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + r.y;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) in.m[k] = ok ? tape[k * S2 + s] : 1.0;
+  }
+  __device__ __forceinline__ void finish(const Input& in, double (&a)[NC], int x,
+                                         const Row& r) const {
+    if (x >= g.lx) return;
+    adjoint_coeffs(a, in.m[0], in.m[1], in.m[2], in.m[3], P);
+    int i;
+    if (r.in && wall_row(g, r.y, i)) wall_adjoint(a, wt, i);
+    store_column(column_rsrc(dst, g, x), g, r.store, a);
+  }
+};
+
+template <int TX, int kAhead, bool kTape>
+__global__ __launch_bounds__(64 * kWaves, TX == 2 ? 4 : 2) void k_coeff_step(
+    const double* __restrict__ src, double* __restrict__ dst, CGeom g, Phys P, WallTable wt,
+    double* __restrict__ tape, unsigned nb, const unsigned* guard, unsigned* word) {
+  __shared__ double lds[kWaves][kWaveLds<TX>];
+  if (other_form(guard, kFormCoeff)) return;
+  set_form(word, kFormCoeff);
+  int w, x0;
+  if (!wave_tile<TX>(g, nb, w, x0)) return;
+  const int lane = threadIdx.x & 63;
+  const StepSite<kTape> site{dst, g, P, wt, tape};
+  Sweep<Forward, TX, kAhead, StepSite<kTape>> s{
+      src, g, site, x0, lane, wave_row(g, w, lane), &lds[threadIdx.x >> 6][kHalo]};
+  s.prefetch();
+  s.template walk<0>();
+}
+
+template <int TX, int kAhead>
+__global__ __launch_bounds__(64 * kWaves, TX == 2 ? 3 : 2) void k_coeff_adjoint(
+    const double* __restrict__ tape, const double* __restrict__ src, double* __restrict__ dst,
+    CGeom g, Phys P, WallTable wt, unsigned nb) {
+  __shared__ double lds[kWaves][kWaveLds<TX>];
+  int w, x0;
+  if (!wave_tile<TX>(g, nb, w, x0)) return;
+  const int lane = threadIdx.x & 63;
+  const AdjointSite site{dst, g, P, wt, tape};
+  Sweep<Adjoint, TX, kAhead, AdjointSite> s{
+      src, g, site, x0, lane, wave_row(g, w, lane), &lds[threadIdx.x >> 6][kHalo]};
+  s.prefetch();
+  s.template walk<0>();
+}
+
+// ---------------------------------------------------------------------------
+// Site kernels: one thread per site.
+// ---------------------------------------------------------------------------
+
+__device__ __forceinline__ void load_coeffs(const double* __restrict__ src, const CGeom& g, int x,
+                                            int y, double (&b)[NC]) {
+  const double* col = src + x * g.cs;
+#pragma unroll
+  for (int m = 0; m < NC / 2; ++m) {
+    const v2d d = *reinterpret_cast<const v2d*>(col + 2 * m * (long long)g.pitch + 2 * y);
+    b[2 * m] = d.x;
+    b[2 * m + 1] = d.y;
+  }
+  b[NC - 1] = col[(NC - 1) * (long long)g.pitch + y];
+}
+__device__ __forceinline__ void store_coeffs(double* __restrict__ dst, const CGeom& g, int x,
+                                             int y, const double (&b)[NC]) {
+  double* col = dst + x * g.cs;
+#pragma unroll
+  for (int m = 0; m < NC / 2; ++m)
+    __builtin_nontemporal_store(
+        (v2d{b[2 * m], b[2 * m + 1]}),
+        reinterpret_cast<v2d*>(col + 2 * m * (long long)g.pitch + 2 * y));
+  __builtin_nontemporal_store(b[NC - 1], &col[(NC - 1) * (long long)g.pitch + y]);
+}
+
+__device__ __forceinline__ Macro load_macro(const double* __restrict__ src, const CGeom& g, int x,
+                                            int y) {
+  const double* col = src + x * g.cs + 2 * y;
+  const v2d u = *reinterpret_cast<const v2d*>(col);
+  const v2d v = *reinterpret_cast<const v2d*>(col + 2 * (long long)g.pitch);
+  const double w = col[4 * (long long)g.pitch];
+  return macro_coeffs(u.x, u.y, v.x, v.y, w);
+}
+
+// adjoint arrays are compact, in the lattice's layout
+struct LamAt {
+  long long ps, cs;
+};
+__device__ __forceinline__ LamAt lam_at(const Geom& g) {
+  const long long s2 = (long long)g.lx * g.ly;
+  return g.ps < g.cs ? LamAt{g.ly, (long long)Q * g.ly} : LamAt{s2, g.ly};
+}
+
+// The step from the 37 stored populations of a padded buffer: gather, walls,
+// collide, coefficients out (296 bytes in, 120 out per site; runs once after
+// the state was replaced).  x wraps here, so the halo columns are not read.
+template <bool kTape>
+__global__ __launch_bounds__(kThreads) void k_coeff_first(
+    const double* __restrict__ src, double* __restrict__ dst, Geom gf, CGeom g, Phys P, WallTable wt,
+    double* __restrict__ tape, int by, int bx, int nty, unsigned nb,
+    const unsigned* guard, unsigned* word) {
+  if (other_form(guard, kFormFull)) return;
+  set_form(word, kFormCoeff);
+  int x, y;
+  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
+  double v[Q];
+#pragma unroll
+  for (int l = 0; l < Q; ++l) {
+    int xs = x - EX[l], ys = y - EY[l];
+    xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
+    const bool outside = ys < 0 || ys >= g.ly;
+    if (g.periodic)
+      ys = ys < 0 ? ys + g.ly : (ys >= g.ly ? ys - g.ly : ys);
+    else if (outside)
+      ys = y;
+    v[l] = src[l * gf.ps + (long long)(xs + HX) * gf.cs + ys + gf.hy];
+    if (!g.periodic && outside) v[l] = 0.0;  // a wall supplies it
+  }
+  double a[NC];
+  project_site<Forward>(v, a);
+  int i;
+  if (wall_row(g, y, i)) wall_coeffs(a, wt, i);
+  if (kTape) {
+    const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + y;
+    tape[s] = a[slot(0, 0)];
+    tape[S2 + s] = a[slot(1, 0)];
+    tape[2 * S2 + s] = a[slot(0, 1)];
+    tape[3 * S2 + s] = mad(2.0, a[slot(0, 0)], a[slot(2, 0)] + a[slot(0, 2)]);
+  }
+  collide_coeffs(a, P);
+  store_coeffs(dst, g, x, y, a);
+}
+
+// f^eq(rho0, u0, T0) as coefficients.
+__global__ __launch_bounds__(kThreads) void k_coeff_init(
+    double* __restrict__ dst, const double* __restrict__ rho, const double* __restrict__ ux,
+    const double* __restrict__ uy, const double* __restrict__ T, CGeom g, int by, int bx, int nty,
+    unsigned nb, unsigned* word) {
+  set_form(word, kFormCoeff);
+  int x, y;
+  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
+  const long long s = (long long)x * g.ly + y;
+  double aeq[5][5], b[NC];
+  equilibrium_coeffs(rho[s], ux[s], uy[s], T[s] - 1.0, aeq);
+#pragma unroll
+  for (int k = 0; k < NC; ++k) b[k] = aeq[kCP[k]][kCQ[k]];
+  b[0] = rho[s];
+  store_coeffs(dst, g, x, y, b);
+}
+
+// The 37 populations into a padded buffer, its halos with them.
+__global__ __launch_bounds__(kThreads) void k_coeff_expand(const double* __restrict__ src,
+                                                           double* __restrict__ dst, CGeom g,
+                                                           Geom gf, int by, int bx, int nty,
+                                                           unsigned nb) {
+  set_form(dst, kFormFull);
+  int x, y;
+  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
+  double b[NC], v[Q];
+  load_coeffs(src, g, x, y, b);
+  expand_site<Forward>(b, v);
+#pragma unroll 1
+  for (int cx = -1; cx <= 1; ++cx) {
+    const int X = x + HX + cx * g.lx;
+    if (X < 0 || X >= gf.nx) continue;
+#pragma unroll 1
+    for (int cy = g.periodic ? -1 : 0; cy <= (g.periodic ? 1 : 0); ++cy) {
+      const int Y = y + cy * g.ly;
+      if (Y < -3 || Y >= g.ly + 3) continue;
+      const long long s = (long long)X * gf.cs + Y + gf.hy;
+#pragma unroll
+      for (int l = 0; l < Q; ++l) dst[l * gf.ps + s] = v[l];
+    }
+  }
+}
+
+// The 37 populations in compact form [37][lx][ly].
+__global__ __launch_bounds__(kThreads) void k_coeff_pack(const double* __restrict__ src,
+                                                         double* __restrict__ out, CGeom g,
+                                                         int by, int bx, int nty, unsigned nb,
+                                                         const unsigned* guard) {
+  if (other_form(guard, kFormCoeff)) return;
+  int x, y;
+  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
+  double b[NC], v[Q];
+  load_coeffs(src, g, x, y, b);
+  expand_site<Forward>(b, v);
+  const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + y;
+#pragma unroll
+  for (int l = 0; l < Q; ++l) __builtin_nontemporal_store(v[l], &out[l * S2 + s]);
+}
+
+// Eq. (2) fields: five coefficients in, four values out (72 bytes per site).
+__global__ __launch_bounds__(kThreads) void k_coeff_moments(
+    const double* __restrict__ src, double* __restrict__ rho, double* __restrict__ ux,
+    double* __restrict__ uy, double* __restrict__ T, CGeom g, int by, int bx, int nty,
+    unsigned nb, const unsigned* guard) {
+  if (other_form(guard, kFormCoeff)) return;
+  int x, y;
+  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
+  const Macro m = load_macro(src, g, x, y);
+  const long long s = (long long)x * g.ly + y;
+  if (rho) rho[s] = m.rho;
+  if (ux) ux[s] = m.ux;
+  if (uy) uy[s] = m.uy;
+  if (T) T[s] = 1.0 + m.th;
+}
+
+__global__ __launch_bounds__(kThreads) void k_coeff_check(const double* __restrict__ src,
+                                                          unsigned* __restrict__ flag, CGeom g,
+                                                          int by, int bx, int nty, unsigned nb,
+                                                          const unsigned* guard) {
+  if (other_form(guard, kFormCoeff)) return;
+  int x, y;
+  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
+  double b[NC], v[Q];
+  load_coeffs(src, g, x, y, b);
+  expand_site<Forward>(b, v);
+  bool bad = false;
+#pragma unroll
+  for (int l = 0; l < Q; ++l) bad |= !isfinite(v[l]);
+  const Macro m = load_macro(src, g, x, y);
+  bad |= !(m.rho > 0.0) || !(1.0 + m.th > 0.0);
+  if (bad) atomicAdd(flag, 1u);
+}
+
+// As k_obs_rows, from the coefficients.
+__global__ __launch_bounds__(kThreads) void k_coeff_obs_rows(const double* __restrict__ src,
+                                                             double* __restrict__ partial,
+                                                             CGeom g, int nchunks,
+                                                             const unsigned* guard) {
+  if (other_form(guard, kFormCoeff)) return;
+  const int y = blockIdx.x * kThreads + threadIdx.x;
+  const int c = blockIdx.y;
+  if (y >= g.ly) return;
+  const int x0 = int((long long)g.lx * c / nchunks), x1 = int((long long)g.lx * (c + 1) / nchunks);
+  double acc[kObservables] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int x = x0; x < x1; ++x) {
+    const Macro m = load_macro(src, g, x, y);
+    const double T = 1.0 + m.th;
+    acc[0] += m.rho;
+    acc[1] += m.ux;
+    acc[2] += m.uy;
+    acc[3] += T;
+    acc[4] += 0.5 * m.rho * (m.ux * m.ux + m.uy * m.uy);
+    acc[5] += m.rho * T;
+  }
+#pragma unroll
+  for (int k = 0; k < kObservables; ++k)
+    partial[((long long)c * kObservables + k) * g.ly + y] = acc[k];
+}
+
+// As k_loss_ke, from the coefficients.
+__global__ __launch_bounds__(kThreads) void k_coeff_loss_ke(const double* __restrict__ src,
+                                                            double* __restrict__ lambda,
+                                                            double* __restrict__ partials,
+                                                            CGeom g, Geom gf, int by, int bx,
+                                                            int nty, unsigned nb,
+                                                            const unsigned* guard) {
+  if (other_form(guard, kFormCoeff)) return;
+  int x, y;
+  double ke = 0.0;
+  if (site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) {
+    const Macro m = load_macro(src, g, x, y);
+    const double u2 = m.ux * m.ux + m.uy * m.uy;
+    ke = 0.5 * m.rho * u2;
+    if (lambda) {
+      const LamAt la = lam_at(gf);
+      const long long s = x * la.cs + y;
+#pragma unroll
+      for (int l = 0; l < Q; ++l)
+        __builtin_nontemporal_store(R * (EX[l] * m.ux + EY[l] * m.uy) - 0.5 * u2,
+                                    &lambda[l * la.ps + s]);
+    }
+  }
+  const double tot = block_sum(ke);
+  if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+}
+
+// ---------------------------------------------------------------------------
+// Adjoint: way in, way out, and the single step on compact arrays.
+// ---------------------------------------------------------------------------
+
+// B_pq of one site whose arriving lambda are given
+__device__ __forceinline__ void adjoint_local(const double (&lam)[Q], const double* tape,
+                                              long long S2, long long s, const CGeom& g,
+                                              const Phys& P, const WallTable& wt, int y,
+                                              double (&B)[NC]) {
+  project_site<Adjoint>(lam, B);
+  adjoint_coeffs(B, tape[s], tape[S2 + s], tape[2 * S2 + s], tape[3 * S2 + s], P);
+  int i;
+  if (wall_row(g, y, i)) wall_adjoint(B, wt, i);
+}
+
+// First kernel of a run: compact lambda in, coefficients of mu out.
+__global__ __launch_bounds__(kThreads) void k_coeff_adjoint_first(
+    const double* __restrict__ tape, const double* __restrict__ lam, double* __restrict__ dst,
+    Geom gf, CGeom g, Phys P, WallTable wt, int by, int bx, int nty, unsigned nb) {
+  int x, y;
+  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
+  const LamAt la = lam_at(gf);
+  const long long sl = x * la.cs + y;
+  double v[Q], B[NC];
+#pragma unroll
+  for (int l = 0; l < Q; ++l) v[l] = lam[l * la.ps + sl];
+  adjoint_local(v, tape, (long long)g.lx * g.ly, (long long)x * g.ly + y, g, P, wt, y, B);
+  store_coeffs(dst, g, x, y, B);
+}
+
+// Last kernel of a run: lambda_l(z) = mu_l(z + e_l), rebuilt from the source
+// site's coefficients and passed to its row as in the sweep.
+template <int ex>
+__device__ __forceinline__ void export_groups(const double* src, double* lam, const CGeom& g,
+                                              const LamAt& la, int x, int lane, const Row& r,
+                                              double* lds) {
+  int xs = x + ex;
+  xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
+  double b[NC], zero;
+  load_column(column_rsrc(src, g, xs), g, r.load, b);
+  put_group<Adjoint, ex>(b, lds, lane, zero);
+  wave_lds_fence();
+  Group f;
+  get_group<Adjoint, ex>(lds, lane, zero, f);
+  wave_lds_fence();
+  if (r.store != kOutside) {
+    double* out = lam + x * la.cs + r.y;
+    __builtin_nontemporal_store(f.zero, &out[label(ex, 0) * la.ps]);
+#pragma unroll
+    for (int k = 1; k <= reach(ex); ++k) {
+      __builtin_nontemporal_store(f.plus[k - 1], &out[label(ex, k) * la.ps]);
+      __builtin_nontemporal_store(f.minus[k - 1], &out[label(ex, -k) * la.ps]);
+    }
+  }
+  if constexpr (ex > -3) export_groups<ex - 1>(src, lam, g, la, x, lane, r, lds);
+}
+
+__global__ __launch_bounds__(64 * kWaves) void k_coeff_adjoint_last(
+    const double* __restrict__ src, double* __restrict__ lam, CGeom g, Geom gf, unsigned nb) {
+  __shared__ double lds[kWaves][kWaveLds<1>];
+  int w, x;
+  if (!wave_tile<1>(g, nb, w, x)) return;
+  const int lane = threadIdx.x & 63;
+  export_groups<3>(src, lam, g, lam_at(gf), x, lane, wave_row(g, w, lane),
+                   &lds[threadIdx.x >> 6][kHalo]);
+}
+
+// One transposed step on compact arrays: aligned reads, every component
+// written to the site it was propagated from; populations that leave through
+// a wall are written as zero by their own site.
+__global__ __launch_bounds__(kThreads) void k_coeff_adjoint_step(
+    const double* __restrict__ tape, const double* __restrict__ lam_in,
+    double* __restrict__ lam_out, Geom gf, CGeom g, Phys P, WallTable wt, int by, int bx, int nty,
+    unsigned nb) {
+  int x, y;
+  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
+  const LamAt la = lam_at(gf);
+  const long long sl = x * la.cs + y;
+  double v[Q], B[NC];
+#pragma unroll
+  for (int l = 0; l < Q; ++l) v[l] = lam_in[l * la.ps + sl];
+  adjoint_local(v, tape, (long long)g.lx * g.ly, (long long)x * g.ly + y, g, P, wt, y, B);
+  expand_site<Adjoint>(B, v);
+#pragma unroll
+  for (int l = 0; l < Q; ++l) {
+    int ys = y - EY[l];
+    if (!g.periodic && (ys < 0 || ys >= g.ly)) continue;
+    if (g.periodic) ys += ys < 0 ? g.ly : (ys >= g.ly ? -g.ly : 0);
+    int xs = x - EX[l];
+    xs += xs < 0 ? g.lx : (xs >= g.lx ? -g.lx : 0);
+    lam_out[l * la.ps + xs * la.cs + ys] = v[l];
+  }
+  int i;
+  if (wall_row(g, y, i)) {
+#pragma unroll
+    for (int l = 0; l < Q; ++l) {
+      const int yd = y + EY[l];
+      if (yd < 0 || yd >= g.ly) lam_out[l * la.ps + sl] = 0.0;
+    }
+  }
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------------------
+// Launchers.  Buffers are whole state buffers: a word that names the form,
+// then (256 bytes in) the coefficients.
+// ---------------------------------------------------------------------------
+
+namespace {
+
+CGeom make_cgeom(const Geom& g) {
+  CGeom c;
+  c.lx = g.lx;
+  c.ly = g.ly;
+  c.periodic = !g.walls;
+  c.nw = (g.ly + kRows - 1) / kRows;
+  c.pitch = unsigned((g.ly + 31) / 32 * 32);
+  c.cs = (long long)NC * c.pitch;
+  return c;
+}
+
+constexpr int kDataOffset = 32;  // doubles
+const double* coeffs(const void* buf) { return static_cast<const double*>(buf) + kDataOffset; }
+double* coeffs(void* buf) { return static_cast<double*>(buf) + kDataOffset; }
+unsigned* word_of(void* buf) { return static_cast<unsigned*>(buf); }
+// the word to check where the host does not know the form
+const unsigned* guard_of(const void* buf, const Geom& g) {
+  return g.form == kFormUnknown ? static_cast<const unsigned*>(buf) : nullptr;
+}
+
+// workgroups of a sweep with TX columns per wave
+unsigned sweep_grid(const CGeom& g, int tx) {
+  const long long waves = (long long)g.nw * ((g.lx + tx - 1) / tx);
+  return unsigned((waves + kWaves - 1) / kWaves);
+}
+
+// Columns per wave: the largest that still gives every SIMD its waves.
+int sweep_columns(const CGeom& g) {
+  const long long cols = (long long)g.nw * g.lx;
+  return cols >= 4 * 4096 ? 4 : cols >= 2048 ? 2 : 1;
+}
+
+}  // namespace
+
+hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const Phys& p,
+                             double* tape, hipStream_t s) {
+  const CGeom g = make_cgeom(gf);
+  const WallTable wt = make_walls(p);
+  const unsigned* guard = guard_of(src, gf);
+  if (gf.form != kFormCoeff) {  // the populations are stored, or may be
+    const Tiling t = make_tiling(g.lx, g.ly);
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(t.nb), dim3(kThreads), 0, s,
+                         static_cast<const double*>(src), coeffs(dst), gf, g, p, wt, tape, t.by, t.bx,
+                         t.nty, t.nb, guard, word_of(dst));
+    };
+    tape ? run(k_coeff_first<true>) : run(k_coeff_first<false>);
+  }
+  if (gf.form != kFormFull) {
+    const int tx = sweep_columns(g);
+    const unsigned nb = sweep_grid(g, tx);
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * kWaves), 0, s, coeffs(src), coeffs(dst), g, p, wt,
+                         tape, nb, guard, word_of(dst));
+    };
+    if (tx == 4)
+      tape ? run(k_coeff_step<4, 2, true>) : run(k_coeff_step<4, 2, false>);
+    else if (tx == 2)
+      tape ? run(k_coeff_step<2, 1, true>) : run(k_coeff_step<2, 1, false>);
+    else
+      tape ? run(k_coeff_step<1, 7, true>) : run(k_coeff_step<1, 7, false>);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_init(void* dst, const double* rho, const double* ux, const double* uy,
+                             const double* T, const Geom& gf, hipStream_t s) {
+  const Tiling t = make_tiling(gf.lx, gf.ly);
+  hipLaunchKernelGGL(k_coeff_init, dim3(t.nb), dim3(kThreads), 0, s, coeffs(dst), rho, ux, uy, T,
+                     make_cgeom(gf), t.by, t.bx, t.nty, t.nb, word_of(dst));
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_expand(const void* src, void* dst, const Geom& gf, hipStream_t s) {
+  const Tiling t = make_tiling(gf.lx, gf.ly);
+  hipLaunchKernelGGL(k_coeff_expand, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src),
+                     static_cast<double*>(dst), make_cgeom(gf), gf, t.by, t.bx, t.nty, t.nb);
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_pack(const void* src, double* out, const Geom& gf, hipStream_t s) {
+  const Tiling t = make_tiling(gf.lx, gf.ly);
+  hipLaunchKernelGGL(k_coeff_pack, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src), out,
+                     make_cgeom(gf), t.by, t.bx, t.nty, t.nb, guard_of(src, gf));
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_moments(const void* src, double* rho, double* ux, double* uy, double* T,
+                                const Geom& gf, hipStream_t s) {
+  const Tiling t = make_tiling(gf.lx, gf.ly);
+  hipLaunchKernelGGL(k_coeff_moments, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src), rho, ux, uy,
+                     T, make_cgeom(gf), t.by, t.bx, t.nty, t.nb, guard_of(src, gf));
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_check(const void* src, unsigned* flag, const Geom& gf, hipStream_t s) {
+  const Tiling t = make_tiling(gf.lx, gf.ly);
+  hipLaunchKernelGGL(k_coeff_check, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src), flag,
+                     make_cgeom(gf), t.by, t.bx, t.nty, t.nb, guard_of(src, gf));
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_obs_rows(const void* src, double* partial, const Geom& gf, int nchunks,
+                                 hipStream_t s) {
+  hipLaunchKernelGGL(k_coeff_obs_rows, dim3(grid_1d(gf.ly), nchunks), dim3(kThreads), 0, s,
+                     coeffs(src), partial, make_cgeom(gf), nchunks, guard_of(src, gf));
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_loss_ke(const void* src, double* lambda, double* partials, const Geom& gf,
+                                hipStream_t s) {
+  const Tiling t = make_tiling(gf.lx, gf.ly);
+  hipLaunchKernelGGL(k_coeff_loss_ke, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src), lambda,
+                     partials, make_cgeom(gf), gf, t.by, t.bx, t.nty, t.nb, guard_of(src, gf));
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_adjoint_mu(const double* tape, const double* in, bool from_compact,
+                                   double* mu_out, const Geom& gf, const Phys& p, hipStream_t s) {
+  const CGeom g = make_cgeom(gf);
+  const WallTable wt = make_walls(p);
+  if (from_compact) {
+    const Tiling t = make_tiling(g.lx, g.ly);
+    hipLaunchKernelGGL(k_coeff_adjoint_first, dim3(t.nb), dim3(kThreads), 0, s, tape, in,
+                       coeffs(static_cast<void*>(mu_out)), gf, g, p, wt, t.by, t.bx, t.nty, t.nb);
+    return hipGetLastError();
+  }
+  const int tx = sweep_columns(g);
+  const unsigned nb = sweep_grid(g, tx);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * kWaves), 0, s, tape, coeffs(static_cast<const void*>(in)),
+                       coeffs(static_cast<void*>(mu_out)), g, p, wt, nb);
+  };
+  if (tx == 4)
+    run(k_coeff_adjoint<4, 1>);
+  else if (tx == 2)
+    run(k_coeff_adjoint<2, 1>);
+  else
+    run(k_coeff_adjoint<1, 7>);
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_adjoint_gather(const double* mu, double* lam, const Geom& gf,
+                                       hipStream_t s) {
+  const CGeom g = make_cgeom(gf);
+  const unsigned nb = sweep_grid(g, 1);
+  hipLaunchKernelGGL(k_coeff_adjoint_last, dim3(nb), dim3(64 * kWaves), 0, s, coeffs(static_cast<const void*>(mu)), lam, g,
+                     gf, nb);
+  return hipGetLastError();
+}
+
+hipError_t launch_coeff_adjoint_step(const double* tape, const double* lam_in, double* lam_out,
+                                     const Geom& gf, const Phys& p, hipStream_t s) {
+  const Tiling t = make_tiling(gf.lx, gf.ly);
+  hipLaunchKernelGGL(k_coeff_adjoint_step, dim3(t.nb), dim3(kThreads), 0, s, tape, lam_in, lam_out,
+                     gf, make_cgeom(gf), p, make_walls(p), t.by, t.bx, t.nty, t.nb);
+  return hipGetLastError();
+}
+
+}  // namespace d2q37

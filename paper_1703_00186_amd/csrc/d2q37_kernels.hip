@@ -13,48 +13,11 @@
 #include <type_traits>
 
 #include "d2q37_launch.h"
+#include "d2q37_tiles.h"
 
 namespace d2q37 {
 
 namespace {
-
-constexpr int kThreads = 256;
-constexpr int kXcds = 8;
-
-struct Tiling {
-  int by, bx;    // tile shape (rows, columns)
-  int nty, ntx;  // tiles along y and x
-  unsigned nb;   // total tiles
-};
-
-Tiling make_tiling(int lx, int ly) {
-  Tiling t;
-  t.by = ly > 128 ? 256 : (ly > 64 ? 128 : 64);
-  t.bx = kThreads / t.by;
-  t.nty = (ly + t.by - 1) / t.by;
-  t.ntx = (lx + t.bx - 1) / t.bx;
-  t.nb = unsigned(t.nty) * unsigned(t.ntx);
-  return t;
-}
-
-// Tile of this workgroup after the XCD-aware remap (a bijection of [0, nb)).
-__device__ __forceinline__ unsigned tile_index(unsigned nb) {
-  const unsigned b = blockIdx.x;
-  const unsigned q = nb / kXcds, rem = nb % kXcds;
-  const unsigned xcd = b % kXcds, j = b / kXcds;
-  return xcd * q + (xcd < rem ? xcd : rem) + j;
-}
-
-// Physical (x, y) of this thread; false if it falls outside the lattice.
-__device__ __forceinline__ bool site_of(const Geom& g, int by, int bx, int nty, unsigned nb,
-                                        int& x, int& y) {
-  const unsigned t = tile_index(nb);
-  const int ty = int(t % unsigned(nty)), tx = int(t / unsigned(nty));
-  const int lin = threadIdx.x;
-  y = ty * by + (lin % by);
-  x = tx * bx + (lin / by);
-  return x < g.lx && y < g.ly;
-}
 
 template <class S>
 __device__ __forceinline__ long long padded(const Geom& g, int X, int Y) {
@@ -312,14 +275,18 @@ __global__ __launch_bounds__(kThreads) void k_bc(S* __restrict__ buf, Geom g, Ph
   }
 }
 
-// Halo columns: X in [0, 3) <- X + lx, X in [lx + 3, lx + 6) <- X - lx, all rows.
+// Halo columns: X in [0, 3) <- X + lx, X in [lx + 3, lx + 6) <- X - lx, the
+// rows that a gather reads (the first padding word names the buffer's form).
 template <class S>
-__global__ __launch_bounds__(kThreads) void k_halo_x(S* __restrict__ buf, Geom g) {
+__global__ __launch_bounds__(kThreads) void k_halo_x(S* __restrict__ buf, Geom g,
+                                                     const unsigned* guard) {
+  if (other_form(guard, kFormFull)) return;
   const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-  const long long per_l = 6LL * g.ny;
+  const int rows = g.ly + 6;  // all that a gather reads
+  const long long per_l = 6LL * rows;
   if (i >= per_l * g.np) return;
   const int l = int(i / per_l);
-  const int c = int((i % per_l) / g.ny), Y = int(i % g.ny);
+  const int c = int((i % per_l) / rows), Y = int(i % rows) + g.hy - 3;
   const int Xd = c < 3 ? c : g.lx + c;
   const int Xs = c < 3 ? g.lx + c : c;
   buf[l * g.ps + (long long)Xd * g.cs + Y] = buf[l * g.ps + (long long)Xs * g.cs + Y];
@@ -327,7 +294,9 @@ __global__ __launch_bounds__(kThreads) void k_halo_x(S* __restrict__ buf, Geom g
 
 // Halo rows (periodic y only): three rows below and above, all padded columns.
 template <class S>
-__global__ __launch_bounds__(kThreads) void k_halo_y(S* __restrict__ buf, Geom g) {
+__global__ __launch_bounds__(kThreads) void k_halo_y(S* __restrict__ buf, Geom g,
+                                                     const unsigned* guard) {
+  if (other_form(guard, kFormFull)) return;
   const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
   const long long per_l = 6LL * g.nx;
   if (i >= per_l * g.np) return;
@@ -407,7 +376,9 @@ __global__ __launch_bounds__(kThreads) void k_moments(const S* __restrict__ src,
                                                       double* __restrict__ ux,
                                                       double* __restrict__ uy,
                                                       double* __restrict__ T, Geom g, Phys P,
-                                                      int by, int bx, int nty, unsigned nb) {
+                                                      int by, int bx, int nty, unsigned nb,
+                                                      const unsigned* guard) {
+  if (other_form(guard, kFormFull)) return;
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
   const Macro m = site_macro<S, A>(src, g, padded<S>(g, x + HX, y + g.hy), P.rho_ref);
@@ -422,7 +393,8 @@ template <class S, class A>
 __global__ __launch_bounds__(kThreads) void k_check(const S* __restrict__ src,
                                                     unsigned int* __restrict__ flag, Geom g,
                                                     Phys P, int by, int bx, int nty,
-                                                    unsigned nb) {
+                                                    unsigned nb, const unsigned* guard) {
+  if (other_form(guard, kFormFull)) return;
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
   const long long site = padded<S>(g, x + HX, y + g.hy);
@@ -466,7 +438,8 @@ __device__ __forceinline__ CompactSite compact_site(const Geom& g, unsigned nyb)
 template <class S>
 __global__ __launch_bounds__(kThreads) void k_pack(const S* __restrict__ padded_buf,
                                                    S* __restrict__ compact, Geom g,
-                                                   unsigned nyb) {
+                                                   unsigned nyb, const unsigned* guard) {
+  if (other_form(guard, kFormFull)) return;
   const CompactSite c = compact_site(g, nyb);
   if (c.in) __builtin_nontemporal_store(padded_buf[c.padded], &compact[c.compact]);
 }
@@ -475,6 +448,7 @@ template <class S>
 __global__ __launch_bounds__(kThreads) void k_unpack(const S* __restrict__ compact,
                                                      S* __restrict__ padded_buf, Geom g,
                                                      unsigned nyb) {
+  set_form(padded_buf, kFormFull);
   const CompactSite c = compact_site(g, nyb);
   if (c.in) __builtin_nontemporal_store(compact[c.compact], &padded_buf[c.padded]);
 }
@@ -482,7 +456,9 @@ __global__ __launch_bounds__(kThreads) void k_unpack(const S* __restrict__ compa
 template <class S, class A>
 __global__ __launch_bounds__(kThreads) void k_populations_f64(const S* __restrict__ padded_buf,
                                                               double* __restrict__ out, Geom g,
-                                                              double rho_ref, unsigned nyb) {
+                                                              double rho_ref, unsigned nyb,
+                                                              const unsigned* guard) {
+  if (other_form(guard, kFormFull)) return;
   const CompactSite c = compact_site(g, nyb);
   if (!c.in) return;
   if constexpr (is_local<A>) {
@@ -510,24 +486,13 @@ __global__ __launch_bounds__(kThreads) void k_zero(unsigned int* __restrict__ p,
 // Adjoint.
 // ---------------------------------------------------------------------------
 
-// Block-wide sum of one double per thread; result valid in thread 0.
-__device__ __forceinline__ double block_sum(double v) {
-  __shared__ double red[kThreads];
-  red[threadIdx.x] = v;
-  __syncthreads();
-#pragma unroll
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  return red[0];
-}
-
 // KE = (1/2) sum rho |u|^2; dKE/df_l = c_l . u - |u|^2 / 2.
 __global__ __launch_bounds__(kThreads) void k_loss_ke(const double* __restrict__ src,
                                                       double* __restrict__ lambda,
                                                       double* __restrict__ partials, Geom g,
-                                                      int by, int bx, int nty, unsigned nb) {
+                                                      int by, int bx, int nty, unsigned nb,
+                                                      const unsigned* guard) {
+  if (other_form(guard, kFormFull)) return;
   int x, y;
   const bool in = site_of(g, by, bx, nty, nb, x, y);
   double ke = 0.0;
@@ -597,11 +562,11 @@ __device__ __forceinline__ void adjoint_project(const double (&lam)[Q], double (
 }
 
 // lambda_out = P^T B^T C^T lambda_in for one step (scatter form).
+// Plain BGK (the Hermite-projected collision's adjoint is in d2q37_coeff.hip):
 // B^T C(m)^T of one site: lam holds lambda^{j+1} at the site's arriving
 // populations, m = (rho, j_x, j_y, sum |c|^2 f) the pre-collision moments of
 // step j; on return mu holds the adjoint of the propagated populations
 // (zero for those a wall supplied).
-template <bool kReg>
 __device__ __forceinline__ void adjoint_site(const double (&lam)[Q], double rho, double jx,
                                              double jy, double e, const Geom& g, const Phys& P,
                                              int y, double (&mu)[Q]) {
@@ -628,17 +593,15 @@ __device__ __forceinline__ void adjoint_site(const double (&lam)[Q], double rho,
 #pragma unroll
   for (int p = 0; p < 5; ++p)
 #pragma unroll
-    for (int q = 0; q + p < 5; ++q) B[p][q] = kReg ? keep * L[p][q] : 0.0;
+    for (int q = 0; q + p < 5; ++q) B[p][q] = 0.0;
   B[0][0] += g00;
   B[1][0] += g10;
   B[0][1] += g01;
   B[2][0] += ge2;
   B[0][2] += ge2;
   expand<double>(B, mu);
-  if (!kReg) {
 #pragma unroll
-    for (int l = 0; l < Q; ++l) mu[l] += keep * lam[l];
-  }
+  for (int l = 0; l < Q; ++l) mu[l] += keep * lam[l];
   // B^T: on wall rows the unknown populations were rho_w v_l with
   // rho_w = sum_K f / sum_K v.
   if (on_wall_rows(g, y)) {
@@ -664,7 +627,6 @@ __device__ __forceinline__ void adjoint_site(const double (&lam)[Q], double rho,
   }
 }
 
-template <bool kReg>
 __global__ __launch_bounds__(kThreads) void k_adjoint(const double* __restrict__ tape,
                                                       const double* __restrict__ lam_in,
                                                       double* __restrict__ lam_out, Geom g,
@@ -680,7 +642,7 @@ __global__ __launch_bounds__(kThreads) void k_adjoint(const double* __restrict__
 #pragma unroll
   for (int l = 0; l < Q; ++l) lam[l] = lam_in[l * ls.ps + sl];
   double mu[Q];
-  adjoint_site<kReg>(lam, tape[s], tape[S2 + s], tape[2 * S2 + s], tape[3 * S2 + s], g, P, y,
+  adjoint_site(lam, tape[s], tape[S2 + s], tape[2 * S2 + s], tape[3 * S2 + s], g, P, y,
                      mu);
   // P^T: the population that arrived here came from (x - e_lx, y - e_ly).
 #pragma unroll
@@ -710,7 +672,7 @@ __global__ __launch_bounds__(kThreads) void k_adjoint(const double* __restrict__
 // lambda^j_l(z) = mu^j_l(z + e_l).  So every load is a shifted coalesced read
 // and every store is aligned, as in the forward step.  kFromCompact: the
 // first kernel of a run reads lambda^{j+1} itself from a compact array.
-template <bool kReg, bool kFromCompact>
+template <bool kFromCompact>
 __global__ __launch_bounds__(kThreads) void k_adjoint_mu(const double* __restrict__ tape,
                                                          const double* __restrict__ in,
                                                          double* __restrict__ mu_out, Geom g,
@@ -731,7 +693,7 @@ __global__ __launch_bounds__(kThreads) void k_adjoint_mu(const double* __restric
     for (int l = 0; l < Q; ++l) lam[l] = in[l * g.ps + site + EX[l] * g.cs + EY[l]];
   }
   double mu[Q];
-  adjoint_site<kReg>(lam, tape[s], tape[S2 + s], tape[2 * S2 + s], tape[3 * S2 + s], g, P, y,
+  adjoint_site(lam, tape[s], tape[S2 + s], tape[2 * S2 + s], tape[3 * S2 + s], g, P, y,
                      mu);
   store_site<double, double>(mu_out, g, site, mu);
   if (x < HX) store_site<double, double>(mu_out, g, site + (long long)g.lx * g.cs, mu);
@@ -800,7 +762,9 @@ __global__ __launch_bounds__(kThreads) void k_init_adjoint(
 template <class S, class A>
 __global__ __launch_bounds__(kThreads) void k_obs_rows(const S* __restrict__ src,
                                                        double* __restrict__ partial, Geom g,
-                                                       Phys P, int nchunks) {
+                                                       Phys P, int nchunks,
+                                                       const unsigned* guard) {
+  if (other_form(guard, kFormFull)) return;
   const int y = blockIdx.x * kThreads + threadIdx.x;
   const int c = blockIdx.y;
   if (y >= g.ly) return;
@@ -864,8 +828,6 @@ __global__ __launch_bounds__(kThreads) void k_obs_scalars(const double* __restri
   }
 }
 
-unsigned grid_1d(long long n) { return unsigned((n + kThreads - 1) / kThreads); }
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -893,6 +855,11 @@ hipError_t by_precision(int prec, Fn fn) {
   return hipGetLastError();
 }
 
+// the word to check where the host does not know a buffer's form
+static const unsigned* guard_of(const void* buf, const Geom& g) {
+  return g.form == kFormUnknown ? static_cast<const unsigned*>(buf) : nullptr;
+}
+
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
   const long long n = (long long)(bytes / 4);
   if (n == 0) return hipSuccess;
@@ -903,20 +870,23 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
 }
 
 hipError_t launch_halo(void* buf, const Geom& g, int prec, hipStream_t s) {
-  const long long nx_el = 6LL * g.ny * g.np, ny_el = 6LL * g.nx * g.np;
+  if (g.form == kFormCoeff) return hipSuccess;  // that form has no halos
+  const long long nx_el = 6LL * (g.ly + 6) * g.np, ny_el = 6LL * g.nx * g.np;
+  const unsigned* guard = guard_of(buf, g);
   return by_precision(prec, [&](auto sv, auto) {
     using S = decltype(sv);
     hipLaunchKernelGGL(k_halo_x<S>, dim3(grid_1d(nx_el)), dim3(kThreads), 0, s,
-                       static_cast<S*>(buf), g);
+                       static_cast<S*>(buf), g, guard);
     if (!g.walls)
       hipLaunchKernelGGL(k_halo_y<S>, dim3(grid_1d(ny_el)), dim3(kThreads), 0, s,
-                         static_cast<S*>(buf), g);
+                         static_cast<S*>(buf), g, guard);
   });
 }
 
 hipError_t launch_fused(const void* src, void* dst, const Geom& g, const Phys& p, int prec,
                         int regularize, double* tape, hipStream_t s) {
   if (tape && prec != kF64) return hipErrorInvalidValue;
+  if (prec == kF64 && regularize) return launch_coeff_step(src, dst, g, p, tape, s);
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto av) {
     using S = decltype(sv);
@@ -943,13 +913,14 @@ hipError_t launch_fused(const void* src, void* dst, const Geom& g, const Phys& p
       else
         hipLaunchKernelGGL((k_fused_local<false, k64>), grid, block, 0, s, a, b, g, p, t.by,
                            t.bx, t.nty, t.nb);
-    } else if (regularize && tape)
-      hipLaunchKernelGGL((k_fused<S, A, true, true>), grid, block, 0, s, a, b, g, p, tape, t.by,
-                         t.bx, t.nty, t.nb);
-    else if (regularize)
-      hipLaunchKernelGGL((k_fused<S, A, true, false>), grid, block, 0, s, a, b, g, p, tape,
-                         t.by, t.bx, t.nty, t.nb);
-    else if (tape)
+    } else if constexpr (std::is_same<S, float>::value) {
+      if (regularize)
+        hipLaunchKernelGGL((k_fused<S, A, true, false>), grid, block, 0, s, a, b, g, p, tape,
+                           t.by, t.bx, t.nty, t.nb);
+      else
+        hipLaunchKernelGGL((k_fused<S, A, false, false>), grid, block, 0, s, a, b, g, p, tape,
+                           t.by, t.bx, t.nty, t.nb);
+    } else if (tape)
       hipLaunchKernelGGL((k_fused<S, A, false, true>), grid, block, 0, s, a, b, g, p, tape,
                          t.by, t.bx, t.nty, t.nb);
     else
@@ -1000,6 +971,7 @@ hipError_t launch_collide(const void* src, void* dst, const Geom& g, const Phys&
 hipError_t launch_init_feq(void* dst, const double* rho, const double* ux, const double* uy,
                            const double* T, const Geom& g, const Phys& p, int prec,
                            hipStream_t s) {
+  if (g.form == kFormCoeff) return launch_coeff_init(dst, rho, ux, uy, T, g, s);
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto av) {
     using S = decltype(sv);
@@ -1014,12 +986,16 @@ hipError_t launch_init_feq(void* dst, const double* rho, const double* ux, const
 
 hipError_t launch_moments(const void* src, double* rho, double* ux, double* uy, double* T,
                           const Geom& g, const Phys& p, int prec, hipStream_t s) {
+  if (g.form != kFormFull) {
+    const hipError_t e = launch_coeff_moments(src, rho, ux, uy, T, g, s);
+    if (e != hipSuccess || g.form == kFormCoeff) return e;
+  }
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto av) {
     using S = decltype(sv);
     hipLaunchKernelGGL((k_moments<S, decltype(av)>), dim3(t.nb), dim3(kThreads), 0, s,
                        static_cast<const S*>(src), rho, ux, uy, T, g, p, t.by, t.bx, t.nty,
-                       t.nb);
+                       t.nb, guard_of(src, g));
   });
 }
 
@@ -1037,16 +1013,22 @@ CompactGrid compact_grid(const Geom& g, int planes) {
 
 hipError_t launch_pack(const void* padded_buf, void* compact, const Geom& g, int prec,
                        hipStream_t s) {
+  if (g.form != kFormFull) {
+    const hipError_t e = launch_coeff_pack(padded_buf, static_cast<double*>(compact), g, s);
+    if (e != hipSuccess || g.form == kFormCoeff) return e;
+  }
   const CompactGrid cg = compact_grid(g, g.np);
   return by_precision(prec, [&](auto sv, auto) {
     using S = decltype(sv);
     hipLaunchKernelGGL(k_pack<S>, cg.grid, dim3(kThreads), 0, s,
-                       static_cast<const S*>(padded_buf), static_cast<S*>(compact), g, cg.nyb);
+                       static_cast<const S*>(padded_buf), static_cast<S*>(compact), g, cg.nyb,
+                       guard_of(padded_buf, g));
   });
 }
 
 hipError_t launch_unpack(const void* compact, void* padded_buf, const Geom& g, int prec,
                          hipStream_t s) {
+  if (g.form == kFormCoeff) return launch_coeff_expand(compact, padded_buf, g, s);
   const CompactGrid cg = compact_grid(g, g.np);
   return by_precision(prec, [&](auto sv, auto) {
     using S = decltype(sv);
@@ -1057,21 +1039,31 @@ hipError_t launch_unpack(const void* compact, void* padded_buf, const Geom& g, i
 
 hipError_t launch_populations_f64(const void* padded_buf, double* out, const Geom& g,
                                   const Phys& p, int prec, hipStream_t s) {
+  if (g.form != kFormFull) {
+    const hipError_t e = launch_coeff_pack(padded_buf, out, g, s);
+    if (e != hipSuccess || g.form == kFormCoeff) return e;
+  }
   const CompactGrid cg = compact_grid(g, Q);
   return by_precision(prec, [&](auto sv, auto av) {
     using S = decltype(sv);
     hipLaunchKernelGGL((k_populations_f64<S, decltype(av)>), cg.grid, dim3(kThreads), 0, s,
-                       static_cast<const S*>(padded_buf), out, g, p.rho_ref, cg.nyb);
+                       static_cast<const S*>(padded_buf), out, g, p.rho_ref, cg.nyb,
+                       guard_of(padded_buf, g));
   });
 }
 
 hipError_t launch_check(const void* src, unsigned int* flag, const Geom& g, const Phys& p,
                         int prec, hipStream_t s) {
+  if (g.form != kFormFull) {
+    const hipError_t e = launch_coeff_check(src, flag, g, s);
+    if (e != hipSuccess || g.form == kFormCoeff) return e;
+  }
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto av) {
     using S = decltype(sv);
-    hipLaunchKernelGGL((k_check<S, decltype(av)>), dim3(t.nb), dim3(kThreads), 0, s, static_cast<const S*>(src),
-                       flag, g, p, t.by, t.bx, t.nty, t.nb);
+    hipLaunchKernelGGL((k_check<S, decltype(av)>), dim3(t.nb), dim3(kThreads), 0, s,
+                       static_cast<const S*>(src), flag, g, p, t.by, t.bx, t.nty, t.nb,
+                       guard_of(src, g));
   });
 }
 
@@ -1081,11 +1073,14 @@ hipError_t launch_observables(const void* src, double* partial, double* profiles
                               double* scalars, const Geom& g, const Phys& p, int prec,
                               double t_bottom, double t_top, hipStream_t s) {
   const int nc = observable_chunks(g);
-  hipError_t e = by_precision(prec, [&](auto sv, auto av) {
-    using S = decltype(sv);
-    hipLaunchKernelGGL((k_obs_rows<S, decltype(av)>), dim3(grid_1d(g.ly), nc), dim3(kThreads), 0, s,
-                       static_cast<const S*>(src), partial, g, p, nc);
-  });
+  hipError_t e = hipSuccess;
+  if (g.form != kFormFull) e = launch_coeff_obs_rows(src, partial, g, nc, s);
+  if (e == hipSuccess && g.form != kFormCoeff)
+    e = by_precision(prec, [&](auto sv, auto av) {
+      using S = decltype(sv);
+      hipLaunchKernelGGL((k_obs_rows<S, decltype(av)>), dim3(grid_1d(g.ly), nc), dim3(kThreads),
+                         0, s, static_cast<const S*>(src), partial, g, p, nc, guard_of(src, g));
+    });
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_obs_reduce, dim3(grid_1d((long long)kObservables * g.ly)), dim3(kThreads),
                      0, s, partial, profiles, g.lx, g.ly, nc);
@@ -1101,10 +1096,14 @@ int loss_ke_blocks(const Geom& g) { return int(make_tiling(g.lx, g.ly).nb); }
 hipError_t launch_loss_ke(const void* src, double* ke, double* lambda, double* partials,
                           const Geom& g, hipStream_t s) {
   const Tiling t = make_tiling(g.lx, g.ly);
-  hipLaunchKernelGGL(k_loss_ke, dim3(t.nb), dim3(kThreads), 0, s,
-                     static_cast<const double*>(src), lambda, partials, g, t.by, t.bx, t.nty,
-                     t.nb);
-  hipError_t e = hipGetLastError();
+  hipError_t e = hipSuccess;
+  if (g.form != kFormFull) e = launch_coeff_loss_ke(src, lambda, partials, g, s);
+  if (e == hipSuccess && g.form != kFormCoeff) {
+    hipLaunchKernelGGL(k_loss_ke, dim3(t.nb), dim3(kThreads), 0, s,
+                       static_cast<const double*>(src), lambda, partials, g, t.by, t.bx, t.nty,
+                       t.nb, guard_of(src, g));
+    e = hipGetLastError();
+  }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_sum, dim3(1), dim3(kThreads), 0, s, partials, int(t.nb), ke);
   return hipGetLastError();
@@ -1112,36 +1111,29 @@ hipError_t launch_loss_ke(const void* src, double* ke, double* lambda, double* p
 
 hipError_t launch_adjoint_step(const double* tape, const double* lam_in, double* lam_out,
                                const Geom& g, const Phys& p, int regularize, hipStream_t s) {
+  if (regularize) return launch_coeff_adjoint_step(tape, lam_in, lam_out, g, p, s);
   const Tiling t = make_tiling(g.lx, g.ly);
-  if (regularize)
-    hipLaunchKernelGGL(k_adjoint<true>, dim3(t.nb), dim3(kThreads), 0, s, tape, lam_in, lam_out,
-                       g, p, t.by, t.bx, t.nty, t.nb);
-  else
-    hipLaunchKernelGGL(k_adjoint<false>, dim3(t.nb), dim3(kThreads), 0, s, tape, lam_in,
-                       lam_out, g, p, t.by, t.bx, t.nty, t.nb);
+  hipLaunchKernelGGL(k_adjoint, dim3(t.nb), dim3(kThreads), 0, s, tape, lam_in, lam_out, g, p,
+                     t.by, t.bx, t.nty, t.nb);
   return hipGetLastError();
 }
 
 hipError_t launch_adjoint_mu(const double* tape, const double* in, bool from_compact, double* mu_out,
                              const Geom& g, const Phys& p, int regularize, hipStream_t s) {
+  if (regularize) return launch_coeff_adjoint_mu(tape, in, from_compact, mu_out, g, p, s);
   const Tiling t = make_tiling(g.lx, g.ly);
   const dim3 grid(t.nb), block(kThreads);
-  if (regularize && from_compact)
-    hipLaunchKernelGGL((k_adjoint_mu<true, true>), grid, block, 0, s, tape, in, mu_out, g, p, t.by,
-                       t.bx, t.nty, t.nb);
-  else if (regularize)
-    hipLaunchKernelGGL((k_adjoint_mu<true, false>), grid, block, 0, s, tape, in, mu_out, g, p,
-                       t.by, t.bx, t.nty, t.nb);
-  else if (from_compact)
-    hipLaunchKernelGGL((k_adjoint_mu<false, true>), grid, block, 0, s, tape, in, mu_out, g, p,
-                       t.by, t.bx, t.nty, t.nb);
+  if (from_compact)
+    hipLaunchKernelGGL(k_adjoint_mu<true>, grid, block, 0, s, tape, in, mu_out, g, p, t.by, t.bx,
+                       t.nty, t.nb);
   else
-    hipLaunchKernelGGL((k_adjoint_mu<false, false>), grid, block, 0, s, tape, in, mu_out, g, p,
-                       t.by, t.bx, t.nty, t.nb);
+    hipLaunchKernelGGL(k_adjoint_mu<false>, grid, block, 0, s, tape, in, mu_out, g, p, t.by, t.bx,
+                       t.nty, t.nb);
   return hipGetLastError();
 }
 
 hipError_t launch_adjoint_gather(const double* mu, double* lam, const Geom& g, hipStream_t s) {
+  if (g.form == kFormCoeff) return launch_coeff_adjoint_gather(mu, lam, g, s);
   const Tiling t = make_tiling(g.lx, g.ly);
   hipLaunchKernelGGL(k_adjoint_gather, dim3(t.nb), dim3(kThreads), 0, s, mu, lam, g, t.by, t.bx,
                      t.nty, t.nb);

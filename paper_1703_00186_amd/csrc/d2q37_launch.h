@@ -1,5 +1,11 @@
-// Host-side launchers of the D2Q37 kernels (implemented in d2q37_kernels.hip).
+// Host-side launchers of the D2Q37 kernels (implemented in d2q37_kernels.hip;
+// launch_coeff_* in d2q37_coeff.hip, reached through the others).
 // Every launcher enqueues on the given stream and returns the launch status.
+// Geom::form is the storage form of the state buffer that is read: with
+// kFormUnknown the kernels of both forms are enqueued and the device word
+// decides.  launch_init_feq writes the form it names, launch_fused always the
+// coefficient form for regularized FP64 and the populations otherwise; the
+// split stages, launch_bc and launch_collide work on populations.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -58,7 +64,9 @@ hipError_t launch_init_feq(void* dst, const double* rho, const double* ux, const
 hipError_t launch_moments(const void* src, double* rho, double* ux, double* uy, double* T,
                           const Geom& g, const Phys& p, int prec, hipStream_t s);
 
-// Copies between a padded buffer and the compact [37][lx][ly] form.
+// Copies between a padded buffer and the compact [37][lx][ly] form.  unpack
+// with form kFormCoeff: `compact` is a state buffer in that form instead,
+// expanded into the padded buffer with its halos.
 hipError_t launch_pack(const void* padded, void* compact, const Geom& g, int prec,
                        hipStream_t s);
 hipError_t launch_unpack(const void* compact, void* padded, const Geom& g, int prec,
@@ -83,7 +91,8 @@ hipError_t launch_observables(const void* src, double* partial, double* profiles
                               double* scalars, const Geom& g, const Phys& p, int prec,
                               double t_bottom, double t_top, hipStream_t s);
 
-// Adjoint (FP64 buffers).
+// Adjoint (FP64 buffers).  The regularized collision's adjoint keeps mu in the
+// coefficient form (launch_adjoint_gather: Geom::form says which it reads).
 // KE of the padded state: per-block partial sums into `partials` (size
 // returned by loss_ke_blocks), then reduced into *ke; lambda (optional)
 // compact, in the lattice's layout ([lx][37][ly] column, [37][lx][ly] SoA),
@@ -107,6 +116,28 @@ hipError_t launch_zero_pad_rows(void* buf, const Geom& g, int prec, hipStream_t 
 hipError_t launch_init_adjoint(const double* lam0, const double* rho, const double* ux,
                                const double* uy, const double* T, double* drho, double* dux,
                                double* duy, double* dT, const Geom& g, hipStream_t s);
+
+// The coefficient form's kernels (d2q37_coeff.hip), FP64.  A buffer in that
+// form takes less than half of the padded populations' bytes.
+hipError_t launch_coeff_step(const void* src, void* dst, const Geom& g, const Phys& p,
+                             double* tape, hipStream_t s);
+hipError_t launch_coeff_init(void* dst, const double* rho, const double* ux, const double* uy,
+                             const double* T, const Geom& g, hipStream_t s);
+hipError_t launch_coeff_expand(const void* src, void* dst, const Geom& g, hipStream_t s);
+hipError_t launch_coeff_pack(const void* src, double* out, const Geom& g, hipStream_t s);
+hipError_t launch_coeff_moments(const void* src, double* rho, double* ux, double* uy, double* T,
+                                const Geom& g, hipStream_t s);
+hipError_t launch_coeff_check(const void* src, unsigned* flag, const Geom& g, hipStream_t s);
+hipError_t launch_coeff_obs_rows(const void* src, double* partial, const Geom& g, int nchunks,
+                                 hipStream_t s);
+hipError_t launch_coeff_loss_ke(const void* src, double* lambda, double* partials, const Geom& g,
+                                hipStream_t s);
+hipError_t launch_coeff_adjoint_mu(const double* tape, const double* in, bool from_compact,
+                                   double* mu_out, const Geom& g, const Phys& p, hipStream_t s);
+hipError_t launch_coeff_adjoint_gather(const double* mu, double* lam, const Geom& g,
+                                       hipStream_t s);
+hipError_t launch_coeff_adjoint_step(const double* tape, const double* lam_in, double* lam_out,
+                                     const Geom& g, const Phys& p, hipStream_t s);
 
 // The library's per-GPU static scratch (lb_adjoint_run_static): its size,
 // and its device address on the current device (looked up on the first call

@@ -1,0 +1,78 @@
+// Tiles of the site kernels (one thread per lattice site) and the
+// workgroup-to-XCD map, shared by the kernel files.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "d2q37_device.h"
+
+namespace d2q37 {
+
+constexpr int kThreads = 256;
+constexpr int kXcds = 8;
+
+struct Tiling {
+  int by, bx;    // tile shape (rows, columns)
+  int nty, ntx;  // tiles along y and x
+  unsigned nb;   // total tiles
+};
+
+inline Tiling make_tiling(int lx, int ly) {
+  Tiling t;
+  t.by = ly > 128 ? 256 : (ly > 64 ? 128 : 64);
+  t.bx = kThreads / t.by;
+  t.nty = (ly + t.by - 1) / t.by;
+  t.ntx = (lx + t.bx - 1) / t.bx;
+  t.nb = unsigned(t.nty) * unsigned(t.ntx);
+  return t;
+}
+
+inline unsigned grid_1d(long long n) { return unsigned((n + kThreads - 1) / kThreads); }
+
+// Tile of this workgroup after the XCD-aware remap (a bijection of [0, nb)).
+__device__ __forceinline__ unsigned tile_index(unsigned nb) {
+  const unsigned b = blockIdx.x;
+  const unsigned q = nb / kXcds, rem = nb % kXcds;
+  const unsigned xcd = b % kXcds, j = b / kXcds;
+  return xcd * q + (xcd < rem ? xcd : rem) + j;
+}
+
+// Physical (x, y) of this thread; false if it falls outside the lattice.
+__device__ __forceinline__ bool site_of(int lx, int ly, int by, int bx, int nty, unsigned nb,
+                                        int& x, int& y) {
+  const unsigned t = tile_index(nb);
+  const int ty = int(t % unsigned(nty)), tx = int(t / unsigned(nty));
+  const int lin = threadIdx.x;
+  y = ty * by + (lin % by);
+  x = tx * bx + (lin / by);
+  return x < lx && y < ly;
+}
+__device__ __forceinline__ bool site_of(const Geom& g, int by, int bx, int nty, unsigned nb,
+                                        int& x, int& y) {
+  return site_of(g.lx, g.ly, by, bx, nty, nb, x, y);
+}
+
+// Block-wide sum of one double per thread; result valid in thread 0.
+__device__ __forceinline__ double block_sum(double v) {
+  __shared__ double red[kThreads];
+  red[threadIdx.x] = v;
+  __syncthreads();
+#pragma unroll
+  for (int s = kThreads / 2; s > 0; s >>= 1) {
+    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    __syncthreads();
+  }
+  return red[0];
+}
+
+// A kernel launched for one storage form of a buffer whose form the host does
+// not know returns at once if the buffer's first word names the other.
+__device__ __forceinline__ bool other_form(const unsigned* word, Form f) {
+  return word && *word != unsigned(f);
+}
+__device__ __forceinline__ void set_form(void* buf, Form f) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+    *static_cast<unsigned*>(buf) = unsigned(f);
+}
+
+}  // namespace d2q37

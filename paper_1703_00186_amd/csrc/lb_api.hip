@@ -27,6 +27,9 @@ struct lb_ctx {
   double* partials;
   double* obs;  // observable scratch (chunk partials | profiles | scalars)
   unsigned int* flag;
+  int a_form, b_form;  // storage form of A and B (d2q37::Form)
+  bool captured;       // a graph recorded on this context may have run: the
+                       // forms are then known only to the device
   bool halos_valid;
   long long steps_since_check;
 };
@@ -117,6 +120,7 @@ Geom make_geom(const lb_lattice& lat) {
   g.ny = int(round_up(size_t(lat.ly) + 2 * size_t(g.hy), size_t(per_line)));
   g.walls = lat.ybc == LB_Y_WALLS;
   g.np = is_local_form(lat.precision) ? d2q37::kLocalPlanes : d2q37::Q;
+  g.form = d2q37::kFormFull;
   if (lat.layout == LB_LAYOUT_SOA) {
     g.ps = (long long)g.nx * g.ny;
     g.cs = g.ny;
@@ -150,6 +154,64 @@ int check_kernel(int prec, const lb_params& par) {
     return fail(LB_E_ARG, "LB_FP32_COLLIDE and LB_FP32_LOCAL run the fused kernel only%s");
   if (par.kernel == LB_KERNEL_SPLIT_MFMA && prec != LB_FP64)
     return fail(LB_E_ARG, "LB_KERNEL_SPLIT_MFMA needs LB_FP64%s");
+  return LB_OK;
+}
+
+// the geometry with the storage form of the buffer that is read
+Geom with_form(const Geom& g, int form) {
+  Geom h = g;
+  h.form = form;
+  return h;
+}
+
+// The state A as populations: before the kernels that work on those.  B is
+// free then (each caller overwrites it).
+int full_state(lb_ctx* c) {
+  if (c->a_form == d2q37::kFormFull) return LB_OK;
+  if (c->a_form == d2q37::kFormCoeff) {
+    LB_HIP(d2q37::launch_unpack(c->A, c->B, with_form(c->g, d2q37::kFormCoeff), c->prec,
+                                c->stream),
+           "expand state");
+    std::swap(c->A, c->B);
+    c->a_form = d2q37::kFormFull;
+    c->b_form = d2q37::kFormCoeff;
+    c->halos_valid = true;
+    return LB_OK;
+  }
+  // a recorded graph may have run: keep the buffers' roles
+  LB_HIP(d2q37::launch_pack(c->A, c->B, with_form(c->g, c->a_form), c->prec, c->stream),
+         "expand state");
+  LB_HIP(d2q37::launch_unpack(c->B, c->A, c->g, c->prec, c->stream), "expand state");
+  c->a_form = d2q37::kFormFull;
+  c->b_form = d2q37::kFormUnknown;
+  c->halos_valid = false;
+  return LB_OK;
+}
+
+// Names a buffer that is about to be overwritten with populations.
+int mark_full(lb_ctx* c, char* buf, int& form) {
+  if (form != d2q37::kFormFull)
+    LB_HIP(d2q37::launch_zero(buf, sizeof(unsigned), c->stream), "mark form");
+  form = d2q37::kFormFull;
+  return LB_OK;
+}
+
+// The scratch B as populations, for lb_bc and lb_collide after a fused step
+// (which leaves the previous state there, in its form).  keep_a: A is still
+// needed; the coefficients of both then fit beside each other.
+int full_scratch(lb_ctx* c, bool keep_a) {
+  if (c->b_form == d2q37::kFormFull) return LB_OK;
+  if (c->b_form == d2q37::kFormCoeff && (!keep_a || c->a_form == d2q37::kFormCoeff)) {
+    const size_t n = buffer_bytes(c->g, c->prec) / (2 * kAlign) * kAlign;
+    char* spare = keep_a ? c->A + n : c->A;
+    LB_HIP(hipMemcpyAsync(spare, c->B, n, hipMemcpyDeviceToDevice, c->stream), "expand scratch");
+    LB_HIP(d2q37::launch_unpack(spare, c->B, with_form(c->g, d2q37::kFormCoeff), c->prec,
+                                c->stream),
+           "expand scratch");
+  } else {
+    LB_HIP(d2q37::launch_zero(c->B, sizeof(unsigned), c->stream), "mark form");
+  }
+  c->b_form = d2q37::kFormFull;
   return LB_OK;
 }
 
@@ -207,20 +269,34 @@ int check_ctx(lb_ctx* ctx) {
   return LB_OK;
 }
 
+// check_ctx for the calls that read or write the state buffers: what the host
+// knows about their forms holds unless a recorded graph may run in between.
+int enter(lb_ctx* ctx) {
+  const int rc = check_ctx(ctx);
+  if (rc) return rc;
+  // work recorded into a graph runs whenever the graph does
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &status) != hipSuccess) (void)hipGetLastError();
+  if (status == hipStreamCaptureStatusActive) ctx->captured = true;
+  if (ctx->captured && ctx->prec == LB_FP64)
+    ctx->a_form = ctx->b_form = d2q37::kFormUnknown;
+  return LB_OK;
+}
+
 int need_fp64(lb_ctx* ctx, const char* what) {
   if (ctx->prec != LB_FP64) return fail(LB_E_STATE, "%s needs an LB_FP64 context", what);
   return LB_OK;
 }
 
 int do_halo(lb_ctx* c) {
-  LB_HIP(d2q37::launch_halo(c->A, c->g, c->prec, c->stream), "halo");
+  LB_HIP(d2q37::launch_halo(c->A, with_form(c->g, c->a_form), c->prec, c->stream), "halo");
   c->halos_valid = true;
   return LB_OK;
 }
 
 int check_finite_now(lb_ctx* c) {
   LB_HIP(d2q37::launch_zero(c->flag, kAlign, c->stream), "check_finite zero");
-  LB_HIP(d2q37::launch_check(c->A, c->flag, c->g, c->p, c->prec, c->stream), "check_finite");
+  LB_HIP(d2q37::launch_check(c->A, c->flag, with_form(c->g, c->a_form), c->p, c->prec, c->stream), "check_finite");
   unsigned int bad = 0;
   LB_HIP(hipMemcpyAsync(&bad, c->flag, sizeof(bad), hipMemcpyDeviceToHost, c->stream),
          "check_finite copy");
@@ -235,9 +311,23 @@ int check_finite_now(lb_ctx* c) {
 }
 
 int one_step(lb_ctx* c, double* tape) {
-  if (c->par.kernel == LB_KERNEL_FUSED || tape) {
+  const bool fused = c->par.kernel == LB_KERNEL_FUSED || tape;
+  if (fused && c->prec == LB_FP64 && c->par.regularize) {
+    // from either form to the coefficient form, which needs no halos
+    LB_HIP(d2q37::launch_fused(c->A, c->B, with_form(c->g, c->a_form), c->p, c->prec, 1, tape,
+                               c->stream),
+           "fused step");
+    std::swap(c->A, c->B);
+    c->b_form = c->a_form;
+    c->a_form = d2q37::kFormCoeff;
+    c->halos_valid = false;
+  } else if (fused) {
+    int rc = full_state(c);
+    if (rc) return rc;
+    rc = mark_full(c, c->B, c->b_form);
+    if (rc) return rc;
     if (!c->halos_valid || !c->g.walls) {
-      int rc = do_halo(c);
+      rc = do_halo(c);
       if (rc) return rc;
     }
     LB_HIP(d2q37::launch_fused(c->A, c->B, c->g, c->p, c->prec, c->par.regularize, tape,
@@ -248,7 +338,11 @@ int one_step(lb_ctx* c, double* tape) {
     // y) are refreshed before the next step
     c->halos_valid = c->g.walls;
   } else {
-    int rc = do_halo(c);
+    int rc = full_state(c);
+    if (rc) return rc;
+    rc = mark_full(c, c->B, c->b_form);
+    if (rc) return rc;
+    rc = do_halo(c);
     if (rc) return rc;
     LB_HIP(propagate_stage(c), "propagate");
     LB_HIP(d2q37::launch_bc(c->B, c->g, c->p, c->prec, c->stream), "bc");
@@ -272,10 +366,24 @@ int adjoint_run(lb_ctx* ctx, int n, const double* tape, double* lambda, char* ws
   const bool walls = g.walls != 0;
   const long long per = 4LL * g.lx * g.ly;
   const int reg = ctx->par.regularize;
-  // Where the two compact lambda arrays fit in the 256 MB Infinity Cache the
-  // scatter form's partial-sector stores cost nothing and it is the faster
-  // one (measured 25 vs 33 us at 512 x 512; the gather form wins from
-  // 768 x 768 up and on lattices too small to fill the GPU); same result.
+  if (reg) {  // mu stays in the coefficient form between the steps
+    LB_HIP(d2q37::launch_adjoint_mu(tape + per * (n - 1), lambda, true, m0, g, ctx->p, reg,
+                                    ctx->stream),
+           "adjoint_run first step");
+    for (int j = n - 2; j >= 0; --j) {
+      LB_HIP(d2q37::launch_adjoint_mu(tape + per * j, m0, false, m1, g, ctx->p, reg, ctx->stream),
+             "adjoint_run step");
+      std::swap(m0, m1);
+    }
+    LB_HIP(d2q37::launch_adjoint_gather(m0, lambda, with_form(g, d2q37::kFormCoeff), ctx->stream),
+           "adjoint_run gather");
+    return LB_OK;
+  }
+  // Plain BGK.  Where the two compact lambda arrays fit in the 256 MB
+  // Infinity Cache the scatter form's partial-sector stores cost nothing and
+  // it is the faster one (measured 25 vs 33 us at 512 x 512; the gather form
+  // wins from 768 x 768 up and on lattices too small to fill the GPU); same
+  // result.
   const long long sites = (long long)g.lx * g.ly;
   const bool scatter = sites >= (1LL << 17) && 2 * 37 * 8 * sites <= (256LL << 20);
   if (scatter) {
@@ -367,10 +475,26 @@ int lb_init(const lb_lattice* lat, const lb_params* par, void* workspace, size_t
                                             observable_bytes(c->g));
   c->halos_valid = false;
   c->steps_since_check = 0;
+  c->captured = false;
+  c->a_form = c->b_form = d2q37::kFormFull;
+  hipError_t e = hipSuccess;
+  if (c->prec == LB_FP64 && par->regularize && par->kernel == LB_KERNEL_FUSED) {
+    // the form the steps work on; it has no halos and no padding that is read
+    c->a_form = d2q37::kFormCoeff;
+    e = d2q37::launch_init_feq(c->A, rho0, ux0, uy0, T0, with_form(c->g, c->a_form), c->p, c->prec,
+                               c->stream);
+    if (e == hipSuccess) e = d2q37::launch_zero(c->B, sizeof(unsigned), c->stream);
+    if (e != hipSuccess) {
+      delete c;
+      return hip_fail(e, "lb_init");
+    }
+    *out = c;
+    return LB_OK;
+  }
   // Rows beyond the walls are never written by a step; the wall rows' gather
   // reads them before bc replaces those populations.  Give them finite values
   // (zero); every other element is written before it is read.
-  hipError_t e = d2q37::launch_zero_pad_rows(c->A, c->g, c->prec, c->stream);
+  e = d2q37::launch_zero_pad_rows(c->A, c->g, c->prec, c->stream);
   if (e == hipSuccess) e = d2q37::launch_zero_pad_rows(c->B, c->g, c->prec, c->stream);
   if (e == hipSuccess)
     e = d2q37::launch_init_feq(c->A, rho0, ux0, uy0, T0, c->g, c->p, c->prec, c->stream);
@@ -414,7 +538,7 @@ int lb_set_params(lb_ctx* ctx, const lb_params* par) {
 }
 
 int lb_step(lb_ctx* ctx, int n) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   if (n < 0) return fail(LB_E_ARG, "n must be >= 0%s");
   for (int i = 0; i < n; ++i) {
@@ -425,66 +549,77 @@ int lb_step(lb_ctx* ctx, int n) {
 }
 
 int lb_moments(lb_ctx* ctx, double* rho, double* ux, double* uy, double* T) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
-  LB_HIP(d2q37::launch_moments(ctx->A, rho, ux, uy, T, ctx->g, ctx->p, ctx->prec, ctx->stream),
+  LB_HIP(d2q37::launch_moments(ctx->A, rho, ux, uy, T, with_form(ctx->g, ctx->a_form), ctx->p, ctx->prec, ctx->stream),
          "moments");
   return LB_OK;
 }
 
 int lb_get_state(lb_ctx* ctx, void* f) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   if (!f) return fail(LB_E_ARG, "f is NULL%s");
-  LB_HIP(d2q37::launch_pack(ctx->A, f, ctx->g, ctx->prec, ctx->stream), "get_state");
+  LB_HIP(d2q37::launch_pack(ctx->A, f, with_form(ctx->g, ctx->a_form), ctx->prec, ctx->stream), "get_state");
   return LB_OK;
 }
 
 int lb_set_state(lb_ctx* ctx, const void* f) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   if (!f) return fail(LB_E_ARG, "f is NULL%s");
   LB_HIP(d2q37::launch_unpack(f, ctx->A, ctx->g, ctx->prec, ctx->stream), "set_state");
+  ctx->a_form = d2q37::kFormFull;
   return do_halo(ctx);
 }
 
 int lb_get_populations(lb_ctx* ctx, double* f) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   if (!f) return fail(LB_E_ARG, "f is NULL%s");
-  LB_HIP(d2q37::launch_populations_f64(ctx->A, f, ctx->g, ctx->p, ctx->prec, ctx->stream),
+  LB_HIP(d2q37::launch_populations_f64(ctx->A, f, with_form(ctx->g, ctx->a_form), ctx->p, ctx->prec, ctx->stream),
          "get_populations");
   return LB_OK;
 }
 
 int lb_halo(lb_ctx* ctx) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   return do_halo(ctx);
 }
 
 int lb_propagate(lb_ctx* ctx) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   rc = no_split_stage(ctx, "lb_propagate");
+  if (rc) return rc;
+  rc = full_state(ctx);
+  if (rc) return rc;
+  rc = mark_full(ctx, ctx->B, ctx->b_form);
   if (rc) return rc;
   LB_HIP(propagate_stage(ctx), "propagate");
   return LB_OK;
 }
 
 int lb_bc(lb_ctx* ctx) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   rc = no_split_stage(ctx, "lb_bc");
+  if (rc) return rc;
+  rc = full_scratch(ctx, true);
   if (rc) return rc;
   LB_HIP(d2q37::launch_bc(ctx->B, ctx->g, ctx->p, ctx->prec, ctx->stream), "bc");
   return LB_OK;
 }
 
 int lb_collide(lb_ctx* ctx) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   rc = no_split_stage(ctx, "lb_collide");
+  if (rc) return rc;
+  rc = full_scratch(ctx, false);
+  if (rc) return rc;
+  rc = mark_full(ctx, ctx->A, ctx->a_form);
   if (rc) return rc;
   LB_HIP(collide_stage(ctx), "collide");
   ctx->halos_valid = false;
@@ -492,40 +627,41 @@ int lb_collide(lb_ctx* ctx) {
 }
 
 int lb_get_scratch(lb_ctx* ctx, void* f) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   rc = no_split_stage(ctx, "lb_get_scratch");
   if (rc) return rc;
   if (!f) return fail(LB_E_ARG, "f is NULL%s");
-  LB_HIP(d2q37::launch_pack(ctx->B, f, ctx->g, ctx->prec, ctx->stream), "get_scratch");
+  LB_HIP(d2q37::launch_pack(ctx->B, f, with_form(ctx->g, ctx->b_form), ctx->prec, ctx->stream), "get_scratch");
   return LB_OK;
 }
 
 int lb_set_scratch(lb_ctx* ctx, const void* f) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   rc = no_split_stage(ctx, "lb_set_scratch");
   if (rc) return rc;
   if (!f) return fail(LB_E_ARG, "f is NULL%s");
   LB_HIP(d2q37::launch_unpack(f, ctx->B, ctx->g, ctx->prec, ctx->stream), "set_scratch");
+  ctx->b_form = d2q37::kFormFull;
   return LB_OK;
 }
 
 int lb_observables(lb_ctx* ctx, double* profiles, double* scalars) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   const size_t prof = size_t(d2q37::kObservables) * size_t(ctx->g.ly);
   double* partial = ctx->obs;
   double* own_prof = ctx->obs + size_t(d2q37::observable_chunks(ctx->g)) * prof;
   LB_HIP(d2q37::launch_observables(ctx->A, partial, profiles ? profiles : own_prof, scalars,
-                                   ctx->g, ctx->p, ctx->prec, ctx->par.t_bottom, ctx->par.t_top,
+                                   with_form(ctx->g, ctx->a_form), ctx->p, ctx->prec, ctx->par.t_bottom, ctx->par.t_top,
                                    ctx->stream),
          "observables");
   return LB_OK;
 }
 
 int lb_run_observed(lb_ctx* ctx, int n, int every, double* series) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   if (n < 0 || every <= 0) return fail(LB_E_ARG, "need n >= 0 and every > 0%s");
   if (n >= every && !series) return fail(LB_E_ARG, "series is NULL%s");
@@ -542,7 +678,7 @@ int lb_run_observed(lb_ctx* ctx, int n, int every, double* series) {
 }
 
 int lb_step_record(lb_ctx* ctx, int n, double* tape) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   rc = need_fp64(ctx, "lb_step_record");
   if (rc) return rc;
@@ -557,12 +693,13 @@ int lb_step_record(lb_ctx* ctx, int n, double* tape) {
 }
 
 int lb_loss_ke(lb_ctx* ctx, double* ke_dev, double* lambda) {
-  int rc = check_ctx(ctx);
+  int rc = enter(ctx);
   if (rc) return rc;
   rc = need_fp64(ctx, "lb_loss_ke");
   if (rc) return rc;
   if (!ke_dev) return fail(LB_E_ARG, "ke_dev is NULL%s");
-  LB_HIP(d2q37::launch_loss_ke(ctx->A, ke_dev, lambda, ctx->partials, ctx->g, ctx->stream),
+  LB_HIP(d2q37::launch_loss_ke(ctx->A, ke_dev, lambda, ctx->partials,
+                               with_form(ctx->g, ctx->a_form), ctx->stream),
          "loss_ke");
   return LB_OK;
 }
