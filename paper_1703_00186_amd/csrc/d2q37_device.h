@@ -42,9 +42,9 @@ struct Geom {
   int walls;       // 1: thermal walls in y, 0: periodic y
   int np;          // planes per padded site: Q, or Q + 1 in the local-reference
                    // form (its packed reference)
+  int form;        // storage form of the buffer a launcher reads (host side)
   long long ps;    // element stride between populations
   long long cs;    // element stride between padded columns
-  int form;        // storage form of the buffer a launcher reads (host side)
 };
 
 // Storage form of a state buffer: the 37 populations of every padded site, or
