@@ -14,13 +14,16 @@
 // six source columns after its first and is collided and stored at once.
 //
 // What bounds it and why this split.  The step moves 240 bytes per site
-// (15 FP64 in, 15 out) instead of the 592 of the 37-population kernel.
-// Rebuilding populations is done once per (source site, e_x group) whatever
-// TX is; TX trades registers (30 VGPRs per column: 4, 3, 2 waves per SIMD at
-// TX = 2, 3, 4) against re-reading source columns ((TX + 6) / TX times, from
-// the XCD's L2: measured 1.07 x, 1.22 x, 1.22 x of the state fetched past L2
-// at TX = 2, 3, 4).  16-byte accesses matter: with 8-byte ones the L1
-// handles half the bytes per cycle (230 against 200 us at 1920 x 2048).
+// (15 FP64 in, 15 out) instead of the 592 of the 37 populations, at 5.5 TB/s
+// (1920 x 2048: 179 us against 405; 4096 x 4096: 750 us against 1646; a copy
+// reaches 5.2 to 5.7 TB/s).  Rebuilding populations is done once per (source
+// site, e_x group) whatever TX is; TX trades registers (30 VGPRs per column:
+// 4, 3, 2, 2 waves per SIMD at TX = 1, 2, 3, 4) against re-reading source
+// columns ((TX + 6) / TX times, nearly all from the XCD's L2: 1.05 x and
+// 1.11 x of the state fetched past it at TX = 3 and 4).  16-byte accesses
+// matter: with 8-byte ones the L1 handles half the bytes per cycle (230
+// against 200 us).  Source columns are loaded two or three ahead of their
+// use (191 -> 181 -> 179 us at TX = 4).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -148,13 +151,21 @@ __device__ __forceinline__ Row wave_row(const CGeom& g, int w, int lane) {
 }
 
 // Wave of this workgroup: rows w, first column x0; false beyond the lattice.
-template <int TX>
+// Consecutive waves go up a strip of TX columns, then to the next strip; the
+// strips are taken in the order in which a wave walks over its columns.  A
+// column that two strips share is then read by the later one sooner than its
+// walk alone would have it, and more often still in the XCD's L2: with the
+// adjoint's descending walk over ascending strips its step fetched 1.23 GB
+// instead of 0.6 at 1920 x 2048 (241 us against 212).
+template <class K, int TX>
 __device__ __forceinline__ bool wave_tile(const CGeom& g, unsigned nb, int& w, int& x0) {
   const unsigned wave = unsigned(__builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)));
   const unsigned t = tile_index(nb) * kWaves + wave;
+  const int strips = (g.lx + TX - 1) / TX;
   w = int(t % unsigned(g.nw));
-  x0 = int(t / unsigned(g.nw)) * TX;
-  return x0 < g.lx;
+  const int s = int(t / unsigned(g.nw));
+  x0 = (kShift<K> > 0 ? s : strips - 1 - s) * TX;
+  return s < strips;
 }
 
 // The sweep of one wave.  Target t of the TX columns (in the order of the
@@ -174,12 +185,12 @@ struct Sweep {
   double zero[TX];
 
   __device__ __forceinline__ int source(int j) const {
-    int x = K::wdown(0) == 1.0 ? x0 - 3 + j : x0 + TX + 2 - j;
+    int x = kShift<K> > 0 ? x0 - 3 + j : x0 + TX + 2 - j;
     x = x < 0 ? x + g.lx : (x >= g.lx ? x - g.lx : x);
     return x;  // (lx >= 6: one wrap reaches every column of a ragged last tile too)
   }
   __device__ __forceinline__ int target(int t) const {
-    return K::wdown(0) == 1.0 ? x0 + t : x0 + TX - 1 - t;
+    return kShift<K> > 0 ? x0 + t : x0 + TX - 1 - t;
   }
   __device__ __forceinline__ void load(int j, double (&v)[NC]) {
     load_column(column_rsrc(src, g, source(j)), g, row.load, v);
@@ -236,6 +247,15 @@ struct Sweep {
   }
 };
 
+__device__ __forceinline__ void store_tape(double* tape, long long S2, long long s,
+                                           const double (&a)[NC]) {
+  __builtin_nontemporal_store(a[slot(0, 0)], &tape[s]);
+  __builtin_nontemporal_store(a[slot(1, 0)], &tape[S2 + s]);
+  __builtin_nontemporal_store(a[slot(0, 1)], &tape[2 * S2 + s]);
+  __builtin_nontemporal_store(mad(2.0, a[slot(0, 0)], a[slot(2, 0)] + a[slot(0, 2)]),
+                              &tape[3 * S2 + s]);
+}
+
 // Forward: walls on the six wall rows, optional tape of the pre-collision
 // moments (rho, j_x, j_y, sum |c|^2 f), collide, store.
 template <bool kTape>
@@ -255,10 +275,7 @@ struct StepSite {
     if (kTape) {
       if (r.store != kOutside) {
         const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + r.y;
-        tape[s] = a[slot(0, 0)];
-        tape[S2 + s] = a[slot(1, 0)];
-        tape[2 * S2 + s] = a[slot(0, 1)];
-        tape[3 * S2 + s] = mad(2.0, a[slot(0, 0)], a[slot(2, 0)] + a[slot(0, 2)]);
+        store_tape(tape, S2, s, a);
       }
     }
     collide_coeffs(a, P);
@@ -280,7 +297,7 @@ struct AdjointSite {
     const bool ok = x < g.lx && r.in;
     const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + r.y;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) in.m[k] = ok ? tape[k * S2 + s] : 1.0;
+    for (int k = 0; k < 4; ++k) in.m[k] = ok ? __builtin_nontemporal_load(&tape[k * S2 + s]) : 1.0;
   }
   __device__ __forceinline__ void finish(const Input& in, double (&a)[NC], int x,
                                          const Row& r) const {
@@ -293,14 +310,14 @@ struct AdjointSite {
 };
 
 template <int TX, int kAhead, bool kTape>
-__global__ __launch_bounds__(64 * kWaves, TX == 2 ? 4 : 2) void k_coeff_step(
+__global__ __launch_bounds__(64 * kWaves, TX == 1 ? 4 : TX == 2 ? 3 : 2) void k_coeff_step(
     const double* __restrict__ src, double* __restrict__ dst, CGeom g, Phys P, WallTable wt,
     double* __restrict__ tape, unsigned nb, const unsigned* guard, unsigned* word) {
   __shared__ double lds[kWaves][kWaveLds<TX>];
   if (other_form(guard, kFormCoeff)) return;
   set_form(word, kFormCoeff);
   int w, x0;
-  if (!wave_tile<TX>(g, nb, w, x0)) return;
+  if (!wave_tile<Forward, TX>(g, nb, w, x0)) return;
   const int lane = threadIdx.x & 63;
   const StepSite<kTape> site{dst, g, P, wt, tape};
   Sweep<Forward, TX, kAhead, StepSite<kTape>> s{
@@ -310,12 +327,12 @@ __global__ __launch_bounds__(64 * kWaves, TX == 2 ? 4 : 2) void k_coeff_step(
 }
 
 template <int TX, int kAhead>
-__global__ __launch_bounds__(64 * kWaves, TX == 2 ? 3 : 2) void k_coeff_adjoint(
+__global__ __launch_bounds__(64 * kWaves, TX == 1 ? 4 : TX == 2 ? 3 : 2) void k_coeff_adjoint(
     const double* __restrict__ tape, const double* __restrict__ src, double* __restrict__ dst,
     CGeom g, Phys P, WallTable wt, unsigned nb) {
   __shared__ double lds[kWaves][kWaveLds<TX>];
   int w, x0;
-  if (!wave_tile<TX>(g, nb, w, x0)) return;
+  if (!wave_tile<Adjoint, TX>(g, nb, w, x0)) return;
   const int lane = threadIdx.x & 63;
   const AdjointSite site{dst, g, P, wt, tape};
   Sweep<Adjoint, TX, kAhead, AdjointSite> s{
@@ -399,10 +416,7 @@ __global__ __launch_bounds__(kThreads) void k_coeff_first(
   if (wall_row(g, y, i)) wall_coeffs(a, wt, i);
   if (kTape) {
     const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + y;
-    tape[s] = a[slot(0, 0)];
-    tape[S2 + s] = a[slot(1, 0)];
-    tape[2 * S2 + s] = a[slot(0, 1)];
-    tape[3 * S2 + s] = mad(2.0, a[slot(0, 0)], a[slot(2, 0)] + a[slot(0, 2)]);
+    store_tape(tape, S2, s, a);
   }
   collide_coeffs(a, P);
   store_coeffs(dst, g, x, y, a);
@@ -587,39 +601,75 @@ __global__ __launch_bounds__(kThreads) void k_coeff_adjoint_first(
 
 // Last kernel of a run: lambda_l(z) = mu_l(z + e_l), rebuilt from the source
 // site's coefficients and passed to its row as in the sweep.
-template <int ex>
-__device__ __forceinline__ void export_groups(const double* src, double* lam, const CGeom& g,
-                                              const LamAt& la, int x, int lane, const Row& r,
-                                              double* lds) {
-  int xs = x + ex;
-  xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
-  double b[NC], zero;
-  load_column(column_rsrc(src, g, xs), g, r.load, b);
-  put_group<Adjoint, ex>(b, lds, lane, zero);
-  wave_lds_fence();
-  Group f;
-  get_group<Adjoint, ex>(lds, lane, zero, f);
-  wave_lds_fence();
-  if (r.store != kOutside) {
-    double* out = lam + x * la.cs + r.y;
-    __builtin_nontemporal_store(f.zero, &out[label(ex, 0) * la.ps]);
-#pragma unroll
-    for (int k = 1; k <= reach(ex); ++k) {
-      __builtin_nontemporal_store(f.plus[k - 1], &out[label(ex, k) * la.ps]);
-      __builtin_nontemporal_store(f.minus[k - 1], &out[label(ex, -k) * la.ps]);
+struct ExportWalk {
+  const double* src;
+  double* lam;
+  const CGeom& g;
+  const LamAt& la;
+  int lane;
+  Row row;
+  double* lds;
+
+  template <int ex>
+  __device__ __forceinline__ void group(const double (&b)[NC], int x) const {
+    double zero;
+    put_group<Adjoint, ex>(b, lds, lane, zero);
+    wave_lds_fence();
+    Group f;
+    get_group<Adjoint, ex>(lds, lane, zero, f);
+    wave_lds_fence();
+    if (row.store == kOutside || x >= g.lx) return;
+    double* out = lam + x * la.cs + row.y;
+    store<ex, 0>(out, f.zero);
+    pair<ex, 1>(out, f);
+  }
+  template <int ex, int ey>
+  __device__ __forceinline__ void store(double* out, double v) const {
+    constexpr int l = label(ex, ey);
+    __builtin_nontemporal_store(v, &out[l * la.ps]);
+  }
+  template <int ex, int k>
+  __device__ __forceinline__ void pair(double* out, const Group& f) const {
+    store<ex, k>(out, f.plus[k - 1]);
+    store<ex, -k>(out, f.minus[k - 1]);
+    if constexpr (k < reach(ex)) pair<ex, k + 1>(out, f);
+  }
+  // source column x0 - 3 + j of a strip of TX columns
+  template <int TX, int j, int t>
+  __device__ __forceinline__ void targets(const double (&b)[NC], int x0) const {
+    if constexpr (t < TX) {
+      constexpr int ex = j - 3 - t;
+      if constexpr (ex >= -3 && ex <= 3) group<ex>(b, x0 + t);
+      targets<TX, j, t + 1>(b, x0);
     }
   }
-  if constexpr (ex > -3) export_groups<ex - 1>(src, lam, g, la, x, lane, r, lds);
-}
+  template <int TX, int j>
+  __device__ __forceinline__ void walk(int x0, double (&b)[NC]) const {
+    if constexpr (j < TX + 6) {
+      double next[NC];
+      if constexpr (j + 1 < TX + 6) load(x0 - 2 + j, next);
+      targets<TX, j, 0>(b, x0);
+      walk<TX, j + 1>(x0, next);
+    }
+  }
+  __device__ __forceinline__ void load(int x, double (&b)[NC]) const {
+    x = x < 0 ? x + g.lx : (x >= g.lx ? x - g.lx : x);
+    load_column(column_rsrc(src, g, x), g, row.load, b);
+  }
+};
 
+template <int TX>
 __global__ __launch_bounds__(64 * kWaves) void k_coeff_adjoint_last(
     const double* __restrict__ src, double* __restrict__ lam, CGeom g, Geom gf, unsigned nb) {
   __shared__ double lds[kWaves][kWaveLds<1>];
-  int w, x;
-  if (!wave_tile<1>(g, nb, w, x)) return;
+  int w, x0;
+  if (!wave_tile<Forward, TX>(g, nb, w, x0)) return;
+  const LamAt la = lam_at(gf);
   const int lane = threadIdx.x & 63;
-  export_groups<3>(src, lam, g, lam_at(gf), x, lane, wave_row(g, w, lane),
-                   &lds[threadIdx.x >> 6][kHalo]);
+  const ExportWalk e{src, lam, g, la, lane, wave_row(g, w, lane), &lds[threadIdx.x >> 6][kHalo]};
+  double b[NC];
+  e.load(x0 - 3, b);
+  e.template walk<TX, 0>(x0, b);
 }
 
 // One transposed step on compact arrays: aligned reads, every component
@@ -692,10 +742,15 @@ unsigned sweep_grid(const CGeom& g, int tx) {
   return unsigned((waves + kWaves - 1) / kWaves);
 }
 
-// Columns per wave: the largest that still gives every SIMD its waves.
+// Columns per wave, by the wave-columns (56 rows of one column) of the
+// lattice.  Measured step times in us for 1 / 2 / 3 / 4 columns per wave:
+// 256 x 128 (768): 6.0 / 7.4 / 9.8 / 11.8; 331 x 205 (1324): 7.7 / 7.7 / 10.0 /
+// 12.1; 512 x 512 (5120): 23 / 20 / 16.6 / 20; 1024 x 1024 (19456): 80 / 58 /
+// 57.2 / 57.4; 1920 x 2048 (71040): 279 / 203 / 185 / 179.  Few wave-columns:
+// the walk's length is what counts; many: the re-read columns.
 int sweep_columns(const CGeom& g) {
   const long long cols = (long long)g.nw * g.lx;
-  return cols >= 4 * 4096 ? 4 : cols >= 2048 ? 2 : 1;
+  return cols >= 40960 ? 4 : cols >= 3584 ? 3 : cols >= 1536 ? 2 : 1;
 }
 
 }  // namespace
@@ -722,11 +777,13 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
                          tape, nb, guard, word_of(dst));
     };
     if (tx == 4)
-      tape ? run(k_coeff_step<4, 2, true>) : run(k_coeff_step<4, 2, false>);
+      tape ? run(k_coeff_step<4, 3, true>) : run(k_coeff_step<4, 3, false>);
+    else if (tx == 3)
+      tape ? run(k_coeff_step<3, 2, true>) : run(k_coeff_step<3, 2, false>);
     else if (tx == 2)
-      tape ? run(k_coeff_step<2, 1, true>) : run(k_coeff_step<2, 1, false>);
+      tape ? run(k_coeff_step<2, 2, true>) : run(k_coeff_step<2, 2, false>);
     else
-      tape ? run(k_coeff_step<1, 7, true>) : run(k_coeff_step<1, 7, false>);
+      tape ? run(k_coeff_step<1, 2, true>) : run(k_coeff_step<1, 2, false>);
   }
   return hipGetLastError();
 }
@@ -800,20 +857,26 @@ hipError_t launch_coeff_adjoint_mu(const double* tape, const double* in, bool fr
                        coeffs(static_cast<void*>(mu_out)), g, p, wt, nb);
   };
   if (tx == 4)
-    run(k_coeff_adjoint<4, 1>);
+    run(k_coeff_adjoint<4, 2>);
+  else if (tx == 3)
+    run(k_coeff_adjoint<3, 2>);
   else if (tx == 2)
-    run(k_coeff_adjoint<2, 1>);
+    run(k_coeff_adjoint<2, 2>);
   else
-    run(k_coeff_adjoint<1, 7>);
+    run(k_coeff_adjoint<1, 2>);
   return hipGetLastError();
 }
 
 hipError_t launch_coeff_adjoint_gather(const double* mu, double* lam, const Geom& gf,
                                        hipStream_t s) {
   const CGeom g = make_cgeom(gf);
-  const unsigned nb = sweep_grid(g, 1);
-  hipLaunchKernelGGL(k_coeff_adjoint_last, dim3(nb), dim3(64 * kWaves), 0, s, coeffs(static_cast<const void*>(mu)), lam, g,
-                     gf, nb);
+  const int tx = sweep_columns(g) > 2 ? 4 : 1;
+  const unsigned nb = sweep_grid(g, tx);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * kWaves), 0, s,
+                       coeffs(static_cast<const void*>(mu)), lam, g, gf, nb);
+  };
+  tx == 4 ? run(k_coeff_adjoint_last<4>) : run(k_coeff_adjoint_last<1>);
   return hipGetLastError();
 }
 
