@@ -1,16 +1,28 @@
 // Device code of the coefficient form of the lattice state.
 //
 // After a collision with the Hermite projection (Sec. 2) the 37 populations
-// of a site are fixed by its 15 relaxed Hermite coefficients b_pq, p + q <= 4:
-//   f_l = w_l sum_pq b_pq He_p(c_lx) He_q(c_ly) / (p! q!).
+// of a site are the weights times a polynomial of degree four in the hop:
+//   f_l = w_l sum_ij c_ij e_lx^i e_ly^j,  i + j <= 4  (15 coefficients).
 // The coefficient form stores those 15 FP64 numbers instead of the 37
 // populations (120 instead of 296 bytes per site); a reader rebuilds a
-// population from its source site's coefficients with the same operations
-// that made the stored populations before, so nothing is rounded in between.
-// The adjoint's mu = B^T C^T lambda has the same structure
-//   mu_l = sum_pq B_pq He_p(c_lx) He_q(c_ly)
-// (times zero for the populations a wall supplied, which no reader asks for)
-// and is stored the same way.
+// population from its source site's coefficients.  The arriving populations
+// enter a regularized collision only through their 15 moments
+//   m_ij = sum_l f_l e_lx^i e_ly^j,
+// so those are what a reader sums up.  Powers of the integer hops cost far
+// less than Hermite polynomials of the scaled velocities c_l = r e_l: most of
+// the factors are 1, 2, 3, 4, 8, 9, .. (additions, or constants the
+// instructions hold), where the Hermite values are 64-bit constants that do
+// not fit the scalar registers all at once.
+//
+// The Hermite projection lives in to_poly, the step from moments to
+// coefficients: with the moments of w itself (Gaussian up to degree eight),
+// m = Gram c, so c = Gram^-1 m; to_poly goes through the scaled Hermite
+// coefficients.  Gram is symmetric, and so the adjoint, which needs the
+// transposed map, uses to_poly as well: its mu = B^T C^T lambda is
+//   mu_l = sum_ij C_ij e_lx^i e_ly^j
+// (times zero for the populations a wall supplied, which no reader asks for),
+// stored the same way, and lambda enters through
+//   M_ij = sum_l w_l lambda_l e_lx^i e_ly^j.
 //
 // Everything here is written with explicit fused multiply-adds and without
 // contraction, so that every kernel that computes the same quantity gets the
@@ -26,10 +38,19 @@
 
 namespace d2q37 {
 
-__host__ __device__ constexpr int slot(int p, int q) {
+// Storage order of the exponents (i, j): the twelve that carry the
+// macroscopic fields in the first six pair planes.
+constexpr int kCI[NC] = {0, 2, 0, 4, 0, 2, 1, 3, 1, 0, 0, 2, 1, 3, 1};
+constexpr int kCJ[NC] = {0, 0, 2, 0, 4, 2, 0, 0, 2, 1, 3, 1, 1, 1, 3};
+__host__ __device__ constexpr int slot(int i, int j) {
   for (int k = 0; k < NC; ++k)
-    if (kCP[k] == p && kCQ[k] == q) return k;
+    if (kCI[k] == i && kCJ[k] == j) return k;
   return -1;
+}
+__host__ __device__ constexpr double ipow(int e, int n) {
+  double v = 1.0;
+  for (int k = 0; k < n; ++k) v *= e;
+  return v;
 }
 
 // Geometry of a coefficient buffer: no halos.  Column x is cs doubles long:
@@ -43,17 +64,27 @@ struct CGeom {
   long long cs;     // NC * pitch
 };
 
-// The walls in coefficient space.  A wall row's unknown populations are
-// rho_w v_l (Sec. 2: fixed temperature, zero velocity), so they add
-// rho_w V_pq, V_pq = sum over the unknown l of v_l H_pq(c_l), to the
-// projection of the known ones; rho_w = a_00(known) / sum over the known l of
-// v_l.  Rows 0..2 from the bottom, then ly - 3 .. ly - 1.
+// Collision parameters in hop units (velocities over r, temperatures over r^2).
+struct CPhys {
+  double omega, keep;  // 1 / tau, 1 - 1 / tau
+  double gx, gy;       // tau g / r
+  double dt;           // temperature shift / r^2
+};
+inline CPhys make_cphys(const Phys& p) {
+  return {p.omega, 1.0 - p.omega, p.tau_gx / R, p.tau_gy / R, p.dtheta / (R * R)};
+}
+
+// The walls in moment space.  A wall row's unknown populations are rho_w v_l
+// (Sec. 2: fixed temperature, zero velocity), so they add rho_w V_ij,
+// V_ij = sum over the unknown l of v_l e_lx^i e_ly^j, to the moments of the
+// known ones; rho_w = m_00(known) / sum over the known l of v_l.  Rows 0..2
+// from the bottom, then ly - 3 .. ly - 1.
 struct WallTable {
-  double v[6][NC];  // V_pq in storage order
+  double v[6][NC];  // V_ij in storage order
   double ivk[6];    // 1 / sum over the known l of v_l
 };
 
-// V_pq and sum_known v are quadratic in th = T_wall - 1: their coefficients.
+// V_ij and sum_known v are quadratic in th = T_wall - 1: their coefficients.
 struct WallBasis {
   double v[3][6][NC], known[3][6];
 };
@@ -69,7 +100,7 @@ constexpr WallBasis make_wall_basis() {
       for (int n = 0; n < 3; ++n) {
         if (!unknown) b.known[n][i] += v[n];
         for (int k = 0; unknown && k < NC; ++k)
-          b.v[n][i][k] += v[n] * he(EX[l], kCP[k]) * he(EY[l], kCQ[k]);
+          b.v[n][i][k] += v[n] * ipow(EX[l], kCI[k]) * ipow(EY[l], kCJ[k]);
       }
     }
   return b;
@@ -106,55 +137,50 @@ __host__ __device__ constexpr int label(int ex, int ey) {
   return -1;
 }
 
-// The two uses of the expansion and its transpose.
-//   Forward: f_l = w_l sum b_pq H_pq / (p! q!),  a_pq = sum f_l H_pq
-//   Adjoint: mu_l = sum B_pq H_pq,               L_pq = sum w_l lambda_l H_pq
-// (the adjoint's 1 / (p! q!) is applied to the finished L_pq).
+// The two uses of the expansion and its transpose: where the weights go.
 struct Forward {
-  static __host__ __device__ constexpr double up(int e, int n) { return hef(e, n); }
   static __host__ __device__ constexpr double wup(int l) { return W[l]; }
   static __host__ __device__ constexpr double wdown(int) { return 1.0; }
 };
 struct Adjoint {
-  static __host__ __device__ constexpr double up(int e, int n) { return he(e, n); }
   static __host__ __device__ constexpr double wup(int) { return 1.0; }
   static __host__ __device__ constexpr double wdown(int l) { return W[l]; }
 };
 
-// P_q = sum_p b_pq He_p(c_x) (/ p!) for the hops with e_x = ex
-template <class K, int ex>
-__device__ __forceinline__ void column_sums(const double (&b)[NC], double (&P)[5]) {
+// y + c x for the constant factors of the sums
+template <class T>
+__device__ __forceinline__ double add_scaled(T c, double x, double y) {
+  return c == 1.0 ? y + x : c == -1.0 ? y - x : mad(c, x, y);
+}
+
+// P_j = sum_i c_ij ex^i
+template <int ex>
+__device__ __forceinline__ void column_sums(const double (&c)[NC], double (&P)[5]) {
 #pragma unroll
-  for (int q = 0; q < 5; ++q) {
-    double s = b[slot(0, q)];
+  for (int j = 0; j < 5; ++j) {
+    double s = c[slot(0, j)];
 #pragma unroll
-    for (int p = 1; p + q < 5; ++p) {
-      const double h = K::up(ex, p);
-      if (h != 0.0) s = mad(h, b[slot(p, q)], s);
-    }
-    P[q] = s;
+    for (int i = 1; i + j < 5; ++i)
+      if (ex != 0) s = add_scaled(ipow(ex, i), c[slot(i, j)], s);
+    P[j] = s;
   }
 }
 
 // populations (ex, 0) and (ex, +-k) from the column sums: the parts even and
-// odd in e_y once, their sum and difference
+// odd in e_y once, then their sum and difference
 template <class K, int ex>
 __device__ __forceinline__ double population0(const double (&P)[5]) {
   constexpr double w = K::wup(label(ex, 0));
-  double e = w == 1.0 ? P[0] : w * P[0];
-  e = mad(w * K::up(0, 2), P[2], e);
-  return mad(w * K::up(0, 4), P[4], e);
+  return w == 1.0 ? P[0] : w * P[0];
 }
 template <class K, int ex, int k>
 __device__ __forceinline__ void populations(const double (&P)[5], double& plus, double& minus) {
-  constexpr double w = K::wup(label(ex, k));
-  double e = w == 1.0 ? P[0] : w * P[0];
-  e = mad(w * K::up(k, 2), P[2], e);
-  e = mad(w * K::up(k, 4), P[4], e);
-  double o = (w * K::up(k, 1)) * P[1];
-  o = mad(w * K::up(k, 3), P[3], o);
-  plus = e + o;
-  minus = e - o;
+  constexpr double w = K::wup(label(ex, k)), wk = w * k;
+  double e = add_scaled(ipow(k, 4), P[4], add_scaled(ipow(k, 2), P[2], P[0]));
+  const double o = add_scaled(ipow(k, 2), P[3], P[1]);
+  if (w != 1.0) e = w * e;
+  plus = add_scaled(wk, o, e);
+  minus = add_scaled(-wk, o, e);
 }
 
 // One e_x group of a site's arriving populations: (ex, 0) and (ex, +-k).
@@ -162,48 +188,49 @@ struct Group {
   double zero, plus[3], minus[3];
 };
 
-// s_q += contributions of (ex, +-k)
+// s_j += contributions of (ex, +-k)
 template <class K, int ex, int k>
 __device__ __forceinline__ void project_pairs(const Group& f, double (&s)[5]) {
   constexpr double w = K::wdown(label(ex, k));
-  constexpr double w1 = w * he(k, 1), w2 = w * he(k, 2), w3 = w * he(k, 3), w4 = w * he(k, 4);
-  const double sum = f.plus[k - 1] + f.minus[k - 1], dif = f.plus[k - 1] - f.minus[k - 1];
-  s[0] = w == 1.0 ? s[0] + sum : mad(w, sum, s[0]);
-  s[1] = k == 1 ? w1 * dif : mad(w1, dif, s[1]);
-  s[2] = mad(w2, sum, s[2]);
-  s[3] = k == 1 ? w3 * dif : mad(w3, dif, s[3]);
-  s[4] = mad(w4, sum, s[4]);
+  double sum = f.plus[k - 1] + f.minus[k - 1], dif = f.plus[k - 1] - f.minus[k - 1];
+  if (w != 1.0) {
+    sum = w * sum;
+    dif = w * dif;
+  }
+  s[0] = s[0] + sum;
+  s[1] = k == 1 ? dif : mad(ipow(k, 1), dif, s[1]);
+  s[2] = k == 1 ? sum : mad(ipow(k, 2), sum, s[2]);
+  s[3] = k == 1 ? dif : mad(ipow(k, 3), dif, s[3]);
+  s[4] = k == 1 ? sum : mad(ipow(k, 4), sum, s[4]);
   if constexpr (k < reach(ex)) project_pairs<K, ex, k + 1>(f, s);
 }
 
-// a_pq += contribution of the group; groups arrive with ex = 3 first (which
+// m_ij += contribution of the group; groups arrive with ex = 3 first (which
 // starts the sums), then 2, ... -3
 template <class K, int ex>
-__device__ __forceinline__ void project_group(const Group& f, double (&a)[NC]) {
+__device__ __forceinline__ void project_group(const Group& f, double (&m)[NC]) {
   constexpr double w = K::wdown(label(ex, 0));
-  const double s0 = w == 1.0 ? f.zero : w * f.zero;
-  double s[5] = {s0, 0.0, -s0, 0.0, 3.0 * s0};
+  double s[5] = {w == 1.0 ? f.zero : w * f.zero, 0.0, 0.0, 0.0, 0.0};
   project_pairs<K, ex, 1>(f, s);
 #pragma unroll
-  for (int p = 0; p < 5; ++p) {
-    const double h = he(ex, p);
-    if (h == 0.0) continue;
+  for (int i = 0; i < (ex == 0 ? 1 : 5); ++i) {
+    const double h = ipow(ex, i);
 #pragma unroll
-    for (int q = 0; p + q < 5; ++q) {
-      double& t = a[slot(p, q)];
+    for (int j = 0; i + j < 5; ++j) {
+      double& t = m[slot(i, j)];
       if (ex == 3)
-        t = p == 0 ? s[q] : h * s[q];
+        t = i == 0 ? s[j] : h * s[j];
       else
-        t = p == 0 ? t + s[q] : mad(h, s[q], t);
+        t = add_scaled(h, s[j], t);
     }
   }
 }
 
 // the populations of one e_x group of a site from its coefficients
 template <class K, int ex>
-__device__ __forceinline__ void expand_group(const double (&b)[NC], Group& f) {
+__device__ __forceinline__ void expand_group(const double (&c)[NC], Group& f) {
   double P[5];
-  column_sums<K, ex>(b, P);
+  column_sums<ex>(c, P);
   f.zero = population0<K, ex>(P);
   populations<K, ex, 1>(P, f.plus[0], f.minus[0]);
   if constexpr (reach(ex) >= 2) populations<K, ex, 2>(P, f.plus[1], f.minus[1]);
@@ -227,134 +254,181 @@ __device__ __forceinline__ void from_labels(const double (&v)[Q], Group& f) {
   if constexpr (k < reach(ex)) from_labels<ex, k + 1>(v, f);
 }
 
-// all 37 populations of a site <-> its coefficients / their projection
+// all 37 populations of a site <-> its coefficients / their moments
 template <class K, int ex = 3>
-__device__ __forceinline__ void expand_site(const double (&b)[NC], double (&v)[Q]) {
+__device__ __forceinline__ void expand_site(const double (&c)[NC], double (&v)[Q]) {
   Group f;
-  expand_group<K, ex>(b, f);
+  expand_group<K, ex>(c, f);
   to_labels<ex>(f, v);
-  if constexpr (ex > -3) expand_site<K, ex - 1>(b, v);
+  if constexpr (ex > -3) expand_site<K, ex - 1>(c, v);
 }
 template <class K, int ex = 3>
-__device__ __forceinline__ void project_site(const double (&v)[Q], double (&a)[NC]) {
+__device__ __forceinline__ void project_site(const double (&v)[Q], double (&m)[NC]) {
   Group f;
   from_labels<ex>(v, f);
-  project_group<K, ex>(f, a);
-  if constexpr (ex > -3) project_site<K, ex - 1>(v, a);
+  project_group<K, ex>(f, m);
+  if constexpr (ex > -3) project_site<K, ex - 1>(v, m);
 }
 
-// The walls: a holds the projection of the known populations.
-__device__ __forceinline__ void wall_coeffs(double (&a)[NC], const WallTable& wt, int i) {
-  const double rho_w = a[0] * wt.ivk[i];
-#pragma unroll
-  for (int k = 0; k < NC; ++k) a[k] = mad(rho_w, wt.v[i][k], a[k]);
+// Powers of r, and the moments of w: sum w e_x^2 = r^-2, sum w e_x^4 = 3 r^-4,
+// sum w e_x^2 e_y^2 = r^-4, ...
+constexpr double kR2 = R * R, kR4 = kR2 * kR2, kR6 = kR4 * kR2, kR8 = kR4 * kR4;
+constexpr double kr2 = 1.0 / kR2, kr4 = 1.0 / kR4, kr6 = 1.0 / kR6;
+
+// Hermite coefficients scaled by r^(p+q) / (p! q!) -> polynomial coefficients,
+// in place (the leading ones are the same; lower ones get the tails of He_n).
+__device__ __forceinline__ void add_tails(double (&b)[NC]) {
+  const double b40 = b[slot(4, 0)], b04 = b[slot(0, 4)], b22 = b[slot(2, 2)];
+  const double b20 = b[slot(2, 0)], b02 = b[slot(0, 2)];
+  double c0 = mad(-kr2, b20 + b02, b[slot(0, 0)]);
+  c0 = mad(3.0 * kr4, b40 + b04, c0);
+  b[slot(0, 0)] = mad(kr4, b22, c0);
+  b[slot(2, 0)] = mad(-6.0 * kr2, b40, mad(-kr2, b22, b20));
+  b[slot(0, 2)] = mad(-6.0 * kr2, b04, mad(-kr2, b22, b02));
+  b[slot(1, 1)] = mad(-3.0 * kr2, b[slot(3, 1)] + b[slot(1, 3)], b[slot(1, 1)]);
+  b[slot(1, 0)] = mad(-3.0 * kr2, b[slot(3, 0)], mad(-kr2, b[slot(1, 2)], b[slot(1, 0)]));
+  b[slot(0, 1)] = mad(-3.0 * kr2, b[slot(0, 3)], mad(-kr2, b[slot(2, 1)], b[slot(0, 1)]));
 }
 
-// collide (Eq. (2) moments, forced equilibrium, relaxation): the projection
-// a_pq of the arriving populations becomes the coefficients b_pq.  Mass is
-// conserved exactly (b_00 = a_00).
-__device__ __forceinline__ void collide_coeffs(double (&a)[NC], const Phys& P) {
-  const double rho = a[slot(0, 0)], inv = 1.0 / rho;
-  const double ux = a[slot(1, 0)] * inv, uy = a[slot(0, 1)] * inv;
-  const double th0 = 0.5 * mad(a[slot(2, 0)] + a[slot(0, 2)], inv, -mad(ux, ux, uy * uy));
-  const double Ux = ux + P.tau_gx, Uy = uy + P.tau_gy, th = th0 + P.dtheta;
-  const double x2 = Ux * Ux, y2 = Uy * Uy, t3 = 3.0 * th, t6 = 6.0 * th, tt = t3 * th;
-  const double hx[5] = {1.0, Ux, x2 + th, Ux * (x2 + t3), mad(x2, x2 + t6, tt)};
-  const double hy[5] = {1.0, Uy, y2 + th, Uy * (y2 + t3), mad(y2, y2 + t6, tt)};
-  const double keep = 1.0 - P.omega, om_rho = P.omega * rho;
+// c = Gram^-1 m: moments -> coefficients of the polynomial with those moments.
+__device__ __forceinline__ void to_poly(double (&m)[NC]) {
+  const double m00 = m[slot(0, 0)], m10 = m[slot(1, 0)], m01 = m[slot(0, 1)];
+  const double m20 = m[slot(2, 0)], m02 = m[slot(0, 2)], m11 = m[slot(1, 1)];
+  // r^4/24 (r^4 m40 - 6 r^2 m20 + 3 m00), ...
+  m[slot(4, 0)] = mad(kR8 / 24.0, m[slot(4, 0)], mad(-kR6 / 4.0, m20, (kR4 / 8.0) * m00));
+  m[slot(0, 4)] = mad(kR8 / 24.0, m[slot(0, 4)], mad(-kR6 / 4.0, m02, (kR4 / 8.0) * m00));
+  m[slot(2, 2)] = mad(kR8 / 4.0, m[slot(2, 2)], mad(-kR6 / 4.0, m20 + m02, (kR4 / 4.0) * m00));
+  m[slot(3, 1)] = mad(kR8 / 6.0, m[slot(3, 1)], (-kR6 / 2.0) * m11);
+  m[slot(1, 3)] = mad(kR8 / 6.0, m[slot(1, 3)], (-kR6 / 2.0) * m11);
+  // r^3/6 (r^3 m30 - 3 r m10), r^3/2 (r^3 m21 - r m01), ...
+  m[slot(3, 0)] = mad(kR6 / 6.0, m[slot(3, 0)], (-kR4 / 2.0) * m10);
+  m[slot(0, 3)] = mad(kR6 / 6.0, m[slot(0, 3)], (-kR4 / 2.0) * m01);
+  m[slot(2, 1)] = mad(kR6 / 2.0, m[slot(2, 1)], (-kR4 / 2.0) * m01);
+  m[slot(1, 2)] = mad(kR6 / 2.0, m[slot(1, 2)], (-kR4 / 2.0) * m10);
+  // r^2/2 (r^2 m20 - m00), r^4 m11, r^2 m10
+  m[slot(2, 0)] = mad(kR4 / 2.0, m20, (-kR2 / 2.0) * m00);
+  m[slot(0, 2)] = mad(kR4 / 2.0, m02, (-kR2 / 2.0) * m00);
+  m[slot(1, 1)] = kR4 * m11;
+  m[slot(1, 0)] = kR2 * m10;
+  m[slot(0, 1)] = kR2 * m01;
+  add_tails(m);
+}
+
+// The walls: m holds the moments of the known populations.
+__device__ __forceinline__ void wall_moments(double (&m)[NC], const WallTable& wt, int i) {
+  const double rho_w = m[0] * wt.ivk[i];
 #pragma unroll
-  for (int p = 0; p < 5; ++p) {
-    const double gp = p == 0 ? om_rho : om_rho * hx[p];
+  for (int k = 0; k < NC; ++k) m[k] = mad(rho_w, wt.v[i][k], m[k]);
+}
+
+// collide: the moments m_ij of the arriving populations become the
+// coefficients c_ij of the collided ones.  Eq. (2) moments; the equilibrium
+// has the raw moments rho G_i(U_x) G_j(U_y) of a Gaussian up to order four
+// (G_0..4 = 1, U, U^2 + T, U^3 + 3 U T, U^4 + 6 U^2 T + 3 T^2), taken at the
+// forced U and T; relaxation with rate omega, then the projection.  Mass is
+// conserved exactly (m_00 is not touched).
+__device__ __forceinline__ void collide_moments(double (&m)[NC], const CPhys& P) {
+  const double rho = m[slot(0, 0)], inv = 1.0 / rho;
+  const double ux = m[slot(1, 0)] * inv, uy = m[slot(0, 1)] * inv;
+  const double t0 = 0.5 * mad(m[slot(2, 0)] + m[slot(0, 2)], inv, -mad(ux, ux, uy * uy));
+  const double Ux = ux + P.gx, Uy = uy + P.gy, T = t0 + P.dt;
+  const double x2 = Ux * Ux, y2 = Uy * Uy, t3 = 3.0 * T, tt = t3 * T;
+  const double gx[5] = {1.0, Ux, x2 + T, Ux * (x2 + t3), mad(x2, mad(6.0, T, x2), tt)};
+  const double gy[5] = {1.0, Uy, y2 + T, Uy * (y2 + t3), mad(y2, mad(6.0, T, y2), tt)};
+  const double om_rho = P.omega * rho;
 #pragma unroll
-    for (int q = 0; p + q < 5; ++q) {
-      if (p + q == 0) continue;
-      double& t = a[slot(p, q)];
-      t = q == 0 ? mad(keep, t, gp) : mad(gp, hy[q], keep * t);
+  for (int i = 0; i < 5; ++i) {
+    const double r = i == 0 ? om_rho : om_rho * gx[i];
+#pragma unroll
+    for (int j = 0; i + j < 5; ++j) {
+      if (i + j == 0) continue;
+      double& t = m[slot(i, j)];
+      t = j == 0 ? mad(P.keep, t, r) : mad(r, gy[j], P.keep * t);
     }
   }
+  to_poly(m);
 }
 
-// Eq. (2) fields of a site from its coefficients.
-__device__ __forceinline__ Macro macro_coeffs(double b00, double b10, double b01, double b20,
-                                              double b02) {
-  Macro m;
-  m.rho = b00;
-  m.inv_rho = 1.0 / b00;
-  m.ux = b10 * m.inv_rho;
-  m.uy = b01 * m.inv_rho;
-  m.th = 0.5 * mad(b20 + b02, m.inv_rho, -mad(m.ux, m.ux, m.uy * m.uy));
-  return m;
+// Eq. (2) fields of a site from its coefficients (the first twelve).
+__device__ __forceinline__ Macro macro_coeffs(const double (&c)[12]) {
+  const double c00 = c[slot(0, 0)], c2s = c[slot(2, 0)] + c[slot(0, 2)];
+  const double c4s = c[slot(4, 0)] + c[slot(0, 4)], c22 = c[slot(2, 2)];
+  const double m10 =
+      mad(kr4, c[slot(1, 2)], mad(3.0 * kr4, c[slot(3, 0)], kr2 * c[slot(1, 0)]));
+  const double m01 =
+      mad(kr4, c[slot(2, 1)], mad(3.0 * kr4, c[slot(0, 3)], kr2 * c[slot(0, 1)]));
+  Macro f;
+  f.rho = mad(kr4, c22, mad(3.0 * kr4, c4s, mad(kr2, c2s, c00)));
+  // sum |c|^2 f = r^2 (m20 + m02)
+  const double e = mad(6.0 * kr4, c22, mad(18.0 * kr4, c4s, mad(4.0 * kr2, c2s, 2.0 * c00)));
+  f.inv_rho = 1.0 / f.rho;
+  f.ux = R * m10 * f.inv_rho;
+  f.uy = R * m01 * f.inv_rho;
+  f.th = 0.5 * mad(e, f.inv_rho, -mad(f.ux, f.ux, f.uy * f.uy)) - 1.0;
+  return f;
 }
 
-// B^T C(m)^T in coefficient space: L holds sum_l w_l lambda_l H_pq at the
-// site's arriving populations, m = (rho, j_x, j_y, sum |c|^2 f) the
-// pre-collision moments; on return L holds the coefficients B_pq of mu, with
-// the wall's share of the unknown populations' adjoint (their sum weighted by
-// v_l, over sum_known v) added to every known one: a shift of B_00.
-__device__ __forceinline__ void adjoint_coeffs(double (&L)[NC], double rho, double jx, double jy,
-                                               double e, const Phys& P) {
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const double s = INVFAC[kCP[k]] * INVFAC[kCQ[k]];
-    if (s != 1.0) L[k] = s * L[k];
-  }
+// B^T C^T of a site: M holds sum_l w_l lambda_l e^ij at the site's arriving
+// populations, (rho, jx, jy, e) the pre-collision moments of the tape (rho,
+// rho u, sum |c|^2 f); on return M holds the coefficients C_ij of mu.
+__device__ __forceinline__ void adjoint_moments(double (&M)[NC], double rho, double jx, double jy,
+                                                double e, const CPhys& P) {
+  to_poly(M);  // now the gradient with respect to the relaxed moments
   const double inv = 1.0 / rho;
-  const double ux = jx * inv, uy = jy * inv;
+  const double ux = (jx * (1.0 / R)) * inv, uy = (jy * (1.0 / R)) * inv;
   const double u2 = mad(ux, ux, uy * uy);
-  const double th = mad(0.5 * e, inv, -1.0) - 0.5 * u2;
-  const double Ux = ux + P.tau_gx, Uy = uy + P.tau_gy, ths = th + P.dtheta;
-  // h_n, dh_n/dU, dh_n/dTh of both directions
-  const double x2 = Ux * Ux, y2 = Uy * Uy, t3 = 3.0 * ths, tt = t3 * ths;
-  const double hx[5] = {1.0, Ux, x2 + ths, Ux * (x2 + t3), mad(x2, mad(6.0, ths, x2), tt)};
-  const double hy[5] = {1.0, Uy, y2 + ths, Uy * (y2 + t3), mad(y2, mad(6.0, ths, y2), tt)};
+  const double t0 = 0.5 * mad(e * kr2, inv, -u2);
+  const double Ux = ux + P.gx, Uy = uy + P.gy, T = t0 + P.dt;
+  // G_n, dG_n/dU = n G_(n-1), dG_n/dT = n (n - 1) / 2 G_(n-2) of both directions
+  const double x2 = Ux * Ux, y2 = Uy * Uy, t3 = 3.0 * T, tt = t3 * T;
+  const double hx[5] = {1.0, Ux, x2 + T, Ux * (x2 + t3), mad(x2, mad(6.0, T, x2), tt)};
+  const double hy[5] = {1.0, Uy, y2 + T, Uy * (y2 + t3), mad(y2, mad(6.0, T, y2), tt)};
   const double dx[5] = {0.0, 1.0, 2.0 * Ux, 3.0 * hx[2], 4.0 * hx[3]};
   const double dy[5] = {0.0, 1.0, 2.0 * Uy, 3.0 * hy[2], 4.0 * hy[3]};
   const double tx[5] = {0.0, 0.0, 1.0, 3.0 * Ux, 6.0 * hx[2]};
   const double ty[5] = {0.0, 0.0, 1.0, 3.0 * Uy, 6.0 * hy[2]};
   double gr = 0.0, gx = 0.0, gy = 0.0, gt = 0.0;
 #pragma unroll
-  for (int p = 0; p < 5; ++p) {
-    // rows over q: sum_q L_pq h_q, sum_q L_pq dh_q/dU, sum_q L_pq dh_q/dTh
-    double r = L[slot(p, 0)], ru = 0.0, rt = 0.0;
+  for (int i = 0; i < 5; ++i) {
+    // over j: sum M_ij G_j, sum M_ij dG_j/dU, sum M_ij dG_j/dT
+    double r = M[slot(i, 0)], ru = 0.0, rt = 0.0;
 #pragma unroll
-    for (int q = 1; p + q < 5; ++q) {
-      const double l = L[slot(p, q)];
-      r = mad(l, hy[q], r);
-      ru = q == 1 ? l : mad(l, dy[q], ru);
-      if (q == 2) rt = l;
-      if (q > 2) rt = mad(l, ty[q], rt);
+    for (int j = 1; i + j < 5; ++j) {
+      const double l = M[slot(i, j)];
+      r = mad(l, hy[j], r);
+      ru = j == 1 ? l : mad(l, dy[j], ru);
+      if (j == 2) rt = l;
+      if (j > 2) rt = mad(l, ty[j], rt);
     }
-    gr = p == 0 ? r : mad(hx[p], r, gr);
-    if (p == 1) gx = r;
-    if (p > 1) gx = mad(dx[p], r, gx);
-    if (p < 4) gy = p == 0 ? ru : mad(hx[p], ru, gy);
-    if (p < 3) gt = p == 0 ? rt : mad(hx[p], rt, gt);
-    if (p > 1) gt = mad(tx[p], r, gt);
+    gr = i == 0 ? r : mad(hx[i], r, gr);
+    if (i == 1) gx = r;
+    if (i > 1) gx = mad(dx[i], r, gx);
+    if (i < 4) gy = i == 0 ? ru : mad(hx[i], ru, gy);
+    if (i < 3) gt = i == 0 ? rt : mad(hx[i], rt, gt);
+    if (i > 1) gt = mad(tx[i], r, gt);
   }
-  const double om = P.omega, orho = om * rho;
-  gr *= om;
-  gx *= orho;
-  gy *= orho;
-  gt *= orho;
-  const double g00 = gr - (mad(ux, gx, uy * gy) - gt * mad(0.5, u2, -th)) * inv;
-  const double g10 = mad(-ux, gt, gx) * inv;
-  const double g01 = mad(-uy, gt, gy) * inv;
-  const double ge2 = 0.5 * gt * inv;
-  const double keep = 1.0 - om;
+  const double om_rho = P.omega * rho;
+  gr *= P.omega;
+  gx *= om_rho;
+  gy *= om_rho;
+  gt *= om_rho;
 #pragma unroll
-  for (int k = 0; k < NC; ++k) L[k] = keep * L[k];
-  L[slot(0, 0)] += g00;
-  L[slot(1, 0)] += g10;
-  L[slot(0, 1)] += g01;
-  L[slot(2, 0)] += ge2;
-  L[slot(0, 2)] += ge2;
+  for (int k = 0; k < NC; ++k) M[k] = P.keep * M[k];
+  M[slot(0, 0)] += gr - (mad(ux, gx, uy * gy) - gt * mad(0.5, u2, -t0)) * inv;
+  M[slot(1, 0)] += mad(-ux, gt, gx) * inv;
+  M[slot(0, 1)] += mad(-uy, gt, gy) * inv;
+  const double ge = 0.5 * gt * inv;
+  M[slot(2, 0)] += ge;
+  M[slot(0, 2)] += ge;
 }
 
-__device__ __forceinline__ void wall_adjoint(double (&B)[NC], const WallTable& wt, int i) {
+// the share of the unknown populations' adjoint (their sum weighted by v_l,
+// over sum_known v) that every known one gets: a shift of C_00
+__device__ __forceinline__ void wall_adjoint(double (&C)[NC], const WallTable& wt, int i) {
   double su = 0.0;
 #pragma unroll
-  for (int k = 0; k < NC; ++k) su = mad(B[k], wt.v[i][k], su);
-  B[slot(0, 0)] = mad(su, wt.ivk[i], B[slot(0, 0)]);
+  for (int k = 0; k < NC; ++k) su = mad(C[k], wt.v[i][k], su);
+  C[slot(0, 0)] = mad(su, wt.ivk[i], C[slot(0, 0)]);
 }
 
 }  // namespace d2q37

@@ -14,16 +14,18 @@
 // six source columns after its first and is collided and stored at once.
 //
 // What bounds it and why this split.  The step moves 240 bytes per site
-// (15 FP64 in, 15 out) instead of the 592 of the 37 populations, at 5.5 TB/s
-// (1920 x 2048: 179 us against 405; 4096 x 4096: 750 us against 1646; a copy
+// (15 FP64 in, 15 out) instead of the 592 of the 37 populations, at 5.3 TB/s
+// (1920 x 2048: 177 us against 405; 4096 x 4096: 735 us against 1646; a copy
 // reaches 5.2 to 5.7 TB/s).  Rebuilding populations is done once per (source
 // site, e_x group) whatever TX is; TX trades registers (30 VGPRs per column:
 // 4, 3, 2, 2 waves per SIMD at TX = 1, 2, 3, 4) against re-reading source
 // columns ((TX + 6) / TX times, nearly all from the XCD's L2: 1.05 x and
 // 1.11 x of the state fetched past it at TX = 3 and 4).  16-byte accesses
 // matter: with 8-byte ones the L1 handles half the bytes per cycle (230
-// against 200 us).  Source columns are loaded two or three ahead of their
-// use (191 -> 181 -> 179 us at TX = 4).
+// against 200 us).  Source columns are loaded ahead of their use (191 -> 181
+// us at TX = 4).  On small lattices the instructions of a wave's walk count:
+// powers of the hops instead of Hermite values as factors took 1305 to 1106
+// instructions per column (256 x 128: 5.7 -> 5.2 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -250,10 +252,9 @@ struct Sweep {
 __device__ __forceinline__ void store_tape(double* tape, long long S2, long long s,
                                            const double (&a)[NC]) {
   __builtin_nontemporal_store(a[slot(0, 0)], &tape[s]);
-  __builtin_nontemporal_store(a[slot(1, 0)], &tape[S2 + s]);
-  __builtin_nontemporal_store(a[slot(0, 1)], &tape[2 * S2 + s]);
-  __builtin_nontemporal_store(mad(2.0, a[slot(0, 0)], a[slot(2, 0)] + a[slot(0, 2)]),
-                              &tape[3 * S2 + s]);
+  __builtin_nontemporal_store(R * a[slot(1, 0)], &tape[S2 + s]);
+  __builtin_nontemporal_store(R * a[slot(0, 1)], &tape[2 * S2 + s]);
+  __builtin_nontemporal_store(kR2 * (a[slot(2, 0)] + a[slot(0, 2)]), &tape[3 * S2 + s]);
 }
 
 // Forward: walls on the six wall rows, optional tape of the pre-collision
@@ -262,7 +263,7 @@ template <bool kTape>
 struct StepSite {
   double* dst;
   const CGeom& g;
-  const Phys& P;
+  const CPhys& P;
   const WallTable& wt;
   double* tape;
   struct Input {};
@@ -271,14 +272,14 @@ struct StepSite {
                                          const Row& r) const {
     if (x >= g.lx) return;  // ragged last tile
     int i;
-    if (r.in && wall_row(g, r.y, i)) wall_coeffs(a, wt, i);
+    if (r.in && wall_row(g, r.y, i)) wall_moments(a, wt, i);
     if (kTape) {
       if (r.store != kOutside) {
         const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + r.y;
         store_tape(tape, S2, s, a);
       }
     }
-    collide_coeffs(a, P);
+    collide_moments(a, P);
     store_column(column_rsrc(dst, g, x), g, r.store, a);
   }
 };
@@ -287,31 +288,43 @@ struct StepSite {
 struct AdjointSite {
   double* dst;
   const CGeom& g;
-  const Phys& P;
+  const CPhys& P;
   const WallTable& wt;
   const double* tape;
   struct Input {
     double m[4];
   };
+  // Issued before the column's exchange and sums, without a branch: in a
+  // masked load the compiler puts the first use, and so the wait, right there.
   __device__ __forceinline__ void load(Input& in, int x, const Row& r) const {
-    const bool ok = x < g.lx && r.in;
-    const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + r.y;
+    if (x >= g.lx) return;  // ragged last tile (the whole wave)
+    const long long S2 = (long long)g.lx * g.ly;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) in.m[k] = ok ? __builtin_nontemporal_load(&tape[k * S2 + s]) : 1.0;
+    for (int k = 0; k < 4; ++k)
+      in.m[k] = __builtin_bit_cast(
+          double, __builtin_amdgcn_raw_buffer_load_b64(
+                      __builtin_amdgcn_make_buffer_rsrc(
+                          (void*)(tape + k * S2 + (long long)x * g.ly), (short)0, g.ly * 8,
+                          kBufferWord3),
+                      r.load >> 1, 0, kNonTemporal));
   }
   __device__ __forceinline__ void finish(const Input& in, double (&a)[NC], int x,
                                          const Row& r) const {
     if (x >= g.lx) return;
-    adjoint_coeffs(a, in.m[0], in.m[1], in.m[2], in.m[3], P);
+    adjoint_moments(a, in.m[0], in.m[1], in.m[2], in.m[3], P);
     int i;
     if (r.in && wall_row(g, r.y, i)) wall_adjoint(a, wt, i);
     store_column(column_rsrc(dst, g, x), g, r.store, a);
   }
 };
 
+// waves per SIMD that a sweep's registers leave room for
+template <int TX, int kAhead>
+constexpr int kOccupancy = TX == 1 ? 4 : (TX == 2 || (TX == 3 && kAhead == 1)) ? 3 : 2;
+
 template <int TX, int kAhead, bool kTape>
-__global__ __launch_bounds__(64 * kWaves, TX == 1 ? 4 : TX == 2 ? 3 : 2) void k_coeff_step(
-    const double* __restrict__ src, double* __restrict__ dst, CGeom g, Phys P, WallTable wt,
+__global__ __launch_bounds__(64 * kWaves, (kOccupancy<TX, kAhead>)) void k_coeff_step(
+    const double* __restrict__ src, double* __restrict__ dst, CGeom g, CPhys P, WallTable wt,
     double* __restrict__ tape, unsigned nb, const unsigned* guard, unsigned* word) {
   __shared__ double lds[kWaves][kWaveLds<TX>];
   if (other_form(guard, kFormCoeff)) return;
@@ -327,9 +340,9 @@ __global__ __launch_bounds__(64 * kWaves, TX == 1 ? 4 : TX == 2 ? 3 : 2) void k_
 }
 
 template <int TX, int kAhead>
-__global__ __launch_bounds__(64 * kWaves, TX == 1 ? 4 : TX == 2 ? 3 : 2) void k_coeff_adjoint(
+__global__ __launch_bounds__(64 * kWaves, (kOccupancy<TX, kAhead>)) void k_coeff_adjoint(
     const double* __restrict__ tape, const double* __restrict__ src, double* __restrict__ dst,
-    CGeom g, Phys P, WallTable wt, unsigned nb) {
+    CGeom g, CPhys P, WallTable wt, unsigned nb) {
   __shared__ double lds[kWaves][kWaveLds<TX>];
   int w, x0;
   if (!wave_tile<Adjoint, TX>(g, nb, w, x0)) return;
@@ -370,10 +383,14 @@ __device__ __forceinline__ void store_coeffs(double* __restrict__ dst, const CGe
 __device__ __forceinline__ Macro load_macro(const double* __restrict__ src, const CGeom& g, int x,
                                             int y) {
   const double* col = src + x * g.cs + 2 * y;
-  const v2d u = *reinterpret_cast<const v2d*>(col);
-  const v2d v = *reinterpret_cast<const v2d*>(col + 2 * (long long)g.pitch);
-  const double w = col[4 * (long long)g.pitch];
-  return macro_coeffs(u.x, u.y, v.x, v.y, w);
+  double c[12];
+#pragma unroll
+  for (int m = 0; m < 6; ++m) {
+    const v2d d = *reinterpret_cast<const v2d*>(col + 2 * m * (long long)g.pitch);
+    c[2 * m] = d.x;
+    c[2 * m + 1] = d.y;
+  }
+  return macro_coeffs(c);
 }
 
 // adjoint arrays are compact, in the lattice's layout
@@ -390,7 +407,7 @@ __device__ __forceinline__ LamAt lam_at(const Geom& g) {
 // the state was replaced).  x wraps here, so the halo columns are not read.
 template <bool kTape>
 __global__ __launch_bounds__(kThreads) void k_coeff_first(
-    const double* __restrict__ src, double* __restrict__ dst, Geom gf, CGeom g, Phys P, WallTable wt,
+    const double* __restrict__ src, double* __restrict__ dst, Geom gf, CGeom g, CPhys P, WallTable wt,
     double* __restrict__ tape, int by, int bx, int nty, unsigned nb,
     const unsigned* guard, unsigned* word) {
   if (other_form(guard, kFormFull)) return;
@@ -413,12 +430,12 @@ __global__ __launch_bounds__(kThreads) void k_coeff_first(
   double a[NC];
   project_site<Forward>(v, a);
   int i;
-  if (wall_row(g, y, i)) wall_coeffs(a, wt, i);
+  if (wall_row(g, y, i)) wall_moments(a, wt, i);
   if (kTape) {
     const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + y;
     store_tape(tape, S2, s, a);
   }
-  collide_coeffs(a, P);
+  collide_moments(a, P);
   store_coeffs(dst, g, x, y, a);
 }
 
@@ -434,8 +451,13 @@ __global__ __launch_bounds__(kThreads) void k_coeff_init(
   double aeq[5][5], b[NC];
   equilibrium_coeffs(rho[s], ux[s], uy[s], T[s] - 1.0, aeq);
 #pragma unroll
-  for (int k = 0; k < NC; ++k) b[k] = aeq[kCP[k]][kCQ[k]];
-  b[0] = rho[s];
+  for (int k = 0; k < NC; ++k) {
+    const int p = kCI[k], q = kCJ[k];
+    double scale = INVFAC[p] * INVFAC[q];  // r^(p+q) / (p! q!)
+    for (int n = 0; n < p + q; ++n) scale *= R;
+    b[k] = scale * aeq[p][q];
+  }
+  add_tails(b);
   store_coeffs(dst, g, x, y, b);
 }
 
@@ -481,7 +503,7 @@ __global__ __launch_bounds__(kThreads) void k_coeff_pack(const double* __restric
   for (int l = 0; l < Q; ++l) __builtin_nontemporal_store(v[l], &out[l * S2 + s]);
 }
 
-// Eq. (2) fields: five coefficients in, four values out (72 bytes per site).
+// Eq. (2) fields: twelve coefficients in, four values out (128 bytes per site).
 __global__ __launch_bounds__(kThreads) void k_coeff_moments(
     const double* __restrict__ src, double* __restrict__ rho, double* __restrict__ ux,
     double* __restrict__ uy, double* __restrict__ T, CGeom g, int by, int bx, int nty,
@@ -573,21 +595,21 @@ __global__ __launch_bounds__(kThreads) void k_coeff_loss_ke(const double* __rest
 // Adjoint: way in, way out, and the single step on compact arrays.
 // ---------------------------------------------------------------------------
 
-// B_pq of one site whose arriving lambda are given
+// C_ij of one site whose arriving lambda are given
 __device__ __forceinline__ void adjoint_local(const double (&lam)[Q], const double* tape,
                                               long long S2, long long s, const CGeom& g,
-                                              const Phys& P, const WallTable& wt, int y,
-                                              double (&B)[NC]) {
-  project_site<Adjoint>(lam, B);
-  adjoint_coeffs(B, tape[s], tape[S2 + s], tape[2 * S2 + s], tape[3 * S2 + s], P);
+                                              const CPhys& P, const WallTable& wt, int y,
+                                              double (&C)[NC]) {
+  project_site<Adjoint>(lam, C);
+  adjoint_moments(C, tape[s], tape[S2 + s], tape[2 * S2 + s], tape[3 * S2 + s], P);
   int i;
-  if (wall_row(g, y, i)) wall_adjoint(B, wt, i);
+  if (wall_row(g, y, i)) wall_adjoint(C, wt, i);
 }
 
 // First kernel of a run: compact lambda in, coefficients of mu out.
 __global__ __launch_bounds__(kThreads) void k_coeff_adjoint_first(
     const double* __restrict__ tape, const double* __restrict__ lam, double* __restrict__ dst,
-    Geom gf, CGeom g, Phys P, WallTable wt, int by, int bx, int nty, unsigned nb) {
+    Geom gf, CGeom g, CPhys P, WallTable wt, int by, int bx, int nty, unsigned nb) {
   int x, y;
   if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
   const LamAt la = lam_at(gf);
@@ -677,7 +699,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_coeff_adjoint_last(
 // a wall are written as zero by their own site.
 __global__ __launch_bounds__(kThreads) void k_coeff_adjoint_step(
     const double* __restrict__ tape, const double* __restrict__ lam_in,
-    double* __restrict__ lam_out, Geom gf, CGeom g, Phys P, WallTable wt, int by, int bx, int nty,
+    double* __restrict__ lam_out, Geom gf, CGeom g, CPhys P, WallTable wt, int by, int bx, int nty,
     unsigned nb) {
   int x, y;
   if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
@@ -743,15 +765,20 @@ unsigned sweep_grid(const CGeom& g, int tx) {
 }
 
 // Columns per wave, by the wave-columns (56 rows of one column) of the
-// lattice.  Measured step times in us for 1 / 2 / 3 / 4 columns per wave:
-// 256 x 128 (768): 6.0 / 7.4 / 9.8 / 11.8; 331 x 205 (1324): 7.7 / 7.7 / 10.0 /
-// 12.1; 512 x 512 (5120): 23 / 20 / 16.6 / 20; 1024 x 1024 (19456): 80 / 58 /
-// 57.2 / 57.4; 1920 x 2048 (71040): 279 / 203 / 185 / 179.  Few wave-columns:
-// the walk's length is what counts; many: the re-read columns.
+// lattice.  Few: the length of a wave's walk is what counts; many: the
+// re-read columns.  Step times in us for 1 / 2 / 3 / 4 columns per wave:
+// 256 x 128 (768): 5.2 / 6.9 / 8.5 / 10.1; 331 x 205 (1324): 7.5 / 7.2 / 8.8 /
+// 10.5; 512 x 512 (5120): 22.9 / 20.7 / 15.5 / 17.6; 777 x 1501 (20979): 90 /
+// 70 / 63.4 / 65.7; 1920 x 2048 (71040): 274 / 208 / 183 / 177.  The adjoint's
+// order is the same (512 x 512: 25.0 / 24.3 / 22.5 / 24.9).
 int sweep_columns(const CGeom& g) {
   const long long cols = (long long)g.nw * g.lx;
-  return cols >= 40960 ? 4 : cols >= 3584 ? 3 : cols >= 1536 ? 2 : 1;
+  return cols >= 40960 ? 4 : cols >= 3584 ? 3 : cols >= 1280 ? 2 : 1;
 }
+// Three columns: with one source column ahead (three waves per SIMD) the
+// forward step is faster while all its waves run at once (512 x 512: 15.5 us
+// against 19.0 with two ahead; 777 x 1501: 71.6 against 63.4).
+bool shallow_sweep(const CGeom& g) { return (long long)g.nw * g.lx < 9216; }
 
 }  // namespace
 
@@ -759,12 +786,13 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
                              double* tape, hipStream_t s) {
   const CGeom g = make_cgeom(gf);
   const WallTable wt = make_walls(p);
+  const CPhys cp = make_cphys(p);
   const unsigned* guard = guard_of(src, gf);
   if (gf.form != kFormCoeff) {  // the populations are stored, or may be
     const Tiling t = make_tiling(g.lx, g.ly);
     auto run = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(t.nb), dim3(kThreads), 0, s,
-                         static_cast<const double*>(src), coeffs(dst), gf, g, p, wt, tape, t.by, t.bx,
+                         static_cast<const double*>(src), coeffs(dst), gf, g, cp, wt, tape, t.by, t.bx,
                          t.nty, t.nb, guard, word_of(dst));
     };
     tape ? run(k_coeff_first<true>) : run(k_coeff_first<false>);
@@ -773,11 +801,13 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
     const int tx = sweep_columns(g);
     const unsigned nb = sweep_grid(g, tx);
     auto run = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * kWaves), 0, s, coeffs(src), coeffs(dst), g, p, wt,
+      hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * kWaves), 0, s, coeffs(src), coeffs(dst), g, cp, wt,
                          tape, nb, guard, word_of(dst));
     };
     if (tx == 4)
-      tape ? run(k_coeff_step<4, 3, true>) : run(k_coeff_step<4, 3, false>);
+      tape ? run(k_coeff_step<4, 2, true>) : run(k_coeff_step<4, 2, false>);
+    else if (tx == 3 && shallow_sweep(g))
+      tape ? run(k_coeff_step<3, 1, true>) : run(k_coeff_step<3, 1, false>);
     else if (tx == 3)
       tape ? run(k_coeff_step<3, 2, true>) : run(k_coeff_step<3, 2, false>);
     else if (tx == 2)
@@ -844,17 +874,18 @@ hipError_t launch_coeff_adjoint_mu(const double* tape, const double* in, bool fr
                                    double* mu_out, const Geom& gf, const Phys& p, hipStream_t s) {
   const CGeom g = make_cgeom(gf);
   const WallTable wt = make_walls(p);
+  const CPhys cp = make_cphys(p);
   if (from_compact) {
     const Tiling t = make_tiling(g.lx, g.ly);
     hipLaunchKernelGGL(k_coeff_adjoint_first, dim3(t.nb), dim3(kThreads), 0, s, tape, in,
-                       coeffs(static_cast<void*>(mu_out)), gf, g, p, wt, t.by, t.bx, t.nty, t.nb);
+                       coeffs(static_cast<void*>(mu_out)), gf, g, cp, wt, t.by, t.bx, t.nty, t.nb);
     return hipGetLastError();
   }
   const int tx = sweep_columns(g);
   const unsigned nb = sweep_grid(g, tx);
   auto run = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * kWaves), 0, s, tape, coeffs(static_cast<const void*>(in)),
-                       coeffs(static_cast<void*>(mu_out)), g, p, wt, nb);
+                       coeffs(static_cast<void*>(mu_out)), g, cp, wt, nb);
   };
   if (tx == 4)
     run(k_coeff_adjoint<4, 2>);
@@ -884,7 +915,7 @@ hipError_t launch_coeff_adjoint_step(const double* tape, const double* lam_in, d
                                      const Geom& gf, const Phys& p, hipStream_t s) {
   const Tiling t = make_tiling(gf.lx, gf.ly);
   hipLaunchKernelGGL(k_coeff_adjoint_step, dim3(t.nb), dim3(kThreads), 0, s, tape, lam_in, lam_out,
-                     gf, make_cgeom(gf), p, make_walls(p), t.by, t.bx, t.nty, t.nb);
+                     gf, make_cgeom(gf), make_cphys(p), make_walls(p), t.by, t.bx, t.nty, t.nb);
   return hipGetLastError();
 }
 

@@ -48,17 +48,13 @@ struct Geom {
 };
 
 // Storage form of a state buffer: the 37 populations of every padded site, or
-// (FP64, after a regularized collision) the 15 Hermite coefficients of every
-// physical site.  The buffer's first word, padding in both forms, names its
+// (FP64, after a regularized collision) the 15 coefficients of every physical
+// site that generate them.  The buffer's first word, padding in both forms, names its
 // form for graphs recorded before the state was replaced; the host passes
 // what it knows in Geom::form, kFormUnknown where a graph may have run.
 enum Form : int { kFormFull = 0, kFormCoeff = 1, kFormUnknown = 2 };
 
-constexpr int NC = 15;  // Hermite coefficients of order p + q <= 4
-// Their storage order: the five that carry the macroscopic fields first, so
-// that a reader of the fields touches three of the seven pair planes.
-constexpr int kCP[NC] = {0, 1, 0, 2, 0, 1, 3, 2, 1, 0, 4, 3, 2, 1, 0};
-constexpr int kCQ[NC] = {0, 0, 1, 0, 2, 1, 0, 1, 2, 3, 0, 1, 2, 3, 4};
+constexpr int NC = 15;  // coefficients of a site: degree i + j <= 4
 
 struct Phys {
   double omega;        // 1 / tau
