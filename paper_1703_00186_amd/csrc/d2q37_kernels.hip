@@ -416,7 +416,9 @@ __global__ __launch_bounds__(kThreads) void k_check(const S* __restrict__ src,
 // compact [37][lx][ly] (or [38], with the packed references) <-> padded.  One
 // thread copies all planes of a site, kBatch of them in flight: a workgroup
 // per (plane, row segment) instead is bound by the launch rate of its
-// 2.5 million workgroups in FP32 (4096 x 4096 x 38: 1.76 ms, 2.9 TB/s).
+// 2.5 million workgroups in FP32 (4096 x 4096 x 38: 1.76 ms, 2.9 TB/s; now
+// 0.93 ms).  Where the tiles alone do not fill the GPU the batches of planes
+// go to workgroups of their own (copy_grid).
 constexpr int kBatch = 8;
 
 template <class S>
@@ -430,7 +432,7 @@ __global__ __launch_bounds__(kThreads) void k_pack(const S* __restrict__ padded_
   const S* from = padded_buf + padded<S>(g, x + HX, y + g.hy);
   S* to = compact + (long long)x * g.ly + y;
   const long long S2 = (long long)g.lx * g.ly;
-  for (int l0 = 0; l0 < g.np; l0 += kBatch) {
+  for (int l0 = blockIdx.y * kBatch; l0 < g.np; l0 += gridDim.y * kBatch) {
     S v[kBatch];
 #pragma unroll
     for (int i = 0; i < kBatch; ++i)
@@ -451,7 +453,7 @@ __global__ __launch_bounds__(kThreads) void k_unpack(const S* __restrict__ compa
   const S* from = compact + (long long)x * g.ly + y;
   S* to = padded_buf + padded<S>(g, x + HX, y + g.hy);
   const long long S2 = (long long)g.lx * g.ly;
-  for (int l0 = 0; l0 < g.np; l0 += kBatch) {
+  for (int l0 = blockIdx.y * kBatch; l0 < g.np; l0 += gridDim.y * kBatch) {
     S v[kBatch];
 #pragma unroll
     for (int i = 0; i < kBatch; ++i)
@@ -1008,6 +1010,12 @@ hipError_t launch_moments(const void* src, double* rho, double* ux, double* uy, 
   });
 }
 
+// tiles of a copy of g.np planes, times its batches of planes while that is
+// fewer than eight workgroups per CU
+static dim3 copy_grid(const Tiling& t, const Geom& g) {
+  return dim3(t.nb, t.nb < 2048 ? unsigned((g.np + kBatch - 1) / kBatch) : 1u);
+}
+
 hipError_t launch_pack(const void* padded_buf, void* compact, const Geom& g, int prec,
                        hipStream_t s) {
   if (g.form != kFormFull) {
@@ -1017,7 +1025,7 @@ hipError_t launch_pack(const void* padded_buf, void* compact, const Geom& g, int
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto) {
     using S = decltype(sv);
-    hipLaunchKernelGGL(k_pack<S>, dim3(t.nb), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL(k_pack<S>, copy_grid(t, g), dim3(kThreads), 0, s,
                        static_cast<const S*>(padded_buf), static_cast<S*>(compact), g, t.by, t.bx,
                        t.nty, t.nb, guard_of(padded_buf, g));
   });
@@ -1029,7 +1037,7 @@ hipError_t launch_unpack(const void* compact, void* padded_buf, const Geom& g, i
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto) {
     using S = decltype(sv);
-    hipLaunchKernelGGL(k_unpack<S>, dim3(t.nb), dim3(kThreads), 0, s,
+    hipLaunchKernelGGL(k_unpack<S>, copy_grid(t, g), dim3(kThreads), 0, s,
                        static_cast<const S*>(compact), static_cast<S*>(padded_buf), g, t.by, t.bx,
                        t.nty, t.nb);
   });
