@@ -8,10 +8,10 @@
 // its target inside the wave, and stores start 128-byte aligned (56 rows of
 // 16-byte pairs).  The wave walks over the TX + 6 source columns.  For each
 // it loads the site's 15 coefficients, rebuilds the populations of every
-// e_x group that reaches one of its TX columns, passes them to their target
-// row through a wave-private LDS buffer (no barrier: a wave's LDS accesses
-// are in order) and adds them to the target's 15 sums; a column is complete
-// six source columns after its first and is collided and stored at once.
+// e_x group that reaches one of its TX columns, shifts them to their target
+// row across its lanes (DPP) and adds them to the target's 15 sums; a column
+// is complete six source columns after its first and is collided and stored
+// at once.
 //
 // What bounds it and why this split.  The step moves 240 bytes per site
 // (15 FP64 in, 15 out) instead of the 592 of the 37 populations, at 5.3 TB/s
@@ -25,7 +25,8 @@
 // against 200 us).  Source columns are loaded ahead of their use (191 -> 181
 // us at TX = 4).  On small lattices the instructions of a wave's walk count:
 // powers of the hops instead of Hermite values as factors took 1305 to 1106
-// instructions per column (256 x 128: 5.7 -> 5.2 us).
+// instructions per column, and DPP instead of LDS took the waits (256 x 128:
+// 5.7 -> 5.2 -> 5.1 us, 331 x 205: 7.8 -> 7.2 -> 6.7).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -51,13 +52,6 @@ constexpr int kNonTemporal = 2;           // cache policy bits of a streaming st
 // any plane's offset lie beyond every column (NC * pitch * 8 < 2^31 bytes), so
 // loads give 0 and stores do nothing.
 constexpr unsigned kOutside = 0x80000000u;
-
-// orders the wave's own LDS accesses (no instruction)
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t column_rsrc(const double* buf, const CGeom& g,
                                                               int x) {
@@ -97,37 +91,34 @@ __device__ __forceinline__ void store_column(__amdgpu_buffer_rsrc_t r, const CGe
                                         kNonTemporal);
 }
 
-// LDS of one wave: per target column six rows of 64 populations ((ex, +-k),
-// k = 1..3), with room for the lanes' shifts at both ends.
-constexpr int kSlot = 6 * 64;
-template <int TX>
-constexpr int kWaveLds = TX * kSlot + 2 * kHalo;
-
-template <class K>
-constexpr int kShift = 1;  // (ex, +k) arrives from the row k below its target
-template <>
-constexpr int kShift<Adjoint> = -1;  // the transposed hop
-
-template <class K, int ex>
-__device__ __forceinline__ void put_group(const double (&b)[NC], double* lds, int lane,
-                                          double& zero) {
-  Group f;
-  expand_group<K, ex>(b, f);
-  zero = f.zero;
-#pragma unroll
-  for (int k = 1; k <= reach(ex); ++k) {
-    lds[(2 * k - 2) * 64 + lane] = f.plus[k - 1];
-    lds[(2 * k - 1) * 64 + lane] = f.minus[k - 1];
+// Lane i gets the value of lane i - n (up) or i + n (down); zero beyond the
+// wave.  A shift of the whole wave by one lane is a DPP move, two for 64 bits.
+constexpr int kUp = 0x138, kDown = 0x130;  // wave_shr:1, wave_shl:1
+template <int ctrl, int n>
+__device__ __forceinline__ double shift_lanes(double v) {
+  if constexpr (n == 0) {
+    return v;
+  } else {
+    const v2u u = __builtin_bit_cast(v2u, v);
+    const v2u w = {unsigned(__builtin_amdgcn_update_dpp(0, int(u.x), ctrl, 0xf, 0xf, true)),
+                   unsigned(__builtin_amdgcn_update_dpp(0, int(u.y), ctrl, 0xf, 0xf, true))};
+    return shift_lanes<ctrl, n - 1>(__builtin_bit_cast(double, w));
   }
 }
-template <class K, int ex>
-__device__ __forceinline__ void get_group(const double* lds, int lane, double zero, Group& f) {
-  f.zero = zero;
-#pragma unroll
-  for (int k = 1; k <= reach(ex); ++k) {
-    f.plus[k - 1] = lds[(2 * k - 2) * 64 + lane - kShift<K> * k];
-    f.minus[k - 1] = lds[(2 * k - 1) * 64 + lane + kShift<K> * k];
-  }
+
+// (ex, +k) arrives from the row k below its target; the transposed hop from
+// the row above.  104 moves per site for the 30 populations that change rows;
+// passing them through LDS (60 accesses) makes every group wait for its round
+// trip: 331 x 205 step 7.2 us against 6.7, 777 x 1501 63.5 against 63.2.
+template <class K>
+constexpr bool kForward = true;
+template <>
+constexpr bool kForward<Adjoint> = false;
+template <class K, int ex, int k = 1>
+__device__ __forceinline__ void shift_group(Group& f) {
+  f.plus[k - 1] = shift_lanes<kForward<K> ? kUp : kDown, k>(f.plus[k - 1]);
+  f.minus[k - 1] = shift_lanes<kForward<K> ? kDown : kUp, k>(f.minus[k - 1]);
+  if constexpr (k < reach(ex)) shift_group<K, ex, k + 1>(f);
 }
 
 // Row of this lane: its index, whether it exists, its byte offset in a pair
@@ -137,7 +128,8 @@ struct Row {
   bool in;
   unsigned load, store;
 };
-__device__ __forceinline__ Row wave_row(const CGeom& g, int w, int lane) {
+__device__ __forceinline__ Row wave_row(const CGeom& g, int w) {
+  const int lane = threadIdx.x & 63;
   Row r;
   r.y = w * kRows - kHalo + lane;
   r.in = r.y >= 0 && r.y < g.ly;
@@ -166,7 +158,7 @@ __device__ __forceinline__ bool wave_tile(const CGeom& g, unsigned nb, int& w, i
   const int strips = (g.lx + TX - 1) / TX;
   w = int(t % unsigned(g.nw));
   const int s = int(t / unsigned(g.nw));
-  x0 = (kShift<K> > 0 ? s : strips - 1 - s) * TX;
+  x0 = (kForward<K> ? s : strips - 1 - s) * TX;
   return s < strips;
 }
 
@@ -179,48 +171,38 @@ struct Sweep {
   const double* src;
   const CGeom& g;
   const Site& site;
-  int x0, lane;
+  int x0;
   Row row;
-  double* lds;
-  double b[kAhead][NC];  // source columns in flight
-  double a[TX][NC];      // sums of the targets
-  double zero[TX];
+  double c[kAhead][NC];  // source columns in flight
+  double m[TX][NC];      // sums of the targets
 
   __device__ __forceinline__ int source(int j) const {
-    int x = kShift<K> > 0 ? x0 - 3 + j : x0 + TX + 2 - j;
+    int x = kForward<K> ? x0 - 3 + j : x0 + TX + 2 - j;
     x = x < 0 ? x + g.lx : (x >= g.lx ? x - g.lx : x);
     return x;  // (lx >= 6: one wrap reaches every column of a ragged last tile too)
   }
   __device__ __forceinline__ int target(int t) const {
-    return kShift<K> > 0 ? x0 + t : x0 + TX - 1 - t;
+    return kForward<K> ? x0 + t : x0 + TX - 1 - t;
   }
   __device__ __forceinline__ void load(int j, double (&v)[NC]) {
     load_column(column_rsrc(src, g, source(j)), g, row.load, v);
   }
   template <int j, int t>
-  __device__ __forceinline__ void put() {
-    if constexpr (t < TX) {
-      constexpr int ex = t + 3 - j;
-      if constexpr (ex >= -3 && ex <= 3)
-        put_group<K, ex>(b[j % kAhead], lds + t * kSlot, lane, zero[t]);
-      put<j, t + 1>();
-    }
-  }
-  template <int j, int t>
-  __device__ __forceinline__ void get() {
+  __device__ __forceinline__ void add() {
     if constexpr (t < TX) {
       constexpr int ex = t + 3 - j;
       if constexpr (ex >= -3 && ex <= 3) {
         Group f;
-        get_group<K, ex>(lds + t * kSlot, lane, zero[t], f);
-        project_group<K, ex>(f, a[t]);
+        expand_group<K, ex>(c[j % kAhead], f);
+        shift_group<K, ex>(f);
+        project_group<K, ex>(f, m[t]);
         // keeps the sums here: left to itself the compiler defers them to
         // the end and holds every group of the target in registers (127
         // instead of 87 VGPRs at TX = 1, spills from TX = 3)
 #pragma unroll
-        for (int k = 0; k < NC; ++k) asm volatile("" : "+v"(a[t][k]));
+        for (int k = 0; k < NC; ++k) asm volatile("" : "+v"(m[t][k]));
       }
-      get<j, t + 1>();
+      add<j, t + 1>();
     }
   }
   template <int j>
@@ -228,22 +210,18 @@ struct Sweep {
     if constexpr (j < TX + 6) {
       typename Site::Input in;
       if constexpr (j >= 6) site.load(in, target(j - 6), row);
-      put<j, 0>();
-      // the next column's loads go out before this one's exchange and sums
+      add<j, 0>();
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (j + kAhead < TX + 6) load(j + kAhead, b[j % kAhead]);
+      if constexpr (j + kAhead < TX + 6) load(j + kAhead, c[j % kAhead]);
       __builtin_amdgcn_sched_barrier(0);
-      wave_lds_fence();
-      get<j, 0>();
-      wave_lds_fence();
-      if constexpr (j >= 6) site.finish(in, a[j - 6], target(j - 6), row);
+      if constexpr (j >= 6) site.finish(in, m[j - 6], target(j - 6), row);
       walk<j + 1>();
     }
   }
   template <int j = 0>
   __device__ __forceinline__ void prefetch() {
     if constexpr (j < kAhead) {
-      load(j, b[j]);
+      load(j, c[j]);
       prefetch<j + 1>();
     }
   }
@@ -326,15 +304,12 @@ template <int TX, int kAhead, bool kTape>
 __global__ __launch_bounds__(64 * kWaves, (kOccupancy<TX, kAhead>)) void k_coeff_step(
     const double* __restrict__ src, double* __restrict__ dst, CGeom g, CPhys P, WallTable wt,
     double* __restrict__ tape, unsigned nb, const unsigned* guard, unsigned* word) {
-  __shared__ double lds[kWaves][kWaveLds<TX>];
   if (other_form(guard, kFormCoeff)) return;
   set_form(word, kFormCoeff);
   int w, x0;
   if (!wave_tile<Forward, TX>(g, nb, w, x0)) return;
-  const int lane = threadIdx.x & 63;
   const StepSite<kTape> site{dst, g, P, wt, tape};
-  Sweep<Forward, TX, kAhead, StepSite<kTape>> s{
-      src, g, site, x0, lane, wave_row(g, w, lane), &lds[threadIdx.x >> 6][kHalo]};
+  Sweep<Forward, TX, kAhead, StepSite<kTape>> s{src, g, site, x0, wave_row(g, w)};
   s.prefetch();
   s.template walk<0>();
 }
@@ -343,13 +318,10 @@ template <int TX, int kAhead>
 __global__ __launch_bounds__(64 * kWaves, (kOccupancy<TX, kAhead>)) void k_coeff_adjoint(
     const double* __restrict__ tape, const double* __restrict__ src, double* __restrict__ dst,
     CGeom g, CPhys P, WallTable wt, unsigned nb) {
-  __shared__ double lds[kWaves][kWaveLds<TX>];
   int w, x0;
   if (!wave_tile<Adjoint, TX>(g, nb, w, x0)) return;
-  const int lane = threadIdx.x & 63;
   const AdjointSite site{dst, g, P, wt, tape};
-  Sweep<Adjoint, TX, kAhead, AdjointSite> s{
-      src, g, site, x0, lane, wave_row(g, w, lane), &lds[threadIdx.x >> 6][kHalo]};
+  Sweep<Adjoint, TX, kAhead, AdjointSite> s{src, g, site, x0, wave_row(g, w)};
   s.prefetch();
   s.template walk<0>();
 }
@@ -628,18 +600,13 @@ struct ExportWalk {
   double* lam;
   const CGeom& g;
   const LamAt& la;
-  int lane;
   Row row;
-  double* lds;
 
   template <int ex>
   __device__ __forceinline__ void group(const double (&b)[NC], int x) const {
-    double zero;
-    put_group<Adjoint, ex>(b, lds, lane, zero);
-    wave_lds_fence();
     Group f;
-    get_group<Adjoint, ex>(lds, lane, zero, f);
-    wave_lds_fence();
+    expand_group<Adjoint, ex>(b, f);
+    shift_group<Adjoint, ex>(f);
     if (row.store == kOutside || x >= g.lx) return;
     double* out = lam + x * la.cs + row.y;
     store<ex, 0>(out, f.zero);
@@ -683,12 +650,10 @@ struct ExportWalk {
 template <int TX>
 __global__ __launch_bounds__(64 * kWaves) void k_coeff_adjoint_last(
     const double* __restrict__ src, double* __restrict__ lam, CGeom g, Geom gf, unsigned nb) {
-  __shared__ double lds[kWaves][kWaveLds<1>];
   int w, x0;
   if (!wave_tile<Forward, TX>(g, nb, w, x0)) return;
   const LamAt la = lam_at(gf);
-  const int lane = threadIdx.x & 63;
-  const ExportWalk e{src, lam, g, la, lane, wave_row(g, w, lane), &lds[threadIdx.x >> 6][kHalo]};
+  const ExportWalk e{src, lam, g, la, wave_row(g, w)};
   double b[NC];
   e.load(x0 - 3, b);
   e.template walk<TX, 0>(x0, b);
@@ -767,17 +732,17 @@ unsigned sweep_grid(const CGeom& g, int tx) {
 // Columns per wave, by the wave-columns (56 rows of one column) of the
 // lattice.  Few: the length of a wave's walk is what counts; many: the
 // re-read columns.  Step times in us for 1 / 2 / 3 / 4 columns per wave:
-// 256 x 128 (768): 5.2 / 6.9 / 8.5 / 10.1; 331 x 205 (1324): 7.5 / 7.2 / 8.8 /
-// 10.5; 512 x 512 (5120): 22.9 / 20.7 / 15.5 / 17.6; 777 x 1501 (20979): 90 /
-// 70 / 63.4 / 65.7; 1920 x 2048 (71040): 274 / 208 / 183 / 177.  The adjoint's
-// order is the same (512 x 512: 25.0 / 24.3 / 22.5 / 24.9).
+// 256 x 128 (768): 5.1 / 6.4 / 8.0 / 9.7; 331 x 205 (1324): 7.4 / 6.7 / 8.3 /
+// 9.9; 512 x 512 (5120): 22.3 / 20.3 / 15.8 / 20.7; 777 x 1501 (20979): 86 /
+// 68.5 / 63.2 / 64.7; 1920 x 2048 (71040): 266 / 203 / 183 / 178.  The adjoint's
+// order is the same (512 x 512: 25.2 / 24.2 / 22.6 / 25.4).
 int sweep_columns(const CGeom& g) {
   const long long cols = (long long)g.nw * g.lx;
   return cols >= 40960 ? 4 : cols >= 3584 ? 3 : cols >= 1280 ? 2 : 1;
 }
 // Three columns: with one source column ahead (three waves per SIMD) the
-// forward step is faster while all its waves run at once (512 x 512: 15.5 us
-// against 19.0 with two ahead; 777 x 1501: 71.6 against 63.4).
+// forward step is faster while all its waves run at once (512 x 512: 15.8 us
+// against 19.8 with two ahead; 777 x 1501: 72.8 against 63.2).
 bool shallow_sweep(const CGeom& g) { return (long long)g.nw * g.lx < 9216; }
 
 }  // namespace
