@@ -128,10 +128,11 @@ struct Row {
   bool in;
   unsigned load, store;
 };
+template <int rows = kRows, int halo = kHalo>
 __device__ __forceinline__ Row wave_row(const CGeom& g, int w) {
   const int lane = threadIdx.x & 63;
   Row r;
-  r.y = w * kRows - kHalo + lane;
+  r.y = w * rows - halo + lane;
   r.in = r.y >= 0 && r.y < g.ly;
   int y = r.y;
   if (g.periodic) {  // rows beyond the three that are read may fold anywhere
@@ -140,7 +141,7 @@ __device__ __forceinline__ Row wave_row(const CGeom& g, int w) {
     if (y < 0 || y >= g.ly) y = 0;
   }
   r.load = r.in || g.periodic ? unsigned(y) * 16u : kOutside;
-  r.store = r.in && lane >= kHalo && lane < kHalo + kRows ? unsigned(r.y) * 16u : kOutside;
+  r.store = r.in && lane >= halo && lane < halo + rows ? unsigned(r.y) * 16u : kOutside;
   return r;
 }
 
@@ -312,6 +313,167 @@ __global__ __launch_bounds__(64 * kWaves, (kOccupancy<TX, kAhead>)) void k_coeff
   Sweep<Forward, TX, kAhead, StepSite<kTape>> s{src, g, site, x0, wave_row(g, w)};
   s.prefetch();
   s.template walk<0>();
+}
+
+// ---------------------------------------------------------------------------
+// Two steps in one launch.  A workgroup takes 52 rows (64 lanes, six halo rows
+// on each side) of `chunk` columns and marches along x, four columns at a
+// time.  Two producer waves make the first step's coefficients of four
+// columns and put them into a ring of ten columns in LDS; two consumer waves
+// make the second step of the four columns three behind from that ring and
+// store it.  While the consumers read iteration i - 1's columns the producers
+// work on iteration i's in registers; a barrier, the ring's four oldest
+// columns are replaced, a barrier.  The producers load four source columns
+// ahead, across iterations.
+//
+// What bounds it.  The state is read and written once for two steps (272 of
+// the 480 bytes per site, with the re-read halo rows), so the vector unit
+// takes over from HBM: 550 instructions per column and wave, on 64 of 52 rows
+// and (chunk + 6) of chunk columns, 58 % of the issue slots; the rest is
+// waiting at the two barriers.  Two workgroups share a CU (77 KB of LDS
+// each), eight waves in all.  Per step, against k_coeff_step: 1920 x 2048 141 us
+// (178), 4096 x 4096 585 us (735), 777 x 1501 48 us (63).  Tried: every wave
+// making first its column of step one, then of step two (216 us: the two
+// phases load the L1 and the LDS in turn instead of together), one workgroup
+// of eight waves (161), rows exchanged through LDS (161), source columns
+// loaded two ahead (162), three and four waves per SIMD with one column each
+// (157, 175).
+// ---------------------------------------------------------------------------
+constexpr int kPairRows = 52, kPairHalo = 6;
+constexpr int kPairWave = 2;                  // columns of a wave
+constexpr int kPairMakers = 2;                // producer waves, and consumer waves
+constexpr int kPairCols = kPairWave * kPairMakers;  // columns of an iteration
+constexpr int kRing = kPairCols + 6, kRingCol = NC * 64;
+constexpr int kPairAhead = 4;  // divides kPairWave + 6: the loads run on across iterations
+
+// One wave's walk over kPairWave + 6 source columns; load(j, v) fetches source
+// column j, beyond the walk's end the next walk's first ones.
+template <int kAhead>
+struct PairWalk {
+  const CGeom& g;
+  const CPhys& P;
+  const WallTable& wt;
+  const Row& row;
+  double m[kPairWave][NC];
+
+  template <int j, int t>
+  __device__ __forceinline__ void add(const double (&c)[NC]) {
+    if constexpr (t < kPairWave) {
+      constexpr int ex = t + 3 - j;
+      if constexpr (ex >= -3 && ex <= 3) {
+        Group f;
+        expand_group<Forward, ex>(c, f);
+        shift_group<Forward, ex>(f);
+        project_group<Forward, ex>(f, m[t]);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) asm volatile("" : "+v"(m[t][k]));  // as in Sweep
+      }
+      add<j, t + 1>(c);
+    }
+  }
+  template <int j = 0, class Load>
+  __device__ __forceinline__ void walk(double (&c)[kAhead][NC], const Load& load) {
+    if constexpr (j < kPairWave + 6) {
+      add<j, 0>(c[j % kAhead]);
+      __builtin_amdgcn_sched_barrier(0);
+      load(j + kAhead, c[j % kAhead]);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (j >= 6) {
+        int i;
+        if (row.in && wall_row(g, row.y, i)) wall_moments(m[j - 6], wt, i);
+        collide_moments(m[j - 6], P);
+      }
+      walk<j + 1>(c, load);
+    }
+  }
+};
+
+__device__ __forceinline__ int ring_slot(int s) { return s >= kRing ? s - kRing : s; }
+
+__global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
+    const double* __restrict__ src, double* __restrict__ dst, CGeom g, CPhys P, WallTable wt,
+    int windows, int chunk, unsigned nb, unsigned* word) {
+  __shared__ __align__(16) double ring[kRing * kRingCol];
+  set_form(word, kFormCoeff);
+  const unsigned t = tile_index(nb);
+  const int xa = int(t / unsigned(windows)) * chunk, xb = min(xa + chunk, g.lx);
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const Row row = wave_row<kPairRows, kPairHalo>(g, int(t % unsigned(windows)));
+  // iteration i: step one of columns xa - 3 + 4 i .., step two of the targets
+  // whose sources iteration i - 1 completed; both barriers every time
+  const int iters = (xb - xa + 6 + kPairCols - 1) / kPairCols;
+  if (wave < kPairMakers) {
+    int slot = wave * kPairWave;
+    int x = xa - 3 + wave * kPairWave;
+    if (x < 0) x += g.lx;
+    auto load = [&](int j, double (&v)[NC]) {
+      int xs = x - 3 + (j < kPairWave + 6 ? j : j - (kPairWave + 6) + kPairCols);
+      xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
+      load_column(column_rsrc(src, g, xs), g, row.load, v);
+    };
+    double c[kPairAhead][NC];
+#pragma unroll
+    for (int j = 0; j < kPairAhead; ++j) load(j, c[j]);
+    for (int i = 0; i <= iters; ++i) {
+      PairWalk<kPairAhead> s{g, P, wt, row};
+      if (i < iters) {
+        s.walk(c, load);
+        if (!g.periodic && !row.in) {  // nothing comes from beyond the walls
+#pragma unroll
+          for (int k = 0; k < kPairWave * NC; ++k) s.m[k / NC][k % NC] = 0.0;
+        }
+      }
+      __syncthreads();
+      if (i < iters) {
+#pragma unroll
+        for (int n = 0; n < kPairWave; ++n) {
+          double* col = ring + ring_slot(slot + n) * kRingCol;
+#pragma unroll
+          for (int m = 0; m < NC / 2; ++m)
+            *reinterpret_cast<v2d*>(col + m * 128 + 2 * lane) =
+                v2d{s.m[n][2 * m], s.m[n][2 * m + 1]};
+          col[(NC - 1) * 64 + lane] = s.m[n][NC - 1];
+        }
+      }
+      __syncthreads();
+      slot = ring_slot(slot + kPairCols);
+      x += kPairCols;
+      if (x >= g.lx) x -= g.lx;
+    }
+  } else {
+    const int first = (wave - kPairMakers) * kPairWave;
+    int base = ring_slot(first + kPairCols);  // the slot of column x - 3
+    for (int i = 0; i <= iters; ++i) {
+      const int x = xa - 6 + (i - 1) * kPairCols + first;
+      if (i > 0) {
+        if (x + kPairWave > xa && x < xb) {
+          auto load = [&](int j, double (&v)[NC]) {
+            if (j >= kPairWave + 6) return;
+            const double* col = ring + ring_slot(base + j) * kRingCol;
+#pragma unroll
+            for (int m = 0; m < NC / 2; ++m) {
+              const v2d d = *reinterpret_cast<const v2d*>(col + m * 128 + 2 * lane);
+              v[2 * m] = d.x;
+              v[2 * m + 1] = d.y;
+            }
+            v[NC - 1] = col[(NC - 1) * 64 + lane];
+          };
+          double c[1][NC];
+          load(0, c[0]);
+          PairWalk<1> s{g, P, wt, row};
+          s.walk(c, load);
+#pragma unroll
+          for (int n = 0; n < kPairWave; ++n)
+            if (x + n >= xa && x + n < xb)
+              store_column(column_rsrc(dst, g, x + n), g, row.store, s.m[n]);
+        }
+        base = ring_slot(base + kPairCols);
+      }
+      __syncthreads();
+      __syncthreads();
+    }
+  }
 }
 
 template <int TX, int kAhead>
@@ -745,6 +907,29 @@ int sweep_columns(const CGeom& g) {
 // against 19.8 with two ahead; 777 x 1501: 72.8 against 63.2).
 bool shallow_sweep(const CGeom& g) { return (long long)g.nw * g.lx < 9216; }
 
+// Columns of a workgroup of k_coeff_pair: its time is the iterations of a
+// chunk, (chunk + 6) / 4 and one to fill the pipeline, times the rounds in
+// which the workgroups pass through the GPU, two to a CU; the chunk with the
+// least of that product.  Chunks of 4 n + 2 columns use every iteration fully.
+int pair_chunk(const CGeom& g, int windows) {
+  const int slots = 2 * 256;
+  int best = kPairCols - 2;
+  double best_cost = 0.0;
+  for (int chunk = kPairCols - 2; chunk < g.lx + kPairCols; chunk += kPairCols) {
+    const long long groups = (long long)windows * ((g.lx + chunk - 1) / chunk);
+    // beyond a few rounds the workgroups even out
+    const double rounds =
+        groups <= 4 * slots ? double((groups + slots - 1) / slots) : double(groups) / slots + 0.5;
+    const double cost = rounds * ((std::min(chunk, g.lx) + 6) / kPairCols + 1);
+    if (best_cost == 0.0 || cost < best_cost) {
+      best = chunk;
+      best_cost = cost;
+    }
+    if (chunk > 512) break;
+  }
+  return best;
+}
+
 }  // namespace
 
 hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const Phys& p,
@@ -753,6 +938,14 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
   const WallTable wt = make_walls(p);
   const CPhys cp = make_cphys(p);
   const unsigned* guard = guard_of(src, gf);
+  if (gf.form == kFormCoeffTwice) {
+    const int windows = (g.ly + kPairRows - 1) / kPairRows;
+    const int chunk = pair_chunk(g, windows);
+    const unsigned nb = unsigned(windows) * unsigned((g.lx + chunk - 1) / chunk);
+    hipLaunchKernelGGL(k_coeff_pair, dim3(nb), dim3(64 * 2 * kPairMakers), 0, s, coeffs(src),
+                       coeffs(dst), g, cp, wt, windows, chunk, nb, word_of(dst));
+    return hipGetLastError();
+  }
   if (gf.form != kFormCoeff) {  // the populations are stored, or may be
     const Tiling t = make_tiling(g.lx, g.ly);
     auto run = [&](auto kernel) {

@@ -37,8 +37,20 @@ hipError_t launch_halo(void* buf, const Geom& g, int prec, hipStream_t s);
 
 // One fused step: dst = collide(bc(propagate(src))), with the periodic x
 // halos of dst written too.  tape (optional, FP64 only): [4][lx][ly].
+// With form kFormCoeffTwice: two steps (regularized FP64, no tape).
 hipError_t launch_fused(const void* src, void* dst, const Geom& g, const Phys& p, int prec,
                         int regularize, double* tape, hipStream_t s);
+
+// Whether two steps in one launch are the faster ones: from the sizes where
+// their workgroups fill the GPU once, unless the waves of 52 rows cover ly
+// much worse than the single step's waves of 56.  Per step, single and double:
+// 512 x 512 16.2 and 18.6 us, 560 x 560 19.8 and 19.1, 700 x 450 23.5 and
+// 19.1, 640 x 640 29.4 and 22.7, 20000 x 30 46.6 and 39.2; on the other side
+// of the row rule 20000 x 56 (two waves against one) 60.9 and 71.3.
+inline bool two_steps_pay(const Geom& g) {
+  const int single = (g.ly + 55) / 56, pair = (g.ly + 51) / 52;
+  return (long long)g.lx * g.ly >= 310000 && 4 * pair <= 5 * single;
+}
 
 // Split path.
 hipError_t launch_propagate(const void* src, void* dst, const Geom& g, int prec, hipStream_t s);

@@ -356,6 +356,38 @@ int one_step(lb_ctx* c, double* tape) {
   return LB_OK;
 }
 
+// Two steps in one launch, for a state in the coefficient form.
+int two_steps(lb_ctx* c) {
+  LB_HIP(d2q37::launch_fused(c->A, c->B, with_form(c->g, d2q37::kFormCoeffTwice), c->p, c->prec, 1,
+                             nullptr, c->stream),
+         "fused steps");
+  std::swap(c->A, c->B);
+  c->b_form = d2q37::kFormCoeff;
+  return LB_OK;
+}
+
+// n steps.  The buffers swap once per launch, and a recorded graph of an even
+// number of steps has to end in the buffer it started from; so launches of
+// two steps come in pairs.  The last step is a single one: it leaves the state
+// before it in the scratch buffer.
+int run_steps(lb_ctx* c, int n) {
+  const bool pairs = c->prec == LB_FP64 && c->par.regularize && c->par.kernel == LB_KERNEL_FUSED &&
+                     c->par.check_finite == 0 && d2q37::two_steps_pay(c->g);
+  for (int i = 0; i < n;) {
+    if (pairs && n - i > 4 && c->a_form == d2q37::kFormCoeff) {
+      int rc = two_steps(c);
+      if (rc == LB_OK) rc = two_steps(c);
+      if (rc) return rc;
+      i += 4;
+    } else {
+      const int rc = one_step(c, nullptr);
+      if (rc) return rc;
+      ++i;
+    }
+  }
+  return LB_OK;
+}
+
 // n transposed steps, lambda^n -> lambda^0 in place, with the two padded FP64
 // buffers at ws (2 * buffer_bytes(g, LB_FP64) bytes, 256-byte aligned).
 int adjoint_run(lb_ctx* ctx, int n, const double* tape, double* lambda, char* ws) {
@@ -541,11 +573,7 @@ int lb_step(lb_ctx* ctx, int n) {
   int rc = enter(ctx);
   if (rc) return rc;
   if (n < 0) return fail(LB_E_ARG, "n must be >= 0%s");
-  for (int i = 0; i < n; ++i) {
-    rc = one_step(ctx, nullptr);
-    if (rc) return rc;
-  }
-  return LB_OK;
+  return run_steps(ctx, n);
 }
 
 int lb_moments(lb_ctx* ctx, double* rho, double* ux, double* uy, double* T) {
@@ -665,16 +693,13 @@ int lb_run_observed(lb_ctx* ctx, int n, int every, double* series) {
   if (rc) return rc;
   if (n < 0 || every <= 0) return fail(LB_E_ARG, "need n >= 0 and every > 0%s");
   if (n >= every && !series) return fail(LB_E_ARG, "series is NULL%s");
-  for (int i = 1; i <= n; ++i) {
-    rc = one_step(ctx, nullptr);
+  for (int k = 0; k < n / every; ++k) {
+    rc = run_steps(ctx, every);
     if (rc) return rc;
-    if (i % every == 0) {
-      rc = lb_observables(ctx, nullptr,
-                          series + size_t(i / every - 1) * d2q37::kObservableScalars);
-      if (rc) return rc;
-    }
+    rc = lb_observables(ctx, nullptr, series + size_t(k) * d2q37::kObservableScalars);
+    if (rc) return rc;
   }
-  return LB_OK;
+  return run_steps(ctx, n % every);
 }
 
 int lb_step_record(lb_ctx* ctx, int n, double* tape) {

@@ -4,8 +4,9 @@ against the 37 stored populations.
 A lattice that has just been given its populations steps from those; one that
 has stepped before steps from its coefficients.  Both must agree bit for bit,
 and with the CPU oracle to FP64 rounding, for every tile the sweep kernels
-are launched with (1, 2 and 4 columns per wave, 56 rows per wave: the sizes
-sit on both sides of a tile and have ragged ends).  Changing the collision,
+are launched with (1 to 4 columns per wave, 56 rows per wave: the sizes
+sit on both sides of a tile and have ragged ends), and so must two steps made
+in one launch.  Changing the collision,
 the split stages, replacing the state of a recorded graph and reading the
 scratch buffer have to find the state whatever form it is in.
 """
@@ -41,10 +42,10 @@ def params(**kw):
     return oracle.Params(**base)
 
 
-# waves of 56 rows x columns of the lattice: below 2048 one column per wave,
-# below 16384 two, from there on four
+# waves of 56 rows x columns of the lattice: below 1280 one column per wave,
+# below 3584 two, below 40960 three (from 9216 on loaded two ahead), then four
 SIZES = [(6, 6), (9, 56), (8, 57), (33, 113), (7, 250), (301, 400), (683, 57 * 4),
-         (1027, 57 * 15)]
+         (640, 401), (1027, 57 * 15), (2051, 57 * 20)]
 
 
 @pytest.mark.parametrize("layout", ["column", "soa"])
@@ -86,6 +87,42 @@ def test_tape_and_transposed_steps(shape, ybc):
         ref, spare = spare, ref
     a.adjoint_run(ta, lam)
     assert torch.equal(lam, ref)
+
+
+# two steps per launch from 310000 sites on: waves of 52 rows, chunks of columns
+# that are walked four at a time; the last lattice is too small for them
+@pytest.mark.parametrize("ybc", ["walls", "periodic"])
+@pytest.mark.parametrize("shape", [(600, 520), (599, 521), (1201, 310), (6, 52000), (8, 40003),
+                                   (31003, 12), (777, 1501), (400, 400)])
+def test_two_steps_per_launch(shape, ybc):
+    """Bit-equal to single steps for every count, eager, observed and recorded;
+    the scratch buffer holds the state before the last step."""
+    lx, ly = shape
+    a, _ = make(lx, ly, ybc=ybc)
+    b, _ = make(lx, ly, ybc=ybc)
+    g = a.capture(6)  # makes two steps
+    b.step(2)
+    for n in (5, 7, 10, 6):
+        a.step(n)
+        for _ in range(n):
+            b.step(1)
+        assert torch.equal(a.get_state(), b.get_state())
+        assert torch.equal(a.get_scratch(), b.get_scratch())
+    for _ in range(2):
+        g.replay()
+        a.step(10)
+        b.set_state(b.get_state())  # from populations
+        for _ in range(16):
+            b.step(1)
+        assert torch.equal(a.get_state(), b.get_state())
+    series = a.run_observed(17, 7)
+    for k in range(2):
+        for _ in range(7):
+            b.step(1)
+        assert torch.equal(series[k], b.observables()[1])
+    for _ in range(3):
+        b.step(1)
+    assert torch.equal(a.get_state(), b.get_state())
 
 
 def test_readers_of_both_forms_agree():
