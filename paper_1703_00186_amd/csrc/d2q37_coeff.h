@@ -60,6 +60,7 @@ struct CGeom {
   int lx, ly;
   int periodic;     // periodic y (rows wrap), else walls
   int nw;           // waves that cover a column
+  int stream;       // columns are stored past the caches
   unsigned pitch;   // rows of a plane (ly rounded up to 32)
   long long cs;     // NC * pitch
 };

@@ -47,7 +47,21 @@ constexpr int kHalo = 4;             // halo rows on each side of a wave
 constexpr int kRows = 64 - 2 * kHalo;  // target rows of a wave
 constexpr int kWaves = 4;            // waves per workgroup (independent)
 constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit buffer, gfx9 family
-constexpr int kNonTemporal = 2;           // cache policy bits of a streaming store
+constexpr int kNonTemporal = 2;           // cache policy bits of a streaming access
+// States from these sizes to kCachedTo are stored into the caches (us per step,
+// streamed and cached).  Steps: 331 x 331 7.1 and 8.3, 512 x 512 15.8 and 16.8,
+// 560 x 560 19.4 and 18.9, 700 x 700 26.9 and 24.3, 1000 x 1000 43.4 and 39.6
+// (with tape 61.0 and 47.6), 1200 x 1200 60.0 and 61.5.  Transposed steps:
+// 331 x 331 11.4 and 11.1, 400 x 400 18.7 and 16.4, 512 x 512 25.3 and 22.4,
+// 1000 x 1000 69.8 and 67.2, 1100 x 1100 86.4 and 89.0.
+constexpr long long kCachedTo = 135LL * 1000 * 1000;
+constexpr long long kStepCachedFrom = 36LL * 1000 * 1000;
+constexpr long long kAdjointCachedFrom = 12LL * 1000 * 1000;
+// Up to this state size the transposed step reads its tape through the caches
+// as well, which hold what a run of steps just recorded (400 x 400 16.4 us
+// past them and 14.7 through them, 512 x 512 22.4 and 22.1, 1000 x 1000 67.4
+// and 70.3).
+constexpr long long kTapeCachedTo = 32LL * 1000 * 1000;
 // Lane offset of rows that do not exist: it, its half, and either of them plus
 // any plane's offset lie beyond every column (NC * pitch * 8 < 2^31 bytes), so
 // loads give 0 and stores do nothing.
@@ -73,22 +87,29 @@ __device__ __forceinline__ void load_column(__amdgpu_buffer_rsrc_t r, const CGeo
       double, __builtin_amdgcn_raw_buffer_load_b64(r, row_bytes >> 1, (NC - 1) * g.pitch * 8u, 0));
 }
 
-// Stores are streamed past the caches: the next step reads them only after
-// the whole lattice (kOutside: not stored).  The plane is added to the lane's
-// offset, not given as the scalar offset of the instruction: with a scalar
-// offset the compiler lets the next vector instruction overwrite the data of
-// a 16-byte store, which here changed the low word of a few stored values in
-// a million.
-__device__ __forceinline__ void store_column(__amdgpu_buffer_rsrc_t r, const CGeom& g,
+// Row `row_bytes` of a column (kOutside: not stored), streamed past the caches
+// where they do not hold the lattice until the next step.  The plane is added
+// to the lane's offset, not given as the scalar offset of the instruction:
+// with a scalar offset the compiler lets the next vector instruction overwrite
+// the data of a 16-byte store, which here changed the low word of a few stored
+// values in a million.
+template <int kPolicy>
+__device__ __forceinline__ void store_planes(__amdgpu_buffer_rsrc_t r, const CGeom& g,
                                              unsigned row_bytes, const double (&b)[NC]) {
 #pragma unroll
   for (int m = 0; m < NC / 2; ++m)
     __builtin_amdgcn_raw_buffer_store_b128(
         __builtin_bit_cast(v4u, (v2d{b[2 * m], b[2 * m + 1]})), r, row_bytes + m * g.pitch * 16u,
-        0, kNonTemporal);
+        0, kPolicy);
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, b[NC - 1]), r,
-                                        (row_bytes >> 1) + (NC - 1) * g.pitch * 8u, 0,
-                                        kNonTemporal);
+                                        (row_bytes >> 1) + (NC - 1) * g.pitch * 8u, 0, kPolicy);
+}
+__device__ __forceinline__ void store_column(__amdgpu_buffer_rsrc_t r, const CGeom& g,
+                                             unsigned row_bytes, const double (&b)[NC]) {
+  if (g.stream)
+    store_planes<kNonTemporal>(r, g, row_bytes, b);
+  else
+    store_planes<0>(r, g, row_bytes, b);
 }
 
 // Lane i gets the value of lane i - n (up) or i + n (down); zero beyond the
@@ -264,6 +285,7 @@ struct StepSite {
 };
 
 // Adjoint: the step's moments from the tape, C^T and B^T, store.
+template <int kTapePolicy>
 struct AdjointSite {
   double* dst;
   const CGeom& g;
@@ -285,7 +307,7 @@ struct AdjointSite {
                       __builtin_amdgcn_make_buffer_rsrc(
                           (void*)(tape + k * S2 + (long long)x * g.ly), (short)0, g.ly * 8,
                           kBufferWord3),
-                      r.load >> 1, 0, kNonTemporal));
+                      r.load >> 1, 0, kTapePolicy));
   }
   __device__ __forceinline__ void finish(const Input& in, double (&a)[NC], int x,
                                          const Row& r) const {
@@ -476,14 +498,14 @@ __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
   }
 }
 
-template <int TX, int kAhead>
+template <int TX, int kAhead, int kTapePolicy>
 __global__ __launch_bounds__(64 * kWaves, (kOccupancy<TX, kAhead>)) void k_coeff_adjoint(
     const double* __restrict__ tape, const double* __restrict__ src, double* __restrict__ dst,
     CGeom g, CPhys P, WallTable wt, unsigned nb) {
   int w, x0;
   if (!wave_tile<Adjoint, TX>(g, nb, w, x0)) return;
-  const AdjointSite site{dst, g, P, wt, tape};
-  Sweep<Adjoint, TX, kAhead, AdjointSite> s{src, g, site, x0, wave_row(g, w)};
+  const AdjointSite<kTapePolicy> site{dst, g, P, wt, tape};
+  Sweep<Adjoint, TX, kAhead, AdjointSite<kTapePolicy>> s{src, g, site, x0, wave_row(g, w)};
   s.prefetch();
   s.template walk<0>();
 }
@@ -865,7 +887,8 @@ __global__ __launch_bounds__(kThreads) void k_coeff_adjoint_step(
 
 namespace {
 
-CGeom make_cgeom(const Geom& g) {
+long long state_bytes(const CGeom& g) { return g.lx * g.cs * (long long)sizeof(double); }
+CGeom make_cgeom(const Geom& g, long long cached_from = kStepCachedFrom) {
   CGeom c;
   c.lx = g.lx;
   c.ly = g.ly;
@@ -873,6 +896,7 @@ CGeom make_cgeom(const Geom& g) {
   c.nw = (g.ly + kRows - 1) / kRows;
   c.pitch = unsigned((g.ly + 31) / 32 * 32);
   c.cs = (long long)NC * c.pitch;
+  c.stream = streams_output(state_bytes(c), cached_from, kCachedTo);
   return c;
 }
 
@@ -1030,7 +1054,7 @@ hipError_t launch_coeff_loss_ke(const void* src, double* lambda, double* partial
 
 hipError_t launch_coeff_adjoint_mu(const double* tape, const double* in, bool from_compact,
                                    double* mu_out, const Geom& gf, const Phys& p, hipStream_t s) {
-  const CGeom g = make_cgeom(gf);
+  const CGeom g = make_cgeom(gf, kAdjointCachedFrom);
   const WallTable wt = make_walls(p);
   const CPhys cp = make_cphys(p);
   if (from_compact) {
@@ -1046,13 +1070,14 @@ hipError_t launch_coeff_adjoint_mu(const double* tape, const double* in, bool fr
                        coeffs(static_cast<void*>(mu_out)), g, cp, wt, nb);
   };
   if (tx == 4)
-    run(k_coeff_adjoint<4, 2>);
+    run(k_coeff_adjoint<4, 2, kNonTemporal>);
   else if (tx == 3)
-    run(k_coeff_adjoint<3, 2>);
+    state_bytes(g) > kTapeCachedTo ? run(k_coeff_adjoint<3, 2, kNonTemporal>)
+                                   : run(k_coeff_adjoint<3, 2, 0>);
   else if (tx == 2)
-    run(k_coeff_adjoint<2, 2>);
+    run(k_coeff_adjoint<2, 2, 0>);
   else
-    run(k_coeff_adjoint<1, 2>);
+    run(k_coeff_adjoint<1, 2, 0>);
   return hipGetLastError();
 }
 

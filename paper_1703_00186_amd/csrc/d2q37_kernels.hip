@@ -39,14 +39,28 @@ __device__ __forceinline__ void load_site(const S* __restrict__ src, const Geom&
   for (int l = 0; l < Q; ++l) f[l] = A(src[l * g.ps + site]);
 }
 
-// Stores of a step's output are streamed past the caches (non-temporal):
-// the next step reads them only after the whole lattice, far more than the
-// caches hold, has been written.
-template <class S, class A>
+// Buffers that a step stores into the caches; us per step, streamed and cached:
+// FP32 with the FP32 collision 360 x 360 13.4 and 14.2, 400 x 400 18.7 and
+// 16.7, 512 x 512 21.5 and 18.4, 700 x 700 37.2 and 31.0, 1000 x 1000 65 and
+// 64, 1200 x 1200 88 and 94; plain FP64 BGK 280 x 280 15.6 and 13.0, 512 x 512
+// 31.5 and 25.2, 700 x 700 56.0 and 50.7, 850 x 850 80.5 and 88.3.
+constexpr long long kCachedFrom = 21LL * 1000 * 1000;
+constexpr long long kCachedTo = 156LL * 1000 * 1000;
+// Stores of a step's output, streamed past the caches (non-temporal) where
+// the caches do not hold the lattice until the next step reads it.
+template <bool kStream, class T>
+__device__ __forceinline__ void store_out(T v, T* p) {
+  if constexpr (kStream) {
+    __builtin_nontemporal_store(v, p);
+  } else {
+    *p = v;
+  }
+}
+template <class S, class A, bool kStream = true>
 __device__ __forceinline__ void store_site(S* __restrict__ dst, const Geom& g, long long site,
                                            const A (&f)[Q]) {
 #pragma unroll
-  for (int l = 0; l < Q; ++l) __builtin_nontemporal_store(S(f[l]), &dst[l * g.ps + site]);
+  for (int l = 0; l < Q; ++l) store_out<kStream>(S(f[l]), &dst[l * g.ps + site]);
 }
 
 // Accumulation-type tags of the local-reference FP32 forms (populations
@@ -78,11 +92,12 @@ __device__ __forceinline__ void load_local(const float* __restrict__ src, const 
   for (int l = 0; l < Q; ++l) f[l] = rest_maxwellian(l, rho, th) + double(src[l * g.ps + site]);
 }
 
+template <bool kStream = true>
 __device__ __forceinline__ void store_local(float* __restrict__ dst, const Geom& g, long long site,
                                             const float (&v)[Q], unsigned ref) {
 #pragma unroll
-  for (int l = 0; l < Q; ++l) __builtin_nontemporal_store(v[l], &dst[l * g.ps + site]);
-  __builtin_nontemporal_store(ref, &reinterpret_cast<unsigned*>(dst)[Q * g.ps + site]);
+  for (int l = 0; l < Q; ++l) store_out<kStream>(v[l], &dst[l * g.ps + site]);
+  store_out<kStream>(ref, &reinterpret_cast<unsigned*>(dst)[Q * g.ps + site]);
 }
 
 // Adjoint arrays are compact (no halos) in the lattice's layout: [lx][37][ly]
@@ -106,7 +121,7 @@ __device__ __forceinline__ bool on_wall_rows(const Geom& g, int y) {
 // edge columns are also written into the opposite halo so the next step needs
 // no separate halo refresh.
 // ---------------------------------------------------------------------------
-template <class S, class A, bool kReg, bool kTape>
+template <class S, class A, bool kReg, bool kTape, bool kStream>
 __global__ __launch_bounds__(kThreads) void k_fused(const S* __restrict__ src,
                                                     S* __restrict__ dst, Geom g, Phys P,
                                                     double* __restrict__ tape, int by, int bx,
@@ -125,9 +140,9 @@ __global__ __launch_bounds__(kThreads) void k_fused(const S* __restrict__ src,
     tape[2 * S2 + s] = m.jy;
     tape[3 * S2 + s] = m.e;
   }
-  store_site<S, A>(dst, g, site, f);
-  if (x < HX) store_site<S, A>(dst, g, site + (long long)g.lx * g.cs, f);
-  if (x >= g.lx - HX) store_site<S, A>(dst, g, site - (long long)g.lx * g.cs, f);
+  store_site<S, A, kStream>(dst, g, site, f);
+  if (x < HX) store_site<S, A, kStream>(dst, g, site + (long long)g.lx * g.cs, f);
+  if (x >= g.lx - HX) store_site<S, A, kStream>(dst, g, site - (long long)g.lx * g.cs, f);
 }
 
 // Fused step of the local-reference FP32 form: each population is rebuilt in
@@ -135,7 +150,7 @@ __global__ __launch_bounds__(kThreads) void k_fused(const S* __restrict__ src,
 // (f_l = M_l(rho_s, th_s of x - e_l) + g_l), then bc, the FP32 collision and
 // the store of the new deviations and reference.  Rows beyond the walls hold
 // zeros (reference 0: M = 0), which bc replaces.
-template <bool kReg, bool kF64Collide>
+template <bool kReg, bool kF64Collide, bool kStream>
 __global__ __launch_bounds__(kThreads) void k_fused_local(const float* __restrict__ src,
                                                           float* __restrict__ dst, Geom g, Phys P,
                                                           int by, int bx, int nty, unsigned nb) {
@@ -160,9 +175,9 @@ __global__ __launch_bounds__(kThreads) void k_fused_local(const float* __restric
   float v[Q];
   const unsigned ref =
       kF64Collide ? collide_site_local64<kReg>(f, v, P) : collide_site_local<kReg>(f, v, P);
-  store_local(dst, g, site, v, ref);
-  if (x < HX) store_local(dst, g, site + (long long)g.lx * g.cs, v, ref);
-  if (x >= g.lx - HX) store_local(dst, g, site - (long long)g.lx * g.cs, v, ref);
+  store_local<kStream>(dst, g, site, v, ref);
+  if (x < HX) store_local<kStream>(dst, g, site + (long long)g.lx * g.cs, v, ref);
+  if (x >= g.lx - HX) store_local<kStream>(dst, g, site - (long long)g.lx * g.cs, v, ref);
 }
 
 // The same step for the column layout, with the loads and stores of the
@@ -175,7 +190,7 @@ __global__ __launch_bounds__(kThreads) void k_fused_local(const float* __restric
 constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit buffer, gfx9 family
 constexpr int kNonTemporal = 2;           // cache policy bits of a streaming store
 
-template <bool kReg, bool kF64Collide>
+template <bool kReg, bool kF64Collide, bool kStream>
 __global__ __launch_bounds__(kThreads) void k_fused_local_col(const float* __restrict__ src,
                                                               float* __restrict__ dst, Geom g,
                                                               Phys P, int by, int bx, int nty,
@@ -221,15 +236,16 @@ __global__ __launch_bounds__(kThreads) void k_fused_local_col(const float* __res
   const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(dst + own), (short)0, unsigned(min((long long)bx * g.cs, (long long)g.nx * g.cs - own) * 4),
       kBufferWord3);
+  constexpr int kPolicy = kStream ? kNonTemporal : 0;
   const unsigned lane_out = (unsigned(x - x0) * cs + Y) * 4u;
 #pragma unroll
   for (int l = 0; l < Q; ++l)
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v[l]), out, lane_out,
-                                          unsigned(l) * ps * 4u, kNonTemporal);
-  __builtin_amdgcn_raw_buffer_store_b32(ref, out, lane_out, Q * ps * 4u, kNonTemporal);
+                                          unsigned(l) * ps * 4u, kPolicy);
+  __builtin_amdgcn_raw_buffer_store_b32(ref, out, lane_out, Q * ps * 4u, kPolicy);
   const long long site = padded<float>(g, x + HX, y + g.hy);
-  if (x < HX) store_local(dst, g, site + (long long)g.lx * g.cs, v, ref);
-  if (x >= g.lx - HX) store_local(dst, g, site - (long long)g.lx * g.cs, v, ref);
+  if (x < HX) store_local<kStream>(dst, g, site + (long long)g.lx * g.cs, v, ref);
+  if (x >= g.lx - HX) store_local<kStream>(dst, g, site - (long long)g.lx * g.cs, v, ref);
 }
 
 template <class S>
@@ -899,44 +915,44 @@ hipError_t launch_fused(const void* src, void* dst, const Geom& g, const Phys& p
   if (tape && prec != kF64) return hipErrorInvalidValue;
   if (prec == kF64 && regularize) return launch_coeff_step(src, dst, g, p, tape, s);
   const Tiling t = make_tiling(g.lx, g.ly);
+  const dim3 grid(t.nb), block(kThreads);
   return by_precision(prec, [&](auto sv, auto av) {
     using S = decltype(sv);
     using A = decltype(av);
     const S* a = static_cast<const S*>(src);
     S* b = static_cast<S*>(dst);
-    const dim3 grid(t.nb), block(kThreads);
-    if constexpr (is_local<A>) {
-      // column layout: buffer-addressed kernel (its per-tile resources span
-      // bx + 6 columns, which must fit the 32-bit byte range of a buffer
-      // resource); SoA, or columns too tall for that: global addressing
-      constexpr bool k64 = A::f64_collide;
-      const bool column = g.ps < g.cs &&
-                          (long long)(t.bx + 2 * HX) * g.cs * (long long)sizeof(float) < (1LL << 32);
-      if (column && regularize)
-        hipLaunchKernelGGL((k_fused_local_col<true, k64>), grid, block, 0, s, a, b, g, p, t.by,
-                           t.bx, t.nty, t.nb);
-      else if (column)
-        hipLaunchKernelGGL((k_fused_local_col<false, k64>), grid, block, 0, s, a, b, g, p, t.by,
-                           t.bx, t.nty, t.nb);
-      else if (regularize)
-        hipLaunchKernelGGL((k_fused_local<true, k64>), grid, block, 0, s, a, b, g, p, t.by, t.bx,
-                           t.nty, t.nb);
-      else
-        hipLaunchKernelGGL((k_fused_local<false, k64>), grid, block, 0, s, a, b, g, p, t.by,
-                           t.bx, t.nty, t.nb);
-    } else if constexpr (std::is_same<S, float>::value) {
-      if (regularize)
-        hipLaunchKernelGGL((k_fused<S, A, true, false>), grid, block, 0, s, a, b, g, p, tape,
-                           t.by, t.bx, t.nty, t.nb);
-      else
-        hipLaunchKernelGGL((k_fused<S, A, false, false>), grid, block, 0, s, a, b, g, p, tape,
-                           t.by, t.bx, t.nty, t.nb);
-    } else if (tape)
-      hipLaunchKernelGGL((k_fused<S, A, false, true>), grid, block, 0, s, a, b, g, p, tape,
-                         t.by, t.bx, t.nty, t.nb);
+    const auto launch = [&](auto streamed) {
+      constexpr bool kStream = decltype(streamed)::value;
+      if constexpr (is_local<A>) {
+        // column layout: buffer-addressed kernel (its per-tile resources span
+        // bx + 6 columns, which must fit the 32-bit byte range of a buffer
+        // resource); SoA, or columns too tall for that: global addressing
+        constexpr bool k64 = A::f64_collide;
+        const bool column = g.ps < g.cs && (long long)(t.bx + 2 * HX) * g.cs *
+                                                   (long long)sizeof(float) <
+                                               (1LL << 32);
+        const auto kernel = column ? (regularize ? k_fused_local_col<true, k64, kStream>
+                                                 : k_fused_local_col<false, k64, kStream>)
+                                   : (regularize ? k_fused_local<true, k64, kStream>
+                                                 : k_fused_local<false, k64, kStream>);
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, a, b, g, p, t.by, t.bx, t.nty, t.nb);
+      } else {
+        const auto kernel = [&] {
+          if constexpr (std::is_same<S, float>::value)
+            return regularize ? k_fused<S, A, true, false, kStream>
+                              : k_fused<S, A, false, false, kStream>;
+          else
+            return tape ? k_fused<S, A, false, true, kStream>
+                        : k_fused<S, A, false, false, kStream>;
+        }();
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, a, b, g, p, tape, t.by, t.bx, t.nty, t.nb);
+      }
+    };
+    if (streams_output((long long)g.np * g.nx * g.ny * (long long)sizeof(S),
+                       kCachedFrom, kCachedTo))
+      launch(std::true_type{});
     else
-      hipLaunchKernelGGL((k_fused<S, A, false, false>), grid, block, 0, s, a, b, g, p, tape,
-                         t.by, t.bx, t.nty, t.nb);
+      launch(std::false_type{});
   });
 }
 

@@ -27,6 +27,16 @@ inline Tiling make_tiling(int lx, int ly) {
   return t;
 }
 
+// Whether a step streams its output past the caches.  The two buffers of a
+// state of up to about 150 MB stay in the 256 MB of Infinity Cache from one
+// step to the next if the stores are ordinary ones; above, they only push out
+// what the step still has to read.  Small states are in the L2s either way,
+// and a streamed store saves the write-back at the kernel's end.  The kernels
+// name their lines and what they measured there.
+inline bool streams_output(long long buffer_bytes, long long cached_from, long long cached_to) {
+  return buffer_bytes < cached_from || buffer_bytes > cached_to;
+}
+
 inline unsigned grid_1d(long long n) { return unsigned((n + kThreads - 1) / kThreads); }
 
 // Tile of this workgroup after the XCD-aware remap (a bijection of [0, nb)).
