@@ -20,9 +20,13 @@ SOURCES = [os.path.join(CSRC, "d2q37_kernels.hip"), os.path.join(CSRC, "d2q37_co
            os.path.join(CSRC, "d2q37_variants.hip"),
            os.path.join(CSRC, "lb_api.hip"), os.path.join(CSRC, "lb_scratch.hip")]
 
+# Loop-invariant code motion on machine code is off: in the marching kernels it
+# moves some 120 FP64 literals out of the loop, which then are spilled and read
+# back lane by lane (349 v_readlane a column in the plain BGK kernel).
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-disable-machine-licm",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]
 

@@ -931,29 +931,6 @@ int sweep_columns(const CGeom& g) {
 // against 19.8 with two ahead; 777 x 1501: 72.8 against 63.2).
 bool shallow_sweep(const CGeom& g) { return (long long)g.nw * g.lx < 9216; }
 
-// Columns of a workgroup of k_coeff_pair: its time is the iterations of a
-// chunk, (chunk + 6) / 4 and one to fill the pipeline, times the rounds in
-// which the workgroups pass through the GPU, two to a CU; the chunk with the
-// least of that product.  Chunks of 4 n + 2 columns use every iteration fully.
-int pair_chunk(const CGeom& g, int windows) {
-  const int slots = 2 * 256;
-  int best = kPairCols - 2;
-  double best_cost = 0.0;
-  for (int chunk = kPairCols - 2; chunk < g.lx + kPairCols; chunk += kPairCols) {
-    const long long groups = (long long)windows * ((g.lx + chunk - 1) / chunk);
-    // beyond a few rounds the workgroups even out
-    const double rounds =
-        groups <= 4 * slots ? double((groups + slots - 1) / slots) : double(groups) / slots + 0.5;
-    const double cost = rounds * ((std::min(chunk, g.lx) + 6) / kPairCols + 1);
-    if (best_cost == 0.0 || cost < best_cost) {
-      best = chunk;
-      best_cost = cost;
-    }
-    if (chunk > 512) break;
-  }
-  return best;
-}
-
 }  // namespace
 
 hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const Phys& p,
@@ -962,9 +939,9 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
   const WallTable wt = make_walls(p);
   const CPhys cp = make_cphys(p);
   const unsigned* guard = guard_of(src, gf);
-  if (gf.form == kFormCoeffTwice) {
+  if (gf.form == kFormTwice) {
     const int windows = (g.ly + kPairRows - 1) / kPairRows;
-    const int chunk = pair_chunk(g, windows);
+    const int chunk = march_chunk(g.lx, windows, 512, kPairCols);
     const unsigned nb = unsigned(windows) * unsigned((g.lx + chunk - 1) / chunk);
     hipLaunchKernelGGL(k_coeff_pair, dim3(nb), dim3(64 * 2 * kPairMakers), 0, s, coeffs(src),
                        coeffs(dst), g, cp, wt, windows, chunk, nb, word_of(dst));

@@ -52,8 +52,9 @@ struct Geom {
 // site that generate them.  The buffer's first word, padding in both forms, names its
 // form for graphs recorded before the state was replaced; the host passes
 // what it knows in Geom::form, kFormUnknown where a graph may have run.
-// kFormCoeffTwice asks launch_fused for two steps from the coefficient form.
-enum Form : int { kFormFull = 0, kFormCoeff = 1, kFormUnknown = 2, kFormCoeffTwice = 3 };
+// kFormTwice asks launch_fused for two steps (from the coefficients where the
+// step has that form, else from the populations).
+enum Form : int { kFormFull = 0, kFormCoeff = 1, kFormUnknown = 2, kFormTwice = 3 };
 
 constexpr int NC = 15;  // coefficients of a site: degree i + j <= 4
 

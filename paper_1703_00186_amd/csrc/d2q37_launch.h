@@ -37,19 +37,40 @@ hipError_t launch_halo(void* buf, const Geom& g, int prec, hipStream_t s);
 
 // One fused step: dst = collide(bc(propagate(src))), with the periodic x
 // halos of dst written too.  tape (optional, FP64 only): [4][lx][ly].
-// With form kFormCoeffTwice: two steps (regularized FP64, no tape).
+// With form kFormTwice: two steps (no tape, where two_steps_pay).
 hipError_t launch_fused(const void* src, void* dst, const Geom& g, const Phys& p, int prec,
                         int regularize, double* tape, hipStream_t s);
 
-// Whether two steps in one launch are the faster ones: from the sizes where
-// their workgroups fill the GPU once, unless the waves of 52 rows cover ly
-// much worse than the single step's waves of 56.  Per step, single and double:
-// 512 x 512 16.2 and 18.6 us, 560 x 560 19.8 and 19.1, 700 x 450 23.5 and
-// 19.1, 640 x 640 29.4 and 22.7, 20000 x 30 46.6 and 39.2; on the other side
-// of the row rule 20000 x 56 (two waves against one) 60.9 and 71.3.
-inline bool two_steps_pay(const Geom& g) {
-  const int single = (g.ly + 55) / 56, pair = (g.ly + 51) / 52;
-  return (long long)g.lx * g.ly >= 310000 && 4 * pair <= 5 * single;
+// Whether two steps in one launch are the faster ones.
+// FP64 coefficients: from the sizes where their workgroups fill the GPU once,
+// unless the waves of 52 rows cover ly much worse than the single step's waves
+// of 56.  Per step, single and double: 512 x 512 16.2 and 18.6 us, 560 x 560
+// 19.8 and 19.1, 700 x 450 23.5 and 19.1, 640 x 640 29.4 and 22.7, 20000 x 30
+// 46.6 and 39.2; on the other side of the row rule 20000 x 56 (two waves
+// against one) 60.9 and 71.3.
+// Populations (plain FP64 BGK and the shifted FP32 forms; for the
+// local-reference forms see k_fused_pair), by columns of windows of 58 rows,
+// in the column layout with a column's seven sources in the 32-bit range of a
+// buffer resource:
+//   up to 512, where a launch costs more than its work: 128 x 128 8.7 and
+//     6.2 us, 100 x 100 7.9 and 6.2 in FP32; 1000 x 16 7.5 and 8.4;
+//   FP64 from 1400 on: 330 x 205 (1320) 10.3 and 9.8, 240 x 240 (1200) 8.3
+//     and 9.2, 1024 x 1000 109 and 80;
+//   FP32 from 14000 on, where the state no longer fits the caches, on windows
+//     three quarters full: 900 x 900 (14400) 50.5 and 40.1, 1000 x 700 (13000)
+//     34.8 and 38.4, 4096 x 4096 852 and 812.
+inline bool two_steps_pay(const Geom& g, int prec, int regularize) {
+  const long long sites = (long long)g.lx * g.ly;
+  if (prec == kF64 && regularize) {
+    const int single = (g.ly + 55) / 56, pair = (g.ly + 51) / 52;
+    return sites >= 310000 && 4 * pair <= 5 * single;
+  }
+  if (prec != kF64 && prec != kF32Shifted && prec != kF32ShiftedF32Sum) return false;
+  if (g.ps > g.cs || 7 * g.cs * 8 >= (1LL << 32)) return false;
+  const long long columns = (long long)g.lx * ((g.ly + 57) / 58);
+  if (columns <= 512) return true;
+  if (prec == kF64) return columns >= 1400;
+  return columns >= 14000 && 4 * sites >= 3 * 58 * columns;
 }
 
 // Split path.

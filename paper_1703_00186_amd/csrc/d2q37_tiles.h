@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "d2q37_device.h"
 
 namespace d2q37 {
@@ -35,6 +37,29 @@ inline Tiling make_tiling(int lx, int ly) {
 // name their lines and what they measured there.
 inline bool streams_output(long long buffer_bytes, long long cached_from, long long cached_to) {
   return buffer_bytes < cached_from || buffer_bytes > cached_to;
+}
+
+// Columns of a workgroup that makes two steps of a window of rows, `cols`
+// columns at a time: its time is the iterations of a chunk, (chunk + 6) / cols
+// and one to fill the pipeline, times the rounds in which the workgroups pass
+// through the GPU, `slots` at once; the chunk with the least of that product.
+// Chunks of cols n - 6 columns use every iteration fully.
+inline int march_chunk(int lx, int windows, int slots, int cols) {
+  const int first = (6 / cols + 1) * cols - 6;
+  int best = first;
+  double best_cost = 0.0;
+  for (int chunk = first; chunk < lx + cols && chunk <= 2048; chunk += cols) {
+    const long long groups = (long long)windows * ((lx + chunk - 1) / chunk);
+    // beyond a few rounds the workgroups even out
+    const double rounds =
+        groups <= 4 * slots ? double((groups + slots - 1) / slots) : double(groups) / slots + 0.5;
+    const double cost = rounds * ((std::min(chunk, lx) + 6) / cols + 1);
+    if (best_cost == 0.0 || cost < best_cost) {
+      best = chunk;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 inline unsigned grid_1d(long long n) { return unsigned((n + kThreads - 1) / kThreads); }

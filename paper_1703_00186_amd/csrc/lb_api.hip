@@ -310,9 +310,12 @@ int check_finite_now(lb_ctx* c) {
   return LB_OK;
 }
 
+// The step that the coefficient form is for (d2q37_coeff.hip).
+bool coeff_step(const lb_ctx* c) { return c->prec == LB_FP64 && c->par.regularize; }
+
 int one_step(lb_ctx* c, double* tape) {
   const bool fused = c->par.kernel == LB_KERNEL_FUSED || tape;
-  if (fused && c->prec == LB_FP64 && c->par.regularize) {
+  if (fused && coeff_step(c)) {
     // from either form to the coefficient form, which needs no halos
     LB_HIP(d2q37::launch_fused(c->A, c->B, with_form(c->g, c->a_form), c->p, c->prec, 1, tape,
                                c->stream),
@@ -356,13 +359,21 @@ int one_step(lb_ctx* c, double* tape) {
   return LB_OK;
 }
 
-// Two steps in one launch, for a state in the coefficient form.
+// Two fused steps in one launch, from the form the step leaves behind.
 int two_steps(lb_ctx* c) {
-  LB_HIP(d2q37::launch_fused(c->A, c->B, with_form(c->g, d2q37::kFormCoeffTwice), c->p, c->prec, 1,
-                             nullptr, c->stream),
+  if (!coeff_step(c)) {
+    int rc = mark_full(c, c->B, c->b_form);
+    if (rc == LB_OK && (!c->halos_valid || !c->g.walls)) rc = do_halo(c);
+    if (rc) return rc;
+  }
+  LB_HIP(d2q37::launch_fused(c->A, c->B, with_form(c->g, d2q37::kFormTwice), c->p, c->prec,
+                             c->par.regularize, nullptr, c->stream),
          "fused steps");
   std::swap(c->A, c->B);
-  c->b_form = d2q37::kFormCoeff;
+  if (coeff_step(c))
+    c->b_form = d2q37::kFormCoeff;
+  else
+    c->halos_valid = c->g.walls;
   return LB_OK;
 }
 
@@ -371,10 +382,11 @@ int two_steps(lb_ctx* c) {
 // two steps come in pairs.  The last step is a single one: it leaves the state
 // before it in the scratch buffer.
 int run_steps(lb_ctx* c, int n) {
-  const bool pairs = c->prec == LB_FP64 && c->par.regularize && c->par.kernel == LB_KERNEL_FUSED &&
-                     c->par.check_finite == 0 && d2q37::two_steps_pay(c->g);
+  const bool pairs = c->par.kernel == LB_KERNEL_FUSED && c->par.check_finite == 0 &&
+                     d2q37::two_steps_pay(c->g, c->prec, c->par.regularize);
+  const int form = coeff_step(c) ? d2q37::kFormCoeff : d2q37::kFormFull;
   for (int i = 0; i < n;) {
-    if (pairs && n - i > 4 && c->a_form == d2q37::kFormCoeff) {
+    if (pairs && n - i > 4 && c->a_form == form) {
       int rc = two_steps(c);
       if (rc == LB_OK) rc = two_steps(c);
       if (rc) return rc;
