@@ -41,6 +41,17 @@ def bytes_per_site(precision: str = "fp64") -> int:
     return 2 * (Q + 1) * 4 if precision in ("fp32c", "fp32l") else 2 * Q * 4
 
 
+def moved_bytes_per_site(precision: str, lx: int, ly: int) -> int:
+    """HBM bytes that the library's fused step has to move per site update: FP64
+    is stored as 15 Hermite coefficients (240 bytes in and out); large
+    lattices make two steps per launch (but for the last one to four of a
+    call) in FP64 and in the shifted FP32 forms, which halves the bytes."""
+    if precision == "fp64":
+        return 120 if lx * ly >= 310000 else 240
+    two = precision in ("fp32s", "fp32s_f32sum") and lx * ((ly + 57) // 58) >= 14000
+    return bytes_per_site(precision) // (2 if two else 1)
+
+
 def mlups(sites: int, seconds: float) -> float:
     return sites / seconds / 1e6
 
@@ -52,6 +63,9 @@ FP32_VALU_SUMMARY = VALU_SUMMARY
 FP64_VECTOR_PEAK_TFLOPS = 78.6
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 KERNEL_SOURCES = ["paper_1703_00186_amd/csrc/d2q37_kernels.hip",
+                  "paper_1703_00186_amd/csrc/d2q37_coeff.hip",
+                  "paper_1703_00186_amd/csrc/d2q37_coeff.h",
+                  "paper_1703_00186_amd/csrc/d2q37_tiles.h",
                   "paper_1703_00186_amd/csrc/d2q37_device.h",
                   "paper_1703_00186_amd/csrc/d2q37_constants.h"]
 
@@ -191,14 +205,15 @@ def time_adjoint(lb, steps: int, torch) -> dict:
     t_rec = ev[0].elapsed_time(ev[1]) / 1e3 / steps
     t_run = ev[2].elapsed_time(ev[3]) / 1e3 / steps
     t_one = ev[4].elapsed_time(ev[5]) / 1e3 / steps
-    gbs = lambda t: round(624 * sites / t / 1e9, 1)  # noqa: E731
+    # coefficients in and out and the tape; the single step's lambda is stored in full
+    gbs = lambda t, b=272: round(b * sites / t / 1e9, 1)  # noqa: E731
     return {"steps": steps, "record_ms_per_step": round(t_rec * 1e3, 5),
             "record_GB/s": gbs(t_rec),
             "adjoint_ms_per_step": round(t_run * 1e3, 5), "adjoint_GB/s": gbs(t_run),
-            "adjoint_frac": round(624 * sites / t_run / 1e9 / HBM_PEAK_GBS, 4),
-            "single_step_ms_per_step": round(t_one * 1e3, 5), "single_step_GB/s": gbs(t_one),
+            "adjoint_frac": round(272 * sites / t_run / 1e9 / HBM_PEAK_GBS, 4),
+            "single_step_ms_per_step": round(t_one * 1e3, 5), "single_step_GB/s": gbs(t_one, 624),
             "run_equals_single_steps": same,
-            "note": "lambda in 296 + tape 32 + lambda out 296 B/site; adjoint_*: lb_adjoint_run "
+            "note": "coefficients in 120 + tape 32 + out 120 B/site; adjoint_*: lb_adjoint_run "
                     "(gather form), single_step_*: lb_adjoint_step (scatter form)"}
 
 
@@ -257,7 +272,7 @@ def fp32_legs(lx: int, ly: int, fields, layout: str, fp64_mlups: float, torch) -
         lb32.step(FP32_ERROR_STEPS - FP32_WARMUP - FP32_TIMED)
         errs = field_errors(host_moments(lb32, torch), m64)
         v32 = mlups(sites * FP32_TIMED, t32)
-        gbs = bytes_per_site(prec) * sites / (t32 / FP32_TIMED) / 1e9
+        gbs = moved_bytes_per_site(prec, lx, ly) * sites / (t32 / FP32_TIMED) / 1e9
         out[key] = {
             "form": what, "precision": prec,
             "MLUPS": round(v32, 2), "ms_per_step": round(t32 / FP32_TIMED * 1e3, 5),
@@ -308,7 +323,7 @@ def precision_leg(torch, layout: str = "column") -> dict:
         t = time_steps(lb, FP32_TIMED, torch)
         lb.step(FP32_ERROR_STEPS - FP32_WARMUP - FP32_TIMED)
         v = mlups(sites * FP32_TIMED, t)
-        gbs = bytes_per_site(prec) * sites / (t / FP32_TIMED) / 1e9
+        gbs = moved_bytes_per_site(prec, lx, ly) * sites / (t / FP32_TIMED) / 1e9
         rec[prec] = {"MLUPS": round(v, 1), "ms_per_step": round(t / FP32_TIMED * 1e3, 4),
                      "GB/s": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4)}
         if prec == "fp64":
@@ -343,7 +358,7 @@ def production_leg(torch, steps: int = 200, warmup: int = 10, n_adj: int = 100,
         lb.step(warmup)
         t = time_steps(lb, steps, torch)
         v = mlups(sites * steps, t)
-        gbs = bytes_per_site(prec) * sites / (t / steps) / 1e9
+        gbs = moved_bytes_per_site(prec, lx, ly) * sites / (t / steps) / 1e9
         rec[prec] = {"MLUPS": round(v, 1), "ms_per_step": round(t / steps * 1e3, 4),
                      "GB/s": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
                      "workspace_bytes": ws}
@@ -627,7 +642,7 @@ def _production_workload(args, torch) -> dict:
         t = time_steps(lb, n - (n_adj if prec == "fp64" else 0), torch)
         steps_done = n - (n_adj if prec == "fp64" else 0)
         v = mlups(sites * steps_done, t)
-        bps = bytes_per_site(prec)
+        bps = moved_bytes_per_site(prec, lx, ly)
         rec[prec] = {"MLUPS": round(v, 1), "GB/s": round(bps * v * 1e6 / 1e9, 1),
                      "hbm_frac": round(bps * v * 1e6 / 1e9 / HBM_PEAK_GBS, 4),
                      "workspace_GB": round(foot / 1e9, 3), "steps_timed": steps_done}
@@ -844,7 +859,7 @@ def run_forms(args, torch) -> list:
         lb = LB(lx, ly, *fields, precision=prec, layout=args.layout)
         lb.step(args.warmup)
         t = time_steps(lb, args.steps, torch)
-        gbs = bytes_per_site(prec) * lx * ly / (t / args.steps) / 1e9
+        gbs = moved_bytes_per_site(prec, lx, ly) * lx * ly / (t / args.steps) / 1e9
         out.append({"form": prec, "lattice": [lx, ly], "steps": args.steps,
                     "ms_per_step": round(t / args.steps * 1e3, 5),
                     "MLUPS": round(mlups(lx * ly * args.steps, t), 1), "GB/s": round(gbs, 1),
@@ -956,7 +971,8 @@ def main(argv=None) -> int:
     t = time_steps(lb, args.steps, torch)
     ms = t / args.steps * 1e3
     value = mlups(sites * args.steps, t)
-    achieved = bytes_per_site("fp64") * sites / (t / args.steps) / 1e9
+    moved = moved_bytes_per_site("fp64", lx, ly)
+    achieved = moved * sites / (t / args.steps) / 1e9
     log("bench: fused FP64 %.4f ms/step, %.1f MLUPS, %.0f GB/s" % (ms, value, achieved))
     out = {
         "metric": METRIC, "value": round(value, 2), "unit": "MLUPS", "n_gpus": 1,
@@ -969,8 +985,10 @@ def main(argv=None) -> int:
                    "t_top": 0.5, "layout": args.layout, "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": None, "kernel": "k_fused<double>",
-                     "bytes_per_site": bytes_per_site("fp64")},
+                     "traffic": None,
+                     "kernel": "k_coeff_pair" if moved == 120 else "k_coeff_step",
+                     "bytes_per_site": moved,
+                     "population_bytes_per_site": bytes_per_site("fp64")},
     }
     fps = counted_flop_per_site()
     if fps is not None:

@@ -202,7 +202,7 @@ int lb_get_populations(lb_ctx* ctx, double* f);
  * lb_propagate and lb_collide run the alternative kernel of the context's
  * LB_KERNEL_SPLIT_* value where it names one (lb_step's split path too).
  * lb_get_scratch / lb_set_scratch copy B's physical region in the compact
- * form of lb_get_state.  The local-reference forms (LB_FP32_COLLIDE,
+ * form of lb_get_state; after fused steps B holds the state before the last.  The local-reference forms (LB_FP32_COLLIDE,
  * LB_FP32_LOCAL) have no split stages: lb_propagate, lb_bc, lb_collide,
  * lb_get_scratch and lb_set_scratch return LB_E_STATE for them. */
 int lb_halo(lb_ctx* ctx);
@@ -256,11 +256,11 @@ int lb_run_observed(lb_ctx* ctx, int n, int every, double* series);
  * place in `lambda`, with tape = [n][4][lx][ly] from lb_step_record (tape
  * step j holds the moments of the step from f^j to f^{j+1}).  The same
  * arithmetic as n calls of lb_adjoint_step, and the same result bit for bit.
- * On lattices beyond the Infinity Cache P^T is applied as a gather by the
- * following step: between steps the adjoint lives in two padded FP64 buffers
- * laid out like the state (aligned stores instead of the scatter's partial
- * ones); on lattices of 2^17 sites up to the cache size the steps are the
- * scatter kernel of lb_adjoint_step.  `workspace`: 256-byte aligned, at least
+ * With regularization the 15 moments that lambda then has are kept between
+ * the steps, in the workspace.  Plain BGK: on lattices beyond the Infinity
+ * Cache P^T is applied as a gather by the next step (aligned stores instead of
+ * the scatter's partial ones); on lattices of 2^17 sites up to the cache size
+ * the steps are the scatter kernel of lb_adjoint_step.  `workspace`: 256-byte aligned, at least
  * the size from lb_adjoint_workspace_bytes, previous contents irrelevant, and
  * overlapping neither tape, lambda nor the context's own workspace.  n = 0
  * leaves lambda unchanged.  Errors: LB_E_STATE (not FP64), LB_E_ARG (n < 0,
