@@ -149,8 +149,8 @@ struct Row {
   bool in;
   unsigned load, store;
 };
-template <int rows = kRows, int halo = kHalo>
-__device__ __forceinline__ Row wave_row(const CGeom& g, int w) {
+__device__ __forceinline__ Row wave_row(const CGeom& g, int w, int rows = kRows,
+                                        int halo = kHalo) {
   const int lane = threadIdx.x & 63;
   Row r;
   r.y = w * rows - halo + lane;
@@ -368,19 +368,19 @@ constexpr int kPairCols = kPairWave * kPairMakers;  // columns of an iteration
 constexpr int kRing = kPairCols + 6, kRingCol = NC * 64;
 constexpr int kPairAhead = 4;  // divides kPairWave + 6: the loads run on across iterations
 
-// One wave's walk over kPairWave + 6 source columns; load(j, v) fetches source
-// column j, beyond the walk's end the next walk's first ones.
-template <int kAhead>
+// One wave's walk over TX + 6 source columns; load(j, v) fetches source column
+// j, beyond the walk's end the next walk's first ones.
+template <int TX, int kAhead>
 struct PairWalk {
   const CGeom& g;
   const CPhys& P;
   const WallTable& wt;
   const Row& row;
-  double m[kPairWave][NC];
+  double m[TX][NC];
 
   template <int j, int t>
   __device__ __forceinline__ void add(const double (&c)[NC]) {
-    if constexpr (t < kPairWave) {
+    if constexpr (t < TX) {
       constexpr int ex = t + 3 - j;
       if constexpr (ex >= -3 && ex <= 3) {
         Group f;
@@ -395,7 +395,7 @@ struct PairWalk {
   }
   template <int j = 0, class Load>
   __device__ __forceinline__ void walk(double (&c)[kAhead][NC], const Load& load) {
-    if constexpr (j < kPairWave + 6) {
+    if constexpr (j < TX + 6) {
       add<j, 0>(c[j % kAhead]);
       __builtin_amdgcn_sched_barrier(0);
       load(j + kAhead, c[j % kAhead]);
@@ -412,6 +412,22 @@ struct PairWalk {
 
 __device__ __forceinline__ int ring_slot(int s) { return s >= kRing ? s - kRing : s; }
 
+__device__ __forceinline__ void ring_store(double* col, int lane, const double* m) {
+#pragma unroll
+  for (int k = 0; k < NC / 2; ++k)
+    *reinterpret_cast<v2d*>(col + k * 128 + 2 * lane) = v2d{m[2 * k], m[2 * k + 1]};
+  col[(NC - 1) * 64 + lane] = m[NC - 1];
+}
+__device__ __forceinline__ void ring_load(const double* col, int lane, double (&v)[NC]) {
+#pragma unroll
+  for (int k = 0; k < NC / 2; ++k) {
+    const v2d d = *reinterpret_cast<const v2d*>(col + k * 128 + 2 * lane);
+    v[2 * k] = d.x;
+    v[2 * k + 1] = d.y;
+  }
+  v[NC - 1] = col[(NC - 1) * 64 + lane];
+}
+
 __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
     const double* __restrict__ src, double* __restrict__ dst, CGeom g, CPhys P, WallTable wt,
     int windows, int chunk, unsigned nb, unsigned* word) {
@@ -421,7 +437,7 @@ __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
   const int xa = int(t / unsigned(windows)) * chunk, xb = min(xa + chunk, g.lx);
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
-  const Row row = wave_row<kPairRows, kPairHalo>(g, int(t % unsigned(windows)));
+  const Row row = wave_row(g, int(t % unsigned(windows)), kPairRows, kPairHalo);
   // iteration i: step one of columns xa - 3 + 4 i .., step two of the targets
   // whose sources iteration i - 1 completed; both barriers every time
   const int iters = (xb - xa + 6 + kPairCols - 1) / kPairCols;
@@ -438,7 +454,7 @@ __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
 #pragma unroll
     for (int j = 0; j < kPairAhead; ++j) load(j, c[j]);
     for (int i = 0; i <= iters; ++i) {
-      PairWalk<kPairAhead> s{g, P, wt, row};
+      PairWalk<kPairWave, kPairAhead> s{g, P, wt, row};
       if (i < iters) {
         s.walk(c, load);
         if (!g.periodic && !row.in) {  // nothing comes from beyond the walls
@@ -451,11 +467,7 @@ __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
 #pragma unroll
         for (int n = 0; n < kPairWave; ++n) {
           double* col = ring + ring_slot(slot + n) * kRingCol;
-#pragma unroll
-          for (int m = 0; m < NC / 2; ++m)
-            *reinterpret_cast<v2d*>(col + m * 128 + 2 * lane) =
-                v2d{s.m[n][2 * m], s.m[n][2 * m + 1]};
-          col[(NC - 1) * 64 + lane] = s.m[n][NC - 1];
+          ring_store(col, lane, s.m[n]);
         }
       }
       __syncthreads();
@@ -473,17 +485,11 @@ __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
           auto load = [&](int j, double (&v)[NC]) {
             if (j >= kPairWave + 6) return;
             const double* col = ring + ring_slot(base + j) * kRingCol;
-#pragma unroll
-            for (int m = 0; m < NC / 2; ++m) {
-              const v2d d = *reinterpret_cast<const v2d*>(col + m * 128 + 2 * lane);
-              v[2 * m] = d.x;
-              v[2 * m + 1] = d.y;
-            }
-            v[NC - 1] = col[(NC - 1) * 64 + lane];
+            ring_load(col, lane, v);
           };
           double c[1][NC];
           load(0, c[0]);
-          PairWalk<1> s{g, P, wt, row};
+          PairWalk<kPairWave, 1> s{g, P, wt, row};
           s.walk(c, load);
 #pragma unroll
           for (int n = 0; n < kPairWave; ++n)
@@ -495,6 +501,56 @@ __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
       __syncthreads();
       __syncthreads();
     }
+  }
+}
+
+// Two steps in one launch for lattices that leave most of the GPU idle, where
+// a launch costs as much as its work: one column of a window of rows by seven
+// waves.  Each makes one column of the first step, from three before to three
+// after, into LDS; the first of them then makes the second step.  The column's
+// chain of instructions (about 600, 1 us) runs three times as often as in two
+// launches of k_coeff_step, on SIMDs that have nothing else to do: per step
+// 16 x 16 4.7 us and 3.7, 64 x 48 4.8 and 3.8, 128 x 48 4.6 and 4.1, but
+// 100 x 100 (200 columns of windows) 4.7 and 4.5, 128 x 128 4.8 and 6.3.  Two
+// columns by eight waves 4.1 at 64 x 48; three steps in a loop over stages 4.7.
+constexpr int kSmallWaves = 7;
+__global__ __launch_bounds__(64 * kSmallWaves) void k_coeff_two(
+    const double* __restrict__ src, double* __restrict__ dst, CGeom g, CPhys P, WallTable wt,
+    int windows, int rows, int halo, unsigned* word) {
+  __shared__ __align__(16) double ring[kSmallWaves * kRingCol];
+  set_form(word, kFormCoeff);
+  const int x = int(blockIdx.x / unsigned(windows));
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const Row row = wave_row(g, int(blockIdx.x % unsigned(windows)), rows, halo);
+  {
+    auto load = [&](int j, double (&v)[NC]) {
+      if (j >= 7) return;
+      int xs = x - 6 + wave + j;
+      xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
+      load_column(column_rsrc(src, g, xs), g, row.load, v);
+    };
+    double c[2][NC];
+    load(0, c[0]);
+    load(1, c[1]);
+    PairWalk<1, 2> s{g, P, wt, row};
+    s.walk(c, load);
+    if (!g.periodic && !row.in) {  // nothing comes from beyond the walls
+#pragma unroll
+      for (int k = 0; k < NC; ++k) s.m[0][k] = 0.0;
+    }
+    ring_store(ring + wave * kRingCol, lane, s.m[0]);
+  }
+  __syncthreads();
+  if (wave == 0) {
+    auto load = [&](int j, double (&v)[NC]) {
+      if (j < 7) ring_load(ring + j * kRingCol, lane, v);
+    };
+    double c[1][NC];
+    load(0, c[0]);
+    PairWalk<1, 1> s{g, P, wt, row};
+    s.walk(c, load);
+    store_column(column_rsrc(dst, g, x), g, row.store, s.m[0]);
   }
 }
 
@@ -939,6 +995,15 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
   const WallTable wt = make_walls(p);
   const CPhys cp = make_cphys(p);
   const unsigned* guard = guard_of(src, gf);
+  if (gf.form == kFormTwice && two_steps_small(gf)) {
+    // between walls 64 rows need no halo rows
+    const bool one = !g.periodic && g.ly <= 64;
+    const int rows = one ? 64 : kPairRows, halo = one ? 0 : kPairHalo;
+    const int windows = (g.ly + rows - 1) / rows;
+    hipLaunchKernelGGL(k_coeff_two, dim3(windows * g.lx), dim3(64 * kSmallWaves), 0, s,
+                       coeffs(src), coeffs(dst), g, cp, wt, windows, rows, halo, word_of(dst));
+    return hipGetLastError();
+  }
   if (gf.form == kFormTwice) {
     const int windows = (g.ly + kPairRows - 1) / kPairRows;
     const int chunk = march_chunk(g.lx, windows, 512, kPairCols);

@@ -41,6 +41,12 @@ hipError_t launch_halo(void* buf, const Geom& g, int prec, hipStream_t s);
 hipError_t launch_fused(const void* src, void* dst, const Geom& g, const Phys& p, int prec,
                         int regularize, double* tape, hipStream_t s);
 
+// FP64 coefficients, lattices of up to 128 columns of windows of rows, by one
+// workgroup each (k_coeff_two has the figures).
+inline bool two_steps_small(const Geom& g) {
+  const int windows = g.walls && g.ly <= 64 ? 1 : (g.ly + 51) / 52;
+  return (long long)g.lx * windows <= 128;
+}
 // Whether two steps in one launch are the faster ones.
 // FP64 coefficients: from the sizes where their workgroups fill the GPU once,
 // unless the waves of 52 rows cover ly much worse than the single step's waves
@@ -63,7 +69,7 @@ inline bool two_steps_pay(const Geom& g, int prec, int regularize) {
   const long long sites = (long long)g.lx * g.ly;
   if (prec == kF64 && regularize) {
     const int single = (g.ly + 55) / 56, pair = (g.ly + 51) / 52;
-    return sites >= 310000 && 4 * pair <= 5 * single;
+    return two_steps_small(g) || (sites >= 310000 && 4 * pair <= 5 * single);
   }
   if (prec != kF64 && prec != kF32Shifted && prec != kF32ShiftedF32Sum) return false;
   if (g.ps > g.cs || 7 * g.cs * 8 >= (1LL << 32)) return false;

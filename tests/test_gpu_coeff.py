@@ -90,10 +90,12 @@ def test_tape_and_transposed_steps(shape, ybc):
 
 
 # two steps per launch from 310000 sites on: waves of 52 rows, chunks of columns
-# that are walked four at a time; the last lattice is too small for them
+# that are walked four at a time; and up to 128 columns of windows (of 52 rows,
+# between walls one of 64).  400 x 400 and 65 x 65 lie between
 @pytest.mark.parametrize("ybc", ["walls", "periodic"])
 @pytest.mark.parametrize("shape", [(600, 520), (599, 521), (1201, 310), (6, 52000), (8, 40003),
-                                   (31003, 12), (777, 1501), (400, 400)])
+                                   (31003, 12), (777, 1501), (400, 400), (6, 6), (64, 48),
+                                   (64, 64), (128, 52), (64, 65), (65, 65), (7, 900)])
 def test_two_steps_per_launch(shape, ybc):
     """Bit-equal to single steps for every count, eager, observed and recorded;
     the scratch buffer holds the state before the last step."""
