@@ -64,6 +64,26 @@ struct CGeom {
   unsigned pitch;   // rows of a plane (ly rounded up to 32)
   long long cs;     // NC * pitch
 };
+__host__ __device__ __forceinline__ CGeom coeff_geom(const Geom& g) {
+  CGeom c{};  // what the site kernels use
+  c.lx = g.lx;
+  c.ly = g.ly;
+  c.periodic = !g.walls;
+  c.pitch = unsigned((g.ly + 31) / 32 * 32);
+  c.cs = (long long)NC * c.pitch;
+  return c;
+}
+
+// A state buffer in this form starts with a header of 256 bytes: the word that
+// names the form, and in the second and third double the wall temperatures of
+// kFormCoeffWalls.
+constexpr int kDataOffset = 32;  // doubles
+__host__ __device__ __forceinline__ const double* coeffs(const void* buf) {
+  return static_cast<const double*>(buf) + kDataOffset;
+}
+__host__ __device__ __forceinline__ double* coeffs(void* buf) {
+  return static_cast<double*>(buf) + kDataOffset;
+}
 
 // Collision parameters in hop units (velocities over r, temperatures over r^2).
 struct CPhys {
@@ -271,6 +291,51 @@ __device__ __forceinline__ void project_site(const double (&v)[Q], double (&m)[N
   if constexpr (ex > -3) project_site<K, ex - 1>(v, m);
 }
 
+// One site of a buffer (the readers' access; a wave's is in d2q37_coeff.hip).
+typedef double v2d __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void load_coeffs(const double* __restrict__ src, const CGeom& g, int x,
+                                            int y, double (&b)[NC]) {
+  const double* col = src + x * g.cs;
+#pragma unroll
+  for (int m = 0; m < NC / 2; ++m) {
+    const v2d d = *reinterpret_cast<const v2d*>(col + 2 * m * (long long)g.pitch + 2 * y);
+    b[2 * m] = d.x;
+    b[2 * m + 1] = d.y;
+  }
+  b[NC - 1] = col[(NC - 1) * (long long)g.pitch + y];
+}
+
+// fn(l, f_l) for the 37 populations of a site, one e_x group after the other
+template <class Fn, int ex = 3>
+__device__ __forceinline__ void each_population(const double (&c)[NC], const Fn& fn) {
+  Group f;
+  expand_group<Forward, ex>(c, f);
+  fn(label(ex, 0), f.zero);
+#pragma unroll
+  for (int k = 1; k <= reach(ex); ++k) {
+    fn(label(ex, -k), f.minus[k - 1]);
+    fn(label(ex, k), f.plus[k - 1]);
+  }
+  if constexpr (ex > -3) each_population<Fn, ex - 1>(c, fn);
+}
+
+// A site that bc was applied to after its coefficients were stored (a scratch
+// buffer): the temperature of its wall.
+__device__ __forceinline__ bool walls_since(const void* buf, const Geom& g, int y, double& th) {
+  if (*static_cast<const unsigned*>(buf) != unsigned(kFormCoeffWalls)) return false;
+  th = static_cast<const double*>(buf)[y < 3 ? 1 : 2];
+  return y < 3 || y >= g.ly - 3;
+}
+
+// The 37 populations of a site of a scratch buffer that holds coefficients.
+__device__ __forceinline__ void scratch_site(const void* buf, const Geom& g, int x, int y,
+                                             double (&v)[Q]) {
+  double c[NC], th;
+  load_coeffs(coeffs(buf), coeff_geom(g), x, y, c);
+  expand_site<Forward>(c, v);
+  if (walls_since(buf, g, y, th)) wall_site<double>(v, y, g.ly, th, th, 0.0);
+}
+
 // Powers of r, and the moments of w: sum w e_x^2 = r^-2, sum w e_x^4 = 3 r^-4,
 // sum w e_x^2 e_y^2 = r^-4, ...
 constexpr double kR2 = R * R, kR4 = kR2 * kR2, kR6 = kR4 * kR2, kR8 = kR4 * kR4;
@@ -433,3 +498,5 @@ __device__ __forceinline__ void wall_adjoint(double (&C)[NC], const WallTable& w
 }
 
 }  // namespace d2q37
+
+#pragma clang fp contract(fast)  // as the rest of the code is compiled

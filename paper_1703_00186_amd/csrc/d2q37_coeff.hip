@@ -35,11 +35,12 @@
 #include "d2q37_launch.h"
 #include "d2q37_tiles.h"
 
+#pragma clang fp contract(off)  // as in d2q37_coeff.h
+
 namespace d2q37 {
 
 namespace {
 
-typedef double v2d __attribute__((ext_vector_type(2)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
@@ -570,17 +571,6 @@ __global__ __launch_bounds__(64 * kWaves, (kOccupancy<TX, kAhead>)) void k_coeff
 // Site kernels: one thread per site.
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ void load_coeffs(const double* __restrict__ src, const CGeom& g, int x,
-                                            int y, double (&b)[NC]) {
-  const double* col = src + x * g.cs;
-#pragma unroll
-  for (int m = 0; m < NC / 2; ++m) {
-    const v2d d = *reinterpret_cast<const v2d*>(col + 2 * m * (long long)g.pitch + 2 * y);
-    b[2 * m] = d.x;
-    b[2 * m + 1] = d.y;
-  }
-  b[NC - 1] = col[(NC - 1) * (long long)g.pitch + y];
-}
 __device__ __forceinline__ void store_coeffs(double* __restrict__ dst, const CGeom& g, int x,
                                              int y, const double (&b)[NC]) {
   double* col = dst + x * g.cs;
@@ -697,22 +687,6 @@ __global__ __launch_bounds__(kThreads) void k_coeff_expand(const double* __restr
       for (int l = 0; l < Q; ++l) dst[l * gf.ps + s] = v[l];
     }
   }
-}
-
-// The 37 populations in compact form [37][lx][ly].
-__global__ __launch_bounds__(kThreads) void k_coeff_pack(const double* __restrict__ src,
-                                                         double* __restrict__ out, CGeom g,
-                                                         int by, int bx, int nty, unsigned nb,
-                                                         const unsigned* guard) {
-  if (other_form(guard, kFormCoeff)) return;
-  int x, y;
-  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
-  double b[NC], v[Q];
-  load_coeffs(src, g, x, y, b);
-  expand_site<Forward>(b, v);
-  const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + y;
-#pragma unroll
-  for (int l = 0; l < Q; ++l) __builtin_nontemporal_store(v[l], &out[l * S2 + s]);
 }
 
 // Eq. (2) fields: twelve coefficients in, four values out (128 bytes per site).
@@ -945,20 +919,12 @@ namespace {
 
 long long state_bytes(const CGeom& g) { return g.lx * g.cs * (long long)sizeof(double); }
 CGeom make_cgeom(const Geom& g, long long cached_from = kStepCachedFrom) {
-  CGeom c;
-  c.lx = g.lx;
-  c.ly = g.ly;
-  c.periodic = !g.walls;
+  CGeom c = coeff_geom(g);
   c.nw = (g.ly + kRows - 1) / kRows;
-  c.pitch = unsigned((g.ly + 31) / 32 * 32);
-  c.cs = (long long)NC * c.pitch;
   c.stream = streams_output(state_bytes(c), cached_from, kCachedTo);
   return c;
 }
 
-constexpr int kDataOffset = 32;  // doubles
-const double* coeffs(const void* buf) { return static_cast<const double*>(buf) + kDataOffset; }
-double* coeffs(void* buf) { return static_cast<double*>(buf) + kDataOffset; }
 unsigned* word_of(void* buf) { return static_cast<unsigned*>(buf); }
 // the word to check where the host does not know the form
 const unsigned* guard_of(const void* buf, const Geom& g) {
@@ -1054,13 +1020,6 @@ hipError_t launch_coeff_expand(const void* src, void* dst, const Geom& gf, hipSt
   const Tiling t = make_tiling(gf.lx, gf.ly);
   hipLaunchKernelGGL(k_coeff_expand, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src),
                      static_cast<double*>(dst), make_cgeom(gf), gf, t.by, t.bx, t.nty, t.nb);
-  return hipGetLastError();
-}
-
-hipError_t launch_coeff_pack(const void* src, double* out, const Geom& gf, hipStream_t s) {
-  const Tiling t = make_tiling(gf.lx, gf.ly);
-  hipLaunchKernelGGL(k_coeff_pack, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src), out,
-                     make_cgeom(gf), t.by, t.bx, t.nty, t.nb, guard_of(src, gf));
   return hipGetLastError();
 }
 

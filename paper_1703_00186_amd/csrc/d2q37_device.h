@@ -53,8 +53,16 @@ struct Geom {
 // form for graphs recorded before the state was replaced; the host passes
 // what it knows in Geom::form, kFormUnknown where a graph may have run.
 // kFormTwice asks launch_fused for two steps (from the coefficients where the
-// step has that form, else from the populations).
-enum Form : int { kFormFull = 0, kFormCoeff = 1, kFormUnknown = 2, kFormTwice = 3 };
+// step has that form, else from the populations).  kFormCoeffWalls: a word
+// only, coefficients of which the walls were applied to afterwards (a scratch
+// buffer after bc; the wall temperatures follow in the buffer's header).
+enum Form : int {
+  kFormFull = 0,
+  kFormCoeff = 1,
+  kFormUnknown = 2,
+  kFormTwice = 3,
+  kFormCoeffWalls = 4
+};
 
 constexpr int NC = 15;  // coefficients of a site: degree i + j <= 4
 

@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "d2q37_coeff.h"
 #include "d2q37_launch.h"
 #include "d2q37_tiles.h"
 
@@ -61,6 +62,12 @@ __device__ __forceinline__ void store_site(S* __restrict__ dst, const Geom& g, l
                                            const A (&f)[Q]) {
 #pragma unroll
   for (int l = 0; l < Q; ++l) store_out<kStream>(S(f[l]), &dst[l * g.ps + site]);
+}
+
+// Names the form of an FP64 buffer that a kernel fills with populations.
+template <class S>
+__device__ __forceinline__ void set_full(S* buf) {
+  if constexpr (std::is_same<S, double>::value) set_form(buf, kFormFull);
 }
 
 // Accumulation-type tags of the local-reference FP32 forms (populations
@@ -126,6 +133,7 @@ __global__ __launch_bounds__(kThreads) void k_fused(const S* __restrict__ src,
                                                     S* __restrict__ dst, Geom g, Phys P,
                                                     double* __restrict__ tape, int by, int bx,
                                                     int nty, unsigned nb) {
+  set_full(dst);
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
   const long long site = padded<S>(g, x + HX, y + g.hy);
@@ -346,6 +354,7 @@ __global__ __launch_bounds__(128 * kPairCols, 2) void k_fused_pair(const S* __re
                                                                   Phys P, int windows, int chunk,
                                                                   unsigned nb) {
   __shared__ __align__(16) S ring[ring_start(4)];
+  set_full(dst);
   const unsigned t = tile_index(nb);
   const int xa = int(t / unsigned(windows)) * chunk, xb = min(xa + chunk, g.lx);
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
@@ -435,6 +444,7 @@ template <class S>
 __global__ __launch_bounds__(kThreads) void k_propagate(const S* __restrict__ src,
                                                         S* __restrict__ dst, Geom g, int by,
                                                         int bx, int nty, unsigned nb) {
+  set_full(dst);
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
   const long long site = padded<S>(g, x + HX, y + g.hy);
@@ -443,22 +453,50 @@ __global__ __launch_bounds__(kThreads) void k_propagate(const S* __restrict__ sr
     __builtin_nontemporal_store(src[l * g.ps + site - EX[l] * g.cs - EY[l]], &dst[l * g.ps + site]);
 }
 
+// A site of the scratch buffer: populations that were propagated there, or the
+// state before a fused step in the form that step read.
+template <class S, class A>
+__device__ __forceinline__ void load_scratch(const S* __restrict__ src, const Geom& g, int x,
+                                             int y, const unsigned* word, A (&f)[Q]) {
+  if constexpr (std::is_same<S, double>::value) {
+    if (holds_coeffs(word)) {
+      scratch_site(src, g, x, y, f);
+      return;
+    }
+  }
+  load_site<S, A>(src, g, padded<S>(g, x + HX, y + g.hy), f);
+}
+
 template <class S, class A, bool kReg>
 __global__ __launch_bounds__(kThreads) void k_collide(const S* __restrict__ src,
                                                       S* __restrict__ dst, Geom g, Phys P,
-                                                      int by, int bx, int nty, unsigned nb) {
+                                                      int by, int bx, int nty, unsigned nb,
+                                                      const unsigned* word) {
+  set_full(dst);
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
   const long long site = padded<S>(g, x + HX, y + g.hy);
   A f[Q];
-  load_site<S, A>(src, g, site, f);
+  load_scratch<S, A>(src, g, x, y, word, f);
   collide<A, kReg>(f, P);
   store_site<S, A>(dst, g, site, f);
 }
 
-// bc on the six wall rows, in place; one thread per (x, wall row).
+// bc on the six wall rows, in place; one thread per (x, wall row).  In a buffer
+// of coefficients there is no place for the walls' populations: it is marked,
+// and its readers apply the walls to what they rebuild.
 template <class S>
-__global__ __launch_bounds__(kThreads) void k_bc(S* __restrict__ buf, Geom g, Phys P) {
+__global__ __launch_bounds__(kThreads) void k_bc(S* buf, Geom g, Phys P, unsigned* word) {
+  if constexpr (std::is_same<S, double>::value) {
+    if (holds_coeffs(word)) {
+      if (blockIdx.x == 0 && threadIdx.x == 0) {
+        buf[1] = P.th_bottom;
+        buf[2] = P.th_top;
+        *word = unsigned(kFormCoeffWalls);
+      }
+      return;
+    }
+  }
   const int i = blockIdx.x * kThreads + threadIdx.x;
   if (i >= g.lx * 6) return;
   const int x = i / 6, r = i % 6;
@@ -620,14 +658,41 @@ __global__ __launch_bounds__(kThreads) void k_check(const S* __restrict__ src,
 // go to workgroups of their own (copy_grid).
 constexpr int kBatch = 8;
 
+__device__ __forceinline__ void pack_coeffs(const double* __restrict__ buf,
+                                            double* __restrict__ out, const Geom& g, int x,
+                                            int y) {
+  const long long S2 = (long long)g.lx * g.ly;
+  out += (long long)x * g.ly + y;
+  double c[NC], th;
+  load_coeffs(coeffs(buf), coeff_geom(g), x, y, c);
+  each_population(c, [&](int l, double v) { __builtin_nontemporal_store(v, &out[l * S2]); });
+  if (walls_since(buf, g, y, th)) {  // as wall_site, one population at a time
+    double sk = 0.0, vk = 0.0;
+#pragma unroll 1
+    for (int l = 0; l < Q; ++l)
+      if (y - EY[l] >= 0 && y - EY[l] < g.ly) {
+        sk += out[l * S2];
+        vk += wall_feq(l, th);
+      }
+#pragma unroll 1
+    for (int l = 0; l < Q; ++l)
+      if (y - EY[l] < 0 || y - EY[l] >= g.ly) out[l * S2] = sk / vk * wall_feq(l, th);
+  }
+}
+
 template <class S>
 __global__ __launch_bounds__(kThreads) void k_pack(const S* __restrict__ padded_buf,
                                                    S* __restrict__ compact, Geom g, int by,
                                                    int bx, int nty, unsigned nb,
-                                                   const unsigned* guard) {
-  if (other_form(guard, kFormFull)) return;
+                                                   const unsigned* word) {
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
+  if constexpr (std::is_same<S, double>::value) {
+    if (holds_coeffs(word)) {  // all planes at once
+      if (blockIdx.y == 0) pack_coeffs(padded_buf, compact, g, x, y);
+      return;
+    }
+  }
   const S* from = padded_buf + padded<S>(g, x + HX, y + g.hy);
   S* to = compact + (long long)x * g.ly + y;
   const long long S2 = (long long)g.lx * g.ly;
@@ -669,10 +734,15 @@ __global__ __launch_bounds__(kThreads) void k_populations_f64(const S* __restric
                                                               double* __restrict__ out, Geom g,
                                                               double rho_ref, int by, int bx,
                                                               int nty, unsigned nb,
-                                                              const unsigned* guard) {
-  if (other_form(guard, kFormFull)) return;
+                                                              const unsigned* word) {
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
+  if constexpr (std::is_same<S, double>::value) {
+    if (holds_coeffs(word)) {
+      pack_coeffs(padded_buf, out, g, x, y);
+      return;
+    }
+  }
   const long long site = padded<S>(g, x + HX, y + g.hy);
   const long long S2 = (long long)g.lx * g.ly, s = (long long)x * g.ly + y;
   double f[Q];
@@ -1070,6 +1140,11 @@ static const unsigned* guard_of(const void* buf, const Geom& g) {
   return g.form == kFormUnknown ? static_cast<const unsigned*>(buf) : nullptr;
 }
 
+// the word of a buffer that may hold coefficients
+static const unsigned* word_of(const void* buf, const Geom& g) {
+  return g.form == kFormFull ? nullptr : static_cast<const unsigned*>(buf);
+}
+
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
   const long long n = (long long)(bytes / 4);
   if (n == 0) return hipSuccess;
@@ -1167,7 +1242,8 @@ hipError_t launch_bc(void* buf, const Geom& g, const Phys& p, int prec, hipStrea
   const unsigned grid = grid_1d(6LL * g.lx);
   return by_precision(prec, [&](auto sv, auto) {
     using S = decltype(sv);
-    hipLaunchKernelGGL(k_bc<S>, dim3(grid), dim3(kThreads), 0, s, static_cast<S*>(buf), g, p);
+    hipLaunchKernelGGL(k_bc<S>, dim3(grid), dim3(kThreads), 0, s, static_cast<S*>(buf), g, p,
+                       g.form == kFormFull ? nullptr : static_cast<unsigned*>(buf));
   });
 }
 
@@ -1183,10 +1259,10 @@ hipError_t launch_collide(const void* src, void* dst, const Geom& g, const Phys&
       return;  // the local-reference form has no split collide (lb_api rejects it)
     else if (regularize)
       hipLaunchKernelGGL((k_collide<S, A, true>), dim3(t.nb), dim3(kThreads), 0, s, a, b, g, p,
-                         t.by, t.bx, t.nty, t.nb);
+                         t.by, t.bx, t.nty, t.nb, word_of(src, g));
     else
       hipLaunchKernelGGL((k_collide<S, A, false>), dim3(t.nb), dim3(kThreads), 0, s, a, b, g,
-                         p, t.by, t.bx, t.nty, t.nb);
+                         p, t.by, t.bx, t.nty, t.nb, word_of(src, g));
   });
 }
 
@@ -1229,16 +1305,12 @@ static dim3 copy_grid(const Tiling& t, const Geom& g) {
 
 hipError_t launch_pack(const void* padded_buf, void* compact, const Geom& g, int prec,
                        hipStream_t s) {
-  if (g.form != kFormFull) {
-    const hipError_t e = launch_coeff_pack(padded_buf, static_cast<double*>(compact), g, s);
-    if (e != hipSuccess || g.form == kFormCoeff) return e;
-  }
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto) {
     using S = decltype(sv);
     hipLaunchKernelGGL(k_pack<S>, copy_grid(t, g), dim3(kThreads), 0, s,
                        static_cast<const S*>(padded_buf), static_cast<S*>(compact), g, t.by, t.bx,
-                       t.nty, t.nb, guard_of(padded_buf, g));
+                       t.nty, t.nb, word_of(padded_buf, g));
   });
 }
 
@@ -1256,16 +1328,12 @@ hipError_t launch_unpack(const void* compact, void* padded_buf, const Geom& g, i
 
 hipError_t launch_populations_f64(const void* padded_buf, double* out, const Geom& g,
                                   const Phys& p, int prec, hipStream_t s) {
-  if (g.form != kFormFull) {
-    const hipError_t e = launch_coeff_pack(padded_buf, out, g, s);
-    if (e != hipSuccess || g.form == kFormCoeff) return e;
-  }
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto av) {
     using S = decltype(sv);
     hipLaunchKernelGGL((k_populations_f64<S, decltype(av)>), dim3(t.nb), dim3(kThreads), 0, s,
                        static_cast<const S*>(padded_buf), out, g, p.rho_ref, t.by, t.bx, t.nty, t.nb,
-                       guard_of(padded_buf, g));
+                       word_of(padded_buf, g));
   });
 }
 

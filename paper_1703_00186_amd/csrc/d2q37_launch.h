@@ -5,7 +5,7 @@
 // kFormUnknown the kernels of both forms are enqueued and the device word
 // decides.  launch_init_feq writes the form it names, launch_fused always the
 // coefficient form for regularized FP64 and the populations otherwise; the
-// split stages, launch_bc and launch_collide work on populations.
+// split stages write populations (launch_bc marks coefficients instead).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -163,7 +163,6 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& g, const Ph
 hipError_t launch_coeff_init(void* dst, const double* rho, const double* ux, const double* uy,
                              const double* T, const Geom& g, hipStream_t s);
 hipError_t launch_coeff_expand(const void* src, void* dst, const Geom& g, hipStream_t s);
-hipError_t launch_coeff_pack(const void* src, double* out, const Geom& g, hipStream_t s);
 hipError_t launch_coeff_moments(const void* src, double* rho, double* ux, double* uy, double* T,
                                 const Geom& g, hipStream_t s);
 hipError_t launch_coeff_check(const void* src, unsigned* flag, const Geom& g, hipStream_t s);

@@ -105,6 +105,11 @@ __device__ __forceinline__ double block_sum(double v) {
 __device__ __forceinline__ bool other_form(const unsigned* word, Form f) {
   return word && *word != unsigned(f);
 }
+// Whether the buffer of this word (null: known to hold populations) holds
+// coefficients.
+__device__ __forceinline__ bool holds_coeffs(const unsigned* word) {
+  return word && (*word == unsigned(kFormCoeff) || *word == unsigned(kFormCoeffWalls));
+}
 __device__ __forceinline__ void set_form(void* buf, Form f) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
     *static_cast<unsigned*>(buf) = unsigned(f);

@@ -17,8 +17,11 @@
 // sums; these kernels are the alternatives that choice is measured against.
 #include <hip/hip_runtime.h>
 
-#include "d2q37_device.h"
+#include <type_traits>
+
+#include "d2q37_coeff.h"
 #include "d2q37_launch.h"
+#include "d2q37_tiles.h"
 
 namespace d2q37 {
 namespace {
@@ -45,6 +48,7 @@ __global__ __launch_bounds__(kVThreads) void k_propagate_lds(const S* __restrict
                                                              S* __restrict__ dst, Geom g,
                                                              int nty) {
   __shared__ S win[kLdsGroup * kLdsRows];
+  if constexpr (std::is_same<S, double>::value) set_form(dst, kFormFull);
   const int x = int(blockIdx.x) / nty;
   const int y0 = (int(blockIdx.x) % nty) * kVThreads;
   const int n = min(kVThreads, g.ly - y0);
@@ -117,6 +121,7 @@ __global__ __launch_bounds__(kVThreads) void k_propagate_wide(const S* __restric
                                                               int nty) {
   using W = Wide<S>;
   constexpr int V = W::V;
+  if constexpr (std::is_same<S, double>::value) set_form(dst, kFormFull);
   const int x = int(blockIdx.x) / nty;
   const int y = (int(blockIdx.x) % nty) * (kVThreads * V) + V * int(threadIdx.x);
   if (y >= g.ly) return;
@@ -215,12 +220,33 @@ __device__ __forceinline__ double eq_row(int row, double rho, const double (&hx)
   return row == 3 ? 0.0 : rho * hx[kRowP[row]] * hy[kRowQ[row]];
 }
 
+// The same from coefficients, which the scratch buffer holds after a fused step:
+// launched beside the other where the host does not know what it holds.
+template <bool kReg>
+__global__ __launch_bounds__(kVThreads) void k_collide_coeffs(const double* __restrict__ src,
+                                                              double* __restrict__ dst, Geom g,
+                                                              Phys P, int nyb,
+                                                              const unsigned* word) {
+  if (!holds_coeffs(word)) return;
+  const int x = int(blockIdx.x) / nyb, y = int(blockIdx.x) % nyb * kVThreads + int(threadIdx.x);
+  if (y >= g.ly) return;
+  double f[Q];
+  scratch_site(src, g, x, y, f);
+  collide<double, kReg>(f, P);
+  double* to = dst + (long long)(x + HX) * g.cs + y + g.hy;
+#pragma unroll
+  for (int l = 0; l < Q; ++l) to[l * g.ps] = f[l];
+}
+
 constexpr int kSets = 2;  // site sets per round (divides 4; 2 keeps 3 waves per SIMD)
 
 template <bool kReg>
 __global__ __launch_bounds__(kVThreads) void k_collide_mfma(const double* __restrict__ src,
                                                             double* __restrict__ dst, Geom g,
-                                                            Phys P, int nyb) {
+                                                            Phys P, int nyb,
+                                                            const unsigned* word) {
+  set_form(dst, kFormFull);
+  if (holds_coeffs(word)) return;
   const int lane = threadIdx.x & 63;
   const int wave = int(blockIdx.x) * (kVThreads / 64) + int(threadIdx.x >> 6);
   const int x = wave / nyb, yb = wave % nyb;
@@ -353,11 +379,15 @@ hipError_t launch_collide_mfma(const void* src, void* dst, const Geom& g, const 
   const unsigned grid = blocks((long long)g.lx * nyb, kVThreads / 64);
   const double* a = static_cast<const double*>(src);
   double* b = static_cast<double*>(dst);
-  if (regularize)
-    hipLaunchKernelGGL(k_collide_mfma<true>, dim3(grid), dim3(kVThreads), 0, s, a, b, g, p, nyb);
-  else
-    hipLaunchKernelGGL(k_collide_mfma<false>, dim3(grid), dim3(kVThreads), 0, s, a, b, g, p,
-                       nyb);
+  const unsigned* word = g.form == kFormFull ? nullptr : static_cast<const unsigned*>(src);
+  hipLaunchKernelGGL(regularize ? k_collide_mfma<true> : k_collide_mfma<false>, dim3(grid),
+                     dim3(kVThreads), 0, s, a, b, g, p, nyb, word);
+  if (word) {
+    const int nty = int(blocks(g.ly, kVThreads));
+    hipLaunchKernelGGL(regularize ? k_collide_coeffs<true> : k_collide_coeffs<false>,
+                       dim3(unsigned(g.lx) * unsigned(nty)), dim3(kVThreads), 0, s, a, b, g, p, nty,
+                       word);
+  }
   return hipGetLastError();
 }
 

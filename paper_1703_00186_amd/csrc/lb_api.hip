@@ -27,7 +27,8 @@ struct lb_ctx {
   double* partials;
   double* obs;  // observable scratch (chunk partials | profiles | scalars)
   unsigned int* flag;
-  int a_form, b_form;  // storage form of A and B (d2q37::Form)
+  int a_form;          // storage form of A (d2q37::Form); B's is in its first
+                       // word, which every kernel that fills it writes
   bool captured;       // a graph recorded on this context may have run: the
                        // forms are then known only to the device
   bool halos_valid;
@@ -174,7 +175,6 @@ int full_state(lb_ctx* c) {
            "expand state");
     std::swap(c->A, c->B);
     c->a_form = d2q37::kFormFull;
-    c->b_form = d2q37::kFormCoeff;
     c->halos_valid = true;
     return LB_OK;
   }
@@ -183,36 +183,14 @@ int full_state(lb_ctx* c) {
          "expand state");
   LB_HIP(d2q37::launch_unpack(c->B, c->A, c->g, c->prec, c->stream), "expand state");
   c->a_form = d2q37::kFormFull;
-  c->b_form = d2q37::kFormUnknown;
   c->halos_valid = false;
   return LB_OK;
 }
 
-// Names a buffer that is about to be overwritten with populations.
-int mark_full(lb_ctx* c, char* buf, int& form) {
-  if (form != d2q37::kFormFull)
-    LB_HIP(d2q37::launch_zero(buf, sizeof(unsigned), c->stream), "mark form");
-  form = d2q37::kFormFull;
-  return LB_OK;
-}
-
-// The scratch B as populations, for lb_bc and lb_collide after a fused step
-// (which leaves the previous state there, in its form).  keep_a: A is still
-// needed; the coefficients of both then fit beside each other.
-int full_scratch(lb_ctx* c, bool keep_a) {
-  if (c->b_form == d2q37::kFormFull) return LB_OK;
-  if (c->b_form == d2q37::kFormCoeff && (!keep_a || c->a_form == d2q37::kFormCoeff)) {
-    const size_t n = buffer_bytes(c->g, c->prec) / (2 * kAlign) * kAlign;
-    char* spare = keep_a ? c->A + n : c->A;
-    LB_HIP(hipMemcpyAsync(spare, c->B, n, hipMemcpyDeviceToDevice, c->stream), "expand scratch");
-    LB_HIP(d2q37::launch_unpack(spare, c->B, with_form(c->g, d2q37::kFormCoeff), c->prec,
-                                c->stream),
-           "expand scratch");
-  } else {
-    LB_HIP(d2q37::launch_zero(c->B, sizeof(unsigned), c->stream), "mark form");
-  }
-  c->b_form = d2q37::kFormFull;
-  return LB_OK;
+// The form of the scratch B: only its word tells what it holds (the state before
+// a fused step in that step's form, or propagated populations).
+int scratch_form(const lb_ctx* c) {
+  return c->prec == LB_FP64 ? d2q37::kFormUnknown : d2q37::kFormFull;
 }
 
 // The split stages, with the alternative kernel the context's kernel value
@@ -227,10 +205,12 @@ hipError_t propagate_stage(lb_ctx* c) {
   return d2q37::launch_propagate(c->A, c->B, c->g, c->prec, c->stream);
 }
 
-hipError_t collide_stage(lb_ctx* c) {
+// form: of the scratch buffer, where the step that filled it is not known
+hipError_t collide_stage(lb_ctx* c, int form = d2q37::kFormFull) {
+  const Geom g = with_form(c->g, form);
   if (c->par.kernel == LB_KERNEL_SPLIT_MFMA)
-    return d2q37::launch_collide_mfma(c->B, c->A, c->g, c->p, c->par.regularize, c->stream);
-  return d2q37::launch_collide(c->B, c->A, c->g, c->p, c->prec, c->par.regularize, c->stream);
+    return d2q37::launch_collide_mfma(c->B, c->A, g, c->p, c->par.regularize, c->stream);
+  return d2q37::launch_collide(c->B, c->A, g, c->p, c->prec, c->par.regularize, c->stream);
 }
 
 int no_split_stage(lb_ctx* ctx, const char* what) {
@@ -279,7 +259,7 @@ int enter(lb_ctx* ctx) {
   if (hipStreamIsCapturing(ctx->stream, &status) != hipSuccess) (void)hipGetLastError();
   if (status == hipStreamCaptureStatusActive) ctx->captured = true;
   if (ctx->captured && ctx->prec == LB_FP64)
-    ctx->a_form = ctx->b_form = d2q37::kFormUnknown;
+    ctx->a_form = d2q37::kFormUnknown;
   return LB_OK;
 }
 
@@ -321,13 +301,10 @@ int one_step(lb_ctx* c, double* tape) {
                                c->stream),
            "fused step");
     std::swap(c->A, c->B);
-    c->b_form = c->a_form;
     c->a_form = d2q37::kFormCoeff;
     c->halos_valid = false;
   } else if (fused) {
     int rc = full_state(c);
-    if (rc) return rc;
-    rc = mark_full(c, c->B, c->b_form);
     if (rc) return rc;
     if (!c->halos_valid || !c->g.walls) {
       rc = do_halo(c);
@@ -342,8 +319,6 @@ int one_step(lb_ctx* c, double* tape) {
     c->halos_valid = c->g.walls;
   } else {
     int rc = full_state(c);
-    if (rc) return rc;
-    rc = mark_full(c, c->B, c->b_form);
     if (rc) return rc;
     rc = do_halo(c);
     if (rc) return rc;
@@ -362,18 +337,16 @@ int one_step(lb_ctx* c, double* tape) {
 // Two fused steps in one launch, from the form the step leaves behind.
 int two_steps(lb_ctx* c) {
   if (!coeff_step(c)) {
-    int rc = mark_full(c, c->B, c->b_form);
-    if (rc == LB_OK && (!c->halos_valid || !c->g.walls)) rc = do_halo(c);
-    if (rc) return rc;
+    if (!c->halos_valid || !c->g.walls) {
+      const int rc = do_halo(c);
+      if (rc) return rc;
+    }
   }
   LB_HIP(d2q37::launch_fused(c->A, c->B, with_form(c->g, d2q37::kFormTwice), c->p, c->prec,
                              c->par.regularize, nullptr, c->stream),
          "fused steps");
   std::swap(c->A, c->B);
-  if (coeff_step(c))
-    c->b_form = d2q37::kFormCoeff;
-  else
-    c->halos_valid = c->g.walls;
+  if (!coeff_step(c)) c->halos_valid = c->g.walls;
   return LB_OK;
 }
 
@@ -520,14 +493,13 @@ int lb_init(const lb_lattice* lat, const lb_params* par, void* workspace, size_t
   c->halos_valid = false;
   c->steps_since_check = 0;
   c->captured = false;
-  c->a_form = c->b_form = d2q37::kFormFull;
+  c->a_form = d2q37::kFormFull;
   hipError_t e = hipSuccess;
   if (c->prec == LB_FP64 && par->regularize && par->kernel == LB_KERNEL_FUSED) {
     // the form the steps work on; it has no halos and no padding that is read
     c->a_form = d2q37::kFormCoeff;
     e = d2q37::launch_init_feq(c->A, rho0, ux0, uy0, T0, with_form(c->g, c->a_form), c->p, c->prec,
                                c->stream);
-    if (e == hipSuccess) e = d2q37::launch_zero(c->B, sizeof(unsigned), c->stream);
     if (e != hipSuccess) {
       delete c;
       return hip_fail(e, "lb_init");
@@ -635,8 +607,6 @@ int lb_propagate(lb_ctx* ctx) {
   if (rc) return rc;
   rc = full_state(ctx);
   if (rc) return rc;
-  rc = mark_full(ctx, ctx->B, ctx->b_form);
-  if (rc) return rc;
   LB_HIP(propagate_stage(ctx), "propagate");
   return LB_OK;
 }
@@ -646,9 +616,7 @@ int lb_bc(lb_ctx* ctx) {
   if (rc) return rc;
   rc = no_split_stage(ctx, "lb_bc");
   if (rc) return rc;
-  rc = full_scratch(ctx, true);
-  if (rc) return rc;
-  LB_HIP(d2q37::launch_bc(ctx->B, ctx->g, ctx->p, ctx->prec, ctx->stream), "bc");
+  LB_HIP(d2q37::launch_bc(ctx->B, with_form(ctx->g, scratch_form(ctx)), ctx->p, ctx->prec, ctx->stream), "bc");
   return LB_OK;
 }
 
@@ -657,11 +625,8 @@ int lb_collide(lb_ctx* ctx) {
   if (rc) return rc;
   rc = no_split_stage(ctx, "lb_collide");
   if (rc) return rc;
-  rc = full_scratch(ctx, false);
-  if (rc) return rc;
-  rc = mark_full(ctx, ctx->A, ctx->a_form);
-  if (rc) return rc;
-  LB_HIP(collide_stage(ctx), "collide");
+  LB_HIP(collide_stage(ctx, scratch_form(ctx)), "collide");
+  ctx->a_form = d2q37::kFormFull;
   ctx->halos_valid = false;
   return LB_OK;
 }
@@ -672,7 +637,7 @@ int lb_get_scratch(lb_ctx* ctx, void* f) {
   rc = no_split_stage(ctx, "lb_get_scratch");
   if (rc) return rc;
   if (!f) return fail(LB_E_ARG, "f is NULL%s");
-  LB_HIP(d2q37::launch_pack(ctx->B, f, with_form(ctx->g, ctx->b_form), ctx->prec, ctx->stream), "get_scratch");
+  LB_HIP(d2q37::launch_pack(ctx->B, f, with_form(ctx->g, scratch_form(ctx)), ctx->prec, ctx->stream), "get_scratch");
   return LB_OK;
 }
 
@@ -683,7 +648,6 @@ int lb_set_scratch(lb_ctx* ctx, const void* f) {
   if (rc) return rc;
   if (!f) return fail(LB_E_ARG, "f is NULL%s");
   LB_HIP(d2q37::launch_unpack(f, ctx->B, ctx->g, ctx->prec, ctx->stream), "set_scratch");
-  ctx->b_form = d2q37::kFormFull;
   return LB_OK;
 }
 

@@ -1,0 +1,109 @@
+"""Which form a state buffer is in, across calls and recorded graphs.
+
+A recorded graph may run at any time on the workspace it was recorded on, also
+after the lattice was restarted, given other parameters or another state; so
+every call has to find the state and the scratch buffer in whatever form they
+are then.  Each test compares with a lattice that makes the same steps eagerly,
+or with the CPU oracle.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+from helpers import gpu_available
+from paper_1703_00186_amd import workload
+
+pytestmark = pytest.mark.gpu
+
+if gpu_available():
+    import torch
+    from paper_1703_00186_amd.lb import LB
+
+G = (1e-3, -2e-3)
+LX, LY = 50, 70  # ragged tiles, two waves of rows
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.detach().cpu().numpy()
+
+
+def fields(lx=LX, ly=LY, seed=21):
+    return workload.rt_fields(lx, ly, seed=seed)[:4]
+
+
+def make(lx=LX, ly=LY, **kw):
+    return LB(lx, ly, *fields(lx, ly), g=G, **kw)
+
+
+def params(**kw):
+    base = dict(tau=0.7, gx=G[0], gy=G[1], t_bottom=1.5, t_top=0.5, regularize=1, ybc=0)
+    base.update(kw)
+    return oracle.Params(**base)
+
+
+def noisy(lb):
+    noise = 1 + 1e-3 * torch.rand(lb.state_shape, dtype=torch.float64, device="cuda")
+    return lb.get_state() * noise
+
+
+def close(x, y):
+    """The same values through other sums: some hundred FP64 roundings of terms
+    no larger than the largest value."""
+    x, y = host(x), y if isinstance(y, np.ndarray) else host(y)
+    return np.abs(x - y).max() <= 1e-13 * np.abs(y).max()
+
+
+# -- the scratch buffer ----------------------------------------------------------
+
+KW = [dict(), dict(layout="soa"), dict(kernel="split_mfma"), dict(regularize=0)]
+
+
+@pytest.mark.parametrize("kw", KW)
+@pytest.mark.parametrize("recorded", [False, True])
+def test_scratch_after_fused_steps(recorded, kw):
+    """After fused steps the scratch buffer holds the state before the last
+    one: get_scratch, bc and collide find it, whatever happened to the state
+    or was recorded in between."""
+    par = {k: kw[k] for k in ("kernel", "regularize") if k in kw}
+    for replace in (False, True):
+        a = make(layout=kw.get("layout", "column"))
+        if recorded:
+            a.capture(2)
+        a.step(2)
+        before = host(a.get_state())
+        a.step(1)
+        a.set_params(**par)
+        if replace:
+            a.set_state(noisy(a))
+        state = a.get_state()
+        assert np.array_equal(host(a.get_scratch()), before)
+        a.bc()
+        ref = oracle.bc(before, 1.5, 0.5)
+        assert close(a.get_scratch(), ref)
+        a.bc()  # once more: nothing changes
+        assert close(a.get_scratch(), ref)
+        assert torch.equal(a.get_state(), state)
+        a.collide()  # of the scratch buffer, walls included
+        assert close(a.get_scratch(), ref)
+        p = params(regularize=kw.get("regularize", 1))
+        assert close(a.get_state(), oracle.collide(ref, p))
+        a.step(1)
+        assert close(a.get_state(), oracle.run(oracle.collide(ref, p), p, 1))
+
+
+def test_bc_of_other_wall_temperatures():
+    """bc twice: the second one's walls count."""
+    a = make()
+    a.step(3)
+    before = host(a.get_scratch())
+    a.bc()
+    a.set_params(t_bottom=1.25, t_top=0.75)
+    a.bc()
+    assert close(a.get_scratch(), oracle.bc(before, 1.25, 0.75))
+    p = make(ybc="periodic")
+    p.step(3)
+    before = p.get_scratch()
+    p.bc()  # no walls
+    assert torch.equal(p.get_scratch(), before)
