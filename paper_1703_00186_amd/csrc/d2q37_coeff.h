@@ -336,6 +336,37 @@ __device__ __forceinline__ void scratch_site(const void* buf, const Geom& g, int
   if (walls_since(buf, g, y, th)) wall_site<double>(v, y, g.ly, th, th, 0.0);
 }
 
+// Population l of a site.
+template <int l>
+__device__ __forceinline__ double population(const double (&c)[NC]) {
+  constexpr int ex = EX[l], ey = EY[l];
+  double P[5], plus, minus;
+  column_sums<ex>(c, P);
+  if constexpr (ey == 0) return population0<Forward, ex>(P);
+  populations<Forward, ex, (ey < 0 ? -ey : ey)>(P, plus, minus);
+  return ey > 0 ? plus : minus;
+}
+
+// propagate from coefficients: fn(l, f_l) for the populations that arrive at a
+// site, each from all 15 coefficients of the site it comes from (0 for those
+// that a wall will supply).  4.4 KB of loads a site, from the caches: as slow as
+// a few steps, for the first step after the collision changed.  One population
+// after the other, which leaves the registers of the kernels it stands in alone.
+template <int l = 0, class Fn>
+__device__ __forceinline__ void gather_coeffs(const double* src, const CGeom& g, int x, int y,
+                                              const Fn& fn) {
+  int xs = x - EX[l], ys = y - EY[l];
+  xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
+  const bool outside = ys < 0 || ys >= g.ly;
+  if (outside) ys = !g.periodic ? y : ys < 0 ? ys + g.ly : ys - g.ly;
+  double c[NC];
+  load_coeffs(src, g, xs, ys, c);
+  double v = population<l>(c);
+  asm volatile("" : "+s"(src), "+v"(v));  // the next site's loads stay behind this
+  fn(l, outside && !g.periodic ? 0.0 : v);
+  if constexpr (l + 1 < Q) gather_coeffs<l + 1>(src, g, x, y, fn);
+}
+
 // Powers of r, and the moments of w: sum w e_x^2 = r^-2, sum w e_x^4 = 3 r^-4,
 // sum w e_x^2 e_y^2 = r^-4, ...
 constexpr double kR2 = R * R, kR4 = kR2 * kR2, kR6 = kR4 * kR2, kR8 = kR4 * kR4;

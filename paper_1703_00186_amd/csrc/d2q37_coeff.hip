@@ -663,32 +663,6 @@ __global__ __launch_bounds__(kThreads) void k_coeff_init(
   store_coeffs(dst, g, x, y, b);
 }
 
-// The 37 populations into a padded buffer, its halos with them.
-__global__ __launch_bounds__(kThreads) void k_coeff_expand(const double* __restrict__ src,
-                                                           double* __restrict__ dst, CGeom g,
-                                                           Geom gf, int by, int bx, int nty,
-                                                           unsigned nb) {
-  set_form(dst, kFormFull);
-  int x, y;
-  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
-  double b[NC], v[Q];
-  load_coeffs(src, g, x, y, b);
-  expand_site<Forward>(b, v);
-#pragma unroll 1
-  for (int cx = -1; cx <= 1; ++cx) {
-    const int X = x + HX + cx * g.lx;
-    if (X < 0 || X >= gf.nx) continue;
-#pragma unroll 1
-    for (int cy = g.periodic ? -1 : 0; cy <= (g.periodic ? 1 : 0); ++cy) {
-      const int Y = y + cy * g.ly;
-      if (Y < -3 || Y >= g.ly + 3) continue;
-      const long long s = (long long)X * gf.cs + Y + gf.hy;
-#pragma unroll
-      for (int l = 0; l < Q; ++l) dst[l * gf.ps + s] = v[l];
-    }
-  }
-}
-
 // Eq. (2) fields: twelve coefficients in, four values out (128 bytes per site).
 __global__ __launch_bounds__(kThreads) void k_coeff_moments(
     const double* __restrict__ src, double* __restrict__ rho, double* __restrict__ ux,
@@ -961,7 +935,7 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
   const WallTable wt = make_walls(p);
   const CPhys cp = make_cphys(p);
   const unsigned* guard = guard_of(src, gf);
-  if (gf.form == kFormTwice && two_steps_small(gf)) {
+  if (gf.steps == 2 && two_steps_small(gf)) {
     // between walls 64 rows need no halo rows
     const bool one = !g.periodic && g.ly <= 64;
     const int rows = one ? 64 : kPairRows, halo = one ? 0 : kPairHalo;
@@ -970,7 +944,7 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
                        coeffs(src), coeffs(dst), g, cp, wt, windows, rows, halo, word_of(dst));
     return hipGetLastError();
   }
-  if (gf.form == kFormTwice) {
+  if (gf.steps == 2) {
     const int windows = (g.ly + kPairRows - 1) / kPairRows;
     const int chunk = march_chunk(g.lx, windows, 512, kPairCols);
     const unsigned nb = unsigned(windows) * unsigned((g.lx + chunk - 1) / chunk);
@@ -1013,13 +987,6 @@ hipError_t launch_coeff_init(void* dst, const double* rho, const double* ux, con
   const Tiling t = make_tiling(gf.lx, gf.ly);
   hipLaunchKernelGGL(k_coeff_init, dim3(t.nb), dim3(kThreads), 0, s, coeffs(dst), rho, ux, uy, T,
                      make_cgeom(gf), t.by, t.bx, t.nty, t.nb, word_of(dst));
-  return hipGetLastError();
-}
-
-hipError_t launch_coeff_expand(const void* src, void* dst, const Geom& gf, hipStream_t s) {
-  const Tiling t = make_tiling(gf.lx, gf.ly);
-  hipLaunchKernelGGL(k_coeff_expand, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src),
-                     static_cast<double*>(dst), make_cgeom(gf), gf, t.by, t.bx, t.nty, t.nb);
   return hipGetLastError();
 }
 

@@ -43,6 +43,7 @@ struct Geom {
   int np;          // planes per padded site: Q, or Q + 1 in the local-reference
                    // form (its packed reference)
   int form;        // storage form of the buffer a launcher reads (host side)
+  int steps;       // steps that launch_fused makes (1 or 2; host side)
   long long ps;    // element stride between populations
   long long cs;    // element stride between padded columns
 };
@@ -52,16 +53,14 @@ struct Geom {
 // site that generate them.  The buffer's first word, padding in both forms, names its
 // form for graphs recorded before the state was replaced; the host passes
 // what it knows in Geom::form, kFormUnknown where a graph may have run.
-// kFormTwice asks launch_fused for two steps (from the coefficients where the
-// step has that form, else from the populations).  kFormCoeffWalls: a word
+// kFormCoeffWalls: a word
 // only, coefficients of which the walls were applied to afterwards (a scratch
 // buffer after bc; the wall temperatures follow in the buffer's header).
 enum Form : int {
   kFormFull = 0,
   kFormCoeff = 1,
   kFormUnknown = 2,
-  kFormTwice = 3,
-  kFormCoeffWalls = 4
+  kFormCoeffWalls = 3
 };
 
 constexpr int NC = 15;  // coefficients of a site: degree i + j <= 4

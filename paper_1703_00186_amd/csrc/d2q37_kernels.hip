@@ -33,6 +33,19 @@ __device__ __forceinline__ void gather(const S* __restrict__ src, const Geom& g,
   for (int l = 0; l < Q; ++l) f[l] = A(src[l * g.ps + site - EX[l] * g.cs - EY[l]]);
 }
 
+// The same from a buffer in either form (word: see holds_coeffs).
+template <class S, class A>
+__device__ __forceinline__ void gather(const S* __restrict__ src, const Geom& g, int x, int y,
+                                       long long site, const unsigned* word, A (&f)[Q]) {
+  if constexpr (std::is_same<S, double>::value) {
+    if (holds_coeffs(word)) {
+      gather_coeffs(coeffs(src), coeff_geom(g), x, y, [&](int l, double v) { f[l] = v; });
+      return;
+    }
+  }
+  gather<S, A>(src, g, site, f);
+}
+
 template <class S, class A>
 __device__ __forceinline__ void load_site(const S* __restrict__ src, const Geom& g,
                                           long long site, A (&f)[Q]) {
@@ -132,13 +145,14 @@ template <class S, class A, bool kReg, bool kTape, bool kStream>
 __global__ __launch_bounds__(kThreads) void k_fused(const S* __restrict__ src,
                                                     S* __restrict__ dst, Geom g, Phys P,
                                                     double* __restrict__ tape, int by, int bx,
-                                                    int nty, unsigned nb) {
+                                                    int nty, unsigned nb,
+                                                    const unsigned* word) {
   set_full(dst);
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
   const long long site = padded<S>(g, x + HX, y + g.hy);
   A f[Q];
-  gather<S, A>(src, g, site, f);
+  gather<S, A>(src, g, x, y, site, word, f);
   if (on_wall_rows(g, y)) wall_site<A>(f, y, g.ly, P.th_bottom, P.th_top, P.rho_ref);
   const Tape4 m = collide<A, kReg>(f, P);
   if (kTape) {
@@ -348,11 +362,12 @@ struct RingSlots {
   }
 };
 
-template <class S, class A, bool kReg, bool kStream>
+template <class S, class A, bool kReg, bool kStream, bool kEither>
 __global__ __launch_bounds__(128 * kPairCols, 2) void k_fused_pair(const S* __restrict__ src,
                                                                   S* __restrict__ dst, Geom g,
                                                                   Phys P, int windows, int chunk,
-                                                                  unsigned nb) {
+                                                                  unsigned nb,
+                                                                  const unsigned* word) {
   __shared__ __align__(16) S ring[ring_start(4)];
   set_full(dst);
   const unsigned t = tile_index(nb);
@@ -370,6 +385,7 @@ __global__ __launch_bounds__(128 * kPairCols, 2) void k_fused_pair(const S* __re
     ys = min(max(ys, 0), g.ly - 1);
     const bool wall = on_wall_rows(g, ys);
     const unsigned lane_in = unsigned(ys + g.hy - 3) * unsigned(sizeof(S));
+    const bool from_coeffs = kEither && holds_coeffs(word);
     RingSlots slot(wave);
     int x = xa - 3 + wave;
     if (x < 0) x += g.lx;
@@ -377,19 +393,24 @@ __global__ __launch_bounds__(128 * kPairCols, 2) void k_fused_pair(const S* __re
       A f[Q];
       if (i < iters) {
         if (x >= g.lx) x -= g.lx;
-        const unsigned cs = recompute(g.cs), ps = recompute(g.ps);
-        // padded columns x .. x + 6, the sources of column x
-        const __amdgpu_buffer_rsrc_t in = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)(src + x * g.cs), (short)0, (2 * HX + 1) * cs * unsigned(sizeof(S)),
-            kBufferWord3);
-        S raw[Q];
+        if (from_coeffs) {
+          if constexpr (kEither)
+            gather_coeffs(coeffs(src), coeff_geom(g), x, ys, [&](int l, double v) { f[l] = v; });
+        } else {
+          const unsigned cs = recompute(g.cs), ps = recompute(g.ps);
+          // padded columns x .. x + 6, the sources of column x
+          const __amdgpu_buffer_rsrc_t in = __builtin_amdgcn_make_buffer_rsrc(
+              (void*)(src + x * g.cs), (short)0, (2 * HX + 1) * cs * unsigned(sizeof(S)),
+              kBufferWord3);
+          S raw[Q];
 #pragma unroll
-        for (int l = 0; l < Q; ++l)
-          load_elem(raw[l], in, lane_in + unsigned(3 - EY[l]) * unsigned(sizeof(S)),
-                    (unsigned(HX - EX[l]) * cs + unsigned(l) * ps) * unsigned(sizeof(S)));
-        __builtin_amdgcn_sched_barrier(0);  // all loads first
+          for (int l = 0; l < Q; ++l)
+            load_elem(raw[l], in, lane_in + unsigned(3 - EY[l]) * unsigned(sizeof(S)),
+                      (unsigned(HX - EX[l]) * cs + unsigned(l) * ps) * unsigned(sizeof(S)));
+          __builtin_amdgcn_sched_barrier(0);  // all loads first
 #pragma unroll
-        for (int l = 0; l < Q; ++l) f[l] = A(raw[l]);
+          for (int l = 0; l < Q; ++l) f[l] = A(raw[l]);
+        }
         if (wall) wall_site<A>(f, ys, g.ly, P.th_bottom, P.th_top, P.rho_ref);
         collide<A, kReg>(f, P);
         x += kPairCols;
@@ -443,11 +464,20 @@ __global__ __launch_bounds__(128 * kPairCols, 2) void k_fused_pair(const S* __re
 template <class S>
 __global__ __launch_bounds__(kThreads) void k_propagate(const S* __restrict__ src,
                                                         S* __restrict__ dst, Geom g, int by,
-                                                        int bx, int nty, unsigned nb) {
+                                                        int bx, int nty, unsigned nb,
+                                                        const unsigned* word) {
   set_full(dst);
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
   const long long site = padded<S>(g, x + HX, y + g.hy);
+  if constexpr (std::is_same<S, double>::value) {
+    if (holds_coeffs(word)) {
+      gather_coeffs(coeffs(src), coeff_geom(g), x, y, [&](int l, double v) {
+        __builtin_nontemporal_store(v, &dst[l * g.ps + site]);
+      });
+      return;
+    }
+  }
 #pragma unroll
   for (int l = 0; l < Q; ++l)
     __builtin_nontemporal_store(src[l * g.ps + site - EX[l] * g.cs - EY[l]], &dst[l * g.ps + site]);
@@ -1194,18 +1224,20 @@ hipError_t launch_fused(const void* src, void* dst, const Geom& g, const Phys& p
                                    : (regularize ? k_fused_local<true, k64, kStream>
                                                  : k_fused_local<false, k64, kStream>);
         hipLaunchKernelGGL(kernel, grid, block, 0, s, a, b, g, p, t.by, t.bx, t.nty, t.nb);
-      } else if (g.form == kFormTwice) {
+      } else if (g.steps == 2) {
         const auto kernel = [&] {
           if constexpr (std::is_same<S, float>::value)
-            return regularize ? k_fused_pair<S, A, true, kStream>
-                              : k_fused_pair<S, A, false, kStream>;
+            return regularize ? k_fused_pair<S, A, true, kStream, false>
+                              : k_fused_pair<S, A, false, kStream, false>;
           else
-            return k_fused_pair<S, A, false, kStream>;
+            return word_of(src, g) ? k_fused_pair<S, A, false, kStream, true>
+                                   : k_fused_pair<S, A, false, kStream, false>;
         }();
         const int windows = (g.ly + kPairRows - 1) / kPairRows;
         const int chunk = march_chunk(g.lx, windows, 256, kPairCols);
         const unsigned n = unsigned(windows) * unsigned((g.lx + chunk - 1) / chunk);
-        hipLaunchKernelGGL(kernel, dim3(n), dim3(128 * kPairCols), 0, s, a, b, g, p, windows, chunk, n);
+        hipLaunchKernelGGL(kernel, dim3(n), dim3(128 * kPairCols), 0, s, a, b, g, p, windows,
+                           chunk, n, word_of(src, g));
       } else {
         const auto kernel = [&] {
           if constexpr (std::is_same<S, float>::value)
@@ -1215,7 +1247,8 @@ hipError_t launch_fused(const void* src, void* dst, const Geom& g, const Phys& p
             return tape ? k_fused<S, A, false, true, kStream>
                         : k_fused<S, A, false, false, kStream>;
         }();
-        hipLaunchKernelGGL(kernel, grid, block, 0, s, a, b, g, p, tape, t.by, t.bx, t.nty, t.nb);
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, a, b, g, p, tape, t.by, t.bx, t.nty, t.nb,
+                           word_of(src, g));
       }
     };
     if (streams_output((long long)g.np * g.nx * g.ny * (long long)sizeof(S),
@@ -1233,7 +1266,7 @@ hipError_t launch_propagate(const void* src, void* dst, const Geom& g, int prec,
     using S = decltype(sv);
     hipLaunchKernelGGL(k_propagate<S>, dim3(t.nb), dim3(kThreads), 0, s,
                        static_cast<const S*>(src), static_cast<S*>(dst), g, t.by, t.bx, t.nty,
-                       t.nb);
+                       t.nb, word_of(src, g));
   });
 }
 
@@ -1316,7 +1349,6 @@ hipError_t launch_pack(const void* padded_buf, void* compact, const Geom& g, int
 
 hipError_t launch_unpack(const void* compact, void* padded_buf, const Geom& g, int prec,
                          hipStream_t s) {
-  if (g.form == kFormCoeff) return launch_coeff_expand(compact, padded_buf, g, s);
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto) {
     using S = decltype(sv);

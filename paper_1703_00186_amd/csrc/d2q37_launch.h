@@ -5,7 +5,8 @@
 // kFormUnknown the kernels of both forms are enqueued and the device word
 // decides.  launch_init_feq writes the form it names, launch_fused always the
 // coefficient form for regularized FP64 and the populations otherwise; the
-// split stages write populations (launch_bc marks coefficients instead).
+// split stages read either and write populations (launch_bc marks coefficients
+// instead).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -37,7 +38,7 @@ hipError_t launch_halo(void* buf, const Geom& g, int prec, hipStream_t s);
 
 // One fused step: dst = collide(bc(propagate(src))), with the periodic x
 // halos of dst written too.  tape (optional, FP64 only): [4][lx][ly].
-// With form kFormTwice: two steps (no tape, where two_steps_pay).
+// With Geom::steps = 2: two steps (no tape, where two_steps_pay).
 hipError_t launch_fused(const void* src, void* dst, const Geom& g, const Phys& p, int prec,
                         int regularize, double* tape, hipStream_t s);
 
@@ -103,9 +104,7 @@ hipError_t launch_init_feq(void* dst, const double* rho, const double* ux, const
 hipError_t launch_moments(const void* src, double* rho, double* ux, double* uy, double* T,
                           const Geom& g, const Phys& p, int prec, hipStream_t s);
 
-// Copies between a padded buffer and the compact [37][lx][ly] form.  unpack
-// with form kFormCoeff: `compact` is a state buffer in that form instead,
-// expanded into the padded buffer with its halos.
+// Copies between a padded buffer and the compact [37][lx][ly] form.
 hipError_t launch_pack(const void* padded, void* compact, const Geom& g, int prec,
                        hipStream_t s);
 hipError_t launch_unpack(const void* compact, void* padded, const Geom& g, int prec,
@@ -162,7 +161,6 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& g, const Ph
                              double* tape, hipStream_t s);
 hipError_t launch_coeff_init(void* dst, const double* rho, const double* ux, const double* uy,
                              const double* T, const Geom& g, hipStream_t s);
-hipError_t launch_coeff_expand(const void* src, void* dst, const Geom& g, hipStream_t s);
 hipError_t launch_coeff_moments(const void* src, double* rho, double* ux, double* uy, double* T,
                                 const Geom& g, hipStream_t s);
 hipError_t launch_coeff_check(const void* src, unsigned* flag, const Geom& g, hipStream_t s);

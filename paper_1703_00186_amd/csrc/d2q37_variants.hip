@@ -28,6 +28,19 @@ namespace {
 
 constexpr int kVThreads = 256;
 
+// From coefficients (a fused step's result) both kernels gather as k_propagate
+// does, their threads taking one site after the other.
+__device__ __forceinline__ void propagate_coeffs(const double* __restrict__ src,
+                                                 double* __restrict__ dst, const Geom& g) {
+  const long long n = (long long)g.lx * g.ly, step = (long long)gridDim.x * kVThreads;
+  for (long long i = (long long)blockIdx.x * kVThreads + threadIdx.x; i < n; i += step) {
+    const int x = int(i / g.ly), y = int(i % g.ly);
+    double* to = dst + (long long)(x + HX) * g.cs + y + g.hy;
+    gather_coeffs(coeffs(src), coeff_geom(g), x, y,
+                  [&](int l, double v) { to[l * g.ps] = v; });
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Propagate through LDS.  One workgroup: `kVThreads` consecutive rows
 // y0 .. y0 + n - 1 of one column x (n < kVThreads only at the top of the
@@ -46,9 +59,12 @@ constexpr int kLdsRows = kVThreads + 6;
 template <class S>
 __global__ __launch_bounds__(kVThreads) void k_propagate_lds(const S* __restrict__ src,
                                                              S* __restrict__ dst, Geom g,
-                                                             int nty) {
+                                                             int nty, const unsigned* word) {
   __shared__ S win[kLdsGroup * kLdsRows];
-  if constexpr (std::is_same<S, double>::value) set_form(dst, kFormFull);
+  if constexpr (std::is_same<S, double>::value) {
+    set_form(dst, kFormFull);
+    if (holds_coeffs(word)) return propagate_coeffs(src, dst, g);
+  }
   const int x = int(blockIdx.x) / nty;
   const int y0 = (int(blockIdx.x) % nty) * kVThreads;
   const int n = min(kVThreads, g.ly - y0);
@@ -118,10 +134,13 @@ struct Wide<float> {
 template <class S>
 __global__ __launch_bounds__(kVThreads) void k_propagate_wide(const S* __restrict__ src,
                                                               S* __restrict__ dst, Geom g,
-                                                              int nty) {
+                                                              int nty, const unsigned* word) {
   using W = Wide<S>;
   constexpr int V = W::V;
-  if constexpr (std::is_same<S, double>::value) set_form(dst, kFormFull);
+  if constexpr (std::is_same<S, double>::value) {
+    set_form(dst, kFormFull);
+    if (holds_coeffs(word)) return propagate_coeffs(src, dst, g);
+  }
   const int x = int(blockIdx.x) / nty;
   const int y = (int(blockIdx.x) % nty) * (kVThreads * V) + V * int(threadIdx.x);
   if (y >= g.ly) return;
@@ -353,14 +372,15 @@ hipError_t launch_propagate_variant(const void* src, void* dst, const Geom& g, i
     using S = decltype(sv);
     const S* a = static_cast<const S*>(src);
     S* b = static_cast<S*>(dst);
+    const unsigned* word = g.form == kFormFull ? nullptr : static_cast<const unsigned*>(src);
     if (variant == kPropagateLds) {
       const int nty = int(blocks(g.ly, kVThreads));
       hipLaunchKernelGGL(k_propagate_lds<S>, dim3(unsigned(g.lx) * unsigned(nty)),
-                         dim3(kVThreads), 0, s, a, b, g, nty);
+                         dim3(kVThreads), 0, s, a, b, g, nty, word);
     } else {
       const int nty = int(blocks(g.ly, (long long)kVThreads * Wide<S>::V));
       hipLaunchKernelGGL(k_propagate_wide<S>, dim3(unsigned(g.lx) * unsigned(nty)),
-                         dim3(kVThreads), 0, s, a, b, g, nty);
+                         dim3(kVThreads), 0, s, a, b, g, nty, word);
     }
   };
   if (variant != kPropagateLds && variant != kPropagateWide) return hipErrorInvalidValue;

@@ -122,6 +122,7 @@ Geom make_geom(const lb_lattice& lat) {
   g.walls = lat.ybc == LB_Y_WALLS;
   g.np = is_local_form(lat.precision) ? d2q37::kLocalPlanes : d2q37::Q;
   g.form = d2q37::kFormFull;
+  g.steps = 1;
   if (lat.layout == LB_LAYOUT_SOA) {
     g.ps = (long long)g.nx * g.ny;
     g.cs = g.ny;
@@ -158,33 +159,13 @@ int check_kernel(int prec, const lb_params& par) {
   return LB_OK;
 }
 
-// the geometry with the storage form of the buffer that is read
-Geom with_form(const Geom& g, int form) {
+// the geometry with the storage form of the buffer that is read, and the steps
+// to make of it
+Geom with_form(const Geom& g, int form, int steps = 1) {
   Geom h = g;
   h.form = form;
+  h.steps = steps;
   return h;
-}
-
-// The state A as populations: before the kernels that work on those.  B is
-// free then (each caller overwrites it).
-int full_state(lb_ctx* c) {
-  if (c->a_form == d2q37::kFormFull) return LB_OK;
-  if (c->a_form == d2q37::kFormCoeff) {
-    LB_HIP(d2q37::launch_unpack(c->A, c->B, with_form(c->g, d2q37::kFormCoeff), c->prec,
-                                c->stream),
-           "expand state");
-    std::swap(c->A, c->B);
-    c->a_form = d2q37::kFormFull;
-    c->halos_valid = true;
-    return LB_OK;
-  }
-  // a recorded graph may have run: keep the buffers' roles
-  LB_HIP(d2q37::launch_pack(c->A, c->B, with_form(c->g, c->a_form), c->prec, c->stream),
-         "expand state");
-  LB_HIP(d2q37::launch_unpack(c->B, c->A, c->g, c->prec, c->stream), "expand state");
-  c->a_form = d2q37::kFormFull;
-  c->halos_valid = false;
-  return LB_OK;
 }
 
 // The form of the scratch B: only its word tells what it holds (the state before
@@ -196,13 +177,13 @@ int scratch_form(const lb_ctx* c) {
 // The split stages, with the alternative kernel the context's kernel value
 // names (same results as the main ones).
 hipError_t propagate_stage(lb_ctx* c) {
+  const Geom g = with_form(c->g, c->a_form);
   if (c->par.kernel == LB_KERNEL_SPLIT_LDS)
-    return d2q37::launch_propagate_variant(c->A, c->B, c->g, c->prec, d2q37::kPropagateLds,
-                                           c->stream);
+    return d2q37::launch_propagate_variant(c->A, c->B, g, c->prec, d2q37::kPropagateLds, c->stream);
   if (c->par.kernel == LB_KERNEL_SPLIT_WIDE)
-    return d2q37::launch_propagate_variant(c->A, c->B, c->g, c->prec, d2q37::kPropagateWide,
+    return d2q37::launch_propagate_variant(c->A, c->B, g, c->prec, d2q37::kPropagateWide,
                                            c->stream);
-  return d2q37::launch_propagate(c->A, c->B, c->g, c->prec, c->stream);
+  return d2q37::launch_propagate(c->A, c->B, g, c->prec, c->stream);
 }
 
 // form: of the scratch buffer, where the step that filled it is not known
@@ -293,60 +274,41 @@ int check_finite_now(lb_ctx* c) {
 // The step that the coefficient form is for (d2q37_coeff.hip).
 bool coeff_step(const lb_ctx* c) { return c->prec == LB_FP64 && c->par.regularize; }
 
+// n (1 or 2) fused steps in one launch, to the form that the collision leaves.
+int fused_steps(lb_ctx* c, int n, double* tape) {
+  // coefficients are read without halos
+  if (!coeff_step(c) && (!c->halos_valid || !c->g.walls)) {
+    const int rc = do_halo(c);
+    if (rc) return rc;
+  }
+  LB_HIP(d2q37::launch_fused(c->A, c->B, with_form(c->g, c->a_form, n), c->p, c->prec,
+                             c->par.regularize, tape, c->stream),
+         "fused step");
+  std::swap(c->A, c->B);
+  c->a_form = coeff_step(c) ? d2q37::kFormCoeff : d2q37::kFormFull;
+  // the fused kernel writes the x halos of its output (coefficients have none);
+  // y halos (periodic y) are refreshed before the next step
+  c->halos_valid = c->g.walls;
+  return LB_OK;
+}
+
 int one_step(lb_ctx* c, double* tape) {
-  const bool fused = c->par.kernel == LB_KERNEL_FUSED || tape;
-  if (fused && coeff_step(c)) {
-    // from either form to the coefficient form, which needs no halos
-    LB_HIP(d2q37::launch_fused(c->A, c->B, with_form(c->g, c->a_form), c->p, c->prec, 1, tape,
-                               c->stream),
-           "fused step");
-    std::swap(c->A, c->B);
-    c->a_form = d2q37::kFormCoeff;
-    c->halos_valid = false;
-  } else if (fused) {
-    int rc = full_state(c);
+  if (c->par.kernel == LB_KERNEL_FUSED || tape) {
+    const int rc = fused_steps(c, 1, tape);
     if (rc) return rc;
-    if (!c->halos_valid || !c->g.walls) {
-      rc = do_halo(c);
-      if (rc) return rc;
-    }
-    LB_HIP(d2q37::launch_fused(c->A, c->B, c->g, c->p, c->prec, c->par.regularize, tape,
-                               c->stream),
-           "fused step");
-    std::swap(c->A, c->B);
-    // the fused kernel writes the x halos of its output; y halos (periodic
-    // y) are refreshed before the next step
-    c->halos_valid = c->g.walls;
   } else {
-    int rc = full_state(c);
-    if (rc) return rc;
-    rc = do_halo(c);
+    const int rc = do_halo(c);
     if (rc) return rc;
     LB_HIP(propagate_stage(c), "propagate");
     LB_HIP(d2q37::launch_bc(c->B, c->g, c->p, c->prec, c->stream), "bc");
     LB_HIP(collide_stage(c), "collide");
+    c->a_form = d2q37::kFormFull;
     c->halos_valid = false;
   }
   if (c->par.check_finite > 0 && ++c->steps_since_check >= c->par.check_finite) {
     c->steps_since_check = 0;
     return check_finite_now(c);
   }
-  return LB_OK;
-}
-
-// Two fused steps in one launch, from the form the step leaves behind.
-int two_steps(lb_ctx* c) {
-  if (!coeff_step(c)) {
-    if (!c->halos_valid || !c->g.walls) {
-      const int rc = do_halo(c);
-      if (rc) return rc;
-    }
-  }
-  LB_HIP(d2q37::launch_fused(c->A, c->B, with_form(c->g, d2q37::kFormTwice), c->p, c->prec,
-                             c->par.regularize, nullptr, c->stream),
-         "fused steps");
-  std::swap(c->A, c->B);
-  if (!coeff_step(c)) c->halos_valid = c->g.walls;
   return LB_OK;
 }
 
@@ -357,11 +319,12 @@ int two_steps(lb_ctx* c) {
 int run_steps(lb_ctx* c, int n) {
   const bool pairs = c->par.kernel == LB_KERNEL_FUSED && c->par.check_finite == 0 &&
                      d2q37::two_steps_pay(c->g, c->prec, c->par.regularize);
-  const int form = coeff_step(c) ? d2q37::kFormCoeff : d2q37::kFormFull;
   for (int i = 0; i < n;) {
-    if (pairs && n - i > 4 && c->a_form == form) {
-      int rc = two_steps(c);
-      if (rc == LB_OK) rc = two_steps(c);
+    // two steps read their own form, plain BGK's either
+    const bool ready = coeff_step(c) ? c->a_form == d2q37::kFormCoeff : true;
+    if (pairs && ready && n - i > 4) {
+      int rc = fused_steps(c, 2, nullptr);
+      if (rc == LB_OK) rc = fused_steps(c, 2, nullptr);
       if (rc) return rc;
       i += 4;
     } else {
@@ -604,8 +567,6 @@ int lb_propagate(lb_ctx* ctx) {
   int rc = enter(ctx);
   if (rc) return rc;
   rc = no_split_stage(ctx, "lb_propagate");
-  if (rc) return rc;
-  rc = full_state(ctx);
   if (rc) return rc;
   LB_HIP(propagate_stage(ctx), "propagate");
   return LB_OK;

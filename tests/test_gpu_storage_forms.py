@@ -107,3 +107,84 @@ def test_bc_of_other_wall_temperatures():
     before = p.get_scratch()
     p.bc()  # no walls
     assert torch.equal(p.get_scratch(), before)
+
+
+# -- plain BGK and the split stages ----------------------------------------------
+
+@pytest.mark.parametrize("kernel", ["split", "split_lds", "split_wide", "split_mfma"])
+@pytest.mark.parametrize("layout", ["column", "soa"])
+@pytest.mark.parametrize("ybc", ["walls", "periodic"])
+@pytest.mark.parametrize("recorded", [False, True])
+def test_split_stages_of_a_stepped_state(recorded, ybc, layout, kernel):
+    """halo, propagate, bc, collide of a state that fused steps left, with and
+    without a recording before; lb_step's split path likewise."""
+    a = make(ybc=ybc, layout=layout)
+    if recorded:
+        a.capture(2)
+    a.step(3)
+    f = host(a.get_state())
+    a.set_params(kernel=kernel)
+    a.halo()
+    a.propagate()
+    known = ~np.isnan(oracle.propagate(f, ybc=int(ybc == "periodic")))
+    assert np.array_equal(host(a.get_scratch())[known],
+                          oracle.propagate(f, ybc=int(ybc == "periodic"))[known])
+    assert np.array_equal(host(a.get_state()), f)
+    a.bc()
+    a.collide()
+    p = params(ybc=int(ybc == "periodic"))
+    f = oracle.run(f, p, 1)
+    assert close(a.get_state(), f)
+    a.set_params(kernel="fused")
+    a.step(2)
+    a.set_params(kernel=kernel)
+    a.step(2)
+    assert close(a.get_state(), oracle.run(f, p, 4))
+
+
+@pytest.mark.parametrize("shape", [(LX, LY), (280, 280), (6, 6), (40, 130)])
+@pytest.mark.parametrize("layout", ["column", "soa"])
+@pytest.mark.parametrize("ybc", ["walls", "periodic"])
+def test_bgk_from_either_form(ybc, layout, shape):
+    """Single and double plain BGK steps from coefficients and from the
+    populations these stand for: the same bits; a recorded graph of them
+    likewise, replayed between regularized steps."""
+    a, b = (make(*shape, ybc=ybc, layout=layout) for _ in range(2))
+    g = None
+    for n in (1, 6, 10):
+        a.set_params(regularize=1)
+        b.set_params(regularize=1)
+        a.step(2)
+        b.step(2)
+        b.set_state(b.get_state())
+        a.set_params(regularize=0)
+        b.set_params(regularize=0)
+        a.step(n)
+        for _ in range(n):
+            b.step(1)
+        assert torch.equal(a.get_state(), b.get_state())
+        if g is None:
+            g = a.capture(6)
+            b.step(2)
+        for reg in (0, 1):
+            a.set_params(regularize=reg)
+            b.set_params(regularize=reg)
+            a.step(2)
+            b.step(2)
+            g.replay()
+            b.set_params(regularize=0)
+            b.set_state(b.get_state())
+            b.step(6)
+            assert torch.equal(a.get_state(), b.get_state())
+
+
+def test_tape_of_bgk_from_either_form():
+    a, b = make(), make()
+    a.step(2)
+    b.set_state(a.get_state())
+    ta, tb = a.new_tape(3), b.new_tape(3)
+    for lb, t in ((a, ta), (b, tb)):
+        lb.set_params(regularize=0)
+        lb.step_record(3, t)
+    assert torch.equal(ta, tb)
+    assert torch.equal(a.get_state(), b.get_state())
