@@ -528,6 +528,44 @@ __device__ __forceinline__ void wall_adjoint(double (&C)[NC], const WallTable& w
   C[slot(0, 0)] = mad(su, wt.ivk[i], C[slot(0, 0)]);
 }
 
+// The readers' share of a site (twelve coefficients, 96 bytes).
+__device__ __forceinline__ Macro load_macro(const double* __restrict__ src, const CGeom& g, int x,
+                                            int y) {
+  const double* col = src + x * g.cs + 2 * y;
+  double c[12];
+#pragma unroll
+  for (int m = 0; m < 6; ++m) {
+    const v2d d = *reinterpret_cast<const v2d*>(col + 2 * m * (long long)g.pitch);
+    c[2 * m] = d.x;
+    c[2 * m + 1] = d.y;
+  }
+  return macro_coeffs(c);
+}
+
+// As k_obs_rows: the sums over the columns x0 .. x1 - 1 of a row.
+__device__ __forceinline__ void sum_observables(const double* __restrict__ src, const CGeom& g,
+                                                int y, int x0, int x1, double (&acc)[6]) {
+#pragma unroll 4
+  for (int x = x0; x < x1; ++x) {
+    const Macro m = load_macro(src, g, x, y);
+    const double T = 1.0 + m.th;
+    acc[0] += m.rho;
+    acc[1] += m.ux;
+    acc[2] += m.uy;
+    acc[3] += T;
+    acc[4] += 0.5 * m.rho * (m.ux * m.ux + m.uy * m.uy);
+    acc[5] += m.rho * T;
+  }
+}
+
+// A site's kinetic energy, and its derivative with respect to population l.
+__device__ __forceinline__ double kinetic(const Macro& m) {
+  return 0.5 * m.rho * (m.ux * m.ux + m.uy * m.uy);
+}
+__device__ __forceinline__ double kinetic_slope(const Macro& m, int l) {
+  return R * (EX[l] * m.ux + EY[l] * m.uy) - 0.5 * (m.ux * m.ux + m.uy * m.uy);
+}
+
 }  // namespace d2q37
 
 #pragma clang fp contract(fast)  // as the rest of the code is compiled

@@ -30,6 +30,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "d2q37_coeff.h"
 #include "d2q37_launch.h"
@@ -146,7 +147,7 @@ __device__ __forceinline__ void shift_group(Group& f) {
 // Row of this lane: its index, whether it exists, its byte offset in a pair
 // plane for loads, and for stores (only the wave's own rows).
 struct Row {
-  int y;
+  int y, from;  // from: the row that is read (inside the lattice)
   bool in;
   unsigned load, store;
 };
@@ -162,6 +163,7 @@ __device__ __forceinline__ Row wave_row(const CGeom& g, int w, int rows = kRows,
     if (y >= g.ly) y -= g.ly;
     if (y < 0 || y >= g.ly) y = 0;
   }
+  r.from = r.in || g.periodic ? y : 0;
   r.load = r.in || g.periodic ? unsigned(y) * 16u : kOutside;
   r.store = r.in && lane >= halo && lane < halo + rows ? unsigned(r.y) * 16u : kOutside;
   return r;
@@ -258,6 +260,39 @@ __device__ __forceinline__ void store_tape(double* tape, long long S2, long long
   __builtin_nontemporal_store(kR2 * (a[slot(2, 0)] + a[slot(0, 2)]), &tape[3 * S2 + s]);
 }
 
+// The way in from 37 stored populations: the moments of those that arrive at a
+// site (0 for the ones a wall will supply).  The columns wrap here, so halo
+// columns are not read.
+__device__ __forceinline__ double arriving(const double* __restrict__ src, const Geom& gf,
+                                           const CGeom& g, int x, int y, int l) {
+  int xs = x - EX[l], ys = y - EY[l];
+  xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
+  const bool outside = ys < 0 || ys >= g.ly;
+  if (g.periodic)
+    ys = ys < 0 ? ys + g.ly : (ys >= g.ly ? ys - g.ly : ys);
+  else if (outside)
+    ys = y;
+  const double v = src[l * gf.ps + (long long)(xs + HX) * gf.cs + ys + gf.hy];
+  return !g.periodic && outside ? 0.0 : v;
+}
+template <int ex = 3>
+__device__ __forceinline__ void project_arriving(const double* src, const Geom& gf,
+                                                 const CGeom& g, int x, int y, double (&m)[NC]) {
+  // one group after the other: the sweep has no registers for more
+  asm volatile("" : "+s"(src));
+  Group f;
+  f.zero = arriving(src, gf, g, x, y, label(ex, 0));
+#pragma unroll
+  for (int k = 1; k <= reach(ex); ++k) {
+    f.plus[k - 1] = arriving(src, gf, g, x, y, label(ex, k));
+    f.minus[k - 1] = arriving(src, gf, g, x, y, label(ex, -k));
+  }
+  project_group<Forward, ex>(f, m);
+#pragma unroll
+  for (int k = 0; k < NC; ++k) asm volatile("" : "+v"(m[k]));
+  if constexpr (ex > -3) project_arriving<ex - 1>(src, gf, g, x, y, m);
+}
+
 // Forward: walls on the six wall rows, optional tape of the pre-collision
 // moments (rho, j_x, j_y, sum |c|^2 f), collide, store.
 template <bool kTape>
@@ -324,16 +359,28 @@ struct AdjointSite {
 template <int TX, int kAhead>
 constexpr int kOccupancy = TX == 1 ? 4 : (TX == 2 || (TX == 3 && kAhead == 1)) ? 3 : 2;
 
-template <int TX, int kAhead, bool kTape>
+// word: of a source whose form is not known (null: coefficients).  Populations
+// are taken through the same tiles; k_coeff_first, which is made for them, is
+// launched where they are expected.
+template <int TX, int kAhead, bool kTape, bool kEither>
 __global__ __launch_bounds__(64 * kWaves, (kOccupancy<TX, kAhead>)) void k_coeff_step(
-    const double* __restrict__ src, double* __restrict__ dst, CGeom g, CPhys P, WallTable wt,
-    double* __restrict__ tape, unsigned nb, const unsigned* guard, unsigned* word) {
-  if (other_form(guard, kFormCoeff)) return;
-  set_form(word, kFormCoeff);
+    const double* __restrict__ src, double* __restrict__ dst, Geom gf, CGeom g, CPhys P,
+    WallTable wt, double* __restrict__ tape, unsigned nb, const unsigned* word) {
+  set_form(dst, kFormCoeff);
   int w, x0;
   if (!wave_tile<Forward, TX>(g, nb, w, x0)) return;
-  const StepSite<kTape> site{dst, g, P, wt, tape};
-  Sweep<Forward, TX, kAhead, StepSite<kTape>> s{src, g, site, x0, wave_row(g, w)};
+  const StepSite<kTape> site{coeffs(dst), g, P, wt, tape};
+  const Row row = wave_row(g, w);
+  if (kEither && holds_populations(word)) {
+#pragma unroll 1
+    for (int x = x0; x < x0 + TX && x < g.lx; ++x) {
+      double m[NC];
+      project_arriving(src, gf, g, x, row.from, m);
+      site.finish({}, m, x, row);
+    }
+    return;
+  }
+  Sweep<Forward, TX, kAhead, StepSite<kTape>> s{coeffs(src), g, site, x0, row};
   s.prefetch();
   s.template walk<0>();
 }
@@ -394,6 +441,11 @@ struct PairWalk {
       add<j, t + 1>(c);
     }
   }
+  __device__ __forceinline__ void finish(double (&a)[NC]) const {
+    int i;
+    if (row.in && wall_row(g, row.y, i)) wall_moments(a, wt, i);
+    collide_moments(a, P);
+  }
   template <int j = 0, class Load>
   __device__ __forceinline__ void walk(double (&c)[kAhead][NC], const Load& load) {
     if constexpr (j < TX + 6) {
@@ -401,12 +453,16 @@ struct PairWalk {
       __builtin_amdgcn_sched_barrier(0);
       load(j + kAhead, c[j % kAhead]);
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (j >= 6) {
-        int i;
-        if (row.in && wall_row(g, row.y, i)) wall_moments(m[j - 6], wt, i);
-        collide_moments(m[j - 6], P);
-      }
+      if constexpr (j >= 6) finish(m[j - 6]);
       walk<j + 1>(c, load);
+    }
+  }
+  // the TX columns from x on, from stored populations
+  __device__ __forceinline__ void from_populations(const double* src, const Geom& gf, int x) {
+#pragma unroll
+    for (int t = 0; t < TX; ++t) {
+      project_arriving(src, gf, g, x + t >= g.lx ? x + t - g.lx : x + t, row.from, m[t]);
+      finish(m[t]);
     }
   }
 };
@@ -429,11 +485,13 @@ __device__ __forceinline__ void ring_load(const double* col, int lane, double (&
   v[NC - 1] = col[(NC - 1) * 64 + lane];
 }
 
+// kEither: the source may hold populations (word, as k_coeff_step).
+template <bool kEither>
 __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
-    const double* __restrict__ src, double* __restrict__ dst, CGeom g, CPhys P, WallTable wt,
-    int windows, int chunk, unsigned nb, unsigned* word) {
+    const double* __restrict__ src, double* __restrict__ dst, Geom gf, CGeom g, CPhys P,
+    WallTable wt, int windows, int chunk, unsigned nb, const unsigned* word) {
   __shared__ __align__(16) double ring[kRing * kRingCol];
-  set_form(word, kFormCoeff);
+  set_form(dst, kFormCoeff);
   const unsigned t = tile_index(nb);
   const int xa = int(t / unsigned(windows)) * chunk, xb = min(xa + chunk, g.lx);
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
@@ -449,32 +507,39 @@ __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
     auto load = [&](int j, double (&v)[NC]) {
       int xs = x - 3 + (j < kPairWave + 6 ? j : j - (kPairWave + 6) + kPairCols);
       xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
-      load_column(column_rsrc(src, g, xs), g, row.load, v);
+      load_column(column_rsrc(coeffs(src), g, xs), g, row.load, v);
     };
-    double c[kPairAhead][NC];
+    const auto march = [&](const auto& make) {
+      for (int i = 0; i <= iters; ++i) {
+        PairWalk<kPairWave, kPairAhead> s{g, P, wt, row};
+        if (i < iters) {
+          make(s);
+          if (!g.periodic && !row.in) {  // nothing comes from beyond the walls
 #pragma unroll
-    for (int j = 0; j < kPairAhead; ++j) load(j, c[j]);
-    for (int i = 0; i <= iters; ++i) {
-      PairWalk<kPairWave, kPairAhead> s{g, P, wt, row};
-      if (i < iters) {
-        s.walk(c, load);
-        if (!g.periodic && !row.in) {  // nothing comes from beyond the walls
-#pragma unroll
-          for (int k = 0; k < kPairWave * NC; ++k) s.m[k / NC][k % NC] = 0.0;
+            for (int k = 0; k < kPairWave * NC; ++k) s.m[k / NC][k % NC] = 0.0;
+          }
         }
-      }
-      __syncthreads();
-      if (i < iters) {
+        __syncthreads();
+        if (i < iters) {
 #pragma unroll
-        for (int n = 0; n < kPairWave; ++n) {
-          double* col = ring + ring_slot(slot + n) * kRingCol;
-          ring_store(col, lane, s.m[n]);
+          for (int n = 0; n < kPairWave; ++n) {
+            double* col = ring + ring_slot(slot + n) * kRingCol;
+            ring_store(col, lane, s.m[n]);
+          }
         }
+        __syncthreads();
+        slot = ring_slot(slot + kPairCols);
+        x += kPairCols;
+        if (x >= g.lx) x -= g.lx;
       }
-      __syncthreads();
-      slot = ring_slot(slot + kPairCols);
-      x += kPairCols;
-      if (x >= g.lx) x -= g.lx;
+    };
+    if (kEither && holds_populations(word)) {
+      march([&](auto& s) { s.from_populations(src, gf, x); });
+    } else {
+      double c[kPairAhead][NC];
+#pragma unroll
+      for (int j = 0; j < kPairAhead; ++j) load(j, c[j]);
+      march([&](auto& s) { s.walk(c, load); });
     }
   } else {
     const int first = (wave - kPairMakers) * kPairWave;
@@ -495,7 +560,7 @@ __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
 #pragma unroll
           for (int n = 0; n < kPairWave; ++n)
             if (x + n >= xa && x + n < xb)
-              store_column(column_rsrc(dst, g, x + n), g, row.store, s.m[n]);
+              store_column(column_rsrc(coeffs(dst), g, x + n), g, row.store, s.m[n]);
         }
         base = ring_slot(base + kPairCols);
       }
@@ -515,11 +580,12 @@ __global__ __launch_bounds__(64 * 2 * kPairMakers, 2) void k_coeff_pair(
 // 100 x 100 (200 columns of windows) 4.7 and 4.5, 128 x 128 4.8 and 6.3.  Two
 // columns by eight waves 4.1 at 64 x 48; three steps in a loop over stages 4.7.
 constexpr int kSmallWaves = 7;
+template <bool kEither>
 __global__ __launch_bounds__(64 * kSmallWaves) void k_coeff_two(
-    const double* __restrict__ src, double* __restrict__ dst, CGeom g, CPhys P, WallTable wt,
-    int windows, int rows, int halo, unsigned* word) {
+    const double* __restrict__ src, double* __restrict__ dst, Geom gf, CGeom g, CPhys P,
+    WallTable wt, int windows, int rows, int halo, const unsigned* word) {
   __shared__ __align__(16) double ring[kSmallWaves * kRingCol];
-  set_form(word, kFormCoeff);
+  set_form(dst, kFormCoeff);
   const int x = int(blockIdx.x / unsigned(windows));
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
@@ -529,13 +595,18 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_coeff_two(
       if (j >= 7) return;
       int xs = x - 6 + wave + j;
       xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
-      load_column(column_rsrc(src, g, xs), g, row.load, v);
+      load_column(column_rsrc(coeffs(src), g, xs), g, row.load, v);
     };
-    double c[2][NC];
-    load(0, c[0]);
-    load(1, c[1]);
     PairWalk<1, 2> s{g, P, wt, row};
-    s.walk(c, load);
+    if (kEither && holds_populations(word)) {
+      const int xw = x - 3 + wave;
+      s.from_populations(src, gf, xw < 0 ? xw + g.lx : (xw >= g.lx ? xw - g.lx : xw));
+    } else {
+      double c[2][NC];
+      load(0, c[0]);
+      load(1, c[1]);
+      s.walk(c, load);
+    }
     if (!g.periodic && !row.in) {  // nothing comes from beyond the walls
 #pragma unroll
       for (int k = 0; k < NC; ++k) s.m[0][k] = 0.0;
@@ -551,7 +622,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_coeff_two(
     load(0, c[0]);
     PairWalk<1, 1> s{g, P, wt, row};
     s.walk(c, load);
-    store_column(column_rsrc(dst, g, x), g, row.store, s.m[0]);
+    store_column(column_rsrc(coeffs(dst), g, x), g, row.store, s.m[0]);
   }
 }
 
@@ -582,19 +653,6 @@ __device__ __forceinline__ void store_coeffs(double* __restrict__ dst, const CGe
   __builtin_nontemporal_store(b[NC - 1], &col[(NC - 1) * (long long)g.pitch + y]);
 }
 
-__device__ __forceinline__ Macro load_macro(const double* __restrict__ src, const CGeom& g, int x,
-                                            int y) {
-  const double* col = src + x * g.cs + 2 * y;
-  double c[12];
-#pragma unroll
-  for (int m = 0; m < 6; ++m) {
-    const v2d d = *reinterpret_cast<const v2d*>(col + 2 * m * (long long)g.pitch);
-    c[2 * m] = d.x;
-    c[2 * m + 1] = d.y;
-  }
-  return macro_coeffs(c);
-}
-
 // adjoint arrays are compact, in the lattice's layout
 struct LamAt {
   long long ps, cs;
@@ -606,28 +664,21 @@ __device__ __forceinline__ LamAt lam_at(const Geom& g) {
 
 // The step from the 37 stored populations of a padded buffer: gather, walls,
 // collide, coefficients out (296 bytes in, 120 out per site; runs once after
-// the state was replaced).  x wraps here, so the halo columns are not read.
+// the state was replaced).  It is launched on the host's guess: if the word
+// names coefficients, it gathers from those.
 template <bool kTape>
 __global__ __launch_bounds__(kThreads) void k_coeff_first(
     const double* __restrict__ src, double* __restrict__ dst, Geom gf, CGeom g, CPhys P, WallTable wt,
-    double* __restrict__ tape, int by, int bx, int nty, unsigned nb,
-    const unsigned* guard, unsigned* word) {
-  if (other_form(guard, kFormFull)) return;
-  set_form(word, kFormCoeff);
+    double* __restrict__ tape, int by, int bx, int nty, unsigned nb, const unsigned* word) {
+  set_form(dst, kFormCoeff);
   int x, y;
   if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
   double v[Q];
+  if (holds_coeffs(word)) {
+    gather_coeffs(coeffs(src), g, x, y, [&](int l, double f) { v[l] = f; });
+  } else {
 #pragma unroll
-  for (int l = 0; l < Q; ++l) {
-    int xs = x - EX[l], ys = y - EY[l];
-    xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
-    const bool outside = ys < 0 || ys >= g.ly;
-    if (g.periodic)
-      ys = ys < 0 ? ys + g.ly : (ys >= g.ly ? ys - g.ly : ys);
-    else if (outside)
-      ys = y;
-    v[l] = src[l * gf.ps + (long long)(xs + HX) * gf.cs + ys + gf.hy];
-    if (!g.periodic && outside) v[l] = 0.0;  // a wall supplies it
+    for (int l = 0; l < Q; ++l) v[l] = arriving(src, gf, g, x, y, l);
   }
   double a[NC];
   project_site<Forward>(v, a);
@@ -638,15 +689,15 @@ __global__ __launch_bounds__(kThreads) void k_coeff_first(
     store_tape(tape, S2, s, a);
   }
   collide_moments(a, P);
-  store_coeffs(dst, g, x, y, a);
+  store_coeffs(coeffs(dst), g, x, y, a);
 }
 
 // f^eq(rho0, u0, T0) as coefficients.
 __global__ __launch_bounds__(kThreads) void k_coeff_init(
     double* __restrict__ dst, const double* __restrict__ rho, const double* __restrict__ ux,
     const double* __restrict__ uy, const double* __restrict__ T, CGeom g, int by, int bx, int nty,
-    unsigned nb, unsigned* word) {
-  set_form(word, kFormCoeff);
+    unsigned nb) {
+  set_form(dst, kFormCoeff);
   int x, y;
   if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
   const long long s = (long long)x * g.ly + y;
@@ -660,95 +711,7 @@ __global__ __launch_bounds__(kThreads) void k_coeff_init(
     b[k] = scale * aeq[p][q];
   }
   add_tails(b);
-  store_coeffs(dst, g, x, y, b);
-}
-
-// Eq. (2) fields: twelve coefficients in, four values out (128 bytes per site).
-__global__ __launch_bounds__(kThreads) void k_coeff_moments(
-    const double* __restrict__ src, double* __restrict__ rho, double* __restrict__ ux,
-    double* __restrict__ uy, double* __restrict__ T, CGeom g, int by, int bx, int nty,
-    unsigned nb, const unsigned* guard) {
-  if (other_form(guard, kFormCoeff)) return;
-  int x, y;
-  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
-  const Macro m = load_macro(src, g, x, y);
-  const long long s = (long long)x * g.ly + y;
-  if (rho) rho[s] = m.rho;
-  if (ux) ux[s] = m.ux;
-  if (uy) uy[s] = m.uy;
-  if (T) T[s] = 1.0 + m.th;
-}
-
-__global__ __launch_bounds__(kThreads) void k_coeff_check(const double* __restrict__ src,
-                                                          unsigned* __restrict__ flag, CGeom g,
-                                                          int by, int bx, int nty, unsigned nb,
-                                                          const unsigned* guard) {
-  if (other_form(guard, kFormCoeff)) return;
-  int x, y;
-  if (!site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) return;
-  double b[NC], v[Q];
-  load_coeffs(src, g, x, y, b);
-  expand_site<Forward>(b, v);
-  bool bad = false;
-#pragma unroll
-  for (int l = 0; l < Q; ++l) bad |= !isfinite(v[l]);
-  const Macro m = load_macro(src, g, x, y);
-  bad |= !(m.rho > 0.0) || !(1.0 + m.th > 0.0);
-  if (bad) atomicAdd(flag, 1u);
-}
-
-// As k_obs_rows, from the coefficients.
-__global__ __launch_bounds__(kThreads) void k_coeff_obs_rows(const double* __restrict__ src,
-                                                             double* __restrict__ partial,
-                                                             CGeom g, int nchunks,
-                                                             const unsigned* guard) {
-  if (other_form(guard, kFormCoeff)) return;
-  const int y = blockIdx.x * kThreads + threadIdx.x;
-  const int c = blockIdx.y;
-  if (y >= g.ly) return;
-  const int x0 = int((long long)g.lx * c / nchunks), x1 = int((long long)g.lx * (c + 1) / nchunks);
-  double acc[kObservables] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int x = x0; x < x1; ++x) {
-    const Macro m = load_macro(src, g, x, y);
-    const double T = 1.0 + m.th;
-    acc[0] += m.rho;
-    acc[1] += m.ux;
-    acc[2] += m.uy;
-    acc[3] += T;
-    acc[4] += 0.5 * m.rho * (m.ux * m.ux + m.uy * m.uy);
-    acc[5] += m.rho * T;
-  }
-#pragma unroll
-  for (int k = 0; k < kObservables; ++k)
-    partial[((long long)c * kObservables + k) * g.ly + y] = acc[k];
-}
-
-// As k_loss_ke, from the coefficients.
-__global__ __launch_bounds__(kThreads) void k_coeff_loss_ke(const double* __restrict__ src,
-                                                            double* __restrict__ lambda,
-                                                            double* __restrict__ partials,
-                                                            CGeom g, Geom gf, int by, int bx,
-                                                            int nty, unsigned nb,
-                                                            const unsigned* guard) {
-  if (other_form(guard, kFormCoeff)) return;
-  int x, y;
-  double ke = 0.0;
-  if (site_of(g.lx, g.ly, by, bx, nty, nb, x, y)) {
-    const Macro m = load_macro(src, g, x, y);
-    const double u2 = m.ux * m.ux + m.uy * m.uy;
-    ke = 0.5 * m.rho * u2;
-    if (lambda) {
-      const LamAt la = lam_at(gf);
-      const long long s = x * la.cs + y;
-#pragma unroll
-      for (int l = 0; l < Q; ++l)
-        __builtin_nontemporal_store(R * (EX[l] * m.ux + EY[l] * m.uy) - 0.5 * u2,
-                                    &lambda[l * la.ps + s]);
-    }
-  }
-  const double tot = block_sum(ke);
-  if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+  store_coeffs(coeffs(dst), g, x, y, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -899,10 +862,11 @@ CGeom make_cgeom(const Geom& g, long long cached_from = kStepCachedFrom) {
   return c;
 }
 
-unsigned* word_of(void* buf) { return static_cast<unsigned*>(buf); }
-// the word to check where the host does not know the form
-const unsigned* guard_of(const void* buf, const Geom& g) {
-  return g.form == kFormUnknown ? static_cast<const unsigned*>(buf) : nullptr;
+// the word of a buffer whose form the host does not know
+const unsigned* word_of(const void* buf, const Geom& g) {
+  return g.form == kFormUnknown || g.form == kFormProbablyCoeff
+             ? static_cast<const unsigned*>(buf)
+             : nullptr;
 }
 
 // workgroups of a sweep with TX columns per wave
@@ -934,89 +898,63 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
   const CGeom g = make_cgeom(gf);
   const WallTable wt = make_walls(p);
   const CPhys cp = make_cphys(p);
-  const unsigned* guard = guard_of(src, gf);
+  const double* from = static_cast<const double*>(src);
+  double* to = static_cast<double*>(dst);
+  const unsigned* word = word_of(src, gf);
   if (gf.steps == 2 && two_steps_small(gf)) {
     // between walls 64 rows need no halo rows
     const bool one = !g.periodic && g.ly <= 64;
     const int rows = one ? 64 : kPairRows, halo = one ? 0 : kPairHalo;
     const int windows = (g.ly + rows - 1) / rows;
-    hipLaunchKernelGGL(k_coeff_two, dim3(windows * g.lx), dim3(64 * kSmallWaves), 0, s,
-                       coeffs(src), coeffs(dst), g, cp, wt, windows, rows, halo, word_of(dst));
+    hipLaunchKernelGGL(word ? k_coeff_two<true> : k_coeff_two<false>, dim3(windows * g.lx),
+                       dim3(64 * kSmallWaves), 0, s, from, to, gf, g, cp, wt, windows, rows, halo,
+                       word);
     return hipGetLastError();
   }
   if (gf.steps == 2) {
     const int windows = (g.ly + kPairRows - 1) / kPairRows;
     const int chunk = march_chunk(g.lx, windows, 512, kPairCols);
     const unsigned nb = unsigned(windows) * unsigned((g.lx + chunk - 1) / chunk);
-    hipLaunchKernelGGL(k_coeff_pair, dim3(nb), dim3(64 * 2 * kPairMakers), 0, s, coeffs(src),
-                       coeffs(dst), g, cp, wt, windows, chunk, nb, word_of(dst));
+    hipLaunchKernelGGL(word ? k_coeff_pair<true> : k_coeff_pair<false>, dim3(nb),
+                       dim3(64 * 2 * kPairMakers), 0, s, from, to, gf, g, cp, wt, windows, chunk, nb,
+                       word);
     return hipGetLastError();
   }
-  if (gf.form != kFormCoeff) {  // the populations are stored, or may be
+  if (gf.form == kFormFull || gf.form == kFormUnknown) {  // probably the populations
     const Tiling t = make_tiling(g.lx, g.ly);
-    auto run = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(t.nb), dim3(kThreads), 0, s,
-                         static_cast<const double*>(src), coeffs(dst), gf, g, cp, wt, tape, t.by, t.bx,
-                         t.nty, t.nb, guard, word_of(dst));
-    };
-    tape ? run(k_coeff_first<true>) : run(k_coeff_first<false>);
+    hipLaunchKernelGGL(tape ? k_coeff_first<true> : k_coeff_first<false>, dim3(t.nb),
+                       dim3(kThreads), 0, s, from, to, gf, g, cp, wt, tape, t.by, t.bx, t.nty, t.nb,
+                       word);
+    return hipGetLastError();
   }
-  if (gf.form != kFormFull) {
-    const int tx = sweep_columns(g);
-    const unsigned nb = sweep_grid(g, tx);
-    auto run = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * kWaves), 0, s, coeffs(src), coeffs(dst), g, cp, wt,
-                         tape, nb, guard, word_of(dst));
-    };
+  const int tx = sweep_columns(g);
+  const unsigned nb = sweep_grid(g, tx);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * kWaves), 0, s, from, to, gf, g, cp, wt, tape, nb,
+                       word);
+  };
+  const auto by_word = [&](auto either) {
+    constexpr bool e = decltype(either)::value;
     if (tx == 4)
-      tape ? run(k_coeff_step<4, 2, true>) : run(k_coeff_step<4, 2, false>);
+      tape ? run(k_coeff_step<4, 2, true, e>) : run(k_coeff_step<4, 2, false, e>);
     else if (tx == 3 && shallow_sweep(g))
-      tape ? run(k_coeff_step<3, 1, true>) : run(k_coeff_step<3, 1, false>);
+      tape ? run(k_coeff_step<3, 1, true, e>) : run(k_coeff_step<3, 1, false, e>);
     else if (tx == 3)
-      tape ? run(k_coeff_step<3, 2, true>) : run(k_coeff_step<3, 2, false>);
+      tape ? run(k_coeff_step<3, 2, true, e>) : run(k_coeff_step<3, 2, false, e>);
     else if (tx == 2)
-      tape ? run(k_coeff_step<2, 2, true>) : run(k_coeff_step<2, 2, false>);
+      tape ? run(k_coeff_step<2, 2, true, e>) : run(k_coeff_step<2, 2, false, e>);
     else
-      tape ? run(k_coeff_step<1, 2, true>) : run(k_coeff_step<1, 2, false>);
-  }
+      tape ? run(k_coeff_step<1, 2, true, e>) : run(k_coeff_step<1, 2, false, e>);
+  };
+  word ? by_word(std::true_type{}) : by_word(std::false_type{});
   return hipGetLastError();
 }
 
 hipError_t launch_coeff_init(void* dst, const double* rho, const double* ux, const double* uy,
                              const double* T, const Geom& gf, hipStream_t s) {
   const Tiling t = make_tiling(gf.lx, gf.ly);
-  hipLaunchKernelGGL(k_coeff_init, dim3(t.nb), dim3(kThreads), 0, s, coeffs(dst), rho, ux, uy, T,
-                     make_cgeom(gf), t.by, t.bx, t.nty, t.nb, word_of(dst));
-  return hipGetLastError();
-}
-
-hipError_t launch_coeff_moments(const void* src, double* rho, double* ux, double* uy, double* T,
-                                const Geom& gf, hipStream_t s) {
-  const Tiling t = make_tiling(gf.lx, gf.ly);
-  hipLaunchKernelGGL(k_coeff_moments, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src), rho, ux, uy,
-                     T, make_cgeom(gf), t.by, t.bx, t.nty, t.nb, guard_of(src, gf));
-  return hipGetLastError();
-}
-
-hipError_t launch_coeff_check(const void* src, unsigned* flag, const Geom& gf, hipStream_t s) {
-  const Tiling t = make_tiling(gf.lx, gf.ly);
-  hipLaunchKernelGGL(k_coeff_check, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src), flag,
-                     make_cgeom(gf), t.by, t.bx, t.nty, t.nb, guard_of(src, gf));
-  return hipGetLastError();
-}
-
-hipError_t launch_coeff_obs_rows(const void* src, double* partial, const Geom& gf, int nchunks,
-                                 hipStream_t s) {
-  hipLaunchKernelGGL(k_coeff_obs_rows, dim3(grid_1d(gf.ly), nchunks), dim3(kThreads), 0, s,
-                     coeffs(src), partial, make_cgeom(gf), nchunks, guard_of(src, gf));
-  return hipGetLastError();
-}
-
-hipError_t launch_coeff_loss_ke(const void* src, double* lambda, double* partials, const Geom& gf,
-                                hipStream_t s) {
-  const Tiling t = make_tiling(gf.lx, gf.ly);
-  hipLaunchKernelGGL(k_coeff_loss_ke, dim3(t.nb), dim3(kThreads), 0, s, coeffs(src), lambda,
-                     partials, make_cgeom(gf), gf, t.by, t.bx, t.nty, t.nb, guard_of(src, gf));
+  hipLaunchKernelGGL(k_coeff_init, dim3(t.nb), dim3(kThreads), 0, s, static_cast<double*>(dst),
+                     rho, ux, uy, T, make_cgeom(gf), t.by, t.bx, t.nty, t.nb);
   return hipGetLastError();
 }
 

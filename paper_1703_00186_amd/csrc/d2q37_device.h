@@ -50,17 +50,21 @@ struct Geom {
 
 // Storage form of a state buffer: the 37 populations of every padded site, or
 // (FP64, after a regularized collision) the 15 coefficients of every physical
-// site that generate them.  The buffer's first word, padding in both forms, names its
-// form for graphs recorded before the state was replaced; the host passes
-// what it knows in Geom::form, kFormUnknown where a graph may have run.
-// kFormCoeffWalls: a word
-// only, coefficients of which the walls were applied to afterwards (a scratch
-// buffer after bc; the wall temperatures follow in the buffer's header).
+// site that generate them.  An FP64 buffer's first word, padding in both forms,
+// names its form; every kernel that fills one writes it.  Only that word is
+// certain: a recorded graph may run at any time on the workspace it was recorded
+// on, whatever context that has by then.  So the host names a form (Geom::form)
+// only to the later launches of a call; to the first one it says kFormUnknown or
+// kFormProbablyCoeff, its guess, which at most decides which kernel looks.
 enum Form : int {
   kFormFull = 0,
   kFormCoeff = 1,
-  kFormUnknown = 2,
-  kFormCoeffWalls = 3
+  // a word only: coefficients of which the walls were applied to afterwards (a
+  // scratch buffer after bc; the wall temperatures follow in its header)
+  kFormCoeffWalls = 2,
+  // host only
+  kFormUnknown = 3,
+  kFormProbablyCoeff = 4
 };
 
 constexpr int NC = 15;  // coefficients of a site: degree i + j <= 4

@@ -546,8 +546,8 @@ __global__ __launch_bounds__(kThreads) void k_bc(S* buf, Geom g, Phys P, unsigne
 // rows that a gather reads (the first padding word names the buffer's form).
 template <class S>
 __global__ __launch_bounds__(kThreads) void k_halo_x(S* __restrict__ buf, Geom g,
-                                                     const unsigned* guard) {
-  if (other_form(guard, kFormFull)) return;
+                                                     const unsigned* word) {
+  if (holds_coeffs(word)) return;
   const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
   const int rows = g.ly + 6;  // all that a gather reads
   const long long per_l = 6LL * rows;
@@ -562,8 +562,8 @@ __global__ __launch_bounds__(kThreads) void k_halo_x(S* __restrict__ buf, Geom g
 // Halo rows (periodic y only): three rows below and above, all padded columns.
 template <class S>
 __global__ __launch_bounds__(kThreads) void k_halo_y(S* __restrict__ buf, Geom g,
-                                                     const unsigned* guard) {
-  if (other_form(guard, kFormFull)) return;
+                                                     const unsigned* word) {
+  if (holds_coeffs(word)) return;
   const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
   const long long per_l = 6LL * g.nx;
   if (i >= per_l * g.np) return;
@@ -637,6 +637,15 @@ __device__ __forceinline__ Macro site_macro(const S* __restrict__ src, const Geo
   return macro_from(rho_ref + a[0][0], a[1][0], a[0][1], a[2][0], a[0][2]);
 }
 
+// The same from a buffer in either form.
+template <class S, class A>
+__device__ __forceinline__ Macro macro_at(const S* __restrict__ src, const Geom& g, int x, int y,
+                                          double rho_ref, const unsigned* word) {
+  if constexpr (std::is_same<S, double>::value)
+    if (holds_coeffs(word)) return load_macro(coeffs(src), coeff_geom(g), x, y);
+  return site_macro<S, A>(src, g, padded<S>(g, x + HX, y + g.hy), rho_ref);
+}
+
 template <class S, class A>
 __global__ __launch_bounds__(kThreads) void k_moments(const S* __restrict__ src,
                                                       double* __restrict__ rho,
@@ -644,11 +653,10 @@ __global__ __launch_bounds__(kThreads) void k_moments(const S* __restrict__ src,
                                                       double* __restrict__ uy,
                                                       double* __restrict__ T, Geom g, Phys P,
                                                       int by, int bx, int nty, unsigned nb,
-                                                      const unsigned* guard) {
-  if (other_form(guard, kFormFull)) return;
+                                                      const unsigned* word) {
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
-  const Macro m = site_macro<S, A>(src, g, padded<S>(g, x + HX, y + g.hy), P.rho_ref);
+  const Macro m = macro_at<S, A>(src, g, x, y, P.rho_ref, word);
   const long long s = (long long)x * g.ly + y;
   if (rho) rho[s] = m.rho;
   if (ux) ux[s] = m.ux;
@@ -660,13 +668,18 @@ template <class S, class A>
 __global__ __launch_bounds__(kThreads) void k_check(const S* __restrict__ src,
                                                     unsigned int* __restrict__ flag, Geom g,
                                                     Phys P, int by, int bx, int nty,
-                                                    unsigned nb, const unsigned* guard) {
-  if (other_form(guard, kFormFull)) return;
+                                                    unsigned nb, const unsigned* word) {
   int x, y;
   if (!site_of(g, by, bx, nty, nb, x, y)) return;
   const long long site = padded<S>(g, x + HX, y + g.hy);
   bool bad = false;
-  if constexpr (is_local<A>) {
+  if (std::is_same<S, double>::value && holds_coeffs(word)) {
+    if constexpr (std::is_same<S, double>::value) {
+      double c[NC];
+      load_coeffs(coeffs(src), coeff_geom(g), x, y, c);
+      each_population(c, [&](int, double v) { bad |= !isfinite(v); });
+    }
+  } else if constexpr (is_local<A>) {
     double f[Q];
     load_local(src, g, site, f);
 #pragma unroll
@@ -675,7 +688,7 @@ __global__ __launch_bounds__(kThreads) void k_check(const S* __restrict__ src,
 #pragma unroll
     for (int l = 0; l < Q; ++l) bad |= !isfinite(double(src[l * g.ps + site]));
   }
-  const Macro m = site_macro<S, A>(src, g, site, P.rho_ref);
+  const Macro m = macro_at<S, A>(src, g, x, y, P.rho_ref, word);
   bad |= !(m.rho > 0.0) || !(1.0 + m.th > 0.0);
   if (bad) atomicAdd(flag, 1u);
 }
@@ -801,21 +814,19 @@ __global__ __launch_bounds__(kThreads) void k_loss_ke(const double* __restrict__
                                                       double* __restrict__ lambda,
                                                       double* __restrict__ partials, Geom g,
                                                       int by, int bx, int nty, unsigned nb,
-                                                      const unsigned* guard) {
-  if (other_form(guard, kFormFull)) return;
+                                                      const unsigned* word) {
   int x, y;
   const bool in = site_of(g, by, bx, nty, nb, x, y);
   double ke = 0.0;
   if (in) {
-    const Macro m = site_macro<double, double>(src, g, padded<double>(g, x + HX, y + g.hy), 0.0);
-    const double u2 = m.ux * m.ux + m.uy * m.uy;
-    ke = 0.5 * m.rho * u2;
+    const Macro m = macro_at<double, double>(src, g, x, y, 0.0, word);
+    ke = kinetic(m);
     if (lambda) {
       const LamStrides ls = lam_strides(g);
       const long long s = (long long)x * ls.cs + y;
 #pragma unroll
       for (int l = 0; l < Q; ++l)
-        lambda[l * ls.ps + s] = R * (EX[l] * m.ux + EY[l] * m.uy) - 0.5 * u2;
+        __builtin_nontemporal_store(kinetic_slope(m, l), &lambda[l * ls.ps + s]);
     }
   }
   const double tot = block_sum(ke);
@@ -1073,14 +1084,19 @@ template <class S, class A>
 __global__ __launch_bounds__(kThreads) void k_obs_rows(const S* __restrict__ src,
                                                        double* __restrict__ partial, Geom g,
                                                        Phys P, int nchunks,
-                                                       const unsigned* guard) {
-  if (other_form(guard, kFormFull)) return;
+                                                       const unsigned* word) {
   const int y = blockIdx.x * kThreads + threadIdx.x;
   const int c = blockIdx.y;
   if (y >= g.ly) return;
   const int x0 = int((long long)g.lx * c / nchunks), x1 = int((long long)g.lx * (c + 1) / nchunks);
   double acc[kObservables] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int x = x0; x < x1; ++x) {
+  int x = x0;
+  if constexpr (std::is_same<S, double>::value)
+    if (holds_coeffs(word)) {
+      sum_observables(coeffs(src), coeff_geom(g), y, x0, x1, acc);
+      x = x1;
+    }
+  for (; x < x1; ++x) {
     const Macro m = site_macro<S, A>(src, g, (long long)(x + HX) * g.cs + (y + g.hy), P.rho_ref);
     const double T = 1.0 + m.th;
     acc[0] += m.rho;
@@ -1165,11 +1181,6 @@ hipError_t by_precision(int prec, Fn fn) {
   return hipGetLastError();
 }
 
-// the word to check where the host does not know a buffer's form
-static const unsigned* guard_of(const void* buf, const Geom& g) {
-  return g.form == kFormUnknown ? static_cast<const unsigned*>(buf) : nullptr;
-}
-
 // the word of a buffer that may hold coefficients
 static const unsigned* word_of(const void* buf, const Geom& g) {
   return g.form == kFormFull ? nullptr : static_cast<const unsigned*>(buf);
@@ -1187,14 +1198,14 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
 hipError_t launch_halo(void* buf, const Geom& g, int prec, hipStream_t s) {
   if (g.form == kFormCoeff) return hipSuccess;  // that form has no halos
   const long long nx_el = 6LL * (g.ly + 6) * g.np, ny_el = 6LL * g.nx * g.np;
-  const unsigned* guard = guard_of(buf, g);
+  const unsigned* word = word_of(buf, g);
   return by_precision(prec, [&](auto sv, auto) {
     using S = decltype(sv);
     hipLaunchKernelGGL(k_halo_x<S>, dim3(grid_1d(nx_el)), dim3(kThreads), 0, s,
-                       static_cast<S*>(buf), g, guard);
+                       static_cast<S*>(buf), g, word);
     if (!g.walls)
       hipLaunchKernelGGL(k_halo_y<S>, dim3(grid_1d(ny_el)), dim3(kThreads), 0, s,
-                         static_cast<S*>(buf), g, guard);
+                         static_cast<S*>(buf), g, word);
   });
 }
 
@@ -1317,16 +1328,12 @@ hipError_t launch_init_feq(void* dst, const double* rho, const double* ux, const
 
 hipError_t launch_moments(const void* src, double* rho, double* ux, double* uy, double* T,
                           const Geom& g, const Phys& p, int prec, hipStream_t s) {
-  if (g.form != kFormFull) {
-    const hipError_t e = launch_coeff_moments(src, rho, ux, uy, T, g, s);
-    if (e != hipSuccess || g.form == kFormCoeff) return e;
-  }
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto av) {
     using S = decltype(sv);
     hipLaunchKernelGGL((k_moments<S, decltype(av)>), dim3(t.nb), dim3(kThreads), 0, s,
                        static_cast<const S*>(src), rho, ux, uy, T, g, p, t.by, t.bx, t.nty,
-                       t.nb, guard_of(src, g));
+                       t.nb, word_of(src, g));
   });
 }
 
@@ -1371,16 +1378,12 @@ hipError_t launch_populations_f64(const void* padded_buf, double* out, const Geo
 
 hipError_t launch_check(const void* src, unsigned int* flag, const Geom& g, const Phys& p,
                         int prec, hipStream_t s) {
-  if (g.form != kFormFull) {
-    const hipError_t e = launch_coeff_check(src, flag, g, s);
-    if (e != hipSuccess || g.form == kFormCoeff) return e;
-  }
   const Tiling t = make_tiling(g.lx, g.ly);
   return by_precision(prec, [&](auto sv, auto av) {
     using S = decltype(sv);
     hipLaunchKernelGGL((k_check<S, decltype(av)>), dim3(t.nb), dim3(kThreads), 0, s,
                        static_cast<const S*>(src), flag, g, p, t.by, t.bx, t.nty, t.nb,
-                       guard_of(src, g));
+                       word_of(src, g));
   });
 }
 
@@ -1390,14 +1393,11 @@ hipError_t launch_observables(const void* src, double* partial, double* profiles
                               double* scalars, const Geom& g, const Phys& p, int prec,
                               double t_bottom, double t_top, hipStream_t s) {
   const int nc = observable_chunks(g);
-  hipError_t e = hipSuccess;
-  if (g.form != kFormFull) e = launch_coeff_obs_rows(src, partial, g, nc, s);
-  if (e == hipSuccess && g.form != kFormCoeff)
-    e = by_precision(prec, [&](auto sv, auto av) {
-      using S = decltype(sv);
-      hipLaunchKernelGGL((k_obs_rows<S, decltype(av)>), dim3(grid_1d(g.ly), nc), dim3(kThreads),
-                         0, s, static_cast<const S*>(src), partial, g, p, nc, guard_of(src, g));
-    });
+  hipError_t e = by_precision(prec, [&](auto sv, auto av) {
+    using S = decltype(sv);
+    hipLaunchKernelGGL((k_obs_rows<S, decltype(av)>), dim3(grid_1d(g.ly), nc), dim3(kThreads), 0, s,
+                       static_cast<const S*>(src), partial, g, p, nc, word_of(src, g));
+  });
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_obs_reduce, dim3(grid_1d((long long)kObservables * g.ly)), dim3(kThreads),
                      0, s, partial, profiles, g.lx, g.ly, nc);
@@ -1413,14 +1413,10 @@ int loss_ke_blocks(const Geom& g) { return int(make_tiling(g.lx, g.ly).nb); }
 hipError_t launch_loss_ke(const void* src, double* ke, double* lambda, double* partials,
                           const Geom& g, hipStream_t s) {
   const Tiling t = make_tiling(g.lx, g.ly);
-  hipError_t e = hipSuccess;
-  if (g.form != kFormFull) e = launch_coeff_loss_ke(src, lambda, partials, g, s);
-  if (e == hipSuccess && g.form != kFormCoeff) {
-    hipLaunchKernelGGL(k_loss_ke, dim3(t.nb), dim3(kThreads), 0, s,
-                       static_cast<const double*>(src), lambda, partials, g, t.by, t.bx, t.nty,
-                       t.nb, guard_of(src, g));
-    e = hipGetLastError();
-  }
+  hipLaunchKernelGGL(k_loss_ke, dim3(t.nb), dim3(kThreads), 0, s,
+                     static_cast<const double*>(src), lambda, partials, g, t.by, t.bx, t.nty, t.nb,
+                     word_of(src, g));
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_sum, dim3(1), dim3(kThreads), 0, s, partials, int(t.nb), ke);
   return hipGetLastError();

@@ -1,12 +1,11 @@
 // Host-side launchers of the D2Q37 kernels (implemented in d2q37_kernels.hip;
 // launch_coeff_* in d2q37_coeff.hip, reached through the others).
 // Every launcher enqueues on the given stream and returns the launch status.
-// Geom::form is the storage form of the state buffer that is read: with
-// kFormUnknown the kernels of both forms are enqueued and the device word
-// decides.  launch_init_feq writes the form it names, launch_fused always the
-// coefficient form for regularized FP64 and the populations otherwise; the
-// split stages read either and write populations (launch_bc marks coefficients
-// instead).
+// Geom::form is the storage form of the state buffer that is read; where it is
+// kFormUnknown or kFormProbablyCoeff the kernels look at the buffer's word.
+// launch_init_feq writes the form it names, launch_fused always the coefficient
+// form for regularized FP64 and the populations otherwise; the split stages read
+// either and write populations (launch_bc marks coefficients instead).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -161,13 +160,6 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& g, const Ph
                              double* tape, hipStream_t s);
 hipError_t launch_coeff_init(void* dst, const double* rho, const double* ux, const double* uy,
                              const double* T, const Geom& g, hipStream_t s);
-hipError_t launch_coeff_moments(const void* src, double* rho, double* ux, double* uy, double* T,
-                                const Geom& g, hipStream_t s);
-hipError_t launch_coeff_check(const void* src, unsigned* flag, const Geom& g, hipStream_t s);
-hipError_t launch_coeff_obs_rows(const void* src, double* partial, const Geom& g, int nchunks,
-                                 hipStream_t s);
-hipError_t launch_coeff_loss_ke(const void* src, double* lambda, double* partials, const Geom& g,
-                                hipStream_t s);
 hipError_t launch_coeff_adjoint_mu(const double* tape, const double* in, bool from_compact,
                                    double* mu_out, const Geom& g, const Phys& p, hipStream_t s);
 hipError_t launch_coeff_adjoint_gather(const double* mu, double* lam, const Geom& g,

@@ -100,13 +100,10 @@ __device__ __forceinline__ double block_sum(double v) {
   return red[0];
 }
 
-// A kernel launched for one storage form of a buffer whose form the host does
-// not know returns at once if the buffer's first word names the other.
-__device__ __forceinline__ bool other_form(const unsigned* word, Form f) {
-  return word && *word != unsigned(f);
+// What a buffer holds, by its first word (null: as the kernel expects).
+__device__ __forceinline__ bool holds_populations(const unsigned* word) {
+  return word && *word == unsigned(kFormFull);
 }
-// Whether the buffer of this word (null: known to hold populations) holds
-// coefficients.
 __device__ __forceinline__ bool holds_coeffs(const unsigned* word) {
   return word && (*word == unsigned(kFormCoeff) || *word == unsigned(kFormCoeffWalls));
 }

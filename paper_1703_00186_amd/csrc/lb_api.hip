@@ -27,10 +27,8 @@ struct lb_ctx {
   double* partials;
   double* obs;  // observable scratch (chunk partials | profiles | scalars)
   unsigned int* flag;
-  int a_form;          // storage form of A (d2q37::Form); B's is in its first
-                       // word, which every kernel that fills it writes
-  bool captured;       // a graph recorded on this context may have run: the
-                       // forms are then known only to the device
+  int a_form;  // storage form of A (d2q37::Form), within a call; at its start
+               // a guess.  B's is always read from its word
   bool halos_valid;
   long long steps_since_check;
 };
@@ -230,17 +228,16 @@ int check_ctx(lb_ctx* ctx) {
   return LB_OK;
 }
 
-// check_ctx for the calls that read or write the state buffers: what the host
-// knows about their forms holds unless a recorded graph may run in between.
+// check_ctx for the calls that read or write the state buffers.  Between two
+// calls any graph recorded on this workspace may run, also one that another
+// context recorded; so what the last call left in an FP64 buffer is a guess.
 int enter(lb_ctx* ctx) {
   const int rc = check_ctx(ctx);
   if (rc) return rc;
-  // work recorded into a graph runs whenever the graph does
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &status) != hipSuccess) (void)hipGetLastError();
-  if (status == hipStreamCaptureStatusActive) ctx->captured = true;
-  if (ctx->captured && ctx->prec == LB_FP64)
-    ctx->a_form = d2q37::kFormUnknown;
+  if (ctx->prec == LB_FP64) {
+    const bool coeff = ctx->a_form == d2q37::kFormCoeff || ctx->a_form == d2q37::kFormProbablyCoeff;
+    ctx->a_form = coeff ? d2q37::kFormProbablyCoeff : d2q37::kFormUnknown;
+  }
   return LB_OK;
 }
 
@@ -320,8 +317,9 @@ int run_steps(lb_ctx* c, int n) {
   const bool pairs = c->par.kernel == LB_KERNEL_FUSED && c->par.check_finite == 0 &&
                      d2q37::two_steps_pay(c->g, c->prec, c->par.regularize);
   for (int i = 0; i < n;) {
-    // two steps read their own form, plain BGK's either
-    const bool ready = coeff_step(c) ? c->a_form == d2q37::kFormCoeff : true;
+    // two regularized steps start from populations only if the guess was wrong
+    const bool ready = !coeff_step(c) || c->a_form == d2q37::kFormCoeff ||
+                       c->a_form == d2q37::kFormProbablyCoeff;
     if (pairs && ready && n - i > 4) {
       int rc = fused_steps(c, 2, nullptr);
       if (rc == LB_OK) rc = fused_steps(c, 2, nullptr);
@@ -333,6 +331,16 @@ int run_steps(lb_ctx* c, int n) {
       ++i;
     }
   }
+  return LB_OK;
+}
+
+int observables(lb_ctx* c, double* profiles, double* scalars) {
+  const size_t prof = size_t(d2q37::kObservables) * size_t(c->g.ly);
+  double* own_prof = c->obs + size_t(d2q37::observable_chunks(c->g)) * prof;
+  LB_HIP(d2q37::launch_observables(c->A, c->obs, profiles ? profiles : own_prof, scalars,
+                                   with_form(c->g, c->a_form), c->p, c->prec, c->par.t_bottom,
+                                   c->par.t_top, c->stream),
+         "observables");
   return LB_OK;
 }
 
@@ -455,7 +463,6 @@ int lb_init(const lb_lattice* lat, const lb_params* par, void* workspace, size_t
                                             observable_bytes(c->g));
   c->halos_valid = false;
   c->steps_since_check = 0;
-  c->captured = false;
   c->a_form = d2q37::kFormFull;
   hipError_t e = hipSuccess;
   if (c->prec == LB_FP64 && par->regularize && par->kernel == LB_KERNEL_FUSED) {
@@ -613,16 +620,8 @@ int lb_set_scratch(lb_ctx* ctx, const void* f) {
 }
 
 int lb_observables(lb_ctx* ctx, double* profiles, double* scalars) {
-  int rc = enter(ctx);
-  if (rc) return rc;
-  const size_t prof = size_t(d2q37::kObservables) * size_t(ctx->g.ly);
-  double* partial = ctx->obs;
-  double* own_prof = ctx->obs + size_t(d2q37::observable_chunks(ctx->g)) * prof;
-  LB_HIP(d2q37::launch_observables(ctx->A, partial, profiles ? profiles : own_prof, scalars,
-                                   with_form(ctx->g, ctx->a_form), ctx->p, ctx->prec, ctx->par.t_bottom, ctx->par.t_top,
-                                   ctx->stream),
-         "observables");
-  return LB_OK;
+  const int rc = enter(ctx);
+  return rc ? rc : observables(ctx, profiles, scalars);
 }
 
 int lb_run_observed(lb_ctx* ctx, int n, int every, double* series) {
@@ -633,7 +632,7 @@ int lb_run_observed(lb_ctx* ctx, int n, int every, double* series) {
   for (int k = 0; k < n / every; ++k) {
     rc = run_steps(ctx, every);
     if (rc) return rc;
-    rc = lb_observables(ctx, nullptr, series + size_t(k) * d2q37::kObservableScalars);
+    rc = observables(ctx, nullptr, series + size_t(k) * d2q37::kObservableScalars);
     if (rc) return rc;
   }
   return run_steps(ctx, n % every);

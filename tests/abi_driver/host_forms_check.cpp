@@ -18,8 +18,11 @@ hipError_t line(const std::string& what) {
   return hipSuccess;
 }
 std::string read(const char* what, const d2q37::Geom& g) {
-  static const char* const names[] = {"full", "coeff", "unknown"};
-  return std::string(what) + " " + names[g.form];
+  const char* form = g.form == d2q37::kFormFull        ? "full"
+                     : g.form == d2q37::kFormCoeff     ? "coeff"
+                     : g.form == d2q37::kFormUnknown   ? "unknown"
+                                                       : "probably coeff";
+  return std::string(what) + " " + form;
 }
 }  // namespace
 
@@ -160,9 +163,78 @@ void plain_bgk_after_a_recording() {
   }
 }
 
+// The first launch of every call that reads an FP64 buffer has to look at its
+// word: a graph may have run since the last call, whatever context recorded it.
+void no_form_is_kept_between_calls() {
+  using Strings = std::vector<std::string>;
+  const auto enqueues = [](const char* what, int rc, const Strings& want) {
+    if (rc != LB_OK || lines != want) {
+      ++failures;
+      std::printf("%s (status %d) enqueues", what, rc);
+      for (const std::string& s : lines) std::printf(", %s", s.c_str());
+      std::printf(" instead of");
+      for (const std::string& s : want) std::printf(", %s", s.c_str());
+      std::printf("\n");
+    }
+    lines.clear();
+  };
+  double d[8] = {};
+  for (int state : {0, 1, 2, 3}) {  // what the calls before left: start, steps, set_state, collide
+    for (int reg : {1, 0}) {
+      Lattice l(reg);
+      const std::string guess = reg && state < 2 ? " probably coeff" : " unknown";
+      if (state == 1) lb_step(l.ctx, 2);
+      if (state == 2) lb_set_state(l.ctx, d);
+      if (state == 3) lb_collide(l.ctx);
+      lines.clear();
+      enqueues("get_state", lb_get_state(l.ctx, d), {"pack" + guess});
+      enqueues("populations", lb_get_populations(l.ctx, d), {"populations" + guess});
+      enqueues("moments", lb_moments(l.ctx, d, d, d, d), {"moments" + guess});
+      enqueues("observables", lb_observables(l.ctx, nullptr, d), {"observables" + guess});
+      enqueues("loss_ke", lb_loss_ke(l.ctx, d, nullptr), {"loss" + guess});
+      enqueues("halo", lb_halo(l.ctx), {"halo" + guess});
+      enqueues("propagate", lb_propagate(l.ctx), {"propagate" + guess});
+      enqueues("bc", lb_bc(l.ctx), {"bc unknown"});
+      enqueues("get_scratch", lb_get_scratch(l.ctx, d), {"pack unknown"});
+      const std::string then = reg ? " coeff" : " full";
+      enqueues("step", lb_step(l.ctx, 2), {"step" + guess, "step" + then});
+      enqueues("step_record", lb_step_record(l.ctx, 2, d),
+               {reg ? "step probably coeff" : "step unknown", "step" + then});
+      enqueues("run_observed", lb_run_observed(l.ctx, 2, 1, d),
+               {reg ? "step probably coeff" : "step unknown", "observables" + then,
+                "step" + then, "observables" + then});
+      enqueues("collide", lb_collide(l.ctx), {"collide unknown"});
+      l.set(reg, LB_KERNEL_SPLIT);
+      enqueues("split step", lb_step(l.ctx, 1),
+               {"halo unknown", "propagate unknown", "bc full", "collide full"});
+      l.init();  // restarted on its workspace
+      lines.clear();
+      enqueues("get_state", lb_get_state(l.ctx, d), {"pack unknown"});
+    }
+  }
+  {
+    Lattice l(1, 1000, 1000);  // two steps per launch
+    lines.clear();
+    enqueues("five steps", lb_step(l.ctx, 5),
+             {"two steps probably coeff", "two steps coeff", "step coeff"});
+    lb_set_state(l.ctx, d);
+    lines.clear();
+    enqueues("six steps", lb_step(l.ctx, 6),
+             {"step unknown", "two steps coeff", "two steps coeff", "step coeff"});
+    Lattice p(0, 1000, 1000);
+    lines.clear();
+    enqueues("five plain BGK steps", lb_step(p.ctx, 5),
+             {"two steps unknown", "two steps full", "step full"});
+    Lattice f(1, 40, 30, LB_FP32_SHIFTED);  // always populations
+    lines.clear();
+    enqueues("FP32", lb_step(f.ctx, 1) | lb_get_state(f.ctx, d), {"step full", "pack full"});
+  }
+}
+
 }  // namespace
 
 int main() {
+  no_form_is_kept_between_calls();
   plain_bgk_after_a_recording();
   std::printf("%d failure(s)\n", failures);
   return failures != 0;

@@ -188,3 +188,109 @@ def test_tape_of_bgk_from_either_form():
         lb.step_record(3, t)
     assert torch.equal(ta, tb)
     assert torch.equal(a.get_state(), b.get_state())
+
+
+# -- restarts --------------------------------------------------------------------
+
+SHAPES = [(LX, LY), (600, 520), (200, 130), (400, 300)]  # each choice of step kernel
+
+
+@pytest.mark.parametrize("layout", ["column", "soa"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_recorded_graph_after_a_restart(shape, layout):
+    """A graph stays valid when its lattice is restarted: it finds the new
+    populations or the new equilibrium, and every reader its result."""
+    a, b = (make(*shape, layout=layout) for _ in range(2))
+    g = a.capture(6)
+    f = fields(*shape, seed=5)
+    state = noisy(b)
+
+    def both():
+        assert torch.equal(a.get_state(), b.get_state())
+        assert torch.equal(a.populations(), b.populations())
+        for x, y in zip(a.moments() + a.observables(), b.moments() + b.observables()):
+            assert torch.equal(x, y)
+        (ka, la), (kb, lb_) = a.loss_ke(), b.loss_ke()
+        assert torch.equal(ka, kb) and torch.equal(la, lb_)
+
+    for n in (1, 2, 5, 6):  # eager steps that follow
+        for lb in (a, b):
+            lb.reinit(*f)
+            lb.set_state(state)
+        g.replay()
+        b.step(6)
+        both()
+        assert torch.equal(a.get_scratch(), b.get_scratch())
+        a.step(n)
+        for _ in range(n):
+            b.step(1)
+        both()
+        for lb in (a, b):
+            lb.reinit(*f)
+        g.replay()
+        b.step(6)
+        both()
+    tape = [lb.new_tape(2) for lb in (a, b)]
+    for lb, t in zip((a, b), tape):
+        lb.reinit(*f)
+        lb.set_state(state)
+    g.replay()
+    b.step(6)
+    a.step_record(2, tape[0])
+    b.step_record(2, tape[1])
+    assert torch.equal(tape[0], tape[1])
+    both()
+
+
+def test_recorded_graph_after_other_parameters_and_a_restart():
+    """Recorded with the projection, replayed on a lattice restarted without."""
+    a, b = make(), make()
+    g = a.capture(2)
+    f = fields(seed=5)
+    for lb in (a, b):
+        lb.set_params(regularize=0)
+        lb.reinit(*f)
+    g.replay()
+    b.set_params(regularize=1)
+    b.step(2)
+    b.set_params(regularize=0)
+    assert close(a.get_state(), b.get_state())
+    for x, y in zip(a.moments() + a.observables(), b.moments() + b.observables()):
+        assert close(x, y)
+    a.step(3)
+    b.step(3)
+    assert close(a.get_state(), b.get_state())
+    a.set_params(check_finite=1)
+    a.step(1)  # raises if it misreads the state
+
+
+def test_state_replaced_inside_a_graph():
+    """The state is replaced, or the lattice restarted, by the graph itself."""
+    a, b = make(), make()
+    state = noisy(b)
+    f = [torch.as_tensor(v, device="cuda") for v in fields(seed=5)]
+    a.step(2)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        a.set_state(state)
+    h = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(h):
+        a.reinit(*f)
+    torch.cuda.synchronize()
+    for _ in range(2):
+        a.reinit(*f)
+        a.step(2)
+        g.replay()
+        b.set_state(state)
+        assert torch.equal(a.get_state(), state)
+        a.step(4)
+        b.step(4)
+        assert torch.equal(a.get_state(), b.get_state())
+        a.set_state(state)
+        h.replay()
+        b.reinit(*f)
+        assert torch.equal(a.get_state(), b.get_state())
+        a.step(4)
+        b.step(4)
+        assert torch.equal(a.get_state(), b.get_state())
