@@ -42,14 +42,11 @@ namespace d2q37 {
 
 namespace {
 
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kHalo = 4;             // halo rows on each side of a wave
 constexpr int kRows = 64 - 2 * kHalo;  // target rows of a wave
 constexpr int kWaves = 4;            // waves per workgroup (independent)
-constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit buffer, gfx9 family
-constexpr int kNonTemporal = 2;           // cache policy bits of a streaming access
 // States from these sizes to kCachedTo are stored into the caches (us per step,
 // streamed and cached).  Steps: 331 x 331 7.1 and 8.3, 512 x 512 15.8 and 16.8,
 // 560 x 560 19.4 and 18.9, 700 x 700 26.9 and 24.3, 1000 x 1000 43.4 and 39.6
@@ -862,13 +859,6 @@ CGeom make_cgeom(const Geom& g, long long cached_from = kStepCachedFrom) {
   return c;
 }
 
-// the word of a buffer whose form the host does not know
-const unsigned* word_of(const void* buf, const Geom& g) {
-  return g.form == kFormUnknown || g.form == kFormProbablyCoeff
-             ? static_cast<const unsigned*>(buf)
-             : nullptr;
-}
-
 // workgroups of a sweep with TX columns per wave
 unsigned sweep_grid(const CGeom& g, int tx) {
   const long long waves = (long long)g.nw * ((g.lx + tx - 1) / tx);
@@ -900,7 +890,7 @@ hipError_t launch_coeff_step(const void* src, void* dst, const Geom& gf, const P
   const CPhys cp = make_cphys(p);
   const double* from = static_cast<const double*>(src);
   double* to = static_cast<double*>(dst);
-  const unsigned* word = word_of(src, gf);
+  const unsigned* word = word_if_unsure(src, gf);
   if (gf.steps == 2 && two_steps_small(gf)) {
     // between walls 64 rows need no halo rows
     const bool one = !g.periodic && g.ly <= 64;

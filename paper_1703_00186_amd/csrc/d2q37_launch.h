@@ -1,5 +1,6 @@
 // Host-side launchers of the D2Q37 kernels (implemented in d2q37_kernels.hip;
-// launch_coeff_* in d2q37_coeff.hip, reached through the others).
+// launch_coeff_* in d2q37_coeff.hip and launch_fused_pair in d2q37_pair.hip,
+// reached through the others).
 // Every launcher enqueues on the given stream and returns the launch status.
 // Geom::form is the storage form of the state buffer that is read; where it is
 // kFormUnknown or kFormProbablyCoeff the kernels look at the buffer's word.
@@ -153,6 +154,10 @@ hipError_t launch_zero_pad_rows(void* buf, const Geom& g, int prec, hipStream_t 
 hipError_t launch_init_adjoint(const double* lam0, const double* rho, const double* ux,
                                const double* uy, const double* T, double* drho, double* dux,
                                double* duy, double* dT, const Geom& g, hipStream_t s);
+
+// launch_fused's two steps from and to populations (d2q37_pair.hip).
+hipError_t launch_fused_pair(const void* src, void* dst, const Geom& g, const Phys& p, int prec,
+                             int regularize, hipStream_t s);
 
 // The coefficient form's kernels (d2q37_coeff.hip), FP64.  A buffer in that
 // form takes less than half of the padded populations' bytes.

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
+#include <type_traits>
 
 #include "d2q37_device.h"
 
@@ -12,6 +14,11 @@ namespace d2q37 {
 
 constexpr int kThreads = 256;
 constexpr int kXcds = 8;
+
+// buffer instructions
+constexpr int kBufferWord3 = 0x00020000;  // raw 32-bit buffer, gfx9 family
+constexpr int kNonTemporal = 2;           // cache policy bits of a streaming access
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
 struct Tiling {
   int by, bx;    // tile shape (rows, columns)
@@ -37,6 +44,16 @@ inline Tiling make_tiling(int lx, int ly) {
 // name their lines and what they measured there.
 inline bool streams_output(long long buffer_bytes, long long cached_from, long long cached_to) {
   return buffer_bytes < cached_from || buffer_bytes > cached_to;
+}
+
+// Populations: us per step, streamed and cached, of FP32 with the FP32 collision
+// 360 x 360 13.4 and 14.2, 400 x 400 18.7 and 16.7, 512 x 512 21.5 and 18.4,
+// 700 x 700 37.2 and 31.0, 1000 x 1000 65 and 64, 1200 x 1200 88 and 94; plain
+// FP64 BGK 280 x 280 15.6 and 13.0, 512 x 512 31.5 and 25.2, 700 x 700 56.0 and
+// 50.7, 850 x 850 80.5 and 88.3.
+inline bool streams_populations(const Geom& g, size_t elem_bytes) {
+  return streams_output((long long)g.np * g.nx * g.ny * (long long)elem_bytes,
+                        21LL * 1000 * 1000, 156LL * 1000 * 1000);
 }
 
 // Columns of a workgroup that makes two steps of a window of rows, `cols`
@@ -110,6 +127,26 @@ __device__ __forceinline__ bool holds_coeffs(const unsigned* word) {
 __device__ __forceinline__ void set_form(void* buf, Form f) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
     *static_cast<unsigned*>(buf) = unsigned(f);
+}
+
+// Names the form of an FP64 buffer that a kernel fills with populations.
+template <class S>
+__device__ __forceinline__ void set_full(S* buf) {
+  if constexpr (std::is_same<S, double>::value) set_form(buf, kFormFull);
+}
+
+__device__ __forceinline__ bool on_wall_rows(const Geom& g, int y) {
+  return g.walls && (y < 3 || y >= g.ly - 3);
+}
+
+// The word by which a kernel tells what a buffer holds: null if populations are
+// certain ...
+inline const unsigned* word_of(const void* buf, const Geom& g) {
+  return g.form == kFormFull ? nullptr : static_cast<const unsigned*>(buf);
+}
+// ... or if either form is.
+inline const unsigned* word_if_unsure(const void* buf, const Geom& g) {
+  return g.form == kFormCoeff ? nullptr : word_of(buf, g);
 }
 
 }  // namespace d2q37

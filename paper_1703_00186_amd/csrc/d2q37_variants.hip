@@ -372,7 +372,7 @@ hipError_t launch_propagate_variant(const void* src, void* dst, const Geom& g, i
     using S = decltype(sv);
     const S* a = static_cast<const S*>(src);
     S* b = static_cast<S*>(dst);
-    const unsigned* word = g.form == kFormFull ? nullptr : static_cast<const unsigned*>(src);
+    const unsigned* word = word_of(src, g);
     if (variant == kPropagateLds) {
       const int nty = int(blocks(g.ly, kVThreads));
       hipLaunchKernelGGL(k_propagate_lds<S>, dim3(unsigned(g.lx) * unsigned(nty)),
@@ -399,7 +399,7 @@ hipError_t launch_collide_mfma(const void* src, void* dst, const Geom& g, const 
   const unsigned grid = blocks((long long)g.lx * nyb, kVThreads / 64);
   const double* a = static_cast<const double*>(src);
   double* b = static_cast<double*>(dst);
-  const unsigned* word = g.form == kFormFull ? nullptr : static_cast<const unsigned*>(src);
+  const unsigned* word = word_of(src, g);
   hipLaunchKernelGGL(regularize ? k_collide_mfma<true> : k_collide_mfma<false>, dim3(grid),
                      dim3(kVThreads), 0, s, a, b, g, p, nyb, word);
   if (word) {
