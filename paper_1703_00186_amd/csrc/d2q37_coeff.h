@@ -320,9 +320,10 @@ __device__ __forceinline__ void each_population(const double (&c)[NC], const Fn&
 }
 
 // A site that bc was applied to after its coefficients were stored (a scratch
-// buffer): the temperature of its wall.
-__device__ __forceinline__ bool walls_since(const void* buf, const Geom& g, int y, double& th) {
-  if (*static_cast<const unsigned*>(buf) != unsigned(kFormCoeffWalls)) return false;
+// buffer, word form): the temperature of its wall.
+__device__ __forceinline__ bool walls_since(const void* buf, unsigned form, const Geom& g, int y,
+                                            double& th) {
+  if (form != unsigned(kFormCoeffWalls)) return false;
   th = static_cast<const double*>(buf)[y < 3 ? 1 : 2];
   return y < 3 || y >= g.ly - 3;
 }
@@ -333,7 +334,8 @@ __device__ __forceinline__ void scratch_site(const void* buf, const Geom& g, int
   double c[NC], th;
   load_coeffs(coeffs(buf), coeff_geom(g), x, y, c);
   expand_site<Forward>(c, v);
-  if (walls_since(buf, g, y, th)) wall_site<double>(v, y, g.ly, th, th, 0.0);
+  if (walls_since(buf, *static_cast<const unsigned*>(buf), g, y, th))
+    wall_site<double>(v, y, g.ly, th, th, 0.0);
 }
 
 // Population l of a site.

@@ -594,14 +594,14 @@ __global__ __launch_bounds__(64 * kSmallWaves) void k_coeff_two(
       xs = xs < 0 ? xs + g.lx : (xs >= g.lx ? xs - g.lx : xs);
       load_column(column_rsrc(coeffs(src), g, xs), g, row.load, v);
     };
+    double c[2][NC];
+    load(0, c[0]);
+    load(1, c[1]);
     PairWalk<1, 2> s{g, P, wt, row};
     if (kEither && holds_populations(word)) {
       const int xw = x - 3 + wave;
       s.from_populations(src, gf, xw < 0 ? xw + g.lx : (xw >= g.lx ? xw - g.lx : xw));
     } else {
-      double c[2][NC];
-      load(0, c[0]);
-      load(1, c[1]);
       s.walk(c, load);
     }
     if (!g.periodic && !row.in) {  // nothing comes from beyond the walls

@@ -117,6 +117,11 @@ __device__ __forceinline__ double block_sum(double v) {
   return red[0];
 }
 
+// Loads before this are issued before the word is read, whose latency then
+// passes beside theirs; they are of what the buffer probably holds, and within
+// it in either form.
+__device__ __forceinline__ void loads_before_word() { asm volatile("" ::: "memory"); }
+
 // What a buffer holds, by its first word (null: as the kernel expects).
 __device__ __forceinline__ bool holds_populations(const unsigned* word) {
   return word && *word == unsigned(kFormFull);

@@ -17,6 +17,7 @@
 // sums; these kernels are the alternatives that choice is measured against.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "d2q37_coeff.h"
@@ -28,10 +29,14 @@ namespace {
 
 constexpr int kVThreads = 256;
 
-// From coefficients (a fused step's result) both kernels gather as k_propagate
-// does, their threads taking one site after the other.
-__device__ __forceinline__ void propagate_coeffs(const double* __restrict__ src,
-                                                 double* __restrict__ dst, const Geom& g) {
+// From coefficients (a fused step's result) both kernels read what is no
+// population, within the buffer; this one, launched after them where the host
+// does not know the form, then gathers as k_propagate does.  Few workgroups, which
+// mostly find nothing to do: the branch inside the kernels cost them 3 %.
+__global__ __launch_bounds__(kVThreads) void k_propagate_coeffs(const double* __restrict__ src,
+                                                                double* __restrict__ dst, Geom g,
+                                                                const unsigned* word) {
+  if (!holds_coeffs(word)) return;
   const long long n = (long long)g.lx * g.ly, step = (long long)gridDim.x * kVThreads;
   for (long long i = (long long)blockIdx.x * kVThreads + threadIdx.x; i < n; i += step) {
     const int x = int(i / g.ly), y = int(i % g.ly);
@@ -59,12 +64,9 @@ constexpr int kLdsRows = kVThreads + 6;
 template <class S>
 __global__ __launch_bounds__(kVThreads) void k_propagate_lds(const S* __restrict__ src,
                                                              S* __restrict__ dst, Geom g,
-                                                             int nty, const unsigned* word) {
+                                                             int nty) {
   __shared__ S win[kLdsGroup * kLdsRows];
-  if constexpr (std::is_same<S, double>::value) {
-    set_form(dst, kFormFull);
-    if (holds_coeffs(word)) return propagate_coeffs(src, dst, g);
-  }
+  if constexpr (std::is_same<S, double>::value) set_form(dst, kFormFull);
   const int x = int(blockIdx.x) / nty;
   const int y0 = (int(blockIdx.x) % nty) * kVThreads;
   const int n = min(kVThreads, g.ly - y0);
@@ -134,13 +136,10 @@ struct Wide<float> {
 template <class S>
 __global__ __launch_bounds__(kVThreads) void k_propagate_wide(const S* __restrict__ src,
                                                               S* __restrict__ dst, Geom g,
-                                                              int nty, const unsigned* word) {
+                                                              int nty) {
   using W = Wide<S>;
   constexpr int V = W::V;
-  if constexpr (std::is_same<S, double>::value) {
-    set_form(dst, kFormFull);
-    if (holds_coeffs(word)) return propagate_coeffs(src, dst, g);
-  }
+  if constexpr (std::is_same<S, double>::value) set_form(dst, kFormFull);
   const int x = int(blockIdx.x) / nty;
   const int y = (int(blockIdx.x) % nty) * (kVThreads * V) + V * int(threadIdx.x);
   if (y >= g.ly) return;
@@ -240,21 +239,23 @@ __device__ __forceinline__ double eq_row(int row, double rho, const double (&hx)
 }
 
 // The same from coefficients, which the scratch buffer holds after a fused step:
-// launched beside the other where the host does not know what it holds.
+// launched beside the other where the host does not know what it holds, with
+// few workgroups, which mostly find nothing to do.
 template <bool kReg>
 __global__ __launch_bounds__(kVThreads) void k_collide_coeffs(const double* __restrict__ src,
                                                               double* __restrict__ dst, Geom g,
-                                                              Phys P, int nyb,
-                                                              const unsigned* word) {
+                                                              Phys P, const unsigned* word) {
   if (!holds_coeffs(word)) return;
-  const int x = int(blockIdx.x) / nyb, y = int(blockIdx.x) % nyb * kVThreads + int(threadIdx.x);
-  if (y >= g.ly) return;
-  double f[Q];
-  scratch_site(src, g, x, y, f);
-  collide<double, kReg>(f, P);
-  double* to = dst + (long long)(x + HX) * g.cs + y + g.hy;
+  const long long n = (long long)g.lx * g.ly, step = (long long)gridDim.x * kVThreads;
+  for (long long i = (long long)blockIdx.x * kVThreads + threadIdx.x; i < n; i += step) {
+    const int x = int(i / g.ly), y = int(i % g.ly);
+    double f[Q];
+    scratch_site(src, g, x, y, f);
+    collide<double, kReg>(f, P);
+    double* to = dst + (long long)(x + HX) * g.cs + y + g.hy;
 #pragma unroll
-  for (int l = 0; l < Q; ++l) to[l * g.ps] = f[l];
+    for (int l = 0; l < Q; ++l) to[l * g.ps] = f[l];
+  }
 }
 
 constexpr int kSets = 2;  // site sets per round (divides 4; 2 keeps 3 waves per SIMD)
@@ -363,6 +364,9 @@ __global__ __launch_bounds__(kVThreads) void k_collide_mfma(const double* __rest
 }
 
 unsigned blocks(long long n, long long per) { return unsigned((n + per - 1) / per); }
+unsigned few_blocks(const Geom& g) {
+  return std::min(blocks((long long)g.lx * g.ly, kVThreads), 1024u);
+}
 
 }  // namespace
 
@@ -372,21 +376,23 @@ hipError_t launch_propagate_variant(const void* src, void* dst, const Geom& g, i
     using S = decltype(sv);
     const S* a = static_cast<const S*>(src);
     S* b = static_cast<S*>(dst);
-    const unsigned* word = word_of(src, g);
     if (variant == kPropagateLds) {
       const int nty = int(blocks(g.ly, kVThreads));
       hipLaunchKernelGGL(k_propagate_lds<S>, dim3(unsigned(g.lx) * unsigned(nty)),
-                         dim3(kVThreads), 0, s, a, b, g, nty, word);
+                         dim3(kVThreads), 0, s, a, b, g, nty);
     } else {
       const int nty = int(blocks(g.ly, (long long)kVThreads * Wide<S>::V));
       hipLaunchKernelGGL(k_propagate_wide<S>, dim3(unsigned(g.lx) * unsigned(nty)),
-                         dim3(kVThreads), 0, s, a, b, g, nty, word);
+                         dim3(kVThreads), 0, s, a, b, g, nty);
     }
   };
   if (variant != kPropagateLds && variant != kPropagateWide) return hipErrorInvalidValue;
-  if (prec == kF64)
+  if (prec == kF64) {
     run(double{});
-  else if (prec == kF32Shifted || prec == kF32ShiftedF32Sum)
+    if (const unsigned* word = word_of(src, g))
+      hipLaunchKernelGGL(k_propagate_coeffs, dim3(few_blocks(g)), dim3(kVThreads), 0, s,
+                         static_cast<const double*>(src), static_cast<double*>(dst), g, word);
+  } else if (prec == kF32Shifted || prec == kF32ShiftedF32Sum)
     run(float{});
   else
     return hipErrorInvalidValue;
@@ -403,10 +409,8 @@ hipError_t launch_collide_mfma(const void* src, void* dst, const Geom& g, const 
   hipLaunchKernelGGL(regularize ? k_collide_mfma<true> : k_collide_mfma<false>, dim3(grid),
                      dim3(kVThreads), 0, s, a, b, g, p, nyb, word);
   if (word) {
-    const int nty = int(blocks(g.ly, kVThreads));
-    hipLaunchKernelGGL(regularize ? k_collide_coeffs<true> : k_collide_coeffs<false>,
-                       dim3(unsigned(g.lx) * unsigned(nty)), dim3(kVThreads), 0, s, a, b, g, p, nty,
-                       word);
+    hipLaunchKernelGGL(regularize ? k_collide_coeffs<true> : k_collide_coeffs<false>, dim3(few_blocks(g)),
+                       dim3(kVThreads), 0, s, a, b, g, p, word);
   }
   return hipGetLastError();
 }
