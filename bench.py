@@ -41,15 +41,17 @@ def bytes_per_site(precision: str = "fp64") -> int:
     return 2 * (Q + 1) * 4 if precision in ("fp32c", "fp32l") else 2 * Q * 4
 
 
-def moved_bytes_per_site(precision: str, lx: int, ly: int) -> int:
-    """HBM bytes that the library's fused step has to move per site update: FP64
-    is stored as 15 Hermite coefficients (240 bytes in and out); large
-    lattices make two steps per launch (but for the last one to four of a
-    call) in FP64 and in the shifted FP32 forms, which halves the bytes."""
-    if precision == "fp64":
-        return 120 if lx * ly >= 310000 else 240
-    two = precision in ("fp32s", "fp32s_f32sum") and lx * ((ly + 57) // 58) >= 14000
-    return bytes_per_site(precision) // (2 if two else 1)
+def moved_bytes_per_site(precision: str, lx: int, ly: int, steps: int,
+                         layout: str = "column") -> float:
+    """HBM bytes that the library's fused steps have to move per site update, in
+    a run of `steps`: a launch reads and writes the state once (FP64: 15 Hermite
+    coefficients a site, 240 bytes in and out), and the library says how many
+    launches it makes of the steps."""
+    from paper_1703_00186_amd import lb as lbmod
+
+    launches = lbmod.step_launches(lbmod.make_lattice(lx, ly, precision, layout=layout),
+                                   lbmod.make_params(), steps)
+    return (240 if precision == "fp64" else bytes_per_site(precision)) * launches / steps
 
 
 def mlups(sites: int, seconds: float) -> float:
@@ -62,8 +64,11 @@ VALU_SUMMARY = os.path.join(PROFILES, "k_fused_forms_rt1920x2048_valu.md")
 FP32_VALU_SUMMARY = VALU_SUMMARY
 FP64_VECTOR_PEAK_TFLOPS = 78.6
 FP32_VECTOR_PEAK_TFLOPS = 157.3
-KERNEL_SOURCES = ["paper_1703_00186_amd/csrc/d2q37_kernels.hip",
+KERNEL_SOURCES = ["paper_1703_00186_amd/build.py",
+                  "paper_1703_00186_amd/csrc/d2q37_kernels.hip",
                   "paper_1703_00186_amd/csrc/d2q37_coeff.hip",
+                  "paper_1703_00186_amd/csrc/d2q37_pair.hip",
+                  "paper_1703_00186_amd/csrc/d2q37_launch.h",
                   "paper_1703_00186_amd/csrc/d2q37_coeff.h",
                   "paper_1703_00186_amd/csrc/d2q37_tiles.h",
                   "paper_1703_00186_amd/csrc/d2q37_device.h",
@@ -272,7 +277,8 @@ def fp32_legs(lx: int, ly: int, fields, layout: str, fp64_mlups: float, torch) -
         lb32.step(FP32_ERROR_STEPS - FP32_WARMUP - FP32_TIMED)
         errs = field_errors(host_moments(lb32, torch), m64)
         v32 = mlups(sites * FP32_TIMED, t32)
-        gbs = moved_bytes_per_site(prec, lx, ly) * sites / (t32 / FP32_TIMED) / 1e9
+        gbs = (moved_bytes_per_site(prec, lx, ly, FP32_TIMED, layout) * sites
+               / (t32 / FP32_TIMED) / 1e9)
         out[key] = {
             "form": what, "precision": prec,
             "MLUPS": round(v32, 2), "ms_per_step": round(t32 / FP32_TIMED * 1e3, 5),
@@ -323,7 +329,8 @@ def precision_leg(torch, layout: str = "column") -> dict:
         t = time_steps(lb, FP32_TIMED, torch)
         lb.step(FP32_ERROR_STEPS - FP32_WARMUP - FP32_TIMED)
         v = mlups(sites * FP32_TIMED, t)
-        gbs = moved_bytes_per_site(prec, lx, ly) * sites / (t / FP32_TIMED) / 1e9
+        gbs = (moved_bytes_per_site(prec, lx, ly, FP32_TIMED, layout) * sites
+               / (t / FP32_TIMED) / 1e9)
         rec[prec] = {"MLUPS": round(v, 1), "ms_per_step": round(t / FP32_TIMED * 1e3, 4),
                      "GB/s": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4)}
         if prec == "fp64":
@@ -358,7 +365,7 @@ def production_leg(torch, steps: int = 200, warmup: int = 10, n_adj: int = 100,
         lb.step(warmup)
         t = time_steps(lb, steps, torch)
         v = mlups(sites * steps, t)
-        gbs = moved_bytes_per_site(prec, lx, ly) * sites / (t / steps) / 1e9
+        gbs = moved_bytes_per_site(prec, lx, ly, steps) * sites / (t / steps) / 1e9
         rec[prec] = {"MLUPS": round(v, 1), "ms_per_step": round(t / steps * 1e3, 4),
                      "GB/s": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
                      "workspace_bytes": ws}
@@ -642,7 +649,7 @@ def _production_workload(args, torch) -> dict:
         t = time_steps(lb, n - (n_adj if prec == "fp64" else 0), torch)
         steps_done = n - (n_adj if prec == "fp64" else 0)
         v = mlups(sites * steps_done, t)
-        bps = moved_bytes_per_site(prec, lx, ly)
+        bps = moved_bytes_per_site(prec, lx, ly, steps_done)
         rec[prec] = {"MLUPS": round(v, 1), "GB/s": round(bps * v * 1e6 / 1e9, 1),
                      "hbm_frac": round(bps * v * 1e6 / 1e9 / HBM_PEAK_GBS, 4),
                      "workspace_GB": round(foot / 1e9, 3), "steps_timed": steps_done}
@@ -859,7 +866,8 @@ def run_forms(args, torch) -> list:
         lb = LB(lx, ly, *fields, precision=prec, layout=args.layout)
         lb.step(args.warmup)
         t = time_steps(lb, args.steps, torch)
-        gbs = moved_bytes_per_site(prec, lx, ly) * lx * ly / (t / args.steps) / 1e9
+        gbs = (moved_bytes_per_site(prec, lx, ly, args.steps, args.layout) * lx * ly
+               / (t / args.steps) / 1e9)
         out.append({"form": prec, "lattice": [lx, ly], "steps": args.steps,
                     "ms_per_step": round(t / args.steps * 1e3, 5),
                     "MLUPS": round(mlups(lx * ly * args.steps, t), 1), "GB/s": round(gbs, 1),
@@ -971,8 +979,18 @@ def main(argv=None) -> int:
     t = time_steps(lb, args.steps, torch)
     ms = t / args.steps * 1e3
     value = mlups(sites * args.steps, t)
-    moved = moved_bytes_per_site("fp64", lx, ly)
+    moved = moved_bytes_per_site("fp64", lx, ly, args.steps, args.layout)
     achieved = moved * sites / (t / args.steps) / 1e9
+    hbm = {"achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+           "frac": round(achieved / HBM_PEAK_GBS, 4)}
+    fps = counted_flop_per_site()
+    vector = None
+    if fps is not None:
+        tflops = fps * sites / (t / args.steps) / 1e12
+        vector = {"achieved": round(tflops, 2), "peak": FP64_VECTOR_PEAK_TFLOPS,
+                  "unit": "TFLOP/s", "frac": round(tflops / FP64_VECTOR_PEAK_TFLOPS, 4)}
+    # the resource of which the step takes the larger share
+    vector_bound = vector is not None and vector["frac"] > hbm["frac"]
     log("bench: fused FP64 %.4f ms/step, %.1f MLUPS, %.0f GB/s" % (ms, value, achieved))
     out = {
         "metric": METRIC, "value": round(value, 2), "unit": "MLUPS", "n_gpus": 1,
@@ -983,19 +1001,14 @@ def main(argv=None) -> int:
                                "propagate+bc+collide" % (lx, ly),
                    "lattice": [lx, ly], "tau": 0.7, "g": 1e-4, "t_bottom": 1.5,
                    "t_top": 0.5, "layout": args.layout, "parallelism": "single GPU"},
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": None,
-                     "kernel": "k_coeff_pair" if moved == 120 else "k_coeff_step",
-                     "bytes_per_site": moved,
-                     "population_bytes_per_site": bytes_per_site("fp64")},
+        "roofline": dict(vector if vector_bound else hbm,
+                         bound="fp64 vector" if vector_bound else "hbm", traffic=None,
+                         kernel="k_coeff_pair" if moved < 240 else "k_coeff_step",
+                         bytes_per_site=moved, population_bytes_per_site=bytes_per_site("fp64"),
+                         hbm=hbm),
     }
-    fps = counted_flop_per_site()
-    if fps is not None:
-        tflops = fps * sites / (t / args.steps) / 1e12
-        out["fp64_compute"] = {"flop_per_site_counted": fps, "achieved": round(tflops, 2),
-                               "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                               "frac": round(tflops / FP64_VECTOR_PEAK_TFLOPS, 4)}
+    if vector is not None:
+        out["fp64_compute"] = dict(vector, flop_per_site_counted=fps)
     traffic = measured_traffic(lx, ly) if args.layout == "column" else None
     if traffic is not None:
         out["roofline"]["traffic"] = traffic

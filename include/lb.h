@@ -172,6 +172,12 @@ int lb_set_params(lb_ctx* ctx, const lb_params* par);
  * state is left as computed). */
 int lb_step(lb_ctx* ctx, int n);
 
+/* How many launches lb_step(n) makes of the fused kernel on such a lattice:
+ * fewer than n where two steps in one launch are the faster ones (n where it
+ * runs the split kernels).  Pure host computation.  Errors: LB_E_ARG (as
+ * lb_workspace_bytes; n < 0, NULL). */
+int lb_step_launches(const lb_lattice* lat, const lb_params* par, int n, int* launches);
+
 /* Eq. (2) of the current (post-collision) state: rho = sum f,
  * rho u = sum c f, 2 rho T = sum |c - u|^2 f, computed in FP64.  Outputs are
  * device FP64 [lx][ly]; any of them may be NULL.  Errors: LB_E_ARG (NULL

@@ -309,18 +309,23 @@ int one_step(lb_ctx* c, double* tape) {
   return LB_OK;
 }
 
-// n steps.  The buffers swap once per launch, and a recorded graph of an even
-// number of steps has to end in the buffer it started from; so launches of
-// two steps come in pairs.  The last step is a single one: it leaves the state
-// before it in the scratch buffer.
+// Whether lb_step makes two steps in one launch.  The buffers swap once per
+// launch, and a recorded graph of an even number of steps has to end in the
+// buffer it started from; so such launches come in pairs.  The last step is a
+// single one: it leaves the state before it in the scratch buffer.
+bool makes_two_steps(const Geom& g, int prec, const lb_params& par) {
+  return par.kernel == LB_KERNEL_FUSED && par.check_finite == 0 &&
+         d2q37::two_steps_pay(g, prec, par.regularize);
+}
+bool four_in_two_launches(bool pairs, int left) { return pairs && left > 4; }
+
 int run_steps(lb_ctx* c, int n) {
-  const bool pairs = c->par.kernel == LB_KERNEL_FUSED && c->par.check_finite == 0 &&
-                     d2q37::two_steps_pay(c->g, c->prec, c->par.regularize);
+  const bool pairs = makes_two_steps(c->g, c->prec, c->par);
   for (int i = 0; i < n;) {
     // two regularized steps start from populations only if the guess was wrong
     const bool ready = !coeff_step(c) || c->a_form == d2q37::kFormCoeff ||
                        c->a_form == d2q37::kFormProbablyCoeff;
-    if (pairs && ready && n - i > 4) {
+    if (ready && four_in_two_launches(pairs, n - i)) {
       int rc = fused_steps(c, 2, nullptr);
       if (rc == LB_OK) rc = fused_steps(c, 2, nullptr);
       if (rc) return rc;
@@ -528,6 +533,18 @@ int lb_step(lb_ctx* ctx, int n) {
   if (rc) return rc;
   if (n < 0) return fail(LB_E_ARG, "n must be >= 0%s");
   return run_steps(ctx, n);
+}
+
+int lb_step_launches(const lb_lattice* lat, const lb_params* par, int n, int* launches) {
+  size_t bytes = 0;
+  const int rc = lb_workspace_bytes(lat, par, &bytes);
+  if (rc) return rc;
+  if (n < 0) return fail(LB_E_ARG, "n must be >= 0%s");
+  if (!launches) return fail(LB_E_ARG, "launches is NULL%s");
+  const bool pairs = makes_two_steps(make_geom(*lat), lat->precision, *par);
+  const int fours = pairs && n > 4 ? (n - 1) / 4 : 0;  // as run_steps counts
+  *launches = n - 2 * fours;
+  return LB_OK;
 }
 
 int lb_moments(lb_ctx* ctx, double* rho, double* ux, double* uy, double* T) {

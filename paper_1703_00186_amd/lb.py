@@ -39,7 +39,7 @@ ERRORS = {-1: "LB_E_ARG", -2: "LB_E_WORKSPACE", -3: "LB_E_HIP", -4: "LB_E_STATE"
 
 EXPORTS = [
     "lb_last_error", "lb_version", "lb_workspace_bytes", "lb_init", "lb_free", "lb_set_stream",
-    "lb_set_params", "lb_step", "lb_moments", "lb_get_state", "lb_set_state",
+    "lb_set_params", "lb_step", "lb_step_launches", "lb_moments", "lb_get_state", "lb_set_state",
     "lb_get_populations", "lb_halo", "lb_propagate", "lb_bc", "lb_collide", "lb_get_scratch",
     "lb_set_scratch", "lb_observables", "lb_run_observed", "lb_step_record", "lb_loss_ke",
     "lb_adjoint_step", "lb_adjoint_workspace_bytes", "lb_adjoint_run", "lb_adjoint_run_static",
@@ -96,6 +96,7 @@ def load_library():
         "lb_set_stream": ([vp, vp], i),
         "lb_set_params": ([vp, Pp], i),
         "lb_step": ([vp, i], i),
+        "lb_step_launches": ([Lp, Pp, i, ctypes.POINTER(i)], i),
         "lb_moments": ([vp, vp, vp, vp, vp], i),
         "lb_get_state": ([vp, vp], i),
         "lb_set_state": ([vp, vp], i),
@@ -149,6 +150,14 @@ def make_lattice(lx, ly, precision="fp64", ybc="walls", layout="column") -> Latt
     y = {"walls": LB_Y_WALLS, "periodic": LB_Y_PERIODIC}[ybc]
     lay = {"soa": LB_LAYOUT_SOA, "column": LB_LAYOUT_COLUMN}[layout]
     return Lattice(int(lx), int(ly), p, y, lay, 0)
+
+
+def step_launches(lat: Lattice, par: Params, n: int) -> int:
+    """Launches of the fused kernel in n steps of such a lattice (host only)."""
+    launches = ctypes.c_int(0)
+    _check(load_library().lb_step_launches(ctypes.byref(lat), ctypes.byref(par), int(n),
+                                           ctypes.byref(launches)))
+    return launches.value
 
 
 def _on_device(method):

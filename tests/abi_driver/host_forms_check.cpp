@@ -231,9 +231,27 @@ void no_form_is_kept_between_calls() {
   }
 }
 
+// lb_step_launches counts what lb_step enqueues.
+void launches_are_counted() {
+  for (int reg : {1, 0})
+    for (int lx : {64, 256, 1000})
+      for (int n : {0, 1, 4, 5, 6, 9, 20}) {
+        Lattice l(reg, lx, lx == 64 ? 48 : 700);
+        lines.clear();
+        lb_step(l.ctx, n);
+        int count = -1;
+        if (lb_step_launches(&l.lat, &l.par, n, &count) || count != int(lines.size())) {
+          ++failures;
+          std::printf("%d steps of %d columns: %d launches, %d counted\n", n, lx,
+                      int(lines.size()), count);
+        }
+      }
+}
+
 }  // namespace
 
 int main() {
+  launches_are_counted();
   no_form_is_kept_between_calls();
   plain_bgk_after_a_recording();
   std::printf("%d failure(s)\n", failures);
