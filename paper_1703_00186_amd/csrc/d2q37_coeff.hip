@@ -254,7 +254,7 @@ __device__ __forceinline__ void store_tape(double* tape, long long S2, long long
   __builtin_nontemporal_store(a[slot(0, 0)], &tape[s]);
   __builtin_nontemporal_store(R * a[slot(1, 0)], &tape[S2 + s]);
   __builtin_nontemporal_store(R * a[slot(0, 1)], &tape[2 * S2 + s]);
-  __builtin_nontemporal_store(kR2 * (a[slot(2, 0)] + a[slot(0, 2)]), &tape[3 * S2 + s]);
+  __builtin_nontemporal_store(R2 * (a[slot(2, 0)] + a[slot(0, 2)]), &tape[3 * S2 + s]);
 }
 
 // The way in from 37 stored populations: the moments of those that arrive at a
@@ -703,9 +703,8 @@ __global__ __launch_bounds__(kThreads) void k_coeff_init(
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
     const int p = kCI[k], q = kCJ[k];
-    double scale = INVFAC[p] * INVFAC[q];  // r^(p+q) / (p! q!)
-    for (int n = 0; n < p + q; ++n) scale *= R;
-    b[k] = scale * aeq[p][q];
+    constexpr double power[5] = {1.0, R, R2, R * R2, R4};
+    b[k] = power[p + q] * INVFAC[p] * INVFAC[q] * aeq[p][q];  // r^(p+q) / (p! q!) a_pq
   }
   add_tails(b);
   store_coeffs(coeffs(dst), g, x, y, b);

@@ -41,5 +41,20 @@ constexpr double HEF[4][5] = {
 };
 // INVFAC[n] = 1 / n!
 constexpr double INVFAC[5] = {0x1.0000000000000p+0, 0x1.0000000000000p+0, 0x1.0000000000000p-1, 0x1.5555555555555p-3, 0x1.5555555555555p-5};
+// powers of r (R2 = r^2, R6_6 = r^6 / 6, IR2_3 = 3 r^-2, ...)
+constexpr double R2 = 0x1.6ec9659248e55p+0;
+constexpr double R4 = 0x1.06c23e6f78397p+1;
+constexpr double R6 = 0x1.78786c072ba31p+1;
+constexpr double R8 = 0x1.0db22b2eda41fp+2;
+constexpr double R6_6 = 0x1.f5f5e55ee4d97p-2;
+constexpr double R8_6 = 0x1.67983993cdad4p-1;
+constexpr double R8_24 = 0x1.67983993cdad4p-3;
+constexpr double IR2 = 0x1.655a23486b0e9p-1;
+constexpr double IR2_3 = 0x1.0c039a76504afp+1;
+constexpr double IR2_6 = 0x1.0c039a76504afp+2;
+// sum w e_x^2, sum w e_x^4, sum w e_x^2 e_y^2
+constexpr double G20 = 0x1.655a23486b0e9p-1;
+constexpr double G40 = 0x1.761f649b9ac71p+0;
+constexpr double G22 = 0x1.f2d48624ce5ecp-2;
 
 }  // namespace d2q37

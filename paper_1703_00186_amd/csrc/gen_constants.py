@@ -12,7 +12,11 @@ Derivation (Sec. 2: 37 populations that hop at most three sites; Hermite basis):
   * lattice velocities c_l = r e_l, with the 8 family weights and r solved
     from sum_l w_l c_lx^p c_ly^q = E[z^p] E[z^q] (standard normal z) for the
     nine even (p, q) of total degree <= 8, plus (4,4); the rule is then exact
-    to degree 9.  Solved with mpmath at 50 digits and rounded to double.
+    to degree 9.  Solved with mpmath at 50 digits and rounded to double;
+  * the powers of r and the even moments of the weights that the coefficient
+    form of the state needs (d2q37_coeff.h), each rounded once, the moments
+    those of the rounded weights: what the map from moments to coefficients
+    takes must be what the populations give back.
 Run as a script to rewrite the header; ``check()`` compares a fresh solve
 with the header on disk.
 """
@@ -115,6 +119,15 @@ def render() -> str:
     a("};")
     a("// INVFAC[n] = 1 / n!")
     a("constexpr double INVFAC[5] = {%s};" % ", ".join(hexf(1 / mp.factorial(n)) for n in range(5)))
+    a("// powers of r (R2 = r^2, R6_6 = r^6 / 6, IR2_3 = 3 r^-2, ...)")
+    for name, v in (("R2", r ** 2), ("R4", r ** 4), ("R6", r ** 6), ("R8", r ** 8),
+                    ("R6_6", r ** 6 / 6), ("R8_6", r ** 8 / 6), ("R8_24", r ** 8 / 24),
+                    ("IR2", r ** -2), ("IR2_3", 3 / r ** 2), ("IR2_6", 6 / r ** 2)):
+        a("constexpr double %s = %s;" % (name, hexf(v)))
+    a("// sum w e_x^2, sum w e_x^4, sum w e_x^2 e_y^2")
+    for name, i, j in (("G20", 2, 0), ("G40", 4, 0), ("G22", 2, 2)):
+        a("constexpr double %s = %s;" % (
+            name, hexf(sum(mp.mpf(float(v)) * e[0] ** i * e[1] ** j for v, e in zip(w, E)))))
     a("")
     a("}  // namespace d2q37")
     a("")
