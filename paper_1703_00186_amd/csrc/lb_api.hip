@@ -161,8 +161,8 @@ int check_kernel(int prec, const lb_params& par) {
 // to make of it
 Geom with_form(const Geom& g, int form, int steps = 1) {
   Geom h = g;
-  h.form = form;
-  h.steps = steps;
+  h.form = short(form);
+  h.steps = short(steps);
   return h;
 }
 
