@@ -34,6 +34,12 @@
  *  - A context belongs to the HIP device current at lb_init; every later call
  *    on it must be made with that device current (else LB_E_STATE).
  *  - A context is not thread-safe; distinct contexts are independent.
+ *  - Calls may be recorded into a HIP graph (not with check_finite > 0, which
+ *    waits).  A graph acts on the workspace it was recorded on and finds the
+ *    state there whatever left it: eager calls, other graphs, other parameters,
+ *    lb_set_state, or a later lb_init on the same workspace.  A and B swap
+ *    with every launch of the fused step, so steps to be replayed are recorded
+ *    in even numbers and mixed with even numbers of others.
  */
 #ifndef D2Q37_LB_H
 #define D2Q37_LB_H
@@ -208,9 +214,10 @@ int lb_get_populations(lb_ctx* ctx, double* f);
  * lb_propagate and lb_collide run the alternative kernel of the context's
  * LB_KERNEL_SPLIT_* value where it names one (lb_step's split path too).
  * lb_get_scratch / lb_set_scratch copy B's physical region in the compact
- * form of lb_get_state; after fused steps B holds the state before the last.  The local-reference forms (LB_FP32_COLLIDE,
- * LB_FP32_LOCAL) have no split stages: lb_propagate, lb_bc, lb_collide,
- * lb_get_scratch and lb_set_scratch return LB_E_STATE for them. */
+ * form of lb_get_state; after fused steps B holds the state before the last.
+ * The local-reference forms (LB_FP32_COLLIDE, LB_FP32_LOCAL) have no split
+ * stages: lb_propagate, lb_bc, lb_collide, lb_get_scratch and lb_set_scratch
+ * return LB_E_STATE for them. */
 int lb_halo(lb_ctx* ctx);
 int lb_propagate(lb_ctx* ctx);
 int lb_bc(lb_ctx* ctx);

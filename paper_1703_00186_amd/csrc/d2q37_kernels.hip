@@ -675,7 +675,6 @@ __device__ __forceinline__ void adjoint_project(const double (&lam)[Q], double (
     for (int q = 0; q + p < 5; ++q) L[p][q] *= INVFAC[p] * INVFAC[q];
 }
 
-// lambda_out = P^T B^T C^T lambda_in for one step (scatter form).
 // Plain BGK (the Hermite-projected collision's adjoint is in d2q37_coeff.hip):
 // B^T C(m)^T of one site: lam holds lambda^{j+1} at the site's arriving
 // populations, m = (rho, j_x, j_y, sum |c|^2 f) the pre-collision moments of
@@ -741,6 +740,7 @@ __device__ __forceinline__ void adjoint_site(const double (&lam)[Q], double rho,
   }
 }
 
+// lambda_out = P^T B^T C^T lambda_in for one step (scatter form).
 __global__ __launch_bounds__(kThreads) void k_adjoint(const double* __restrict__ tape,
                                                       const double* __restrict__ lam_in,
                                                       double* __restrict__ lam_out, Geom g,
