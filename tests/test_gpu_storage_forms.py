@@ -294,3 +294,36 @@ def test_state_replaced_inside_a_graph():
         a.step(4)
         b.step(4)
         assert torch.equal(a.get_state(), b.get_state())
+
+
+# one, two, three (loaded one and two ahead) and four columns per wave, ragged
+SWEEPS = [(6, 6), (33, 113), (301, 400), (683, 57 * 4), (1027, 57 * 15), (2051, 57 * 20)]
+
+
+@pytest.mark.parametrize("layout", ["column", "soa"])
+@pytest.mark.parametrize("ybc", ["walls", "periodic"])
+@pytest.mark.parametrize("shape", SWEEPS)
+def test_sweep_that_finds_populations(shape, ybc, layout):
+    """A graph recorded on coefficients, with and without a tape, replayed on a
+    state just given as populations: the bits of eager steps."""
+    a, b = (make(*shape, ybc=ybc, layout=layout) for _ in range(2))
+    g = a.capture(2)
+    tape, ref = a.new_tape(2), b.new_tape(2)
+    torch.cuda.synchronize()
+    h = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(h):
+        a.step_record(2, tape)
+    torch.cuda.synchronize()
+    state = noisy(b)
+    for _ in range(2):
+        for lb in (a, b):
+            lb.set_state(state)
+        g.replay()
+        b.step(2)
+        assert torch.equal(a.get_state(), b.get_state())
+        for lb in (a, b):
+            lb.set_state(state)
+        h.replay()
+        b.step_record(2, ref)
+        assert torch.equal(a.get_state(), b.get_state())
+        assert torch.equal(tape, ref)
