@@ -275,14 +275,16 @@ __device__ __forceinline__ double arriving(const double* __restrict__ src, const
 template <int ex = 3>
 __device__ __forceinline__ void project_arriving(const double* src, const Geom& gf,
                                                  const CGeom& g, int x, int y, double (&m)[NC]) {
-  // one group after the other: the sweep has no registers for more
-  asm volatile("" : "+s"(src));
+  // one group after the other, and no strides kept from one column to the
+  // next: the sweep has no registers for more
+  Geom h = gf;
+  asm volatile("" : "+s"(src), "+s"(h.ps), "+s"(h.cs));
   Group f;
-  f.zero = arriving(src, gf, g, x, y, label(ex, 0));
+  f.zero = arriving(src, h, g, x, y, label(ex, 0));
 #pragma unroll
   for (int k = 1; k <= reach(ex); ++k) {
-    f.plus[k - 1] = arriving(src, gf, g, x, y, label(ex, k));
-    f.minus[k - 1] = arriving(src, gf, g, x, y, label(ex, -k));
+    f.plus[k - 1] = arriving(src, h, g, x, y, label(ex, k));
+    f.minus[k - 1] = arriving(src, h, g, x, y, label(ex, -k));
   }
   project_group<Forward, ex>(f, m);
 #pragma unroll
