@@ -370,14 +370,16 @@ __device__ __forceinline__ void gather_coeffs(const double* src, const CGeom& g,
 }
 
 // Hermite coefficients scaled by r^(p+q) / (p! q!) -> polynomial coefficients,
-// in place (the leading ones are the same; lower ones get the tails of He_n).
+// in place (the leading ones are the same; lower ones get the tails of He_n),
+// the second ones from s b_20 and s b_02.
 // c_00 comes last, as what the others leave of the mass with the weights'
 // moments G20 = sum w e_x^2 (about r^-2), G40 = sum w e_x^4 (3 r^-4) and
 // G22 = sum w e_x^2 e_y^2 (r^-4): their rounding then does not touch it.
-__device__ __forceinline__ void add_tails(double (&b)[NC]) {
+__device__ __forceinline__ void add_tails(double (&b)[NC], double s = 1.0) {
   const double c40 = b[slot(4, 0)], c04 = b[slot(0, 4)], c22 = b[slot(2, 2)];
-  const double c20 = mad(-IR2_6, c40, mad(-IR2, c22, b[slot(2, 0)]));
-  const double c02 = mad(-IR2_6, c04, mad(-IR2, c22, b[slot(0, 2)]));
+  const double tail = -IR2 * c22;
+  const double c20 = mad(s, b[slot(2, 0)], mad(-IR2_6, c40, tail));
+  const double c02 = mad(s, b[slot(0, 2)], mad(-IR2_6, c04, tail));
   b[slot(2, 0)] = c20;
   b[slot(0, 2)] = c02;
   b[slot(0, 0)] = b[slot(0, 0)] - mad(G20, c20 + c02, mad(G40, c40 + c04, G22 * c22));
@@ -413,13 +415,11 @@ __device__ __forceinline__ void to_poly_centred(double (&m)[NC]) {
   m[slot(0, 3)] = mad(R6_6, m[slot(0, 3)], (-R4 / 2.0) * m01);
   m[slot(2, 1)] = mad(R6 / 2.0, m[slot(2, 1)], (-R4 / 2.0) * m01);
   m[slot(1, 2)] = mad(R6 / 2.0, m[slot(1, 2)], (-R4 / 2.0) * m10);
-  // r^2/2 (r^2 m20 - m00), r^4 m11, r^2 m10
-  m[slot(2, 0)] = (R4 / 2.0) * t20;
-  m[slot(0, 2)] = (R4 / 2.0) * t02;
+  // r^4 m11, r^2 m10; the second ones are r^4/2 t20, r^4/2 t02
   m[slot(1, 1)] = R4 * m11;
   m[slot(1, 0)] = R2 * m10;
   m[slot(0, 1)] = R2 * m01;
-  add_tails(m);
+  add_tails(m, R4 / 2.0);
 }
 __device__ __forceinline__ void to_poly(double (&m)[NC]) {
   m[slot(2, 0)] = centred(m[slot(2, 0)], m[slot(0, 0)]);
