@@ -5,7 +5,7 @@
 Workload: the Rayleigh-Taylor lattice of the paper's Table 1, 1920 x 2048
 sites (Sec. 5), FP64, tau 0.7, g = 1e-4 along -y, walls at T = 1.5 / 0.5.  A
 step is one pass of the whole hot path: periodic halo, propagate, bc and
-collide, run as the fused kernel (one launch per step).  Inputs are resident
+collide, run as the fused kernels (one step or two per launch).  Inputs are resident
 in HBM before timing starts.  Printed: one JSON line with the headline FP64
 MLUPS, the roofline of the fused kernel, the split kernels, the adjoint, the
 FP32 storage forms on this lattice and on the 4096 x 4096 precision lattice
@@ -64,6 +64,7 @@ VALU_SUMMARY = os.path.join(PROFILES, "k_fused_forms_rt1920x2048_valu.md")
 FP32_VALU_SUMMARY = VALU_SUMMARY
 FP64_VECTOR_PEAK_TFLOPS = 78.6
 FP32_VECTOR_PEAK_TFLOPS = 157.3
+VALU_PEAK_GINST = 1024 * 2.4 / 4  # wave64 instructions of 4 cycles on 1,024 SIMDs at 2.4 GHz
 KERNEL_SOURCES = ["paper_1703_00186_amd/build.py",
                   "paper_1703_00186_amd/csrc/d2q37_kernels.hip",
                   "paper_1703_00186_amd/csrc/d2q37_coeff.hip",
@@ -98,23 +99,34 @@ def summary_values(path: str) -> dict:
     return vals if vals.get("source_sha256_16") == kernel_source_hash() else {}
 
 
-def measured_traffic(lx: int, ly: int):
-    """HBM bytes per fused launch from the committed counter summary, or None
-    when the summary is missing, is for another lattice, or the kernel
-    sources changed since the counters were taken."""
+def measured_traffic(lx: int, ly: int, key: str = "hbm_bytes_per_launch"):
+    """HBM bytes per fused launch (of two FP64 steps, where no other `key` is
+    asked for) from the committed counter summary, or None when the summary is
+    missing, is for another lattice, or the kernel sources changed since the
+    counters were taken."""
     vals = summary_values(TRAFFIC_SUMMARY)
     try:
         if vals.get("lattice") != "%dx%d" % (lx, ly):
             return None
-        return float(vals["hbm_bytes_per_launch"])
+        return float(vals[key])
     except (KeyError, ValueError):
         return None
 
 
-def counted_flop_per_site():
-    """FP64 flop per site counted by the VALU counters (None if stale)."""
+def counted_fp64_work(lx: int, ly: int, steps: int, launches: int):
+    """(VALU wave instructions, FP64 flop) of `steps` FP64 steps in `launches`
+    launches, from the committed counter summary of this lattice: a launch makes
+    one step or two.  None if the summary is missing, stale or of another
+    lattice."""
+    vals = summary_values(VALU_SUMMARY)
     try:
-        return float(summary_values(VALU_SUMMARY)["flop_per_site"])
+        if vals.get("lattice") != "%dx%d" % (lx, ly):
+            return None
+        pairs = steps - launches
+        singles = steps - 2 * pairs
+        return tuple(pairs * float(vals["fp64_pair_%s_per_launch" % what])
+                     + singles * float(vals["fp64_step_%s_per_launch" % what])
+                     for what in ("valu", "flop"))
     except (KeyError, ValueError):
         return None
 
@@ -179,9 +191,10 @@ def time_steps(lb, steps: int, torch) -> float:
 
 def time_adjoint(lb, steps: int, torch) -> dict:
     """The adjoint on the headline lattice with a full tape: `steps` steps
-    recorded (fused step + 4-moment tape, 624 B/site), then `steps` transposed
-    steps in one lb_adjoint_run (gather form, k_adjoint_mu: 624 B/site) and,
-    for comparison, as single lb_adjoint_step calls (scatter form, k_adjoint);
+    recorded (k_coeff_step with the 4-moment tape, 272 B/site), then `steps`
+    transposed steps in one lb_adjoint_run (k_coeff_adjoint: 272 B/site) and,
+    for comparison, as single lb_adjoint_step calls (k_coeff_adjoint_step, lambda
+    as 37 populations: 624 B/site);
     HIP events on the kernels' stream.  The lattice advances by `steps`."""
     sites = lb.lx * lb.ly
     tape = lb.new_tape(steps)
@@ -219,7 +232,8 @@ def time_adjoint(lb, steps: int, torch) -> dict:
             "single_step_ms_per_step": round(t_one * 1e3, 5), "single_step_GB/s": gbs(t_one, 624),
             "run_equals_single_steps": same,
             "note": "coefficients in 120 + tape 32 + out 120 B/site; adjoint_*: lb_adjoint_run "
-                    "(gather form), single_step_*: lb_adjoint_step (scatter form)"}
+                    "(lambda as coefficients between steps), single_step_*: lb_adjoint_step "
+                    "(lambda as 37 populations, 624 B/site)"}
 
 
 def time_split_kernels(lb, steps: int, torch) -> dict:
@@ -983,13 +997,14 @@ def main(argv=None) -> int:
     achieved = moved * sites / (t / args.steps) / 1e9
     hbm = {"achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4)}
-    fps = counted_flop_per_site()
+    launches = round(moved * args.steps / 240)
+    work = (counted_fp64_work(lx, ly, args.steps, launches) if args.layout == "column" else None)
     vector = None
-    if fps is not None:
-        tflops = fps * sites / (t / args.steps) / 1e12
-        vector = {"achieved": round(tflops, 2), "peak": FP64_VECTOR_PEAK_TFLOPS,
-                  "unit": "TFLOP/s", "frac": round(tflops / FP64_VECTOR_PEAK_TFLOPS, 4)}
-    # the resource of which the step takes the larger share
+    if work is not None:
+        rate = work[0] / t / 1e9
+        vector = {"achieved": round(rate, 1), "peak": VALU_PEAK_GINST, "unit": "G wave instr/s",
+                  "frac": round(rate / VALU_PEAK_GINST, 4)}
+    # the resource of which the steps take the larger share
     vector_bound = vector is not None and vector["frac"] > hbm["frac"]
     log("bench: fused FP64 %.4f ms/step, %.1f MLUPS, %.0f GB/s" % (ms, value, achieved))
     out = {
@@ -1002,14 +1017,21 @@ def main(argv=None) -> int:
                    "lattice": [lx, ly], "tau": 0.7, "g": 1e-4, "t_bottom": 1.5,
                    "t_top": 0.5, "layout": args.layout, "parallelism": "single GPU"},
         "roofline": dict(vector if vector_bound else hbm,
-                         bound="fp64 vector" if vector_bound else "hbm", traffic=None,
+                         bound="vector issue" if vector_bound else "hbm", traffic=None,
                          kernel="k_coeff_pair" if moved < 240 else "k_coeff_step",
                          bytes_per_site=moved, population_bytes_per_site=bytes_per_site("fp64"),
                          hbm=hbm),
     }
-    if vector is not None:
-        out["fp64_compute"] = dict(vector, flop_per_site_counted=fps)
-    traffic = measured_traffic(lx, ly) if args.layout == "column" else None
+    if work is not None:
+        tflops = work[1] / t / 1e12
+        out["fp64_compute"] = {
+            "flop_per_site_counted": round(work[1] / (sites * args.steps), 1),
+            "achieved": round(tflops, 2), "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
+            "frac": round(tflops / FP64_VECTOR_PEAK_TFLOPS, 4)}
+    traffic = None
+    if args.layout == "column":
+        traffic = measured_traffic(lx, ly, "hbm_bytes_per_launch" if moved < 240
+                                   else "fp64_step_hbm_bytes_per_launch")
     if traffic is not None:
         out["roofline"]["traffic"] = traffic
         out["roofline"]["traffic_unit"] = "bytes per launch"

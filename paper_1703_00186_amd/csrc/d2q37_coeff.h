@@ -398,8 +398,9 @@ __device__ __forceinline__ void add_tails(double (&b)[NC], double s = 1.0) {
 // the energy is relaxed and mapped as its distance from that of T = 1, which
 // leaves 6e-17 of the constants' rounding at T = 0.5 and 1e-17 at 1.  Against an
 // extended-precision run, 256 x 128 after 50 steps: T 1.2e-14 to 1.9e-15 (rms),
-// rho 9.2e-15 to 2.7e-15, u 4.1e-13 to 8.7e-14 of the largest; 1920 x 2048
-// 3463 and 3477 us for 20 steps with their start and results.
+// rho 9.2e-15 to 2.7e-15, u 4.1e-13 to 8.7e-14 of the largest; gradients of
+// the kinetic energy after 20 to 40 steps 4.7e-14 to 1.2e-14.  1920 x 2048: 3463 and
+// 3477 us for 20 steps with their start and results.
 __device__ __forceinline__ double centred(double m20, double m00) { return mad(-G20, m00, m20); }
 __device__ __forceinline__ void to_poly_centred(double (&m)[NC]) {
   const double m00 = m[slot(0, 0)], m10 = m[slot(1, 0)], m01 = m[slot(0, 1)];

@@ -15,7 +15,7 @@
 //
 // What bounds it and why this split.  The step moves 240 bytes per site
 // (15 FP64 in, 15 out) instead of the 592 of the 37 populations, at 5.3 TB/s
-// (1920 x 2048: 177 us against 405; 4096 x 4096: 735 us against 1646; a copy
+// (1920 x 2048: 176 us against 405; 4096 x 4096: 735 us against 1646; a copy
 // reaches 5.2 to 5.7 TB/s).  Rebuilding populations is done once per (source
 // site, e_x group) whatever TX is; TX trades registers (30 VGPRs per column:
 // 4, 3, 2, 2 waves per SIMD at TX = 1, 2, 3, 4) against re-reading source
@@ -398,10 +398,10 @@ __global__ __launch_bounds__(64 * kWaves, (kOccupancy<TX, kAhead>)) void k_coeff
 // What bounds it.  The state is read and written once for two steps (272 of
 // the 480 bytes per site, with the re-read halo rows), so the vector unit
 // takes over from HBM: 550 instructions per column and wave, on 64 of 52 rows
-// and (chunk + 6) of chunk columns, 58 % of the issue slots; the rest is
+// and (chunk + 6) of chunk columns, 55 % of the issue slots; the rest is
 // waiting at the two barriers.  Two workgroups share a CU (77 KB of LDS
-// each), eight waves in all.  Per step, against k_coeff_step: 1920 x 2048 141 us
-// (178), 4096 x 4096 585 us (735), 777 x 1501 48 us (63).  Tried: every wave
+// each), eight waves in all.  Per step, against k_coeff_step: 1920 x 2048 140 us
+// (176), 4096 x 4096 577 us (735), 777 x 1501 48 us (63).  Tried: every wave
 // making first its column of step one, then of step two (216 us: the two
 // phases load the L1 and the LDS in turn instead of together), one workgroup
 // of eight waves (161), rows exchanged through LDS (161), source columns
