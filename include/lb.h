@@ -210,7 +210,7 @@ int lb_get_populations(lb_ctx* ctx, double* f);
  *                 the walls are left unspecified for bc.
  *   lb_bc:        applies the thermal walls to B in place (rows 0..2 and
  *                 ly-3..ly-1; no-op for LB_Y_PERIODIC).
- *   lb_collide:   A = collide(B), site by site.
+ *   lb_collide:   A = collide(B), site by site, and the x halos of A.
  * lb_propagate and lb_collide run the alternative kernel of the context's
  * LB_KERNEL_SPLIT_* value where it names one (lb_step's split path too).
  * lb_get_scratch / lb_set_scratch copy B's physical region in the compact

@@ -279,7 +279,8 @@ __global__ __launch_bounds__(kThreads) void k_propagate(const S* __restrict__ sr
 }
 
 // kEither: of a scratch buffer that may hold the state before a fused step in the
-// form which that step read.
+// form which that step read.  The edge columns are also written into the opposite
+// halo: a recorded fused step that finds this state does not refresh it.
 template <class S, class A, bool kReg, bool kEither>
 __global__ __launch_bounds__(kThreads) void k_collide(const S* __restrict__ src,
                                                       S* __restrict__ dst, Geom g, Phys P,
@@ -297,6 +298,8 @@ __global__ __launch_bounds__(kThreads) void k_collide(const S* __restrict__ src,
   }
   collide<A, kReg>(f, P);
   store_site<S, A>(dst, g, site, f);
+  if (x < HX) store_site<S, A>(dst, g, site + (long long)g.lx * g.cs, f);
+  if (x >= g.lx - HX) store_site<S, A>(dst, g, site - (long long)g.lx * g.cs, f);
 }
 
 // bc on the six wall rows, in place; one thread per (x, wall row).  In a buffer

@@ -238,6 +238,11 @@ __device__ __forceinline__ double eq_row(int row, double rho, const double (&hx)
   return row == 3 ? 0.0 : rho * hx[kRowP[row]] * hy[kRowQ[row]];
 }
 
+// From an edge column to the opposite halo column (0: column x has none).
+__device__ __forceinline__ long long halo_of(const Geom& g, int x) {
+  return x < HX ? g.lx * g.cs : x >= g.lx - HX ? -g.lx * g.cs : 0;
+}
+
 // The same from coefficients, which the scratch buffer holds after a fused step:
 // launched beside the other where the host does not know what it holds, with
 // few workgroups, which mostly find nothing to do.
@@ -253,8 +258,12 @@ __global__ __launch_bounds__(kVThreads) void k_collide_coeffs(const double* __re
     scratch_site(src, g, x, y, f);
     collide<double, kReg>(f, P);
     double* to = dst + (long long)(x + HX) * g.cs + y + g.hy;
+    const long long halo = halo_of(g, x);
 #pragma unroll
-    for (int l = 0; l < Q; ++l) to[l * g.ps] = f[l];
+    for (int l = 0; l < Q; ++l) {
+      to[l * g.ps] = f[l];
+      if (halo) to[l * g.ps + halo] = f[l];
+    }
   }
 }
 
@@ -281,6 +290,7 @@ __global__ __launch_bounds__(kVThreads) void k_collide_mfma(const double* __rest
     for (int m = 0; m < 4; ++m) ra[t][m] = kMfma.rec[t][m][lane];
   const double keep = 1.0 - P.omega, om = P.omega;
   const long long col = (long long)(x + HX) * g.cs + g.hy;
+  const long long halo = halo_of(g, x);
   // kSets site sets at a time, their products interleaved so that
   // consecutive matrix instructions are independent (a chain of dependent
   // ones waits out each one's latency)
@@ -357,6 +367,7 @@ __global__ __launch_bounds__(kVThreads) void k_collide_mfma(const double* __rest
             double v = out[s][r];
             if (!kReg) v = keep * src[a] + om * v;
             __builtin_nontemporal_store(v, &dst[a]);
+            if (halo) __builtin_nontemporal_store(v, &dst[a + halo]);
           }
         }
     }

@@ -29,7 +29,6 @@ struct lb_ctx {
   unsigned int* flag;
   int a_form;  // storage form of A (d2q37::Form), within a call; at its start
                // a guess.  B's is always read from its word
-  bool halos_valid;
   long long steps_since_check;
 };
 
@@ -246,9 +245,11 @@ int need_fp64(lb_ctx* ctx, const char* what) {
   return LB_OK;
 }
 
+// Whatever fills the state fills its x halos, here or in the kernel itself, so a
+// fused step, recorded or not, finds them whatever ran before it.  The y halos
+// (periodic y) are refreshed before each step.
 int do_halo(lb_ctx* c) {
   LB_HIP(d2q37::launch_halo(c->A, with_form(c->g, c->a_form), c->prec, c->stream), "halo");
-  c->halos_valid = true;
   return LB_OK;
 }
 
@@ -274,7 +275,7 @@ bool coeff_step(const lb_ctx* c) { return c->prec == LB_FP64 && c->par.regulariz
 // n (1 or 2) fused steps in one launch, to the form that the collision leaves.
 int fused_steps(lb_ctx* c, int n, double* tape) {
   // coefficients are read without halos
-  if (!coeff_step(c) && (!c->halos_valid || !c->g.walls)) {
+  if (!coeff_step(c) && !c->g.walls) {
     const int rc = do_halo(c);
     if (rc) return rc;
   }
@@ -283,9 +284,6 @@ int fused_steps(lb_ctx* c, int n, double* tape) {
          "fused step");
   std::swap(c->A, c->B);
   c->a_form = coeff_step(c) ? d2q37::kFormCoeff : d2q37::kFormFull;
-  // the fused kernel writes the x halos of its output (coefficients have none);
-  // y halos (periodic y) are refreshed before the next step
-  c->halos_valid = c->g.walls;
   return LB_OK;
 }
 
@@ -300,7 +298,6 @@ int one_step(lb_ctx* c, double* tape) {
     LB_HIP(d2q37::launch_bc(c->B, c->g, c->p, c->prec, c->stream), "bc");
     LB_HIP(collide_stage(c), "collide");
     c->a_form = d2q37::kFormFull;
-    c->halos_valid = false;
   }
   if (c->par.check_finite > 0 && ++c->steps_since_check >= c->par.check_finite) {
     c->steps_since_check = 0;
@@ -466,7 +463,6 @@ int lb_init(const lb_lattice* lat, const lb_params* par, void* workspace, size_t
   c->obs = reinterpret_cast<double*>(ws + 2 * nb + partial_bytes(c->g));
   c->flag = reinterpret_cast<unsigned int*>(ws + 2 * nb + partial_bytes(c->g) +
                                             observable_bytes(c->g));
-  c->halos_valid = false;
   c->steps_since_check = 0;
   c->a_form = d2q37::kFormFull;
   hipError_t e = hipSuccess;
@@ -612,7 +608,6 @@ int lb_collide(lb_ctx* ctx) {
   if (rc) return rc;
   LB_HIP(collide_stage(ctx, scratch_form(ctx)), "collide");
   ctx->a_form = d2q37::kFormFull;
-  ctx->halos_valid = false;
   return LB_OK;
 }
 

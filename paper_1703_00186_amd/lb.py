@@ -308,7 +308,7 @@ class LB:
         stream; graph.replay() then advances this lattice by n steps.
 
         Two ordinary steps run first (the lattice advances by 2), so that the
-        halos are valid and the buffer roles settled when recording starts.
+        buffer roles are settled when recording starts.
         The buffers swap once per step, so an even n returns the state to the
         buffer it started in, which is what lets the same graph run again.
         Only the fused path without check_finite is capturable.
@@ -317,7 +317,7 @@ class LB:
             raise ValueError("n must be a positive even number")
         if self.params.get("check_finite", 0) or self.params.get("kernel", "fused") != "fused":
             raise ValueError("capture needs kernel='fused' and check_finite=0")
-        self.step(2)  # halos valid, buffers settled before capture
+        self.step(2)  # buffers settled before capture
         torch.cuda.synchronize(self.device)
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, pool=pool):
