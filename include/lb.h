@@ -39,7 +39,8 @@
  *    state there whatever left it: eager calls, other graphs, other parameters,
  *    lb_set_state, or a later lb_init on the same workspace.  A and B swap
  *    with every launch of the fused step, so steps to be replayed are recorded
- *    in even numbers and mixed with even numbers of others.
+ *    in even numbers and mixed with even numbers of others, counted from
+ *    lb_init (which always puts the state into the same buffer).
  */
 #ifndef D2Q37_LB_H
 #define D2Q37_LB_H

@@ -308,16 +308,19 @@ class LB:
         stream; graph.replay() then advances this lattice by n steps.
 
         Two ordinary steps run first (the lattice advances by 2), so that the
-        buffer roles are settled when recording starts.
+        kernels are loaded when recording starts.
         The buffers swap once per step, so an even n returns the state to the
         buffer it started in, which is what lets the same graph run again.
+        A graph that is to run after reinit, too, has to be recorded an even
+        number of steps after the lattice was made: reinit puts the state into
+        the first buffer.
         Only the fused path without check_finite is capturable.
         """
         if n <= 0 or n % 2:
             raise ValueError("n must be a positive even number")
         if self.params.get("check_finite", 0) or self.params.get("kernel", "fused") != "fused":
             raise ValueError("capture needs kernel='fused' and check_finite=0")
-        self.step(2)  # buffers settled before capture
+        self.step(2)  # kernels loaded before capture
         torch.cuda.synchronize(self.device)
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, pool=pool):
